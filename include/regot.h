@@ -227,8 +227,13 @@ int regot_sinkhorn_half_step(int64_t n, int64_t m,
  * `sweeps` Sinkhorn sweeps in place: each is the alpha half-step followed by the beta half-step (the order
  * of the block coordinate ascent of Sec. 1; the candidate generator of Sec. 4.3 and the start of the
  * experiments in Sec. 6.1 run a fixed number of them).  alpha [n] and beta [m] are read and replaced;
- * the first half-step does not read alpha, so it need not be initialised.  2 * sweeps passes over M are
- * enqueued; exactly what the same sequence of regot_sinkhorn_half_step calls gives.  sweeps >= 0.
+ * the first half-step does not read alpha, so it need not be initialised.  sweeps >= 0.
+ * For n * m < 2^20 (and for fewer than 64 rows or columns, or more than 61440 columns) this is exactly the same
+ * sequence of regot_sinkhorn_half_step calls, bit for bit.  Otherwise a sweep reads M once instead of twice: the
+ * beta update is formed from the exponentials of the alpha update while they are on chip, which is the same update
+ * up to rounding (a few 1e-16 of the duals; bit-reproducible run to run), and a column whose terms would underflow
+ * that way is done again from alpha and M relative to its maximum, as in the half-step.  A NaN among the costs of a
+ * row makes that row's alpha and every beta NaN there.
  */
 int regot_sinkhorn_sweeps(int64_t n, int64_t m,
                           const double *M, int64_t ldM,

@@ -129,6 +129,16 @@ __device__ __forceinline__ double wave_reduce4(double a0, double a1, double a2, 
 
 __device__ __forceinline__ int quad_row(int lane) { return ((lane >> 5) & 1) | (((lane >> 4) & 1) << 1); }
 
+// the same for two values: lanes 0-31 end with the result of row 0, lanes 32-63 with that of row 1
+template <typename Op>
+__device__ __forceinline__ double wave_reduce2(double a0, double a1)
+{
+    swap32(a0, a1);
+    double b = row16_reduce<Op>(Op::apply(a0, a1)), c = b;
+    swap16(b, c);
+    return Op::apply(b, c);
+}
+
 // value of lane `src` (a compile-time-free uniform index) broadcast to the wave
 __device__ __forceinline__ double read_lane(double v, int src)
 {

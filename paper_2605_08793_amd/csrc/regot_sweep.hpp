@@ -1,0 +1,435 @@
+// One Sinkhorn sweep (alpha half-step, then beta half-step) from ONE read of the cost matrix.
+//
+// Run as two half-steps a sweep reads M twice, because the beta update of a column needs the new alpha of every row.
+// But the entries of a row are still on chip when the row's log-sum-exp is complete, and its exponentials are already
+// formed: with e_ij = exp((beta_j - M_ij - max_i) / eta), S_i = sum_j e_ij and the new alpha_i = eta log a_i -
+// (max_i + eta log S_i), the plan entry at (new alpha, old beta) is
+//     T_ij = exp((alpha_i + beta_j - M_ij) / eta) = e_ij a_i / S_i,
+// one multiplication instead of another exponential, and with c_j = sum_i T_ij the exact maximiser in beta is
+//     beta_j + eta (log b_j - log c_j).
+// T_ij <= a_i, so nothing overflows; a column whose c_j is so small that terms may have been lost to underflow (or whose
+// old beta is not finite) is done again from alpha and M in the log domain (sweep_finalize_kernel).
+//
+// A row of 20000 doubles is 160 KB, too much for one compute unit to hold twice (the row being worked on and the one
+// in flight) next to the column sums, so K = ceil(m / 3840) workgroups -- a cluster, one workgroup per compute unit --
+// share a block of rows, each owning `width` columns.  Fifteen waves work on the matrix: a lane owns up to 4 columns, keeps
+// their sums in registers for all rows of the block, has two batches of kSweepRows = 4 rows in registers (the one whose
+// exponentials are being formed and the one in flight) and the exponentials of the batch before in LDS.  The sixteenth wave
+// finds the factors a_i / S_i: it publishes the workgroup's (max, sum) per row in the workspace, reads the other members',
+// and has the time the workers take for the next batch to do it.  (It has to be a wave of its own: memory loads return in
+// order, so a wave that also streams the matrix would see the other members' numbers only behind its own prefetch.)
+// One barrier per batch.
+//
+// What bounds it: memory latency times what a compute unit can keep in flight, with the exponentials on top.  20000 x 20000:
+// 596 us a sweep = 5.4 TB/s of M against 975 us for the two half-steps (two reads at 6.6 TB/s); with the exponentials
+// replaced by one operation 550 us.  A member's numbers take 0.8 us to reach the others, but the members of a cluster
+// drift apart by up to the one batch (5 us) they are allowed; a cluster of one (m <= 3840) runs at 5.8 TB/s.  Measured on
+// the way: seven workers with twice the columns each 616 us; all of a batch's loads requested at once 673 us (the waves then
+// stand in line to issue them); counters in LDS instead of the barrier: no change; members on one die: no change.
+#pragma once
+
+#include "regot_kernels.hpp"
+
+namespace regot {
+
+constexpr int kSweepWaves = 15;                              // that work on the matrix; one more finds the factors
+constexpr int kSweepLanes = kSweepWaves * kLanes;
+constexpr int kSweepThreads = kSweepLanes + kLanes;
+constexpr int kSweepRows = 4;                               // rows of a batch
+constexpr int kSweepGroups = 2;                             // groups of 128 columns a wave can own
+constexpr int kSweepCols = kSweepWaves * 2 * kLanes * kSweepGroups;  // columns a workgroup can own (3840)
+constexpr int kSweepMaxK = 16;                              // members of a cluster: one lane of a DPP row each
+static_assert(kSweepRows * 16 == kLanes && kSweepWaves <= 16, "a DPP row of 16 lanes per row of the batch");
+
+// What an unpublished word holds: a NaN with all bits set.  Published NaNs have other bits.
+constexpr unsigned long long kUnpublished = ~0ull;
+
+// c_j below this is recomputed: a term lost to underflow is below 1e-307, so up to 2^31 of them are below 1e-16 of it
+constexpr double kSweepTiny = 1e-280;
+
+struct SweepArgs {
+    int n, m;
+    int64_t ldM;
+    const double *M;
+    const double *a, *b;
+    double *alpha, *beta;
+    double eta;
+    int K, P;         // members of a cluster, clusters
+    int width;        // columns per member (even; the last member may have fewer)
+    double *exch;     // [n][K][2] published (max, sum); K > 1
+    double *colpart;  // [P][m] column sums of a cluster's rows
+    int *ticket;      // K > 1: number of workgroups that have started
+    ExpParams ex;
+};
+
+__global__ __launch_bounds__(kThreads) void sweep_init_kernel(unsigned long long *exch, int64_t words, int *ticket)
+{
+    const int64_t i0 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i0 == 0) *ticket = 0;
+    for (int64_t i = i0; i < words; i += (int64_t)gridDim.x * kThreads) exch[i] = kUnpublished;
+}
+
+template <int NU>
+struct SweepShared {
+    dbl2 prev[kSweepRows][NU][kSweepLanes];  // a lane's exponentials of the batch before; read back by the same lane
+    dbl2 beta[NU][kSweepLanes];                // a lane's beta; likewise
+    dbl2 pairs[2][kSweepRows][kSweepWaves];   // (max, sum) per row and wave, by parity of the batch
+    double fac[2][kSweepRows][kSweepWaves];   // what a wave's exponentials of a row are to be multiplied by
+    int role;
+};
+
+// Batches a cluster works through: an even number (see sweep_wave); rows beyond the last are its last row again, with a
+// factor of 0.
+__device__ __forceinline__ int sweep_batches(int r_begin, int r_end)
+{
+    return ((r_end - r_begin + 2 * kSweepRows - 1) / (2 * kSweepRows)) * 2;
+}
+
+// NU: groups of 128 columns per wave, group u of wave w being columns c0 + 128 (15 u + w) + 2 lane + e.
+// MASKED: not all of the wave's groups are full (the last columns of the member).
+// The loads of a batch are issued by every wave unconditionally and in the same number, so that waiting for one batch
+// never waits for the one requested behind it: where the member has no column a lane reads its last two again.
+template <int NU, bool MASKED>
+__device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU> &L, int cluster, int r_begin, int r_end,
+                                           int c0, int ncol, int w, int lane)
+{
+    typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));  // 16 bytes wherever a double may lie
+    constexpr int kStride = 2 * kLanes * kSweepWaves;
+    const int first = 2 * kLanes * w + 2 * lane;
+    int nu = 0;         // groups that hold any column
+    unsigned off[NU];   // byte offset of the pair a lane loads
+    bool cv[NU][2], last[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const int c = first + u * kStride;
+        if (2 * kLanes * (u * kSweepWaves + w) < ncol) nu = u + 1;
+        cv[u][0] = !MASKED || c < ncol;
+        cv[u][1] = !MASKED || c + 1 < ncol;
+        last[u] = MASKED && c == ncol - 1;                // its column is the second of the pair it loads
+        off[u] = (unsigned)(MASKED ? min(c, ncol - 2) : c) * (unsigned)sizeof(double);
+    }
+    nu = MASKED ? __builtin_amdgcn_readfirstlane(nu) : NU;
+    double csum[NU][2];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        csum[u][0] = csum[u][1] = 0.0;
+        const double *src = A.beta + c0 + first + u * kStride;
+        L.beta[u][threadIdx.x] = dbl2{cv[u][0] ? src[0] : 0.0, cv[u][1] ? src[1] : 0.0};
+    }
+
+    const double *M0 = A.M + c0;
+    auto load_row = [&](double (&v)[NU][2], int row) {
+        const double *prow = M0 + (int64_t)min(row, r_end - 1) * A.ldM;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const dbl2u x = __builtin_nontemporal_load(reinterpret_cast<const dbl2u *>(reinterpret_cast<const char *>(prow) + off[u]));
+            v[u][0] = x.x;
+            v[u][1] = x.y;
+        }
+    };
+
+    // One row: costs relative to wmax -> exponentials; returns the lane's sum
+    auto exponentials = [&](double (&v)[NU][2], double wmax, int row) -> double {
+        double acc = 0.0;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            if (MASKED && u >= nu) continue;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                double t = exp_eta(v[u][e] - wmax, A.ex);
+                if constexpr (MASKED) t = cv[u][e] ? t : 0.0;
+                v[u][e] = t;
+                acc += t;
+            }
+        }
+        if (__ballot(not_finite(acc)) != 0) {
+            // an infinite cost or an infinite beta in the row: again from memory, with the IEEE limits of exp.  A column
+            // with beta = -inf (zero mass) has no T; what is added up for it instead is whether its costs are finite,
+            // which is all that decides its next beta.
+            acc = 0.0;
+            const double *prow = M0 + (int64_t)min(row, r_end - 1) * A.ldM + first;
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                const dbl2 bet = L.beta[u][threadIdx.x];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    double t = 0.0;
+                    if (first + u * kStride + e < ncol) {
+                        const double c = prow[u * kStride + e];
+                        t = exp_eta_any((bet[e] - c) - wmax, A.ex);
+                        acc += t;
+                        if (bet[e] == -INFINITY) t = c == INFINITY ? 0.0 : c - c + 1.0;  // (NaN for NaN and -inf)
+                    }
+                    v[u][e] = t;
+                }
+            }
+            // without this the code after the branch has to assume that these loads are still on their way, and waits
+            // for everything requested since, the next batch included
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+        }
+        return acc;
+    };
+
+    // Column sums of one row: its exponentials (in LDS, of two batches ago) times its factor
+    auto accumulate = [&](const dbl2 (&x)[NU], double f) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            csum[u][0] = __builtin_fma(f, x[u].x, csum[u][0]);
+            csum[u][1] = __builtin_fma(f, x[u].y, csum[u][1]);
+            // (here and now: sunk to where the sums are needed next, the additions would keep all they read in registers)
+            asm volatile("" : "+v"(csum[u][0]), "+v"(csum[u][1]));
+        }
+    };
+
+    // Batch b: its costs are in `cur`, the exponentials of batch b - 1 in `old`, those of batch b - 2 in LDS, and their
+    // factors are known.  Row by row: the column sums of batch b - 2, batch b - 1 to LDS, the costs of batch b + 1 requested
+    // into its registers (behind the last batch: the last row again), and, two rows at a time, the exponentials of batch b.
+    // The requests are spread over the batch because all waves are in step: requested at once they fill the memory
+    // pipeline of the compute unit, and the waves wait to issue them instead of computing.
+    auto batch = [&](int b, double (&cur)[kSweepRows][NU][2], double (&old)[kSweepRows][NU][2]) {
+        const int row0 = r_begin + b * kSweepRows, par = b & 1;
+#pragma unroll
+        for (int h = 0; h < kSweepRows; h += 2) {
+            auto turn = [&](int r, dbl2 (&x)[NU]) {
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    x[u] = L.prev[r][u][threadIdx.x];
+                    L.prev[r][u][threadIdx.x] = dbl2{old[r][u][0], old[r][u][1]};
+                }
+                load_row(old[r], row0 + kSweepRows + r);
+                __builtin_amdgcn_sched_barrier(0);  // (in this order: what is waited for is counted from the youngest load)
+            };
+            dbl2 x[NU];
+            turn(h, x);
+            double lmax[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                if (MASKED && u >= nu) continue;
+                const dbl2 bet = L.beta[u][threadIdx.x];
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    double(&c)[2] = cur[h + r][u];
+                    // (the subtraction stays here: moved to where the costs are requested it would have to wait for them)
+                    asm volatile("" : "+v"(c[0]), "+v"(c[1]));
+                    if (MASKED && last[u]) c[0] = c[1];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        c[e] = bet[e] - c[e];
+                        if (cv[u][e]) lmax[r] = fmax(lmax[r], c[e]);
+                    }
+                }
+            }
+            // (at least -DBL_MAX: a segment of infinite costs gives terms 0 and an empty partial sum)
+            const double mx = fmax(wave_reduce2<OpMax>(lmax[0], lmax[1]), -kDblMax);
+            accumulate(x, L.fac[par][h][w]);
+            const double s0 = exponentials(cur[h], read_lane(mx, 0), row0 + h);
+            turn(h + 1, x);
+            const double s1 = exponentials(cur[h + 1], read_lane(mx, 32), row0 + h + 1);
+            accumulate(x, L.fac[par][h + 1][w]);
+            const double sm = wave_reduce2<OpSum>(s0, s1);
+            if ((lane & 31) == 0) L.pairs[par][h + (lane >> 5)][w] = dbl2{mx, sm};
+        }
+        __syncthreads();
+    };
+    const int nb = sweep_batches(r_begin, r_end);
+    double v0[kSweepRows][NU][2], v1[kSweepRows][NU][2];
+#pragma unroll
+    for (int r = 0; r < kSweepRows; ++r)
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            L.prev[r][u][threadIdx.x] = dbl2{0.0, 0.0};
+            v1[r][u][0] = v1[r][u][1] = 0.0;
+        }
+    // (the two batches before the first; read back by this wave only, before anyone writes it)
+    if (lane < 2 * kSweepRows) L.fac[lane / kSweepRows][lane % kSweepRows][w] = 0.0;
+#pragma unroll
+    for (int r = 0; r < kSweepRows; ++r) load_row(v0[r], r_begin + r);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int b = 0; b < nb; b += 2) {
+        batch(b, v0, v1);
+        batch(b + 1, v1, v0);
+    }
+    // the last two batches: one in LDS, one in registers (nb is even: in v1)
+#pragma unroll
+    for (int r = 0; r < kSweepRows; ++r) {
+        dbl2 x[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) x[u] = L.prev[r][u][threadIdx.x];
+        accumulate(x, L.fac[0][r][w]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSweepRows; ++r) {
+        dbl2 x[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) x[u] = dbl2{v1[r][u][0], v1[r][u][1]};
+        accumulate(x, L.fac[1][r][w]);
+    }
+    double *out = A.colpart + (int64_t)cluster * A.m + c0 + first;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        if (cv[u][0]) out[u * kStride] = csum[u][0];
+        if (cv[u][1]) out[u * kStride + 1] = csum[u][1];
+    }
+}
+
+// The factors of every batch, by one wave: lanes 16 r + j work on row r of the batch, j being a wave of the workgroup or a
+// member of the cluster.
+template <int NU>
+__device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU> &L, int member, int r_begin, int r_end, int lane)
+{
+    const int r16 = lane >> 4, j16 = lane & 15;
+    const int nb = sweep_batches(r_begin, r_end);
+    unsigned long long *exch = reinterpret_cast<unsigned long long *>(A.exch);
+    bool waiting = true;
+    __builtin_amdgcn_s_setprio(3);  // a few instructions that fifteen waves wait for (50000 x 50000: 4.23 -> 4.00 ms a sweep)
+    for (int b = 0; b < nb; ++b) {
+        const int row0 = r_begin + b * kSweepRows, par = b & 1;
+        const bool live = row0 + r16 < r_end;
+        const int row = min(row0 + r16, r_end - 1);
+        const double ai = A.a[row];
+        __syncthreads();  // the workers' (max, sum) of batch b are there
+        const dbl2 mine = j16 < kSweepWaves ? L.pairs[par][r16][j16] : dbl2{-kDblMax, 0.0};
+        double mx = row16_reduce<OpMax>(mine.x);
+        double sum = row16_reduce<OpSum>(mine.y * exp_eta_any(mine.x - mx, A.ex));
+        if (A.K > 1) {
+            unsigned long long word = (unsigned long long)__double_as_longlong(j16 == 0 ? mx : sum);
+            if (word == kUnpublished) word = 0x7ff8000000000000ull;
+            if (j16 < 2 && live)
+                __hip_atomic_store(exch + ((int64_t)row * A.K + member) * 2 + j16, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // The other members run, or will as soon as a compute unit is free (see sweep_pass_kernel), so their words
+            // arrive; the bound (4 s at 100 MHz) only keeps a workspace that someone else writes to from hanging the device.
+            const unsigned long long *src = exch + ((int64_t)row * A.K + j16) * 2;
+            const bool take = live && j16 < A.K;
+            unsigned long long x = 0, y = 0;
+            const unsigned long long t0 = wall_clock64();
+            for (;;) {
+                if (take) {
+                    x = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    y = __hip_atomic_load(src + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (__ballot(take && (x == kUnpublished || y == kUnpublished)) == 0 || !waiting) break;
+                if (wall_clock64() - t0 > 400000000ull) waiting = false;
+            }
+            const double px = take ? __longlong_as_double((long long)x) : -kDblMax;
+            const double py = take ? __longlong_as_double((long long)y) : 0.0;
+            mx = row16_reduce<OpMax>(px);
+            sum = row16_reduce<OpSum>(py * exp_eta_any(px - mx, A.ex));
+        }
+        const bool fine = sum > 0.0 && sum <= kDblMax && ai >= 0.0 && ai <= kDblMax;
+        const double scale = fine ? ai / sum : __builtin_nan("");  // NaN: every column is done again from alpha and M
+        if (j16 < kSweepWaves) L.fac[par][r16][j16] = live ? scale * exp_eta_any(mine.x - mx, A.ex) : 0.0;
+        if (b % A.K == member && j16 == 0 && live) A.alpha[row] = A.eta * log(ai) - (mx + A.eta * log(sum));
+    }
+    __syncthreads();
+}
+
+// Which member of which cluster a workgroup is follows from the order in which the workgroups start (a counter in the
+// workspace): only the cluster formed last can be incomplete while its members wait for each other, and the clusters
+// before it finish whatever happens, so a place for the missing members always comes free, other kernels on the device
+// or not.  Which workgroup does what has no influence on the results.
+template <int NU>
+__global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_kernel(SweepArgs A)
+{
+    __shared__ SweepShared<NU> L;
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (threadIdx.x == 0) {
+        L.role = A.K > 1 ? atomicAdd(A.ticket, 1) : (int)blockIdx.x;
+    }
+    __syncthreads();
+    const int role = __builtin_amdgcn_readfirstlane(L.role);
+    if (role < 0 || role >= A.P * A.K) return;
+    const int cluster = role / A.K, member = role - cluster * A.K;
+    int r_begin, r_end;
+    chunk_rows(cluster, A.P, A.n, r_begin, r_end);
+    const int c0 = member * A.width;
+    const int ncol = min(A.width, A.m - c0);
+    if (w == kSweepWaves) {
+        sweep_factors<NU>(A, L, member, r_begin, r_end, lane);
+    } else if (2 * kLanes * ((NU - 1) * kSweepWaves + w + 1) <= ncol) {  // the wave's last group is full
+        sweep_wave<NU, false>(A, L, cluster, r_begin, r_end, c0, ncol, w, lane);
+    } else {
+        sweep_wave<NU, true>(A, L, cluster, r_begin, r_end, c0, ncol, w, lane);
+    }
+}
+
+// Column sums over the clusters and the new beta; 64 columns per workgroup, one wave per share of the clusters.  Also
+// clears the exchange words and the counter for the next sweep.
+constexpr int kSweepFinWaves = 16;
+
+__global__ __launch_bounds__(kSweepFinWaves *kLanes) void sweep_finalize_kernel(SweepArgs A)
+{
+    __shared__ double lds_a[kSweepFinWaves][kLanes], lds_b[kSweepFinWaves][kLanes];
+    __shared__ unsigned long long lds_bad;
+    const int l = threadIdx.x & (kLanes - 1), sub = threadIdx.x >> 6;
+    const int64_t j = (int64_t)blockIdx.x * kLanes + l;
+    const bool live = j < A.m;
+    if (A.K > 1) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) *A.ticket = 0;
+        const int64_t words = (int64_t)A.n * A.K * 2;
+        unsigned long long *ex = reinterpret_cast<unsigned long long *>(A.exch);
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += (int64_t)gridDim.x * blockDim.x)
+            ex[i] = kUnpublished;
+    }
+    double s = 0.0;
+    if (live) {
+#pragma unroll 4
+        for (int p = sub; p < A.P; p += kSweepFinWaves) s += A.colpart[(int64_t)p * A.m + j];
+    }
+    lds_a[sub][l] = s;
+    __syncthreads();
+    double out = 0.0, bj = 0.0;
+    if (sub == 0) {
+        double c = lds_a[0][l];
+#pragma unroll
+        for (int q = 1; q < kSweepFinWaves; ++q) c += lds_a[q][l];
+        bool ok = true;
+        if (live) {
+            const double bo = A.beta[j];
+            bj = A.b[j];
+            ok = c >= kSweepTiny && c <= kDblMax;
+            if (bo == -INFINITY) {  // no T in this column; c > 0: it has a finite cost (see sweep_wave)
+                ok = ok && bj == 0.0;
+                out = -INFINITY;
+            } else {
+                ok = ok && bo <= kDblMax;
+                out = bo + A.eta * (log(bj) - log(c));
+            }
+        }
+        const unsigned long long bad = __ballot(!ok);
+        if (l == 0) lds_bad = bad;
+    }
+    __syncthreads();
+    const unsigned long long bad = lds_bad;
+    if (bad != 0) {
+        // these columns again from alpha and M: the beta half-step as it is written, relative to the running maximum
+        const bool redo = ((bad >> l) & 1) != 0;
+        double mx = -kDblMax, sum = 0.0;
+        if (redo) {
+#pragma unroll 4
+            for (int i = sub; i < A.n; i += kSweepFinWaves) {
+                const double v = A.alpha[i] - A.M[(int64_t)i * A.ldM + j];
+                const double nm = fmax(mx, v);
+                sum = sum * exp_eta_any(mx - nm, A.ex) + exp_eta_any(v - nm, A.ex);
+                mx = nm;
+            }
+        }
+        __syncthreads();
+        lds_a[sub][l] = mx;
+        lds_b[sub][l] = sum;
+        __syncthreads();
+        if (sub == 0 && redo) {
+            mx = lds_a[0][l];
+#pragma unroll
+            for (int q = 1; q < kSweepFinWaves; ++q) mx = fmax(mx, lds_a[q][l]);
+            sum = 0.0;
+#pragma unroll
+            for (int q = 0; q < kSweepFinWaves; ++q) sum += lds_b[q][l] * exp_eta_any(lds_a[q][l] - mx, A.ex);
+            out = A.eta * log(bj) - (mx + A.eta * log(sum));
+        }
+    }
+    if (sub == 0 && live) A.beta[j] = out;
+}
+
+}  // namespace regot

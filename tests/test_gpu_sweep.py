@@ -1,0 +1,140 @@
+"""Sweeps that read M once (regot_sinkhorn_sweeps for n * m >= 2^20) against the oracle's sweeps and against the
+half-steps, at the edges of the cut: one member and several, groups of columns that are full, partial and absent, blocks
+of rows that do not divide into batches, matrices whose rows do not start at 16-byte boundaries."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2605_08793_amd import binding as B
+from paper_2605_08793_amd import workloads as W
+from paper_2605_08793_amd.driver import DualPass
+from parity_utils import assert_half_step_close
+
+pytestmark = pytest.mark.gpu
+INF = float("inf")
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def sweep_gpu(Md, a, b, eta, sweeps, beta0, dirty=True):
+    n, m = Md.shape
+    dp = DualPass(n, m)
+    if dirty:
+        dp.workspace.fill_(0x5A)
+    al = torch.full((n,), float("nan"), dtype=torch.float64, device="cuda")
+    be = dev(beta0)
+    B.regot_sinkhorn_sweeps(Md, dev(a), dev(b), al, be, eta, sweeps, workspace=dp.workspace)
+    torch.cuda.synchronize()
+    return al.cpu().numpy(), be.cpu().numpy()
+
+
+def check(M, a, b, eta, sweeps, beta0, label, Md=None):
+    n, m = M.shape
+    print(f"[sweep] {label} n={n} m={m} eta={eta} sweeps={sweeps}", flush=True)
+    assert n * m >= 1 << 20
+    got_a, got_b = sweep_gpu(dev(M) if Md is None else Md, a, b, eta, sweeps, beta0)
+    ra, rb = oracle.sinkhorn_sweeps(M, a, b, eta, sweeps, np.zeros(n), beta0)
+    # every half-step is within 1e-10 * max(|dual|, eta) of the oracle's (parity_utils); the error of one enters the next
+    # with a factor of at most 1 (a log-sum-exp does not magnify), so a few sweeps stay within a few of those
+    zero_a, zero_b = ~np.isfinite(ra), ~np.isfinite(rb)
+    for got, ref, zero, what in ((got_a, ra, zero_a, "alpha"), (got_b, rb, zero_b, "beta")):
+        np.testing.assert_array_equal(got[zero], ref[zero], err_msg=what)
+        assert_half_step_close(got[~zero], ref[~zero], eta, f"{label} {what}")
+    return got_a, got_b
+
+
+@pytest.mark.parametrize("n,m", [
+    (4096, 256), (16384, 64), (64, 16385),        # few columns; the fewest of either
+    (1100, 1920), (1101, 1921),                   # the last width with one group of columns a wave, and one more
+    (300, 3840), (301, 3841), (283, 3839),        # one member, full; two members
+    (200, 7680), (191, 7681), (137, 11000),       # two, three
+    (71, 61440),                                  # sixteen members
+    (1031, 1500), (2049, 513), (3001, 1111),      # rows that do not divide into batches
+])
+def test_edges_of_the_cut(n, m):
+    eta = 0.05
+    M, a, b, _, beta = W.random_small(n, m, seed=n + m, eta=eta)
+    check(M, a, b, eta, 2, beta, "edges")
+
+
+@pytest.mark.parametrize("n,m,ld,shift", [(1200, 1000, 1001, 0), (1200, 1000, 1000, 1), (600, 3841, 3845, 1)])
+def test_rows_off_16_byte_boundaries(n, m, ld, shift):
+    eta = 0.05
+    M, a, b, _, beta = W.random_small(n, m, seed=7, eta=eta)
+    store = torch.full((n * ld + shift,), float("nan"), dtype=torch.float64, device="cuda")
+    Md = store[shift:].as_strided((n, m), (ld, 1), storage_offset=shift)
+    Md.copy_(dev(M))
+    # one buffer that ends with the last entry of M: nothing behind it may be read
+    check(M, a, b, eta, 2, beta, "unaligned", Md=Md)
+
+
+@pytest.mark.parametrize("n,m", [(1100, 1300), (300, 4500)])
+def test_infinite_costs_zero_masses_and_underflow(n, m):
+    rng = np.random.default_rng(m)
+    M, a, b, _, beta = W.random_small(n, m, seed=m, eta=0.05)
+    # infinite costs, among them whole segments of rows, nearly whole rows and columns
+    Mi = M.copy()
+    Mi[rng.random((n, m)) < 0.02] = INF
+    Mi[3, : m // 2] = INF
+    Mi[7, :] = INF; Mi[7, m // 3] = 0.3
+    Mi[:, 9] = INF; Mi[n - 1, 9] = 0.1
+    Mi[n // 2:, m - 1] = INF
+    check(Mi, a, b, 0.05, 2, beta, "infinite costs")
+    # zero masses: the dual is -inf, and stays it in later sweeps
+    az, bz = a.copy(), b.copy()
+    az[::17] = 0.0; bz[::13] = 0.0; bz[m - 1] = 0.0
+    check(Mi, az / az.sum(), bz / bz.sum(), 0.05, 3, beta, "zero masses")
+    # a start from -inf in columns that have mass; columns whose every term underflows at the old beta
+    check(M, a, b, 0.05, 2, np.where(np.arange(m) % 5 == 0, -INF, beta), "beta starts at -inf")
+    check(M, a, b, 1e-4, 2, np.where(np.arange(m) % 7 == 0, -3.0, beta), "underflow at the old beta")
+    check(M, a, b, 2e-4, 2, np.zeros(m), "small eta from zero")
+
+
+def test_nan_and_empty_rows_come_back():
+    n, m, eta = 1100, 1000, 0.05
+    M, a, b, _, beta = W.random_small(n, m, seed=3, eta=eta)
+    for bad in (float("nan"), INF):
+        X = M.copy()
+        X[411, 17 if bad != INF else slice(None)] = bad
+        al, be = sweep_gpu(dev(X), a, b, eta, 1, beta)
+        keep = np.arange(n) != 411
+        ref = oracle.sinkhorn_half_step(M, a, np.zeros(n), beta, eta, 0)
+        assert_half_step_close(al[keep], ref[keep], eta, "rows without it")
+        assert not np.isfinite(al[411]) and np.isnan(be).all()
+
+
+def test_same_bits_again_and_in_a_graph():
+    p = W.make_problem("c2", device="cuda", n=1500, m=4100)      # two members to a cluster
+    dp = DualPass(p.n, p.m)
+    al = torch.zeros(p.n, dtype=torch.float64, device="cuda"); be = torch.zeros(p.m, dtype=torch.float64, device="cuda")
+
+    def run():
+        B.regot_sinkhorn_sweeps(p.M, p.a, p.b, al, be, p.eta, 3, workspace=dp.workspace)
+
+    run(); torch.cuda.synchronize()
+    first = (al.clone(), be.clone())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+    for replay in range(3):
+        be.zero_(); al.fill_(float("nan"))
+        graph.replay(); torch.cuda.synchronize()
+        assert torch.equal(al, first[0]) and torch.equal(be, first[1]), replay
+        be.zero_(); dp.workspace.fill_(replay)
+        run(); torch.cuda.synchronize()
+        assert torch.equal(al, first[0]) and torch.equal(be, first[1]), replay
+    # two streams at once, each with its own workspace: the clusters of both complete
+    side, dp2 = torch.cuda.Stream(), DualPass(p.n, p.m)
+    al2, be2 = torch.zeros_like(al), torch.zeros_like(be)
+    be.zero_(); torch.cuda.synchronize()
+    for _ in range(5):
+        with torch.cuda.stream(side):
+            be2.zero_()
+            B.regot_sinkhorn_sweeps(p.M, p.a, p.b, al2, be2, p.eta, 3, workspace=dp2.workspace)
+        be.zero_(); run()
+    torch.cuda.synchronize()
+    assert torch.equal(al, first[0]) and torch.equal(be, first[1])
+    assert torch.equal(al2, first[0]) and torch.equal(be2, first[1])
