@@ -1181,7 +1181,8 @@ int regot_sinkhorn_half_step(int64_t n, int64_t m, const double *M, int64_t ldM,
     }
     prof_end(s);
     const unsigned fin = (unsigned)((F.len + kLanes - 1) / kLanes);
-    hipLaunchKernelGGL(lse_finalize_kernel, dim3(fin), dim3(kThreads), 0, s, F);
+    if (F.parts <= kLseFewParts) hipLaunchKernelGGL(lse_finalize_kernel<kWaves>, dim3(fin), dim3(kThreads), 0, s, F);
+    else hipLaunchKernelGGL(lse_finalize_kernel<16>, dim3(fin), dim3(16 * kLanes), 0, s, F);
     return hip_status();
 }
 

@@ -1861,7 +1861,13 @@ __global__ __launch_bounds__(kThreads) REGOT_WAVES_ATTR(REGOT_COLLSE_WAVES_PER_E
 // Merge the partial (smax, sum) pairs of one row / column and finish the update:
 // out = eta*log(marginal) - (smax + eta*log(sum)).
 // Pair q of element i sits at part[(i + q*len) * 2].  A workgroup handles 64 elements; each of its
-// four waves merges a quarter of the parts (coalesced over the elements), then wave 0 merges the four.
+// WAVES waves merges a share of the parts (coalesced over the elements), then wave 0 merges those.
+// A chain of memory latencies like finalize_kernel: the parts are fetched kLseRegs at a time and kept in registers between
+// their maximum and their sum.  Four waves where that is one batch each (larger workgroups only start later: 0.5-0.8 us
+// with few parts), else sixteen: with four waves that read every pair twice in a row the beta half-step took 26 us at
+// 2001 x 2003 (125 parts) and 73 us at 20000 x 400 (512 parts); now 17.6 and 33.7.
+constexpr int kLseRegs = 8;
+constexpr int kLseFewParts = kWaves * kLseRegs;
 struct LseFinalizeArgs {
     int64_t len;        // n for which = 0, m for which = 1
     int parts;          // g_c for which = 0, g_r for which = 1
@@ -1872,32 +1878,37 @@ struct LseFinalizeArgs {
     ExpParams ex;
 };
 
-__global__ __launch_bounds__(kThreads) void lse_finalize_kernel(LseFinalizeArgs L)
+template <int WAVES>
+__global__ __launch_bounds__(WAVES *kLanes) void lse_finalize_kernel(LseFinalizeArgs L)
 {
-    __shared__ double lds_max[kWaves][kLanes];
-    __shared__ double lds_sum[kWaves][kLanes];
+    __shared__ double lds_max[WAVES][kLanes];
+    __shared__ double lds_sum[WAVES][kLanes];
     const int l = threadIdx.x & (kLanes - 1), sub = threadIdx.x >> 6;
     const int64_t i = (int64_t)blockIdx.x * kLanes + l;
     const bool live = i < L.len;
-    const int per = (L.parts + kWaves - 1) / kWaves;
+    const int per = (L.parts + WAVES - 1) / WAVES;
     const int q0 = min(L.parts, sub * per), q1 = min(L.parts, q0 + per);
     const dbl2 *pairs = reinterpret_cast<const dbl2 *>(L.part);
     // an empty partial has sum 0; a non-empty one has sum >= 1 (its maximum contributes exp(0))
     double mx = 0.0, sum = 0.0;
     if (live) {
-        bool any = false;
-#pragma unroll 4
-        for (int q = q0; q < q1; ++q) {
-            const dbl2 pr = pairs[(size_t)q * L.len + i];
-            if (pr.y > 0.0) {
-                mx = any ? fmax(mx, pr.x) : pr.x;
-                any = true;
-            }
-        }
-#pragma unroll 4
-        for (int q = q0; q < q1; ++q) {
-            const dbl2 pr = pairs[(size_t)q * L.len + i];
-            if (pr.y > 0.0) sum += pr.y * exp_eta(pr.x - mx, L.ex);
+        for (int q = q0; q < q1; q += kLseRegs) {
+            dbl2 pr[kLseRegs];
+#pragma unroll
+            for (int j = 0; j < kLseRegs; ++j) pr[j] = q + j < q1 ? pairs[(size_t)(q + j) * L.len + i] : dbl2{0.0, 0.0};
+            double nm = mx;
+            bool any = sum > 0.0;
+#pragma unroll
+            for (int j = 0; j < kLseRegs; ++j)
+                if (pr[j].y > 0.0) {
+                    nm = any ? fmax(nm, pr[j].x) : pr[j].x;
+                    any = true;
+                }
+            if (sum > 0.0) sum *= exp_eta(mx - nm, L.ex);  // (exactly 1 where the maximum stays)
+            mx = nm;
+#pragma unroll
+            for (int j = 0; j < kLseRegs; ++j)
+                if (pr[j].y > 0.0) sum += pr[j].y * exp_eta(pr[j].x - mx, L.ex);
         }
     }
     lds_max[sub][l] = mx;
@@ -1907,14 +1918,14 @@ __global__ __launch_bounds__(kThreads) void lse_finalize_kernel(LseFinalizeArgs 
     bool any = false;
     mx = 0.0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w)
+    for (int w = 0; w < WAVES; ++w)
         if (lds_sum[w][l] > 0.0) {
             mx = any ? fmax(mx, lds_max[w][l]) : lds_max[w][l];
             any = true;
         }
     sum = 0.0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w)
+    for (int w = 0; w < WAVES; ++w)
         if (lds_sum[w][l] > 0.0) sum += lds_sum[w][l] * exp_eta(lds_max[w][l] - mx, L.ex);
     L.out[i] = L.eta * log(L.marginal[i]) - (mx + L.eta * log(sum));
 }
