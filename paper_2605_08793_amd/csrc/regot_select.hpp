@@ -5,8 +5,11 @@
 // order-preserving 64-bit integer (the "key") and the k-th largest key is found exactly:
 //
 //   sample    A stratified sample of 65536 entries is gathered; two histogram kernels locate two
-//             of its order statistics to 26 bits and so bracket the k-th key: lo <= key_k <= hi
+//             of its order statistics to 13 or 26 bits of the sample's range and so bracket the k-th key: lo <= key_k <= hi
 //             with overwhelming probability, with a fraction of a percent of all keys in [lo, hi].
+//             (Bits of the range from the smallest to the largest sample key, not of the keys: their leading 13 bits are
+//             sign, exponent and one bit more, the same few values for everything, so that the additions of a
+//             whole wave went to one LDS counter, 16 us for the first histogram, and the second was always needed.)
 //   bracket   One pass over M counts the keys above hi and copies the keys inside [lo, hi] to a
 //             pool in the workspace.  If the counts show that the k-th key is in the pool
 //             (above < k <= above + pool size, checked exactly), the search continues on the pool.
@@ -15,7 +18,8 @@
 //             builds the histogram of the next 13 bits of all keys that share the bits found so
 //             far; once the surviving bucket fits the pool the pass also copies it there.
 //   pool      The remaining bits are fixed by histogram passes over the pool (a few MB), which
-//             move on to a second, small pool as soon as the bucket fits it.
+//             move on to a second, small pool as soon as the bucket fits it; the last kernel finishes as soon
+//             as a few keys are left of a pool that one workgroup can read.
 //
 // The result never depends on the sample, only the number of passes does.  All kernels of the
 // worst case are enqueued up front (10 launches).  Each one starts by working out, from the
@@ -45,7 +49,9 @@ constexpr int kSampleSlots = 2;             // two more slots: second sample his
 constexpr int kSampleLog2 = 16;
 constexpr int kSample = 1 << kSampleLog2;   // sampled entries
 constexpr int kSamplePasses = 2;            // histogram kernels over the sample: its keys are located to 26 bits
-constexpr int kSampleFew = 4;               // a sample bucket this small is not refined further
+constexpr int kSampleFew = 4;               // a sample bucket of twice this many keys is not refined further
+constexpr int kFinishKeys = 256;            // the result kernel selects among this many keys by itself ...
+constexpr int kFinishPool = 1 << 14;        // ... out of a pool of at most this many (step kernels then return at once)
 constexpr double kBracketZ = 5.0;           // half-width of the bracket in standard deviations of the sample rank
 static_assert((1 << kBracketBits) < kThreads, "one thread per bin of the bracket histogram");
 static_assert(kKeyBuf >= 2 * kPanel, "a wave appends up to one panel row between two checks");
@@ -119,6 +125,8 @@ struct SelState {
     int sbits;           // leading bits of the two sample keys fixed so far
     int act;             // SelAct of the kernel that owns this record
     int error;           // a count did not add up (cannot happen with finite inputs)
+    u64 sbase;           // sample keys are searched as (key - sbase) << slshift: the sample's range stretched over 64 bits
+    int slshift;
 };
 
 struct SelCounters {     // cleared by the gather kernel
@@ -199,12 +207,13 @@ struct RankHit {
     int bin;
     u64 run, cnt;
 };
+// reuse: the copy in LDS is that of the previous call, on the same histogram.
 __device__ __forceinline__ RankHit find_rank(const u64 *hist, int nbins, u64 k_rem, ResolveLds &L,
-                                             u64 *copy /* LDS [kBins] */)
+                                             u64 *copy /* LDS [kBins] */, bool reuse = false)
 {
     const int tid = threadIdx.x;
     const int lane = tid & (kLanes - 1);
-    {
+    if (!reuse) {
         // all loads of a thread are issued before the first one is used (nbins is a multiple of 2)
         constexpr int kLoads = kBins / (2 * kThreads);
         ulonglong2 v[kLoads];
@@ -260,6 +269,20 @@ __device__ __forceinline__ RankHit find_rank(const u64 *hist, int nbins, u64 k_r
     return hit;
 }
 
+// bounds of the keys a sample bucket can hold
+__device__ __forceinline__ u64 sample_bucket_lo(const SelState &st, int e) { return st.sbase + (st.side[e].prefix >> st.slshift); }
+__device__ __forceinline__ u64 sample_bucket_hi(const SelState &st, int e)
+{
+    const u64 hi = st.sbase + ((st.side[e].prefix | ~lead_mask(st.sbits)) >> st.slshift);
+    return hi < st.sbase ? ~0ull : hi;
+}
+
+// the pass over what is left of the pool is the result kernel's
+__device__ __forceinline__ bool finish_open(const SelState &st)
+{
+    return st.collected && !st.error && st.bits < st.bits_end && st.bucket <= (long long)kFinishKeys && st.pool_count <= (unsigned)kFinishPool;
+}
+
 // Ranks (1 = largest) of the two sample keys that bracket the k-th of all keys, and whether the
 // bracket is worth trying.  The sample rank of the k-th key is close to ks = k * kSample / nm, with
 // standard deviation at most sqrt(ks (1 - ks / kSample)).
@@ -307,14 +330,16 @@ __device__ __forceinline__ SelState start_state(const SelectArgs &A)
     st.sbits = 0;
     st.act = kActIdle;
     st.error = 0;
+    st.sbase = 0;
+    st.slshift = 0;
     return st;
 }
 
 // does the sample search still have something to narrow down
 __device__ __forceinline__ bool sample_open(const SelState &st)
 {
-    return st.use_bracket && ((st.side[0].need && st.side[0].bucket > (unsigned)kSampleFew) ||
-                              (st.side[1].need && st.side[1].bucket > (unsigned)kSampleFew));
+    return st.use_bracket && ((st.side[0].need && st.side[0].bucket > (unsigned)(2 * kSampleFew)) ||
+                              (st.side[1].need && st.side[1].bucket > (unsigned)(2 * kSampleFew)));
 }
 
 // State at the entry of kernel idx (>= 1), from the record of kernel idx - 1 and what that kernel
@@ -330,7 +355,7 @@ __device__ __forceinline__ SelState resolve_entry(const SelectArgs &A, int idx, 
         for (int e = 0; e < 2; ++e) {
             if (!prev.side[e].need) continue;
             const u64 *hist = prev.sbits == 0 ? main_slot(A, idx - 1) : sample_slot(A, e);
-            const RankHit hit = find_rank(hist, kBins, prev.side[e].k_rem, L, scratch);
+            const RankHit hit = find_rank(hist, kBins, prev.side[e].k_rem, L, scratch, e == 1 && prev.sbits == 0 && prev.side[0].need);
             if (hit.bin < 0) {
                 cur.use_bracket = 0;  // cannot happen; the radix passes do not need the sample
             } else {
@@ -421,6 +446,28 @@ __device__ __forceinline__ unsigned mix32(unsigned x)
     return x ^ (x >> 16);
 }
 
+// smallest lo and largest hi of the workgroup -> lds_lo[0], lds_hi[0]
+__device__ __forceinline__ void block_range(u64 lo, u64 hi, u64 *lds_lo /* LDS [kWaves] */, u64 *lds_hi)
+{
+#pragma unroll
+    for (int d = 1; d < kLanes; d <<= 1) {
+        const u64 a = __shfl_xor(lo, d, kLanes), b = __shfl_xor(hi, d, kLanes);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
+    }
+    if ((threadIdx.x & (kLanes - 1)) == 0) {
+        lds_lo[threadIdx.x >> 6] = lo;
+        lds_hi[threadIdx.x >> 6] = hi;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < kWaves; ++w) {
+            lds_lo[0] = lds_lo[w] < lds_lo[0] ? lds_lo[w] : lds_lo[0];
+            lds_hi[0] = lds_hi[w] > lds_hi[0] ? lds_hi[w] : lds_hi[0];
+        }
+    __syncthreads();
+}
+
 // First kernel of a call: clears counters and histogram slots, and gathers the sample.  Stratum t =
 // entries [t*q, (t+1)*q) in row-major order, q = nm / kSample (the last nm % kSample entries are
 // never sampled, which only matters to the quality of the bracket); thread t takes one entry of it.
@@ -457,7 +504,15 @@ __global__ __launch_bounds__(kThreads) void select_gather_kernel(SelectArgs A)
         jj -= A.m;
         ++i;
     }
-    A.sample[t] = entry_key(A.alpha[i], A.beta[jj], A.M[(int64_t)i * A.ldM + jj]);
+    const u64 key = entry_key(A.alpha[i], A.beta[jj], A.M[(int64_t)i * A.ldM + jj]);
+    A.sample[t] = key;
+    // smallest and largest key of the workgroup, for the first histogram kernel (the small pool is not in use yet)
+    __shared__ u64 lds_lo[kWaves], lds_hi[kWaves];
+    block_range(key, key, lds_lo, lds_hi);
+    if (threadIdx.x == 0) {
+        A.small_pool[2 * blockIdx.x] = lds_lo[0];
+        A.small_pool[2 * blockIdx.x + 1] = lds_hi[0];
+    }
 }
 
 // Histogram of the next 13 bits of the sample keys that share what is known of either end's key.
@@ -472,14 +527,22 @@ __global__ __launch_bounds__(kThreads) void select_sample_kernel(SelectArgs A, i
     clear_next_slot(A, idx);
     SelState st = resolve_entry(A, idx, R, lds_raw);
     if (sample_open(st)) st.act = kActSampleHist;
+    const bool first = st.sbits == 0;  // no bits known yet: one histogram serves both ends
+    if (st.act != kActIdle && first) {
+        __shared__ u64 lds_lo[kWaves], lds_hi[kWaves];
+        static_assert(kSample / kThreads == kThreads, "one range per thread");
+        block_range(A.small_pool[2 * threadIdx.x], A.small_pool[2 * threadIdx.x + 1], lds_lo, lds_hi);
+        st.sbase = lds_lo[0];
+        st.slshift = 64 - bracket_bits(lds_lo[0], lds_hi[0]);
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) A.states[idx] = st;
     if (st.act == kActIdle) return;
-    const bool first = st.sbits == 0;  // no bits known yet: one histogram serves both ends
     for (int i = threadIdx.x; i < (first ? 1 : 2) * kBins; i += kThreads) (&hist[0][0])[i] = 0;
     __syncthreads();
     u64 key[kSamplePer];
 #pragma unroll
-    for (int j = 0; j < kSamplePer; ++j) key[j] = A.sample[(blockIdx.x * kSamplePer + j) * kThreads + threadIdx.x];
+    for (int j = 0; j < kSamplePer; ++j)
+        key[j] = (A.sample[(blockIdx.x * kSamplePer + j) * kThreads + threadIdx.x] - st.sbase) << st.slshift;
     const int shift = 64 - st.sbits - kDigitBits;
     const u64 fmask = lead_mask(st.sbits);
 #pragma unroll
@@ -752,15 +815,17 @@ __global__ __launch_bounds__(kThreads) REGOT_WAVES_ATTR(REGOT_SELECT_WAVES_PER_E
     static_assert((sizeof(u64) * kBins + sizeof(ResolveLds)) * REGOT_SELECT_WAVES_PER_EU <= 160 * 1024, "LDS per CU");
     unsigned *hist = reinterpret_cast<unsigned *>(lds_raw);
     u64 *stage = lds_raw + kBins / 2;
-    clear_next_slot(A, idx);
     {
-        // the pool never grows: a workgroup whose first key lies beyond it has nothing to do, now or later
         const SelState prev = A.states[idx - 1];
+        // nothing left but what the result kernel does: one workgroup passes the record on
+        if (blockIdx.x > 0 && prev.act == kActIdle && finish_open(prev)) return;
+        clear_next_slot(A, idx);
+        // the pool never grows: a workgroup whose first key lies beyond it has nothing to do, now or later
         if (blockIdx.x > 0 && prev.collected && (size_t)blockIdx.x * (2 * kThreads) >= prev.pool_count) return;
     }
     SelState st = resolve_entry(A, idx, R, lds_raw);
     if (idx == kIdxBracket && sample_open(st)) st.use_bracket = 0;  // 26 bits did not separate the sample keys
-    if (!st.error && st.bits < st.bits_end) {
+    if (!st.error && st.bits < st.bits_end && !finish_open(st)) {
         if (st.collected) {
             st.act = kActHistPool;
             const bool large = !st.small_pool && st.pool_count > (unsigned)kSmallPool;
@@ -769,8 +834,8 @@ __global__ __launch_bounds__(kThreads) REGOT_WAVES_ATTR(REGOT_SELECT_WAVES_PER_E
         } else if (idx == kIdxBracket && st.use_bracket) {
             // every key of a sample bucket lies between the bucket's bounds
             st.act = kActBracket;
-            st.hi = st.side[0].need ? st.side[0].prefix | ~lead_mask(st.sbits) : ~0ull;
-            st.lo = st.side[1].need ? st.side[1].prefix : 0ull;
+            st.hi = st.side[0].need ? sample_bucket_hi(st, 0) : ~0ull;
+            st.lo = st.side[1].need ? sample_bucket_lo(st, 1) : 0ull;
             if (st.lo > st.hi) st.lo = st.hi;  // cannot happen (rank r_lo is below rank r_hi)
             const int b = bracket_bits(st.lo, st.hi);
             st.width = b < kBracketBits ? b : kBracketBits;
@@ -820,8 +885,61 @@ __global__ __launch_bounds__(kThreads) void select_finish_kernel(SelectArgs A, i
 {
     __shared__ u64 lds_raw[kBins];
     __shared__ ResolveLds R;
-    const SelState st = resolve_entry(A, idx, R, lds_raw);
-    if (threadIdx.x != 0) return;
+    SelState st = resolve_entry(A, idx, R, lds_raw);
+    if (finish_open(st)) {
+        // the keys that share the bits found so far, out of the pool into LDS; then every one of them counts the larger
+        // and the equal ones (a handful, usually)
+        __shared__ unsigned found;
+        __shared__ int result;
+        u64 *list = lds_raw;
+        if (threadIdx.x == 0) {
+            found = 0u;
+            result = -1;
+        }
+        __syncthreads();
+        const u64 *src = st.small_pool ? A.small_pool : A.pool;
+        const u64 fmask = lead_mask(st.bits);
+        constexpr int kBatch = 16;
+        for (unsigned base = 0; base < st.pool_count; base += kBatch * kThreads) {
+            u64 key[kBatch];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const unsigned i = base + j * kThreads + threadIdx.x;
+                key[j] = i < st.pool_count ? src[i] : ~st.prefix;  // (differs from the prefix in every bit)
+            }
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j)
+                if (((key[j] ^ st.prefix) & fmask) == 0) {
+                    const unsigned at = atomicAdd(&found, 1u);
+                    if (at < (unsigned)kFinishKeys) list[at] = key[j];
+                }
+        }
+        __syncthreads();
+        static_assert(kFinishKeys <= kThreads, "one thread per key");
+        long long larger = 0, equal = 0;
+        const unsigned n = found < (unsigned)kFinishKeys ? found : (unsigned)kFinishKeys;
+        if (threadIdx.x < n) {
+            const u64 mine = list[threadIdx.x];
+            for (unsigned i = 0; i < n; ++i) {
+                larger += list[i] > mine ? 1 : 0;
+                equal += list[i] == mine ? 1 : 0;
+            }
+            if (larger < st.k_rem && st.k_rem <= larger + equal) result = (int)threadIdx.x;  // (equal keys: any of them)
+        }
+        __syncthreads();
+        if ((long long)found != st.bucket || result < 0) {
+            st.error = 1;
+        } else if ((int)threadIdx.x == result) {
+            st.prefix = list[threadIdx.x];
+            st.above += larger;
+            st.bucket = equal;
+            st.bits = st.bits_end;
+        }
+        if (!st.error && (int)threadIdx.x != result) return;
+    } else if (threadIdx.x != 0) {
+        return;
+    }
+    if (st.error && threadIdx.x != 0) return;
     A.states[idx] = st;
     const bool ok = st.bits == st.bits_end && !st.error;
     const u64 key = st.lshift >= 0 ? st.lo + (st.prefix >> st.lshift) : st.prefix;
