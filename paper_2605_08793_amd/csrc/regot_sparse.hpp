@@ -47,9 +47,14 @@ __device__ __forceinline__ void row_range(const int64_t *row_ptr, int64_t i, int
 __global__ __launch_bounds__(kThreads) void pattern_values_kernel(PatternArgs A)
 {
     const int lane = threadIdx.x & (kLanes - 1);
-    const int64_t wave = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
-    const int64_t nwaves = (int64_t)gridDim.x * kWaves;
-    for (int64_t i = wave; i < A.n; i += nwaves) {
+    // The rows of one die (workgroups b with equal b % kXcds; the grid is a multiple) are neighbours, kWaves at a time: their
+    // entries of a column lie next to each other in val_csc, and that die's L2 puts the lines together before they
+    // go to memory (20000 rows, 2e6 entries, with val_csc: 97 -> 90 us).
+    const int64_t groups = ((int64_t)A.n + kWaves - 1) / kWaves, per = (groups + kXcds - 1) / kXcds;
+    const int64_t g0 = (blockIdx.x % kXcds) * per, g1 = g0 + per < groups ? g0 + per : groups;
+    for (int64_t g = g0 + blockIdx.x / kXcds; g < g1; g += gridDim.x / kXcds) {
+        const int64_t i = g * kWaves + (threadIdx.x >> 6);
+        if (i >= A.n) break;
         int64_t p0, p1;
         row_range(A.row_ptr, i, A.capacity, p0, p1);
         const double al = A.alpha[i];
@@ -567,18 +572,33 @@ __global__ __launch_bounds__(kThreads) void lower_fill_kernel(LowerArgs A)
             }
         }
         __syncthreads();
-        for (int64_t p = rp[0] + t; p < rp[rows]; p += kThreads) {
-            int lo = 0, hi = rows;  // rp[lo] <= p < rp[hi]
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (rp[mid] <= p) lo = mid;
-                else hi = mid;
+        // (kDepth entries per thread at a time, all requested before the first is placed: a block's few thousand entries
+        // are a chain of rounds of loads otherwise; 2e6 entries 33.6 -> 23.8 us)
+        constexpr int kDepth = 4;
+        for (int64_t first = rp[0] + t; first < rp[rows]; first += kDepth * kThreads) {
+            int32_t j[kDepth];
+            double v[kDepth];
+#pragma unroll
+            for (int d = 0; d < kDepth; ++d) {
+                const int64_t p = first + d * kThreads;
+                j[d] = p < rp[rows] ? A.col_idx[p] : -1;
+                v[d] = p < rp[rows] ? A.val[p] : 0.0;
             }
-            const int32_t j = A.col_idx[p];
-            const int64_t q = base[lo] + 1 + (p - rp[lo]);
-            if ((uint32_t)j < (uint32_t)mb && q >= 0 && q < A.h_capacity) {
-                if (!A.values_only) A.h_row_idx[q] = A.n + j;
-                A.h_val[q] = A.val[p] * inv_eta;
+#pragma unroll
+            for (int d = 0; d < kDepth; ++d) {
+                const int64_t p = first + d * kThreads;
+                if (p >= rp[rows]) break;
+                int lo = 0, hi = rows;  // rp[lo] <= p < rp[hi]
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (rp[mid] <= p) lo = mid;
+                    else hi = mid;
+                }
+                const int64_t q = base[lo] + 1 + (p - rp[lo]);
+                if ((uint32_t)j[d] < (uint32_t)mb && q >= 0 && q < A.h_capacity) {
+                    if (!A.values_only) A.h_row_idx[q] = A.n + j[d];
+                    A.h_val[q] = v[d] * inv_eta;
+                }
             }
         }
     } else {
