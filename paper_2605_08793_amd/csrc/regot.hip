@@ -836,14 +836,19 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
 constexpr int64_t kSweepMinEntries = 1LL << 20;
 struct SweepPlan {
     int K = 0, P = 0, width = 0;
+    void (*kernel)(SweepArgs) = nullptr;
 };
 
 SweepPlan make_sweep_plan(int64_t n, int64_t m)
 {
     SweepPlan S;
-    const int64_t K = (m + kSweepCols - 1) / kSweepCols;
-    if (n * m < kSweepMinEntries || K > kSweepMaxK || n < 64 || m < 64) return S;
+    if (n * m < kSweepMinEntries || n < 64 || m < 64) return S;
+    const int64_t K2 = (m + kSweepCols - 1) / kSweepCols, K1 = (m + kSweepCols1 - 1) / kSweepCols1;
+    const bool eight = K1 < 2 * K2 && K1 <= kSweepMaxK8 && n >= kSweepRows8 * (kNumCU / K1);
+    const int64_t K = eight ? K1 : K2;
+    if (K > kSweepMaxK) return S;
     S.K = (int)K;
+    S.kernel = eight ? sweep_pass_kernel<1, 8> : m <= kSweepCols1 ? sweep_pass_kernel<1, 4> : sweep_pass_kernel<2, 4>;
     S.P = (int)(kNumCU / K < n / 8 ? kNumCU / K : n / 8);  // (at least 4 rows each)
     S.width = (int)(((m + K - 1) / K + 1) / 2 * 2);
     return S;
@@ -874,11 +879,10 @@ int run_sweeps(const SweepPlan &Q, int64_t n, int64_t m, const double *M, int64_
     if (A.K > 1)
         hipLaunchKernelGGL(sweep_init_kernel, dim3(kNumCU), dim3(kThreads), 0, s, reinterpret_cast<unsigned long long *>(A.exch),
                            n * A.K * 2, A.ticket);
-    auto kernel = A.width <= kSweepCols / 2 ? sweep_pass_kernel<1> : sweep_pass_kernel<2>;
     const dim3 grid((unsigned)(A.P * A.K)), fin((unsigned)((m + kLanes - 1) / kLanes));
     for (int i = 0; i < sweeps; ++i) {
         if (i == 0) prof_begin(s);
-        hipLaunchKernelGGL(kernel, grid, dim3(kSweepThreads), 0, s, A);
+        hipLaunchKernelGGL(Q.kernel, grid, dim3(kSweepThreads), 0, s, A);
         if (i == 0) prof_end(s);
         hipLaunchKernelGGL(sweep_finalize_kernel, fin, dim3(kSweepFinWaves * kLanes), 0, s, A);
     }

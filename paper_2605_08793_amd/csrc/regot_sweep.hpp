@@ -13,12 +13,20 @@
 // A row of 20000 doubles is 160 KB, too much for one compute unit to hold twice (the row being worked on and the one
 // in flight) next to the column sums, so K = ceil(m / 3840) workgroups -- a cluster, one workgroup per compute unit --
 // share a block of rows, each owning `width` columns.  Fifteen waves work on the matrix: a lane owns up to 4 columns, keeps
-// their sums in registers for all rows of the block, has two batches of kSweepRows = 4 rows in registers (the one whose
-// exponentials are being formed and the one in flight) and the exponentials of the batch before in LDS.  The sixteenth wave
+// their sums in registers for all rows of the block, has two batches of 4 rows in registers (the one whose exponentials are
+// being formed and the one in flight) and the exponentials of the batch before in LDS.  The sixteenth wave
 // finds the factors a_i / S_i: it publishes the workgroup's (max, sum) per row in the workspace, reads the other members',
 // and has the time the workers take for the next batch to do it.  (It has to be a wave of its own: memory loads return in
 // order, so a wave that also streams the matrix would see the other members' numbers only behind its own prefetch.)
 // One barrier per batch.
+//
+// Where half the columns per workgroup make better use of the fifteen waves, K = ceil(m / 1920) workgroups take batches of
+// eight rows instead: 4999 columns are 2500 of 3840 in two workgroups and 1667 of 1920 in three, and a workgroup has that
+// much more in flight.  7001 x 4999 75 -> 69 us a sweep, 20000 x 4000 168 -> 151, 9000 x 9500 151 -> 141, 30000 x 1800
+// 110 -> 96.  Not where the exchange is among more than kSweepMaxK8 workgroups (9000 x 12500, seven: 189 -> 195;
+// 20000 x 20000, eleven: 607 -> 667), and not where a block has fewer than kSweepRows8 rows: a few batches of eight
+// overlap less than twice as many of four (5000 x 1900, 20 rows: 28.3 -> 29.1; 2000 x 4999, 24: 32.2 -> 33.7;
+// 8192 x 1500, 32: 32.4 -> 31.8).
 //
 // What bounds it: memory latency times what a compute unit can keep in flight, with the exponentials on top.  20000 x 20000:
 // 596 us a sweep = 5.4 TB/s of M against 975 us for the two half-steps (two reads at 6.6 TB/s); with the exponentials
@@ -35,11 +43,12 @@ namespace regot {
 constexpr int kSweepWaves = 15;                              // that work on the matrix; one more finds the factors
 constexpr int kSweepLanes = kSweepWaves * kLanes;
 constexpr int kSweepThreads = kSweepLanes + kLanes;
-constexpr int kSweepRows = 4;                               // rows of a batch
-constexpr int kSweepGroups = 2;                             // groups of 128 columns a wave can own
-constexpr int kSweepCols = kSweepWaves * 2 * kLanes * kSweepGroups;  // columns a workgroup can own (3840)
+constexpr int kSweepCols1 = kSweepWaves * 2 * kLanes;       // columns of a workgroup with one group of 128 per wave (1920)
+constexpr int kSweepCols = 2 * kSweepCols1;                 // most columns a workgroup can own: two groups per wave (3840)
+constexpr int kSweepMaxK8 = 5;                              // most members and fewest rows of a cluster whose batches are
+constexpr int kSweepRows8 = 32;                             // eight rows (see above)
 constexpr int kSweepMaxK = 16;                              // members of a cluster: one lane of a DPP row each
-static_assert(kSweepRows * 16 == kLanes && kSweepWaves <= 16, "a DPP row of 16 lanes per row of the batch");
+static_assert(kSweepWaves <= 16, "a DPP row of 16 lanes per row in sweep_factors");
 
 // What an unpublished word holds: a NaN with all bits set.  Published NaNs have other bits.
 constexpr unsigned long long kUnpublished = ~0ull;
@@ -69,32 +78,40 @@ __global__ __launch_bounds__(kThreads) void sweep_init_kernel(unsigned long long
     for (int64_t i = i0; i < words; i += (int64_t)gridDim.x * kThreads) exch[i] = kUnpublished;
 }
 
-template <int NU>
+template <int NU, int R>
 struct SweepShared {
-    dbl2 prev[kSweepRows][NU][kSweepLanes];  // a lane's exponentials of the batch before; read back by the same lane
+    dbl2 prev[R][NU][kSweepLanes];  // a lane's exponentials of the batch before; read back by the same lane
     dbl2 beta[NU][kSweepLanes];                // a lane's beta; likewise
-    dbl2 pairs[2][kSweepRows][kSweepWaves];   // (max, sum) per row and wave, by parity of the batch
-    double fac[2][kSweepRows][kSweepWaves];   // what a wave's exponentials of a row are to be multiplied by
+    dbl2 pairs[2][R][kSweepWaves];  // (max, sum) per row and wave, by parity of the batch
+    double fac[2][R][kSweepWaves];  // what a wave's exponentials of a row are to be multiplied by
     int role;
 };
 
-// Batches a cluster works through: an even number (see sweep_wave); rows beyond the last are its last row again, with a
-// factor of 0.
+// Batches a cluster works through; rows beyond the last are its last row again, with a factor of 0.  An even number of batches
+// of four: eight rows are little to round up to.
+template <int R>
 __device__ __forceinline__ int sweep_batches(int r_begin, int r_end)
 {
-    return ((r_end - r_begin + 2 * kSweepRows - 1) / (2 * kSweepRows)) * 2;
+    const int nb = (r_end - r_begin + R - 1) / R;
+    return R == 4 ? (nb + 1) & ~1 : nb;
 }
 
-// NU: groups of 128 columns per wave, group u of wave w being columns c0 + 128 (15 u + w) + 2 lane + e.
+// Reductions of 2 or 4 rows at once: row r ends up in lane 32 (r & 1) + 16 (r >> 1)
+template <typename Op>
+__device__ __forceinline__ double wave_reduce_rows(const double (&v)[2]) { return wave_reduce2<Op>(v[0], v[1]); }
+template <typename Op>
+__device__ __forceinline__ double wave_reduce_rows(const double (&v)[4]) { return wave_reduce4<Op>(v[0], v[1], v[2], v[3]); }
+
+// R: rows of a batch, G of them at a time; NU: groups of 128 columns per wave, group u of wave w being columns c0 + 128 (15 u + w) + 2 lane + e.
 // MASKED: not all of the wave's groups are full (the last columns of the member).
 // The loads of a batch are issued by every wave unconditionally and in the same number, so that waiting for one batch
 // never waits for the one requested behind it: where the member has no column a lane reads its last two again.
-template <int NU, bool MASKED>
-__device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU> &L, int cluster, int r_begin, int r_end,
+template <int NU, int R, bool MASKED>
+__device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R> &L, int cluster, int r_begin, int r_end,
                                            int c0, int ncol, int w, int lane)
 {
     typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));  // 16 bytes wherever a double may lie
-    constexpr int kStride = 2 * kLanes * kSweepWaves;
+    constexpr int kStride = 2 * kLanes * kSweepWaves, G = R / 2;
     const int first = 2 * kLanes * w + 2 * lane;
     int nu = 0;         // groups that hold any column
     unsigned off[NU];   // byte offset of the pair a lane loads
@@ -183,31 +200,33 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU> &
 
     // Batch b: its costs are in `cur`, the exponentials of batch b - 1 in `old`, those of batch b - 2 in LDS, and their
     // factors are known.  Row by row: the column sums of batch b - 2, batch b - 1 to LDS, the costs of batch b + 1 requested
-    // into its registers (behind the last batch: the last row again), and, two rows at a time, the exponentials of batch b.
+    // into its registers (behind the last batch: the last row again), and, G rows at a time, the exponentials of batch b.
     // The requests are spread over the batch because all waves are in step: requested at once they fill the memory
     // pipeline of the compute unit, and the waves wait to issue them instead of computing.
-    auto batch = [&](int b, double (&cur)[kSweepRows][NU][2], double (&old)[kSweepRows][NU][2]) {
-        const int row0 = r_begin + b * kSweepRows, par = b & 1;
+    auto batch = [&](int b, double (&cur)[R][NU][2], double (&old)[R][NU][2]) {
+        const int row0 = r_begin + b * R, par = b & 1;
 #pragma unroll
-        for (int h = 0; h < kSweepRows; h += 2) {
+        for (int h = 0; h < R; h += G) {
             auto turn = [&](int r, dbl2 (&x)[NU]) {
 #pragma unroll
                 for (int u = 0; u < NU; ++u) {
                     x[u] = L.prev[r][u][threadIdx.x];
                     L.prev[r][u][threadIdx.x] = dbl2{old[r][u][0], old[r][u][1]};
                 }
-                load_row(old[r], row0 + kSweepRows + r);
+                load_row(old[r], row0 + R + r);
                 __builtin_amdgcn_sched_barrier(0);  // (in this order: what is waited for is counted from the youngest load)
             };
             dbl2 x[NU];
             turn(h, x);
-            double lmax[2] = {-INFINITY, -INFINITY};
+            double lmax[G], lsum[G];
+#pragma unroll
+            for (int r = 0; r < G; ++r) lmax[r] = -INFINITY;
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
                 if (MASKED && u >= nu) continue;
                 const dbl2 bet = L.beta[u][threadIdx.x];
 #pragma unroll
-                for (int r = 0; r < 2; ++r) {
+                for (int r = 0; r < G; ++r) {
                     double(&c)[2] = cur[h + r][u];
                     // (the subtraction stays here: moved to where the costs are requested it would have to wait for them)
                     asm volatile("" : "+v"(c[0]), "+v"(c[1]));
@@ -220,50 +239,65 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU> &
                 }
             }
             // (at least -DBL_MAX: a segment of infinite costs gives terms 0 and an empty partial sum)
-            const double mx = fmax(wave_reduce2<OpMax>(lmax[0], lmax[1]), -kDblMax);
+            const double mx = fmax(wave_reduce_rows<OpMax>(lmax), -kDblMax);
             accumulate(x, L.fac[par][h][w]);
-            const double s0 = exponentials(cur[h], read_lane(mx, 0), row0 + h);
-            turn(h + 1, x);
-            const double s1 = exponentials(cur[h + 1], read_lane(mx, 32), row0 + h + 1);
-            accumulate(x, L.fac[par][h + 1][w]);
-            const double sm = wave_reduce2<OpSum>(s0, s1);
-            if ((lane & 31) == 0) L.pairs[par][h + (lane >> 5)][w] = dbl2{mx, sm};
+            lsum[0] = exponentials(cur[h], read_lane(mx, 0), row0 + h);
+#pragma unroll
+            for (int r = 1; r < G; ++r) {
+                turn(h + r, x);
+                lsum[r] = exponentials(cur[h + r], read_lane(mx, 32 * (r & 1) + 16 * (r >> 1)), row0 + h + r);
+                accumulate(x, L.fac[par][h + r][w]);
+            }
+            const double sm = wave_reduce_rows<OpSum>(lsum);
+            if (lane % (kLanes / G) == 0) L.pairs[par][h + quad_row(lane)][w] = dbl2{mx, sm};
         }
         __syncthreads();
     };
-    const int nb = sweep_batches(r_begin, r_end);
-    double v0[kSweepRows][NU][2], v1[kSweepRows][NU][2];
+    const int nb = sweep_batches<R>(r_begin, r_end);
+    double v0[R][NU][2], v1[R][NU][2];
 #pragma unroll
-    for (int r = 0; r < kSweepRows; ++r)
+    for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             L.prev[r][u][threadIdx.x] = dbl2{0.0, 0.0};
             v1[r][u][0] = v1[r][u][1] = 0.0;
         }
     // (the two batches before the first; read back by this wave only, before anyone writes it)
-    if (lane < 2 * kSweepRows) L.fac[lane / kSweepRows][lane % kSweepRows][w] = 0.0;
+    if (lane < 2 * R) L.fac[lane / R][lane % R][w] = 0.0;
 #pragma unroll
-    for (int r = 0; r < kSweepRows; ++r) load_row(v0[r], r_begin + r);
+    for (int r = 0; r < R; ++r) load_row(v0[r], r_begin + r);
     __builtin_amdgcn_sched_barrier(0);
-    for (int b = 0; b < nb; b += 2) {
+    for (int b = 0; b + 1 < nb; b += 2) {
         batch(b, v0, v1);
         batch(b + 1, v1, v0);
     }
-    // the last two batches: one in LDS, one in registers (nb is even: in v1)
+    if (R != 4 && (nb & 1)) {
+        batch(nb - 1, v0, v1);
+        // (copied, so that what follows is there once: written out for either, it takes registers from the loop)
 #pragma unroll
-    for (int r = 0; r < kSweepRows; ++r) {
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                v1[r][u][0] = v0[r][u][0];
+                v1[r][u][1] = v0[r][u][1];
+            }
+    }
+    // the last two batches: one in LDS, one in registers
+    const int par = (nb - 1) & 1;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
         dbl2 x[NU];
 #pragma unroll
         for (int u = 0; u < NU; ++u) x[u] = L.prev[r][u][threadIdx.x];
-        accumulate(x, L.fac[0][r][w]);
+        accumulate(x, L.fac[par ^ 1][r][w]);
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kSweepRows; ++r) {
+    for (int r = 0; r < R; ++r) {
         dbl2 x[NU];
 #pragma unroll
         for (int u = 0; u < NU; ++u) x[u] = dbl2{v1[r][u][0], v1[r][u][1]};
-        accumulate(x, L.fac[1][r][w]);
+        accumulate(x, L.fac[par][r][w]);
     }
     double *out = A.colpart + (int64_t)cluster * A.m + c0 + first;
 #pragma unroll
@@ -273,53 +307,83 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU> &
     }
 }
 
-// The factors of every batch, by one wave: lanes 16 r + j work on row r of the batch, j being a wave of the workgroup or a
-// member of the cluster.
-template <int NU>
-__device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU> &L, int member, int r_begin, int r_end, int lane)
+// The factors of every batch, by one wave: lanes 16 r + j work on rows r, r + 4 of the batch, j being a wave of the
+// workgroup or a member of the cluster.
+template <int NU, int R>
+__device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU, R> &L, int member, int r_begin, int r_end, int lane)
 {
+    constexpr int Q = R / 4;
     const int r16 = lane >> 4, j16 = lane & 15;
-    const int nb = sweep_batches(r_begin, r_end);
+    const int nb = sweep_batches<R>(r_begin, r_end);
     unsigned long long *exch = reinterpret_cast<unsigned long long *>(A.exch);
     bool waiting = true;
     __builtin_amdgcn_s_setprio(3);  // a few instructions that fifteen waves wait for (50000 x 50000: 4.23 -> 4.00 ms a sweep)
     for (int b = 0; b < nb; ++b) {
-        const int row0 = r_begin + b * kSweepRows, par = b & 1;
-        const bool live = row0 + r16 < r_end;
-        const int row = min(row0 + r16, r_end - 1);
-        const double ai = A.a[row];
+        const int par = b & 1;
+        int row[Q];
+        bool live[Q];
+        double ai[Q], mx[Q], sum[Q];
+        dbl2 mine[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            row[q] = r_begin + b * R + 4 * q + r16;
+            live[q] = row[q] < r_end;
+            row[q] = min(row[q], r_end - 1);
+            ai[q] = A.a[row[q]];
+        }
         __syncthreads();  // the workers' (max, sum) of batch b are there
-        const dbl2 mine = j16 < kSweepWaves ? L.pairs[par][r16][j16] : dbl2{-kDblMax, 0.0};
-        double mx = row16_reduce<OpMax>(mine.x);
-        double sum = row16_reduce<OpSum>(mine.y * exp_eta_any(mine.x - mx, A.ex));
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            mine[q] = j16 < kSweepWaves ? L.pairs[par][4 * q + r16][j16] : dbl2{-kDblMax, 0.0};
+            mx[q] = row16_reduce<OpMax>(mine[q].x);
+            sum[q] = row16_reduce<OpSum>(mine[q].y * exp_eta_any(mine[q].x - mx[q], A.ex));
+        }
         if (A.K > 1) {
-            unsigned long long word = (unsigned long long)__double_as_longlong(j16 == 0 ? mx : sum);
-            if (word == kUnpublished) word = 0x7ff8000000000000ull;
-            if (j16 < 2 && live)
-                __hip_atomic_store(exch + ((int64_t)row * A.K + member) * 2 + j16, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            unsigned long long x[Q], y[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                unsigned long long word = (unsigned long long)__double_as_longlong(j16 == 0 ? mx[q] : sum[q]);
+                if (word == kUnpublished) word = 0x7ff8000000000000ull;
+                if (j16 < 2 && live[q])
+                    __hip_atomic_store(exch + ((int64_t)row[q] * A.K + member) * 2 + j16, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                x[q] = y[q] = 0;
+            }
             // The other members run, or will as soon as a compute unit is free (see sweep_pass_kernel), so their words
             // arrive; the bound (4 s at 100 MHz) only keeps a workspace that someone else writes to from hanging the device.
-            const unsigned long long *src = exch + ((int64_t)row * A.K + j16) * 2;
-            const bool take = live && j16 < A.K;
-            unsigned long long x = 0, y = 0;
             const unsigned long long t0 = wall_clock64();
             for (;;) {
-                if (take) {
-                    x = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    y = __hip_atomic_load(src + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                bool missing = false;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    if (live[q] && j16 < A.K) {
+                        const unsigned long long *src = exch + ((int64_t)row[q] * A.K + j16) * 2;
+                        x[q] = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        y[q] = __hip_atomic_load(src + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
                 }
-                if (__ballot(take && (x == kUnpublished || y == kUnpublished)) == 0 || !waiting) break;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) missing = missing || x[q] == kUnpublished || y[q] == kUnpublished;
+                if (__ballot(missing) == 0 || !waiting) break;
                 if (wall_clock64() - t0 > 400000000ull) waiting = false;
             }
-            const double px = take ? __longlong_as_double((long long)x) : -kDblMax;
-            const double py = take ? __longlong_as_double((long long)y) : 0.0;
-            mx = row16_reduce<OpMax>(px);
-            sum = row16_reduce<OpSum>(py * exp_eta_any(px - mx, A.ex));
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const bool take = live[q] && j16 < A.K;
+                const double px = take ? __longlong_as_double((long long)x[q]) : -kDblMax;
+                const double py = take ? __longlong_as_double((long long)y[q]) : 0.0;
+                mx[q] = row16_reduce<OpMax>(px);
+                sum[q] = row16_reduce<OpSum>(py * exp_eta_any(px - mx[q], A.ex));
+            }
         }
-        const bool fine = sum > 0.0 && sum <= kDblMax && ai >= 0.0 && ai <= kDblMax;
-        const double scale = fine ? ai / sum : __builtin_nan("");  // NaN: every column is done again from alpha and M
-        if (j16 < kSweepWaves) L.fac[par][r16][j16] = live ? scale * exp_eta_any(mine.x - mx, A.ex) : 0.0;
-        if (b % A.K == member && j16 == 0 && live) A.alpha[row] = A.eta * log(ai) - (mx + A.eta * log(sum));
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const bool fine = sum[q] > 0.0 && sum[q] <= kDblMax && ai[q] >= 0.0 && ai[q] <= kDblMax;
+            const double scale = fine ? ai[q] / sum[q] : __builtin_nan("");  // NaN: every column is done again from alpha and M
+            if (j16 < kSweepWaves) L.fac[par][4 * q + r16][j16] = live[q] ? scale * exp_eta_any(mine[q].x - mx[q], A.ex) : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (b % A.K == member && j16 == 0 && live[q]) A.alpha[row[q]] = A.eta * log(ai[q]) - (mx[q] + A.eta * log(sum[q]));
     }
     __syncthreads();
 }
@@ -328,10 +392,11 @@ __device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU
 // workspace): only the cluster formed last can be incomplete while its members wait for each other, and the clusters
 // before it finish whatever happens, so a place for the missing members always comes free, other kernels on the device
 // or not.  Which workgroup does what has no influence on the results.
-template <int NU>
+template <int NU, int R>
 __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_kernel(SweepArgs A)
 {
-    __shared__ SweepShared<NU> L;
+    static_assert(NU * R <= 8 && (R == 4 || R == 8), "registers and LDS of a lane; rows of sweep_factors");
+    __shared__ SweepShared<NU, R> L;
     const int lane = threadIdx.x & (kLanes - 1);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (threadIdx.x == 0) {
@@ -346,11 +411,11 @@ __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_
     const int c0 = member * A.width;
     const int ncol = min(A.width, A.m - c0);
     if (w == kSweepWaves) {
-        sweep_factors<NU>(A, L, member, r_begin, r_end, lane);
+        sweep_factors<NU, R>(A, L, member, r_begin, r_end, lane);
     } else if (2 * kLanes * ((NU - 1) * kSweepWaves + w + 1) <= ncol) {  // the wave's last group is full
-        sweep_wave<NU, false>(A, L, cluster, r_begin, r_end, c0, ncol, w, lane);
+        sweep_wave<NU, R, false>(A, L, cluster, r_begin, r_end, c0, ncol, w, lane);
     } else {
-        sweep_wave<NU, true>(A, L, cluster, r_begin, r_end, c0, ncol, w, lane);
+        sweep_wave<NU, R, true>(A, L, cluster, r_begin, r_end, c0, ncol, w, lane);
     }
 }
 

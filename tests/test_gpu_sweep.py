@@ -138,3 +138,24 @@ def test_same_bits_again_and_in_a_graph():
     torch.cuda.synchronize()
     assert torch.equal(al, first[0]) and torch.equal(be, first[1])
     assert torch.equal(al2, first[0]) and torch.equal(be2, first[1])
+
+
+@pytest.mark.parametrize("n,m,shift", [
+    (8191, 257, 0), (8192, 257, 1), (8449, 1920, 0), (10241, 1919, 1),    # one member: either side of the rule; 33 rows
+    (2719, 3841, 0), (2720, 3841, 1), (2805, 5760, 0), (3001, 5759, 1),   # three members, and the two below the rule
+    (1631, 7681, 0), (1632, 7682, 0), (1700, 9599, 1), (1640, 9601, 0),   # five members; three of two groups again
+])
+def test_batches_of_eight_rows(n, m, shift):
+    """Blocks of at least 32 rows in one, three or five members: batches of eight rows, an even or an odd number of them."""
+    eta = 0.05
+    M, a, b, _, beta = W.random_small(n, m, seed=n + m, eta=eta)
+    if shift:  # also infinite costs: a segment of a row, a column but for its last entry, single entries
+        M[5, : m // 2] = INF
+        M[:-1, 7] = INF
+        M[np.arange(0, n, 3), np.arange(0, n, 3) * 13 % (m - 64) + 64] = INF
+    store = torch.full((n * m + shift,), float("nan"), dtype=torch.float64, device="cuda")
+    Md = store[shift:].view(n, m)
+    Md.copy_(dev(M))
+    got = check(M, a, b, eta, 2, beta, "eight rows", Md=Md)
+    again = sweep_gpu(Md, a, b, eta, 2, beta, dirty=False)
+    assert all(np.isfinite(x).all() and np.array_equal(x, y) for x, y in zip(got, again))
