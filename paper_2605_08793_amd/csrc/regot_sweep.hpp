@@ -102,7 +102,8 @@ __device__ __forceinline__ double wave_reduce_rows(const double (&v)[2]) { retur
 template <typename Op>
 __device__ __forceinline__ double wave_reduce_rows(const double (&v)[4]) { return wave_reduce4<Op>(v[0], v[1], v[2], v[3]); }
 
-// R: rows of a batch, G of them at a time; NU: groups of 128 columns per wave, group u of wave w being columns c0 + 128 (15 u + w) + 2 lane + e.
+// R: rows of a batch, G of them at a time.
+// NU: groups of 128 columns per wave, group u of wave w being columns c0 + 128 (15 u + w) + 2 lane + e.
 // MASKED: not all of the wave's groups are full (the last columns of the member).
 // The loads of a batch are issued by every wave unconditionally and in the same number, so that waiting for one batch
 // never waits for the one requested behind it: where the member has no column a lane reads its last two again.
