@@ -1718,14 +1718,14 @@ __device__ __forceinline__ void col_lse_pass(const Stage1Args &A, double (*lds_m
         bool any = false;
 #pragma unroll
         for (int ww = 0; ww < kWaves; ++ww)
-            if (lds_sum[ww][c] > 0.0) {
+            if (lds_sum[ww][c] != 0.0) {  // (a NaN counts: it is to come out)
                 mx = any ? fmax(mx, lds_max[ww][c]) : lds_max[ww][c];
                 any = true;
             }
         double sum = 0.0;
 #pragma unroll
         for (int ww = 0; ww < kWaves; ++ww)
-            if (lds_sum[ww][c] > 0.0) sum += lds_sum[ww][c] * exp_eta(lds_max[ww][c] - mx, A.ex);
+            if (lds_sum[ww][c] != 0.0) sum += lds_sum[ww][c] * exp_eta(lds_max[ww][c] - mx, A.ex);
         const size_t k = ((size_t)g * A.m + col0 + c) * 2;
         A.colpart[k] = mx;
         A.colpart[k + 1] = sum;
@@ -1820,7 +1820,7 @@ __device__ __forceinline__ void col_lse_strip(const Stage1Args &A, double (*lds_
 #pragma unroll
                 for (int r = 0; r < kStripRowsPerLoad; ++r) {
                     const int k = 2 * (kStripLanes * r) + c;
-                    if (lds_sum[ww][k] > 0.0) {
+                    if (lds_sum[ww][k] != 0.0) {
                         mx = any ? fmax(mx, lds_max[ww][k]) : lds_max[ww][k];
                         any = true;
                     }
@@ -1831,7 +1831,7 @@ __device__ __forceinline__ void col_lse_strip(const Stage1Args &A, double (*lds_
 #pragma unroll
                 for (int r = 0; r < kStripRowsPerLoad; ++r) {
                     const int k = 2 * (kStripLanes * r) + c;
-                    if (lds_sum[ww][k] > 0.0) sum += lds_sum[ww][k] * exp_eta(lds_max[ww][k] - mx, A.ex);
+                    if (lds_sum[ww][k] != 0.0) sum += lds_sum[ww][k] * exp_eta(lds_max[ww][k] - mx, A.ex);
                 }
             const size_t k = ((size_t)g * A.m + L.first + c) * 2;
             A.colpart[k] = mx;
@@ -1889,7 +1889,7 @@ __global__ __launch_bounds__(WAVES *kLanes) void lse_finalize_kernel(LseFinalize
     const int per = (L.parts + WAVES - 1) / WAVES;
     const int q0 = min(L.parts, sub * per), q1 = min(L.parts, q0 + per);
     const dbl2 *pairs = reinterpret_cast<const dbl2 *>(L.part);
-    // an empty partial has sum 0; a non-empty one has sum >= 1 (its maximum contributes exp(0))
+    // an empty partial has sum 0; a non-empty one has sum >= 1 (its maximum contributes exp(0)) or, with a NaN in it, NaN
     double mx = 0.0, sum = 0.0;
     if (live) {
         for (int q = q0; q < q1; q += kLseRegs) {
@@ -1897,18 +1897,18 @@ __global__ __launch_bounds__(WAVES *kLanes) void lse_finalize_kernel(LseFinalize
 #pragma unroll
             for (int j = 0; j < kLseRegs; ++j) pr[j] = q + j < q1 ? pairs[(size_t)(q + j) * L.len + i] : dbl2{0.0, 0.0};
             double nm = mx;
-            bool any = sum > 0.0;
+            bool any = sum != 0.0;
 #pragma unroll
             for (int j = 0; j < kLseRegs; ++j)
-                if (pr[j].y > 0.0) {
+                if (pr[j].y != 0.0) {
                     nm = any ? fmax(nm, pr[j].x) : pr[j].x;
                     any = true;
                 }
-            if (sum > 0.0) sum *= exp_eta(mx - nm, L.ex);  // (exactly 1 where the maximum stays)
+            if (sum != 0.0) sum *= exp_eta(mx - nm, L.ex);  // (exactly 1 where the maximum stays)
             mx = nm;
 #pragma unroll
             for (int j = 0; j < kLseRegs; ++j)
-                if (pr[j].y > 0.0) sum += pr[j].y * exp_eta(pr[j].x - mx, L.ex);
+                if (pr[j].y != 0.0) sum += pr[j].y * exp_eta(pr[j].x - mx, L.ex);
         }
     }
     lds_max[sub][l] = mx;
@@ -1919,14 +1919,14 @@ __global__ __launch_bounds__(WAVES *kLanes) void lse_finalize_kernel(LseFinalize
     mx = 0.0;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w)
-        if (lds_sum[w][l] > 0.0) {
+        if (lds_sum[w][l] != 0.0) {
             mx = any ? fmax(mx, lds_max[w][l]) : lds_max[w][l];
             any = true;
         }
     sum = 0.0;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w)
-        if (lds_sum[w][l] > 0.0) sum += lds_sum[w][l] * exp_eta(lds_max[w][l] - mx, L.ex);
+        if (lds_sum[w][l] != 0.0) sum += lds_sum[w][l] * exp_eta(lds_max[w][l] - mx, L.ex);
     L.out[i] = L.eta * log(L.marginal[i]) - (mx + L.eta * log(sum));
 }
 

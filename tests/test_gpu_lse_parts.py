@@ -40,3 +40,44 @@ def test_alpha_half_step_by_number_of_panels(m):
     dp.half_step(*(torch.from_numpy(x).cuda() for x in (M, a, alpha, beta)), eta, 0, out)
     torch.cuda.synchronize()
     assert_half_step_close(out.cpu().numpy(), oracle.sinkhorn_half_step(M, a, alpha, beta, eta, 0), eta, f"m={m}")
+
+
+def half_step(M, marginal, alpha, beta, eta, which):
+    n, m = M.shape
+    dp = DualPass(n, m)
+    out = torch.zeros(m if which else n, dtype=torch.float64, device="cuda")
+    dp.half_step(*(torch.from_numpy(x).cuda() for x in (M, marginal, alpha, beta)), eta, which, out)
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+# one part and several, of rows and of columns; the last columns by strip workgroups (1060 = 2 x 512 + 36)
+@pytest.mark.parametrize("n,m", [(16, 70), (16, 600), (48, 1060), (560, 70), (2100, 1060), (70, 512 * 33 + 5)])
+def test_a_nan_comes_out_where_it_contributes(n, m):
+    eta = 0.05
+    M, a, b, alpha, beta = W.random_small(n, m, seed=n + m, eta=eta)
+    for i, j in ((0, 0), (n // 2, m - 1), (n - 1, m // 3)):
+        X = M.copy()
+        X[i, j] = np.nan
+        for which, marginal, at in ((0, a, i), (1, b, j)):
+            got, ref = half_step(X, marginal, alpha, beta, eta, which), oracle.sinkhorn_half_step(X, marginal, alpha, beta, eta, which)
+            bad = np.arange(len(ref)) == at
+            assert np.array_equal(np.isnan(ref), bad) and np.array_equal(np.isnan(got), bad), (which, i, j)
+            assert_half_step_close(got[~bad], ref[~bad], eta, f"which={which} NaN at {i},{j}")
+
+
+def test_a_nan_and_an_empty_row_in_small_sweeps():
+    # (fewer than 2^20 entries: the half-steps one after the other)
+    n, m, eta = 900, 1000, 0.05
+    M, a, b, alpha, beta = W.random_small(n, m, seed=5, eta=eta)
+    for bad in (np.nan, np.inf):
+        X = M.copy()
+        X[411, 17 if bad != np.inf else slice(None)] = bad
+        dp = DualPass(n, m)
+        al, be = (torch.from_numpy(x.copy()).cuda() for x in (alpha, beta))
+        dp.sinkhorn_sweeps(*(torch.from_numpy(x).cuda() for x in (X, a, b)), eta, 1, al, be)
+        torch.cuda.synchronize()
+        al, be = al.cpu().numpy(), be.cpu().numpy()
+        keep = np.arange(n) != 411
+        assert_half_step_close(al[keep], oracle.sinkhorn_half_step(M, a, alpha, beta, eta, 0)[keep], eta, "rows without it")
+        assert not np.isfinite(al[411]) and np.isnan(be).all()
