@@ -4,6 +4,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "regot.h"
@@ -876,10 +877,18 @@ int run_sweeps(const SweepPlan &Q, int64_t n, int64_t m, const double *M, int64_
     A.colpart = at<double>(workspace, L.colpart);
     A.ticket = at<int>(workspace, L.header) + HDR_SWEEP_TICKET;
     A.ex = make_exp_params(eta);
+    // Workgroups per 64 columns that share the rows of columns to be done again (sweep_finalize_kernel): as many as are on
+    // the chip at once (two of 1024 threads per compute unit), but at least three, since it is rarely all columns (20000 x
+    // 20000 at eta = 1e-4 / 3e-5 813 / 1096 us with one, 646 / 976 with three; 10000 x 10000 190 / 265 with three, 179 / 297
+    // with six); at least 1024 rows for each, and as many as there is room for behind the column sums.
+    const int64_t groups = (m + kLanes - 1) / kLanes, room = (int64_t)((L.objpart - L.colpart) / (sizeof(double) * m)) - Q.P;
+    A.splits = (int)std::max<int64_t>(1, std::min({std::max<int64_t>(2 * kNumCU / groups, 3), (n + 1023) / 1024, (int64_t)kSweepMaxSplits, room / 2}));
+    A.redo = A.colpart + (int64_t)Q.P * m;
+    A.redo_count = at<int>(workspace, L.objpart);  // (three doubles per 64 columns and more)
     if (A.K > 1)
         hipLaunchKernelGGL(sweep_init_kernel, dim3(kNumCU), dim3(kThreads), 0, s, reinterpret_cast<unsigned long long *>(A.exch),
                            n * A.K * 2, A.ticket);
-    const dim3 grid((unsigned)(A.P * A.K)), fin((unsigned)((m + kLanes - 1) / kLanes));
+    const dim3 grid((unsigned)(A.P * A.K)), fin((unsigned)groups, (unsigned)A.splits);
     for (int i = 0; i < sweeps; ++i) {
         if (i == 0) prof_begin(s);
         hipLaunchKernelGGL(Q.kernel, grid, dim3(kSweepThreads), 0, s, A);

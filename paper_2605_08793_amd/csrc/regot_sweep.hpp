@@ -68,6 +68,9 @@ struct SweepArgs {
     double *exch;     // [n][K][2] published (max, sum); K > 1
     double *colpart;  // [P][m] column sums of a cluster's rows
     int *ticket;      // K > 1: number of workgroups that have started
+    int splits;       // workgroups of sweep_finalize_kernel per 64 columns
+    double *redo;     // splits > 1: [splits][2][m] (max, sum) of the columns that are done again
+    int *redo_count;  // splits > 1: [groups of 64 columns] workgroups that have written theirs
     ExpParams ex;
 };
 
@@ -161,9 +164,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R
             }
         }
         if (__ballot(not_finite(acc)) != 0) {
-            // an infinite cost or an infinite beta in the row: again from memory, with the IEEE limits of exp.  A column
-            // with beta = -inf (zero mass) has no T; what is added up for it instead is whether its costs are finite,
-            // which is all that decides its next beta.
+            // an infinite cost or an infinite beta in the row: again from memory, with the IEEE limits of exp
             acc = 0.0;
             const double *prow = M0 + (int64_t)min(row, r_end - 1) * A.ldM + first;
 #pragma unroll
@@ -173,10 +174,8 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R
                 for (int e = 0; e < 2; ++e) {
                     double t = 0.0;
                     if (first + u * kStride + e < ncol) {
-                        const double c = prow[u * kStride + e];
-                        t = exp_eta_any((bet[e] - c) - wmax, A.ex);
+                        t = exp_eta_any((bet[e] - prow[u * kStride + e]) - wmax, A.ex);
                         acc += t;
-                        if (bet[e] == -INFINITY) t = c == INFINITY ? 0.0 : c - c + 1.0;  // (NaN for NaN and -inf)
                     }
                     v[u][e] = t;
                 }
@@ -406,6 +405,8 @@ __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_
     __syncthreads();
     const int role = __builtin_amdgcn_readfirstlane(L.role);
     if (role < 0 || role >= A.P * A.K) return;
+    if (role == 0 && A.splits > 1)  // (for sweep_finalize_kernel)
+        for (int i = threadIdx.x; i < (A.m + kLanes - 1) / kLanes; i += kSweepThreads) A.redo_count[i] = 0;
     const int cluster = role / A.K, member = role - cluster * A.K;
     int r_begin, r_end;
     chunk_rows(cluster, A.P, A.n, r_begin, r_end);
@@ -422,21 +423,56 @@ __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_
 
 // Column sums over the clusters and the new beta; 64 columns per workgroup, one wave per share of the clusters.  Also
 // clears the exchange words and the counter for the next sweep.
+//
+// A column whose sum is too small is done again from alpha and M, as the beta half-step is written.  That is every column
+// whose beta is -inf (mass 0: there is no T), where one finite cost settles it, and columns so far below the others that all
+// of their T underflow: with eta = 1e-4 some in the first sweep from zero.  For those the `splits` workgroups of a group of
+// 64 columns share the rows; the last of them to be ready puts the parts together.  The others than the first see from a
+// few of the sums that there is nothing to do, nearly always, and cost next to nothing then.  Gaussian clouds in ten dimensions, one sweep from zero, us, eta = 1e-3 / 1e-4 / 3e-5: 3000^2
+// 33 / 52 / 54, 10000^2 166 / 190 / 265, 20000^2 619 / 646 / 976; by the one workgroup that has a column, row after row:
+// 33 / 352 / 340, 164 / 1190 / 1061, 616 / 2690 / 4220; the two half-steps: 53, 275, 988.
 constexpr int kSweepFinWaves = 16;
+constexpr int kSweepFinRows = 8;       // rows of a column that a lane asks for at a time
+constexpr int kSweepMaxSplits = 16;
+constexpr int kSweepMerge = 4;         // of their results asked for at a time
 
-__global__ __launch_bounds__(kSweepFinWaves *kLanes) void sweep_finalize_kernel(SweepArgs A)
+__global__ __launch_bounds__(kSweepFinWaves *kLanes) REGOT_WAVES_ATTR(8) void sweep_finalize_kernel(SweepArgs A)
 {
     __shared__ double lds_a[kSweepFinWaves][kLanes], lds_b[kSweepFinWaves][kLanes];
     __shared__ unsigned long long lds_bad;
-    const int l = threadIdx.x & (kLanes - 1), sub = threadIdx.x >> 6;
-    const int64_t j = (int64_t)blockIdx.x * kLanes + l;
+    const int l = threadIdx.x & (kLanes - 1);
+    const int sub = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int group = (int)blockIdx.x, split = (int)blockIdx.y;
+    const int64_t j = (int64_t)group * kLanes + l;
     const bool live = j < A.m;
     if (A.K > 1) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *A.ticket = 0;
-        const int64_t words = (int64_t)A.n * A.K * 2;
+        const int64_t words = split == 0 ? (int64_t)A.n * A.K * 2 : 0;
         unsigned long long *ex = reinterpret_cast<unsigned long long *>(A.exch);
         for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += (int64_t)gridDim.x * blockDim.x)
             ex[i] = kUnpublished;
+    }
+    double bo = 0.0, bj = 1.0;  // (asked for before the sums are there)
+    if (live && sub == 0 && split == 0) {
+        bo = A.beta[j];
+        bj = A.b[j];
+    }
+    if (split > 0) {
+        // nothing to do, usually: sixteen of the clusters' sums are enough to see it (a sum of all is no smaller than a part
+        // of it, up to rounding)
+        lds_a[sub][l] = live ? A.colpart[(int64_t)(sub * A.P / kSweepFinWaves) * A.m + j] : 1.0;
+        __syncthreads();
+        if (sub == 0) {
+            double c = lds_a[0][l];
+            if (A.P >= kSweepFinWaves)
+#pragma unroll
+                for (int q = 1; q < kSweepFinWaves; ++q) c += lds_a[q][l];
+            const unsigned long long open = __ballot(!(c >= 2.0 * kSweepTiny));
+            if (l == 0) lds_bad = open;
+        }
+        __syncthreads();
+        if (lds_bad == 0) return;
+        __syncthreads();
     }
     double s = 0.0;
     if (live) {
@@ -445,57 +481,98 @@ __global__ __launch_bounds__(kSweepFinWaves *kLanes) void sweep_finalize_kernel(
     }
     lds_a[sub][l] = s;
     __syncthreads();
-    double out = 0.0, bj = 0.0;
     if (sub == 0) {
         double c = lds_a[0][l];
 #pragma unroll
         for (int q = 1; q < kSweepFinWaves; ++q) c += lds_a[q][l];
-        bool ok = true;
-        if (live) {
-            const double bo = A.beta[j];
-            bj = A.b[j];
-            ok = c >= kSweepTiny && c <= kDblMax;
-            if (bo == -INFINITY) {  // no T in this column; c > 0: it has a finite cost (see sweep_wave)
-                ok = ok && bj == 0.0;
-                out = -INFINITY;
-            } else {
-                ok = ok && bo <= kDblMax;
-                out = bo + A.eta * (log(bj) - log(c));
-            }
-        }
+        // (c is NaN only where an alpha is NaN or +inf -- a NaN among a row's costs, or no finite one -- and so is then every
+        // log-sum-exp of a column: NaN is the result)
+        const bool ok = !live || c >= kSweepTiny || c != c;
+        if (live && ok && split == 0) A.beta[j] = bo + A.eta * (log(bj) - log(c));
         const unsigned long long bad = __ballot(!ok);
         if (l == 0) lds_bad = bad;
     }
     __syncthreads();
     const unsigned long long bad = lds_bad;
-    if (bad != 0) {
-        // these columns again from alpha and M: the beta half-step as it is written, relative to the running maximum
-        const bool redo = ((bad >> l) & 1) != 0;
-        double mx = -kDblMax, sum = 0.0;
-        if (redo) {
-#pragma unroll 4
-            for (int i = sub; i < A.n; i += kSweepFinWaves) {
-                const double v = A.alpha[i] - A.M[(int64_t)i * A.ldM + j];
-                const double nm = fmax(mx, v);
-                sum = sum * exp_eta_any(mx - nm, A.ex) + exp_eta_any(v - nm, A.ex);
-                mx = nm;
-            }
+    if (bad == 0) return;
+    // (the arguments from here on are fetched here: at the start, they would be in the way of what is always done)
+    typedef const __attribute__((address_space(4))) SweepArgs ArgsAt;
+    ArgsAt *at = (ArgsAt *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(at));
+    const SweepArgs C = *(const SweepArgs *)at;
+    const bool redo = ((bad >> l) & 1) != 0;
+    bj = redo ? A.b[j] : 1.0;
+    const int64_t per = ((int64_t)C.n + C.splits - 1) / C.splits, r0 = split * per, r1 = r0 + per < C.n ? r0 + per : C.n;
+    const auto *alpha = (const __attribute__((address_space(4))) double *)C.alpha;  // (complete: written by the pass)
+    double mx = -kDblMax, sum = 0.0;
+    for (int64_t i = r0 + sub; i < r1; i += kSweepFinWaves * kSweepFinRows) {
+        // (a column without mass is -inf as soon as it has one finite cost)
+        const bool need = redo && (bj != 0.0 || sum == 0.0);
+        if (__ballot(need) == 0) break;
+        double v[kSweepFinRows], nm = mx;
+        const double *src = C.M + i * C.ldM + j;
+#pragma unroll
+        for (int q = 0; q < kSweepFinRows; ++q) v[q] = need && i + q * kSweepFinWaves < r1 ? src[q * kSweepFinWaves * C.ldM] : INFINITY;
+#pragma unroll
+        for (int q = 0; q < kSweepFinRows; ++q) {
+            const int64_t row = i + q * kSweepFinWaves;
+            v[q] = alpha[row < r1 ? row : r1 - 1] - v[q];
         }
-        __syncthreads();
-        lds_a[sub][l] = mx;
-        lds_b[sub][l] = sum;
-        __syncthreads();
-        if (sub == 0 && redo) {
-            mx = lds_a[0][l];
 #pragma unroll
-            for (int q = 1; q < kSweepFinWaves; ++q) mx = fmax(mx, lds_a[q][l]);
-            sum = 0.0;
+        for (int q = 0; q < kSweepFinRows; ++q) nm = fmax(nm, v[q]);
+        if (__ballot(nm > mx) != 0) {
+            sum *= exp_eta_any(mx - nm, C.ex);
+            mx = nm;
+        }
 #pragma unroll
-            for (int q = 0; q < kSweepFinWaves; ++q) sum += lds_b[q][l] * exp_eta_any(lds_a[q][l] - mx, A.ex);
-            out = A.eta * log(bj) - (mx + A.eta * log(sum));
+        for (int q = 0; q < kSweepFinRows; ++q) {
+            const double d = v[q] - mx;
+            // (where eta is so small that columns are done again, most terms are 0)
+            if (__ballot(d * C.ex.c1 >= -1100.0) != 0) sum += exp_eta_any(d, C.ex);
         }
     }
-    if (sub == 0 && live) A.beta[j] = out;
+    __syncthreads();
+    lds_a[sub][l] = mx;
+    lds_b[sub][l] = sum;
+    __syncthreads();
+    if (sub != 0) return;
+#pragma unroll
+    for (int q = 1; q < kSweepFinWaves; ++q) mx = fmax(mx, lds_a[q][l]);
+    sum = 0.0;
+#pragma unroll
+    for (int q = 0; q < kSweepFinWaves; ++q) sum += lds_b[q][l] * exp_eta_any(lds_a[q][l] - mx, C.ex);
+    if (C.splits > 1) {
+        unsigned long long *mine = reinterpret_cast<unsigned long long *>(C.redo) + 2 * (int64_t)split * C.m + j;
+        if (redo) {
+            __hip_atomic_store(mine, (unsigned long long)__double_as_longlong(mx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(mine + C.m, (unsigned long long)__double_as_longlong(sum), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        int before = 0;
+        if (l == 0) before = __hip_atomic_fetch_add(C.redo_count + group, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_readfirstlane(before) != C.splits - 1) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        double pm[kSweepMerge];  // (requested together)
+        mx = -kDblMax;
+        sum = 0.0;
+        for (int q0 = 0; q0 < C.splits; q0 += kSweepMerge) {
+            double ps[kSweepMerge], nm = mx;
+#pragma unroll
+            for (int q = 0; q < kSweepMerge; ++q) {
+                const double *part = C.redo + 2 * (int64_t)(q0 + q) * C.m + j;
+                const bool on = redo && q0 + q < C.splits;
+                pm[q] = on ? part[0] : -kDblMax;
+                ps[q] = on ? part[C.m] : 0.0;
+            }
+#pragma unroll
+            for (int q = 0; q < kSweepMerge; ++q) nm = fmax(nm, pm[q]);
+            sum *= exp_eta_any(mx - nm, C.ex);
+            mx = nm;
+#pragma unroll
+            for (int q = 0; q < kSweepMerge; ++q) sum += ps[q] * exp_eta_any(pm[q] - mx, C.ex);
+        }
+    }
+    if (redo) A.beta[j] = A.eta * log(bj) - (mx + A.eta * log(sum));
 }
 
 }  // namespace regot

@@ -159,3 +159,38 @@ def test_batches_of_eight_rows(n, m, shift):
     got = check(M, a, b, eta, 2, beta, "eight rows", Md=Md)
     again = sweep_gpu(Md, a, b, eta, 2, beta, dirty=False)
     assert all(np.isfinite(x).all() and np.array_equal(x, y) for x, y in zip(got, again))
+
+
+# the rows of 64 columns in one workgroup's hands (1100), and shared by 3, 2, 4, 10 and 2 of them where they are done again
+@pytest.mark.parametrize("n,m", [(1100, 1300), (2113, 1000), (2050, 4500), (4097, 300), (9217, 1300), (5003, 7690)])
+def test_columns_that_are_done_again(n, m):
+    """Columns without mass next to each other and at the end, columns far below the others, columns without a finite
+    cost, a start from -inf: sums that say nothing, so that sweep_finalize_kernel goes back to alpha and M."""
+    eta = 1e-3
+    rng = np.random.default_rng(n)
+    M, a, b, _, beta = W.random_small(n, m, seed=n * m, eta=eta)
+    bz = b.copy()
+    bz[m // 4: m // 2] = 0.0; bz[m - 70:] = 0.0; bz[::11] = 0.0; bz[3] = 0.5
+    check(M, a, bz / bz.sum(), eta, 3, beta, "blocks without mass")
+    Mi = M.copy()
+    Mi[n // 3:, m // 3] = INF; Mi[: n - 1, m // 3 + 1] = INF      # one without mass whose only finite cost is the last row's
+    check(Mi, a, bz / bz.sum(), eta, 3, beta, "blocks without mass, infinite costs")
+    check(M, a, b, eta, 1, np.where(rng.random(m) < 0.3, -3.0, beta), "far below")
+    check(M, a, b, eta, 2, np.where(np.arange(m) < m // 2, -INF, beta), "from -inf")
+    x = rng.standard_normal((n, 10)); y = rng.standard_normal((m, 10)) + 0.5
+    far = (x * x).sum(1)[:, None] + (y * y).sum(1) - 2 * x @ y.T
+    far = np.ascontiguousarray(np.maximum(far, 0) / far.max())
+    for small in (1e-4, 2e-5):                                    # Gaussian clouds from zero
+        check(far, a, b, small, 2, np.zeros(m), f"clouds eta={small}")
+
+
+def test_a_column_without_a_finite_cost():
+    n, m, eta = 2113, 1000, 0.05
+    M, a, b, _, beta = W.random_small(n, m, seed=3, eta=eta)
+    M[:, 500] = INF; M[:, 501] = INF
+    b[501] = 0.0; b /= b.sum()
+    al, be = sweep_gpu(dev(M), a, b, eta, 1, beta)
+    ra, rb = oracle.sinkhorn_sweeps(M, a, b, eta, 1, np.zeros(n), beta)
+    keep = (np.arange(m) != 500) & (np.arange(m) != 501)
+    assert not np.isfinite(be[500]) and np.isnan(be[501]) and np.isnan(rb[~keep]).all()
+    assert_half_step_close(al, ra, eta, "alpha"); assert_half_step_close(be[keep], rb[keep], eta, "beta")
