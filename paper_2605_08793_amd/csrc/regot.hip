@@ -877,6 +877,8 @@ int run_sweeps(const SweepPlan &Q, int64_t n, int64_t m, const double *M, int64_
     A.colpart = at<double>(workspace, L.colpart);
     A.ticket = at<int>(workspace, L.header) + HDR_SWEEP_TICKET;
     A.ex = make_exp_params(eta);
+    A.floor = -1e44 * eta;  // (-inf for an eta above 1e264: no floor.  exp_eta gives 0 up to about 1e46 eta below the maximum)
+    A.floor_max = std::max(0.5 * A.floor, -kDblMax);
     // Workgroups per 64 columns that share the rows of columns to be done again (sweep_finalize_kernel): as many as are on
     // the chip at once (two of 1024 threads per compute unit), but at least three, since it is rarely all columns (20000 x
     // 20000 at eta = 1e-4 / 3e-5 813 / 1096 us with one, 646 / 976 with three; 10000 x 10000 190 / 265 with three, 179 / 297

@@ -194,3 +194,22 @@ def test_a_column_without_a_finite_cost():
     keep = (np.arange(m) != 500) & (np.arange(m) != 501)
     assert not np.isfinite(be[500]) and np.isnan(be[501]) and np.isnan(rb[~keep]).all()
     assert_half_step_close(al, ra, eta, "alpha"); assert_half_step_close(be[keep], rb[keep], eta, "beta")
+
+
+# one, two and five members; batches of four and of eight rows, an even and an odd number of them
+@pytest.mark.parametrize("n,m", [(1200, 1000), (283, 4500), (8449, 1920), (10241, 1919), (2805, 5760), (1700, 9599)])
+def test_infinite_terms_met_on_the_way(n, m):
+    """A wave puts a floor under its terms once it has met an infinite one: at the first row of a block, at the last, in
+    some waves and not in others, with large finite costs among them; the results do not depend on it."""
+    eta = 0.02
+    M, a, b, _, beta = W.random_small(n, m, seed=m, eta=eta)
+    clean = check(M, a, b, eta, 1, beta, "none")
+    X = M.copy()
+    X[n - 1, m - 1] = INF; X[n // 2 + 1, m // 2] = INF; X[0, 0] = INF
+    got = check(X, a, b, eta, 1, beta, "three")
+    same = np.ones(n, bool); same[[0, n // 2 + 1, n - 1]] = False
+    assert np.array_equal(got[0][same], clean[0][same])          # rows behind the first one met: bit for bit
+    X[np.arange(n)[:, None] * m // n < np.arange(m)[None, :] - m // 3] = INF
+    X[:, 5] = 1e30; X[7, m // 4: m // 2] = 1e30; X[n // 3, : m // 2] = INF
+    bz = b.copy(); bz[m // 5: m // 5 + 200] = 0.0; bz[::97] = 0.0
+    check(X, a, bz / bz.sum(), eta, 3, beta, "band, large costs, columns without mass")
