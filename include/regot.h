@@ -39,7 +39,7 @@
  *     256-byte aligned).
  *     The library allocates and frees no device memory and keeps no state that
  *     a result depends on.  (What it does keep: the event pair of
- *     regot_profile_stage1, per host thread, and the per-device address of the
+ *     regot_profile_stage1 and the number of regot_sweep_patience, per host thread, and the per-device address of the
  *     static workspace of regot_dual_eval_noalloc, looked up once.)  Inputs are
  *     never written.  Outputs must not overlap
  *     inputs or each other, except where a parameter comment allows it.
@@ -233,7 +233,9 @@ int regot_sinkhorn_half_step(int64_t n, int64_t m,
  * beta update is formed from the exponentials of the alpha update while they are on chip, which is the same update
  * up to rounding (a few 1e-16 of the duals; bit-reproducible run to run), and a column whose terms would underflow
  * that way is done again from alpha and M relative to its maximum, as in the half-step.  A NaN among the costs of a
- * row makes that row's alpha and every beta NaN there.
+ * row makes that row's alpha and every beta NaN, as it does in the half-steps.  For m > 1920 up to 16 workgroups share
+ * the rows; where they cannot run at the same time (a stream limited to a few compute units, kernels of other streams
+ * that hold the rest) the call takes longer and gives the same bits.
  */
 int regot_sinkhorn_sweeps(int64_t n, int64_t m,
                           const double *M, int64_t ldM,
@@ -555,6 +557,14 @@ int regot_placement_probe(int grid, uint32_t *ids /* device, [2 * grid] out */, 
  * The request is state of the calling host thread only.
  */
 int regot_profile_stage1(void *start_event /* host handle */, void *stop_event /* host handle */);
+
+/*
+ * Testing aid, not part of the method.  In the next regot_sinkhorn_sweeps call of the calling host thread that reads M
+ * once a sweep, a workgroup looks at most 1 + `looks` times (looks >= 0) for the numbers of the others it shares rows
+ * with before it computes them itself.  The results do not depend on it, only the time does.  State of the calling host
+ * thread only, consumed by that call.
+ */
+int regot_sweep_patience(int looks);
 
 #ifdef __cplusplus
 }

@@ -43,6 +43,7 @@ SYMBOLS = (
     "regot_pcg_solve2_reduced",
     "regot_splr_direction",
     "regot_profile_stage1",
+    "regot_sweep_patience",
     "regot_stream_read_probe",
     "regot_placement_probe",
 )
@@ -101,6 +102,7 @@ def load():
     lib.regot_pcg_solve2_reduced.argtypes = lib.regot_pcg_solve2.argtypes
     lib.regot_splr_direction.argtypes = [i64, i64, p, p, p, p, p, p, p, p, sz, p]
     lib.regot_profile_stage1.argtypes = [p, p]
+    lib.regot_sweep_patience.argtypes = [ctypes.c_int]
     lib.regot_stream_read_probe.argtypes = [i64, i64, p, i64, p, p, sz, p]
     lib.regot_placement_probe.argtypes = [ctypes.c_int, p, p]
     for name in SYMBOLS[1:]:
@@ -488,3 +490,8 @@ def regot_placement_probe(ids, *, stream=None) -> None:
     if ids.dtype != torch.int32 or not ids.is_cuda or ids.dim() != 1 or ids.numel() % 2 or not ids.is_contiguous():
         raise TypeError("ids must be a contiguous 1-D int32 CUDA tensor of even length")
     _check(load().regot_placement_probe(ids.numel() // 2, _p(ids), _stream(stream)), "regot_placement_probe")
+
+
+def regot_sweep_patience(looks: int) -> None:
+    """For tests: how often the next single-read sweeps look for other workgroups' numbers before computing them."""
+    _check(load().regot_sweep_patience(int(looks)), "regot_sweep_patience")

@@ -215,6 +215,9 @@ void prof_end(hipStream_t s)
     g_prof_start = g_prof_stop = nullptr;
 }
 
+// one-shot test hook (regot_sweep_patience): looks of the next sweeps at the words of other workgroups; < 0: as ever
+thread_local int g_sweep_looks = -1;
+
 template <typename T>
 T *at(void *ws, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(ws) + off); }
 
@@ -877,6 +880,7 @@ int run_sweeps(const SweepPlan &Q, int64_t n, int64_t m, const double *M, int64_
     A.colpart = at<double>(workspace, L.colpart);
     A.ticket = at<int>(workspace, L.header) + HDR_SWEEP_TICKET;
     A.ex = make_exp_params(eta);
+    A.looks = g_sweep_looks >= 0 ? g_sweep_looks : kSweepLooks;
     A.floor = -1e44 * eta;  // (-inf for an eta above 1e264: no floor.  exp_eta gives 0 up to about 1e46 eta below the maximum)
     A.floor_max = std::max(0.5 * A.floor, -kDblMax);
     // Workgroups per 64 columns that share the rows of columns to be done again (sweep_finalize_kernel): as many as are on
@@ -925,6 +929,13 @@ int regot_profile_stage1(void *start_event, void *stop_event)
 {
     g_prof_start = static_cast<hipEvent_t>(start_event);
     g_prof_stop = static_cast<hipEvent_t>(stop_event);
+    return REGOT_OK;
+}
+
+int regot_sweep_patience(int looks)
+{
+    if (looks < 0) return REGOT_ERR_ARG;
+    g_sweep_looks = looks;
     return REGOT_OK;
 }
 
@@ -1295,7 +1306,9 @@ int regot_sinkhorn_sweeps(int64_t n, int64_t m, const double *M, int64_t ldM, co
         const Layout L = make_layout(n, m, -1);
         st = check_workspace(workspace, workspace_bytes, L.total);
         if (st != REGOT_OK) return st;
-        return run_sweeps(Q, n, m, M, ldM, a, b, alpha, beta, eta, sweeps, workspace, L, static_cast<hipStream_t>(stream));
+        st = run_sweeps(Q, n, m, M, ldM, a, b, alpha, beta, eta, sweeps, workspace, L, static_cast<hipStream_t>(stream));
+        g_sweep_looks = -1;
+        return st;
     }
     for (int s = 0; s < sweeps; ++s) {
         int st = regot_sinkhorn_half_step(n, m, M, ldM, a, alpha, beta, eta, 0, alpha, workspace, workspace_bytes, stream);

@@ -52,6 +52,7 @@ static_assert(kSweepWaves <= 16, "a DPP row of 16 lanes per row in sweep_factors
 
 // What an unpublished word holds: a NaN with all bits set.  Published NaNs have other bits.
 constexpr unsigned long long kUnpublished = ~0ull;
+constexpr int kSweepLooks = 1 << 14;  // at the words of the other members, one to two us each, before they are done without
 
 // c_j below this is recomputed: a term lost to underflow is below 1e-307, so up to 2^31 of them are below 1e-16 of it
 constexpr double kSweepTiny = 1e-280;
@@ -68,12 +69,23 @@ struct SweepArgs {
     double *exch;     // [n][K][2] published (max, sum); K > 1
     double *colpart;  // [P][m] column sums of a cluster's rows
     int *ticket;      // K > 1: number of workgroups that have started
+    int looks;        // K > 1: kSweepLooks, or what a test asked for
     int splits;       // workgroups of sweep_finalize_kernel per 64 columns
     double *redo;     // splits > 1: [splits][2][m] (max, sum) of the columns that are done again
     int *redo_count;  // splits > 1: [groups of 64 columns] workgroups that have written theirs
     double floor, floor_max;  // see sweep_wave
     ExpParams ex;
 };
+
+// The arguments of the running kernel, fetched where this stands.  For code that hardly ever runs: what it needs would
+// otherwise be fetched when the kernel starts, and there is not room for it (0.2 us a launch).
+__device__ __forceinline__ SweepArgs sweep_args_here()
+{
+    typedef const __attribute__((address_space(4))) SweepArgs ArgsAt;
+    ArgsAt *at = (ArgsAt *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(at));
+    return *(const SweepArgs *)at;
+}
 
 __global__ __launch_bounds__(kThreads) void sweep_init_kernel(unsigned long long *exch, int64_t words, int *ticket)
 {
@@ -139,6 +151,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R
         L.beta[u][threadIdx.x] = dbl2{cv[u][0] ? src[0] : 0.0, cv[u][1] ? src[1] : 0.0};
     }
     int floor_on = 0;  // (see before the loops below)
+    double floor = -INFINITY, floor_max = -kDblMax;
 
     const double *M0 = A.M + c0;
     auto load_row = [&](double (&v)[NU][2], int row) {
@@ -238,13 +251,13 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R
 #pragma unroll
                     for (int e = 0; e < 2; ++e) {
                         c[e] = bet[e] - c[e];
-                        if constexpr (FLOOR) c[e] = c[e] < A.floor ? A.floor : c[e];
+                        if constexpr (FLOOR) c[e] = c[e] < floor ? floor : c[e];
                         if (cv[u][e]) lmax[r] = fmax(lmax[r], c[e]);
                     }
                 }
             }
             // (at least -DBL_MAX, or above the floor: a segment of infinite costs gives terms 0 and an empty partial sum)
-            const double mx = fmax(wave_reduce_rows<OpMax>(lmax), FLOOR ? A.floor_max : -kDblMax);
+            const double mx = fmax(wave_reduce_rows<OpMax>(lmax), FLOOR ? floor_max : -kDblMax);
             accumulate(x, L.fac[par][h][w]);
             lsum[0] = exponentials(cur[h], read_lane(mx, 0), row0 + h);
 #pragma unroll
@@ -290,6 +303,11 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R
         batch(std::false_type{}, b, v0, v1);
         batch(std::false_type{}, b + 1, v1, v0);
     }
+    if (b < nb) {
+        const SweepArgs C = sweep_args_here();
+        floor = C.floor;
+        floor_max = C.floor_max;
+    }
     for (; b + 1 < nb; b += 2) {
         batch(std::true_type{}, b, v0, v1);
         batch(std::true_type{}, b + 1, v1, v0);
@@ -330,6 +348,52 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R
     }
 }
 
+// (max, sum) of the 16 lanes of a DPP row, each with a pair of its own.  (The products are rounded before they are added, so
+// that two places in the code cannot differ in that.)
+__device__ __forceinline__ dbl2 merge_pairs16(dbl2 pair, const ExpParams &ex)
+{
+#pragma clang fp contract(off)
+    const double mx = row16_reduce<OpMax>(pair.x);
+    const double scaled = pair.y * exp_eta_any(pair.x - mx, ex);
+    return dbl2{mx, row16_reduce<OpSum>(scaled)};
+}
+
+// What a member publishes for a row: the (max, sum) of each of its waves as sweep_wave forms them, and of those as
+// sweep_factors does, operation by operation, by one wave.  For a member that is not there in time.
+template <int NU, int R>
+__device__ __forceinline__ dbl2 sweep_member_row(const SweepArgs &A, int row, int member, int lane)
+{
+    const int c0 = member * A.width, ncol = min(A.width, A.m - c0);
+    const double *src = A.M + (int64_t)row * A.ldM + c0, *beta = A.beta + c0;
+    dbl2 mine{-kDblMax, 0.0};
+#pragma unroll 1
+    for (int w = 0; w < kSweepWaves; ++w) {
+        double v[NU][2], all[R / 2], acc = 0.0, lmax = -INFINITY;
+        bool in[NU][2];
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int c = 2 * kLanes * (u * kSweepWaves + w) + 2 * lane + e;
+                in[u][e] = c < ncol;
+                v[u][e] = in[u][e] ? beta[c] - src[c] : 0.0;
+                if (in[u][e]) lmax = fmax(lmax, v[u][e]);
+            }
+#pragma unroll
+        for (int r = 0; r < R / 2; ++r) all[r] = lmax;
+        const double mx = fmax(wave_reduce_rows<OpMax>(all), -kDblMax);
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) acc += in[u][e] ? exp_eta_any(v[u][e] - mx, A.ex) : 0.0;
+#pragma unroll
+        for (int r = 0; r < R / 2; ++r) all[r] = acc;
+        const double sum = wave_reduce_rows<OpSum>(all);
+        if ((lane & 15) == w) mine = dbl2{mx, sum};
+    }
+    return merge_pairs16(mine, A.ex);
+}
+
 // The factors of every batch, by one wave: lanes 16 r + j work on rows r, r + 4 of the batch, j being a wave of the
 // workgroup or a member of the cluster.
 template <int NU, int R>
@@ -339,7 +403,7 @@ __device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU
     const int r16 = lane >> 4, j16 = lane & 15;
     const int nb = sweep_batches<R>(r_begin, r_end);
     unsigned long long *exch = reinterpret_cast<unsigned long long *>(A.exch);
-    bool waiting = true;
+    int patience = A.looks;
     __builtin_amdgcn_s_setprio(3);  // a few instructions that fifteen waves wait for (50000 x 50000: 4.23 -> 4.00 ms a sweep)
     for (int b = 0; b < nb; ++b) {
         const int par = b & 1;
@@ -358,8 +422,9 @@ __device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             mine[q] = j16 < kSweepWaves ? L.pairs[par][4 * q + r16][j16] : dbl2{-kDblMax, 0.0};
-            mx[q] = row16_reduce<OpMax>(mine[q].x);
-            sum[q] = row16_reduce<OpSum>(mine[q].y * exp_eta_any(mine[q].x - mx[q], A.ex));
+            const dbl2 own = merge_pairs16(mine[q], A.ex);
+            mx[q] = own.x;
+            sum[q] = own.y;
         }
         if (A.K > 1) {
             unsigned long long x[Q], y[Q];
@@ -371,10 +436,12 @@ __device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU
                     __hip_atomic_store(exch + ((int64_t)row[q] * A.K + member) * 2 + j16, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 x[q] = y[q] = 0;
             }
-            // The other members run, or will as soon as a compute unit is free (see sweep_pass_kernel), so their words
-            // arrive; the bound (4 s at 100 MHz) only keeps a workspace that someone else writes to from hanging the device.
-            const unsigned long long t0 = wall_clock64();
-            for (;;) {
+            // The other members run, or will as soon as a compute unit is free (see sweep_pass_kernel).  How long that takes is
+            // up to whatever else is on the device, so nothing depends on it: what is not there after kSweepLooks looks
+            // (some 20 ms) is computed from M, the same bits, and then after one look a batch until all are there again.
+            // (Looks, not time: a queue that is switched out does not look.)
+            bool late = false;
+            for (int left = patience;; --left) {
                 bool missing = false;
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
@@ -386,16 +453,33 @@ __device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU
                 }
 #pragma unroll
                 for (int q = 0; q < Q; ++q) missing = missing || x[q] == kUnpublished || y[q] == kUnpublished;
-                if (__ballot(missing) == 0 || !waiting) break;
-                if (wall_clock64() - t0 > 400000000ull) waiting = false;
+                late = __ballot(missing) != 0;
+                if (!late || left <= 0) break;
+            }
+            patience = late ? 0 : A.looks;
+            if (late) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    unsigned long long open = __ballot(x[q] == kUnpublished || y[q] == kUnpublished);
+                    while (open != 0) {
+                        const int at = __builtin_ctzll(open);
+                        open &= open - 1;
+                        const dbl2 pair = sweep_member_row<NU, R>(A, r_begin + b * R + 4 * q + (at >> 4), at & 15, lane);
+                        if (lane == at) {
+                            x[q] = (unsigned long long)__double_as_longlong(pair.x);
+                            y[q] = (unsigned long long)__double_as_longlong(pair.y);
+                        }
+                    }
+                }
             }
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
                 const bool take = live[q] && j16 < A.K;
                 const double px = take ? __longlong_as_double((long long)x[q]) : -kDblMax;
                 const double py = take ? __longlong_as_double((long long)y[q]) : 0.0;
-                mx[q] = row16_reduce<OpMax>(px);
-                sum[q] = row16_reduce<OpSum>(py * exp_eta_any(px - mx[q], A.ex));
+                const dbl2 whole = merge_pairs16(dbl2{px, py}, A.ex);
+                mx[q] = whole.x;
+                sum[q] = whole.y;
             }
         }
 #pragma unroll
@@ -413,8 +497,9 @@ __device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU
 
 // Which member of which cluster a workgroup is follows from the order in which the workgroups start (a counter in the
 // workspace): only the cluster formed last can be incomplete while its members wait for each other, and the clusters
-// before it finish whatever happens, so a place for the missing members always comes free, other kernels on the device
-// or not.  Which workgroup does what has no influence on the results.
+// before it finish whatever happens, so a place for the missing members comes free unless other kernels hold all that is
+// left, or the stream may use fewer compute units than a cluster has members; then they are waited for for a while and
+// done without (see sweep_factors).  Which workgroup does what has no influence on the results.
 template <int NU, int R>
 __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_kernel(SweepArgs A)
 {
@@ -428,15 +513,16 @@ __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_
     __syncthreads();
     const int role = __builtin_amdgcn_readfirstlane(L.role);
     if (role < 0 || role >= A.P * A.K) return;
-    if (role == 0 && A.splits > 1)  // (for sweep_finalize_kernel)
-        for (int i = threadIdx.x; i < (A.m + kLanes - 1) / kLanes; i += kSweepThreads) A.redo_count[i] = 0;
     const int cluster = role / A.K, member = role - cluster * A.K;
     int r_begin, r_end;
     chunk_rows(cluster, A.P, A.n, r_begin, r_end);
     const int c0 = member * A.width;
     const int ncol = min(A.width, A.m - c0);
     if (w == kSweepWaves) {
-        sweep_factors<NU, R>(A, L, member, r_begin, r_end, lane);
+        const SweepArgs C = sweep_args_here();
+        if (role == 0 && C.splits > 1)  // (for sweep_finalize_kernel)
+            for (int i = lane; i < (C.m + kLanes - 1) / kLanes; i += kLanes) C.redo_count[i] = 0;
+        sweep_factors<NU, R>(C, L, member, r_begin, r_end, lane);
     } else if (2 * kLanes * ((NU - 1) * kSweepWaves + w + 1) <= ncol) {  // the wave's last group is full
         sweep_wave<NU, R, false>(A, L, cluster, r_begin, r_end, c0, ncol, w, lane);
     } else {
@@ -518,11 +604,7 @@ __global__ __launch_bounds__(kSweepFinWaves *kLanes) REGOT_WAVES_ATTR(8) void sw
     __syncthreads();
     const unsigned long long bad = lds_bad;
     if (bad == 0) return;
-    // (the arguments from here on are fetched here: at the start, they would be in the way of what is always done)
-    typedef const __attribute__((address_space(4))) SweepArgs ArgsAt;
-    ArgsAt *at = (ArgsAt *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(at));
-    const SweepArgs C = *(const SweepArgs *)at;
+    const SweepArgs C = sweep_args_here();
     const bool redo = ((bad >> l) & 1) != 0;
     bj = redo ? A.b[j] : 1.0;
     const int64_t per = ((int64_t)C.n + C.splits - 1) / C.splits, r0 = split * per, r1 = r0 + per < C.n ? r0 + per : C.n;

@@ -492,6 +492,11 @@ def test_sinkhorn_sweeps_argument_errors(lib):
     assert sweeps(k=0, b=None) == -1 and sweeps(k=0, ld=2) == -4
 
 
+def test_sweep_patience_argument_errors(lib):
+    assert lib.regot_sweep_patience(-1) == -7
+    assert lib.regot_sweep_patience(1 << 14) == 0     # (what it is without a request)
+
+
 def test_header_is_plain_c_and_links_from_c(tmp_path):
     """include/regot.h compiles as C99 and as C++ without warnings, and a C program linked against the library can make
     the host-side calls (no GPU work is enqueued)."""

@@ -213,3 +213,22 @@ def test_infinite_terms_met_on_the_way(n, m):
     X[:, 5] = 1e30; X[7, m // 4: m // 2] = 1e30; X[n // 3, : m // 2] = INF
     bz = b.copy(); bz[m // 5: m // 5 + 200] = 0.0; bz[::97] = 0.0
     check(X, a, bz / bz.sum(), eta, 3, beta, "band, large costs, columns without mass")
+
+
+# two, three, five (batches of eight rows) and sixteen members; two of two groups of columns a wave
+@pytest.mark.parametrize("n,m", [(283, 4500), (2805, 5760), (1700, 9599), (71, 61440), (150, 7680)])
+def test_members_that_are_done_without(n, m):
+    """A workgroup that does not find another's numbers for a row computes them: at the first look, at the second, never.
+    The bits are the same, with infinite costs and columns without mass too."""
+    eta = 0.05
+    M, a, b, _, beta = W.random_small(n, m, seed=m + 1, eta=eta)
+    M[n // 2:, m // 3: m // 2] = INF; M[3, :] = INF; M[3, m - 2] = 0.4
+    b[m // 4: m // 4 + 300] = 0.0; b /= b.sum()
+    want = check(M, a, b, eta, 2, beta, "never")
+    Md = dev(M)
+    for looks in (0, 1):
+        B.regot_sweep_patience(looks)
+        got = sweep_gpu(Md, a, b, eta, 2, beta)
+        assert all(np.array_equal(x, y) for x, y in zip(got, want)), looks
+    got = sweep_gpu(Md, a, b, eta, 2, beta)          # (the request held for one call)
+    assert all(np.array_equal(x, y) for x, y in zip(got, want))
