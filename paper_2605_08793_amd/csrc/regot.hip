@@ -1348,7 +1348,7 @@ int regot_pattern_values(int64_t n, int64_t m, const double *M, int64_t ldM, con
     A.val = val;
     A.val_csc = val_csc;
     A.ex = make_exp_params(eta);
-    const int64_t want = ((n + kWaves - 1) / kWaves + kXcds - 1) / kXcds * kXcds;
+    const int64_t want = (n + kWaves - 1) / kWaves;
     const unsigned grid = (unsigned)(want < 16 * kNumCU ? want : 16 * kNumCU);
     hipLaunchKernelGGL(pattern_values_kernel, dim3(grid), dim3(kThreads), 0, static_cast<hipStream_t>(stream), A);
     return hip_status();
