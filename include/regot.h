@@ -228,8 +228,9 @@ int regot_sinkhorn_half_step(int64_t n, int64_t m,
  * of the block coordinate ascent of Sec. 1; the candidate generator of Sec. 4.3 and the start of the
  * experiments in Sec. 6.1 run a fixed number of them).  alpha [n] and beta [m] are read and replaced;
  * the first half-step does not read alpha, so it need not be initialised.  sweeps >= 0.
- * For n * m < 2^20 (and for fewer than 64 rows or columns, or more than 61440 columns) this is exactly the same
- * sequence of regot_sinkhorn_half_step calls, bit for bit.  Otherwise a sweep reads M once instead of twice: the
+ * For n * m < 2^20 (and for fewer than 64 rows or columns, more than 61440 columns, and tall narrow matrices: at
+ * least 20000 rows of at most 128 columns, 37000 of 256, 90000 of 512) this is exactly the same sequence of
+ * regot_sinkhorn_half_step calls, bit for bit.  Otherwise a sweep reads M once instead of twice: the
  * beta update is formed from the exponentials of the alpha update while they are on chip, which is the same update
  * up to rounding (a few 1e-16 of the duals; bit-reproducible run to run), and a column whose terms would underflow
  * that way is done again from alpha and M relative to its maximum, as in the half-step.  A NaN among the costs of a

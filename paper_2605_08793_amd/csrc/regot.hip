@@ -833,10 +833,16 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
 }
 
 // Whole sweeps from one read of M each (regot_sweep.hpp): the clusters for an n x m matrix, or K = 0 if the sweep is to be
-// run as its two half-steps.  The one read is the faster way at every size measured (a sweep of 1600 x 1200 13.7 us against
-// 31.6, 7001 x 4999 75 against 121, 10000^2 158 against 277, 20000^2 596 against 979, 50000^2 4.0 ms against 6.5); below
-// 2^20 entries, where what is left to gain is a launch or two, sweeps stay bit for bit the half-steps' (documented).  Also
-// the two half-steps: more columns than 16 members can own, a handful of rows or columns.
+// run as its two half-steps.  A sweep of 1600 x 1200 takes 13.7 us against 31, 7001 x 4999 69 against 119, 10000^2 157
+// against 277, 20000^2 594 against 985, 50000^2 4.0 ms against 6.5; 64 x 16500 19 against 21 us, 512 x 61440 68 against 105,
+// 1000000 x 1536 2.4 ms against 3.8.  The half-steps it is
+//   - below 2^20 entries, where sweeps stay the half-steps' bit for bit (1025 x 1024: 15 us a sweep against the half-steps' 25);
+//   - for more columns than 16 members can own, and a handful of rows or columns;
+//   - for tall and narrow matrices: a wave takes 128 columns, so fewer than five of the fifteen have work, and a row costs
+//     a compute unit the same 0.33 us whatever its length.  That meets the half-steps at 17000 rows of 64 columns (35 us
+//     both), 21000 of 128, 34000 of 160, 41000 of 256, 83000 of 320, 160000 of 384, 120000 of 448, 68000 of 512; 100000
+//     rows of 64 take 140 us against 85, 600000 rows 786 against 380 (64 columns), 773 against 553 (256), 901 against 777
+//     (512), but 922 against 1117 (576).
 constexpr int64_t kSweepMinEntries = 1LL << 20;
 struct SweepPlan {
     int K = 0, P = 0, width = 0;
@@ -847,6 +853,7 @@ SweepPlan make_sweep_plan(int64_t n, int64_t m)
 {
     SweepPlan S;
     if (n * m < kSweepMinEntries || n < 64 || m < 64) return S;
+    if (n >= (m <= 128 ? 20000 : m <= 256 ? 37000 : m <= 512 ? 90000 : INT64_MAX)) return S;
     const int64_t K2 = (m + kSweepCols - 1) / kSweepCols, K1 = (m + kSweepCols1 - 1) / kSweepCols1;
     const bool eight = K1 < 2 * K2 && K1 <= kSweepMaxK8 && n >= kSweepRows8 * (kNumCU / K1);
     const int64_t K = eight ? K1 : K2;

@@ -232,3 +232,26 @@ def test_members_that_are_done_without(n, m):
         assert all(np.array_equal(x, y) for x, y in zip(got, want)), looks
     got = sweep_gpu(Md, a, b, eta, 2, beta)          # (the request held for one call)
     assert all(np.array_equal(x, y) for x, y in zip(got, want))
+
+
+# either side of what the single read is used for: 2^20 entries, 64 rows, 64 and 61440 columns, tall narrow matrices
+@pytest.mark.parametrize("n,m,halves", [
+    (1024, 1023, True), (1024, 1024, False), (63, 17000, True), (64, 17000, False), (17000, 63, True), (17000, 64, False),
+    (64, 61441, True), (64, 61439, False), (20000, 128, True), (19999, 128, False), (20000, 129, False),
+    (37000, 256, True), (36999, 255, False), (37000, 257, False), (90000, 257, True), (20001, 70, True),
+])
+def test_which_sweeps_are_the_half_steps(n, m, halves):
+    eta, sweeps = 0.05, 2
+    M, a, b, _, beta = W.random_small(n, m, seed=n + 3 * m, eta=eta)
+    Md, ad, bd = dev(M), dev(a), dev(b)
+    got = sweep_gpu(Md, a, b, eta, sweeps, beta)
+    dp = DualPass(n, m)
+    al, be = torch.zeros(n, dtype=torch.float64, device="cuda"), dev(beta)
+    for _ in range(sweeps):
+        dp.half_step(Md, ad, al, be, eta, 0, al)
+        dp.half_step(Md, bd, al, be, eta, 1, be)
+    torch.cuda.synchronize()
+    want = (al.cpu().numpy(), be.cpu().numpy())
+    assert all(np.array_equal(x, y) for x, y in zip(got, want)) == halves
+    for x, y, what in zip(got, want, ("alpha", "beta")):
+        assert_half_step_close(x, y, eta, f"{what} n={n} m={m}")
