@@ -886,6 +886,7 @@ int run_sweeps(const SweepPlan &Q, int64_t n, int64_t m, const double *M, int64_
     A.exch = at<double>(workspace, L.rowpart);
     A.colpart = at<double>(workspace, L.colpart);
     A.ticket = at<int>(workspace, L.header) + HDR_SWEEP_TICKET;
+    A.huge = at<int>(workspace, L.header) + HDR_SWEEP_HUGE;
     A.ex = make_exp_params(eta);
     A.looks = g_sweep_looks >= 0 ? g_sweep_looks : kSweepLooks;
     A.floor = -1e44 * eta;  // (-inf for an eta above 1e264: no floor.  exp_eta gives 0 up to about 1e46 eta below the maximum)
@@ -903,6 +904,7 @@ int run_sweeps(const SweepPlan &Q, int64_t n, int64_t m, const double *M, int64_
                            n * A.K * 2, A.ticket);
     const dim3 grid((unsigned)(A.P * A.K)), fin((unsigned)groups, (unsigned)A.splits);
     for (int i = 0; i < sweeps; ++i) {
+        A.turn = i & 1;
         if (i == 0) prof_begin(s);
         hipLaunchKernelGGL(Q.kernel, grid, dim3(kSweepThreads), 0, s, A);
         if (i == 0) prof_end(s);

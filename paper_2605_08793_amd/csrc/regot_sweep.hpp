@@ -54,8 +54,11 @@ static_assert(kSweepWaves <= 16, "a DPP row of 16 lanes per row in sweep_factors
 constexpr unsigned long long kUnpublished = ~0ull;
 constexpr int kSweepLooks = 1 << 14;  // at the words of the other members, one to two us each, before they are done without
 
-// c_j below this is recomputed: a term lost to underflow is below 1e-307, so up to 2^31 of them are below 1e-16 of it
-constexpr double kSweepTiny = 1e-280;
+// c_j below this is recomputed: what underflow takes from a term is below 3e-308 kSweepHuge, so from up to 2^31 of them
+// less than 1e-16 of it.  Where a row's mass is beyond kSweepHuge (marginals are not asked to sum to 1), every column is.
+constexpr double kSweepTiny = 1e-250;
+constexpr double kSweepHuge = 1e30;
+constexpr int kSweepHugeMark = 0x48554745;
 
 struct SweepArgs {
     int n, m;
@@ -75,6 +78,8 @@ struct SweepArgs {
     int *redo_count;  // splits > 1: [groups of 64 columns] workgroups that have written theirs
     double floor, floor_max;  // see sweep_wave
     ExpParams ex;
+    int *huge;        // [2] kSweepHugeMark in [turn]: a mass beyond kSweepHuge was met
+    int turn;         // parity of the sweep
 };
 
 // The arguments of the running kernel, fetched where this stands.  For code that hardly ever runs: what it needs would
@@ -100,7 +105,7 @@ struct SweepShared {
     dbl2 beta[NU][kSweepLanes];                // a lane's beta; likewise
     dbl2 pairs[2][R][kSweepWaves];  // (max, sum) per row and wave, by parity of the batch
     double fac[2][R][kSweepWaves];  // what a wave's exponentials of a row are to be multiplied by
-    int role;
+    int role, huge;                 // (huge: a row's mass is beyond kSweepHuge)
 };
 
 // Batches a cluster works through; rows beyond the last are its last row again, with a factor of 0.  An even number of batches
@@ -333,12 +338,19 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R
         accumulate(x, L.fac[par ^ 1][r][w]);
     }
     __syncthreads();
+    const int huge = L.huge;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         dbl2 x[NU];
 #pragma unroll
         for (int u = 0; u < NU; ++u) x[u] = dbl2{v1[r][u][0], v1[r][u][1]};
         accumulate(x, L.fac[par][r][w]);
+    }
+    if (__builtin_amdgcn_readfirstlane(huge) != 0) {  // these sums are not to be used
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) csum[u][e] = csum[u][e] == csum[u][e] ? -INFINITY : csum[u][e];
     }
     double *out = A.colpart + (int64_t)cluster * A.m + c0 + first;
 #pragma unroll
@@ -404,6 +416,13 @@ __device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU
     const int nb = sweep_batches<R>(r_begin, r_end);
     unsigned long long *exch = reinterpret_cast<unsigned long long *>(A.exch);
     int patience = A.looks;
+    // (now, while the workers wait for their first rows)
+    bool huge = false;
+    for (int i = r_begin + lane; i < r_end; i += kLanes) huge = huge || A.a[i] > kSweepHuge;
+    if (__ballot(huge) != 0 && lane == 0) {
+        L.huge = 1;
+        A.huge[A.turn] = kSweepHugeMark;
+    }
     __builtin_amdgcn_s_setprio(3);  // a few instructions that fifteen waves wait for (50000 x 50000: 4.23 -> 4.00 ms a sweep)
     for (int b = 0; b < nb; ++b) {
         const int par = b & 1;
@@ -508,6 +527,7 @@ __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_
     const int lane = threadIdx.x & (kLanes - 1);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (threadIdx.x == 0) {
+        L.huge = 0;
         L.role = A.K > 1 ? atomicAdd(A.ticket, 1) : (int)blockIdx.x;
     }
     __syncthreads();
@@ -520,6 +540,7 @@ __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_
     const int ncol = min(A.width, A.m - c0);
     if (w == kSweepWaves) {
         const SweepArgs C = sweep_args_here();
+        if (role == 0 && lane == 0) C.huge[C.turn ^ 1] = 0;  // (last read behind the sweep before)
         if (role == 0 && C.splits > 1)  // (for sweep_finalize_kernel)
             for (int i = lane; i < (C.m + kLanes - 1) / kLanes; i += kLanes) C.redo_count[i] = 0;
         sweep_factors<NU, R>(C, L, member, r_begin, r_end, lane);
@@ -567,6 +588,7 @@ __global__ __launch_bounds__(kSweepFinWaves *kLanes) REGOT_WAVES_ATTR(8) void sw
         bj = A.b[j];
     }
     if (split > 0) {
+        const int huge = A.huge[A.turn];
         // nothing to do, usually: sixteen of the clusters' sums are enough to see it (a sum of all is no smaller than a part
         // of it, up to rounding)
         lds_a[sub][l] = live ? A.colpart[(int64_t)(sub * A.P / kSweepFinWaves) * A.m + j] : 1.0;
@@ -576,7 +598,7 @@ __global__ __launch_bounds__(kSweepFinWaves *kLanes) REGOT_WAVES_ATTR(8) void sw
             if (A.P >= kSweepFinWaves)
 #pragma unroll
                 for (int q = 1; q < kSweepFinWaves; ++q) c += lds_a[q][l];
-            const unsigned long long open = __ballot(!(c >= 2.0 * kSweepTiny));
+            const unsigned long long open = __ballot(!(c >= 2.0 * kSweepTiny) || huge == kSweepHugeMark);
             if (l == 0) lds_bad = open;
         }
         __syncthreads();

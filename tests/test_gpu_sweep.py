@@ -255,3 +255,19 @@ def test_which_sweeps_are_the_half_steps(n, m, halves):
     assert all(np.array_equal(x, y) for x, y in zip(got, want)) == halves
     for x, y, what in zip(got, want, ("alpha", "beta")):
         assert_half_step_close(x, y, eta, f"{what} n={n} m={m}")
+
+
+@pytest.mark.parametrize("n,m", [(1100, 1000), (2113, 1000), (283, 4500)])
+@pytest.mark.parametrize("big", [1e20, 1e60, 1e300])
+def test_masses_far_from_one(n, m, big):
+    """Marginals need not sum to 1: a column whose sum looks fine although what underflowed in the rows of large mass is
+    far more than what is there, sums that overflow, and very small masses."""
+    eta = 1e-3
+    M, a, b, _, beta = W.random_small(n, m, seed=n, eta=eta)
+    M *= 0.1; beta *= 0.0
+    a = a * n * big
+    a[0] = 1e-270                                      # one row of next to no mass ...
+    M[1:, 17] = 0.7465 + 1e-4 * M[1:, 17]; M[0, 17] = 0.0   # ... has nearly all of what can be seen of column 17
+    check(M, a, b, eta, 1, beta, f"mass {big}")
+    check(M, a, b * m * big, eta, 3, beta, f"mass {big}, three sweeps")
+    check(M, np.full(n, 1e-290), np.full(m, 1e-300), eta, 2, beta, "small masses")
