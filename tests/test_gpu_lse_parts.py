@@ -81,3 +81,19 @@ def test_a_nan_and_an_empty_row_in_small_sweeps():
         keep = np.arange(n) != 411
         assert_half_step_close(al[keep], oracle.sinkhorn_half_step(M, a, alpha, beta, eta, 0)[keep], eta, "rows without it")
         assert not np.isfinite(al[411]) and np.isnan(be).all()
+
+
+@pytest.mark.parametrize("far", [1e30, 1e120, 1e300])
+@pytest.mark.parametrize("n,m", [(48, 1060), (2100, 1060), (70, 512 * 33 + 5)])
+def test_parts_any_distance_apart(n, m, far):
+    """Parts that hold nothing but very large finite costs beside ordinary ones, in the merges of waves, strips and parts."""
+    eta = 0.05
+    M, a, b, alpha, beta = W.random_small(n, m, seed=n * m, eta=eta)
+    M[:, : m // 2] = far; M[0, 3] = 0.2
+    for which, marginal in ((0, a), (1, b)):
+        X = M if which == 0 else np.ascontiguousarray(M[:, ::-1])
+        if which:
+            X[: n // 2, m // 3:] = far; X[n - 1] = 0.5
+        ref = oracle.sinkhorn_half_step(X, marginal, alpha, beta, eta, which)
+        assert np.isfinite(ref).all()
+        assert_half_step_close(half_step(X, marginal, alpha, beta, eta, which), ref, eta, f"which={which} far={far}")
