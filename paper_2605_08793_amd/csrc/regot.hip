@@ -551,7 +551,7 @@ int64_t refresh_candidate_capacity(int64_t n, int64_t m, int64_t k)
     const double nm = (double)n * (double)m;
     const double ks = (double)k * (double)kSample / nm;
     const double sg = sqrt(fmax(ks * (1.0 - ks / (double)kSample), 1.0));
-    double r_lo = ceil(ks + kBracketZ * sg) + 1.0 + 2.0 * kSampleFew;
+    double r_lo = ceil(ks + kBracketZ * sg) + 1.0 + kSampleFew;
     if (r_lo > (double)kSample) r_lo = (double)kSample;
     double cap = 1.25 * r_lo / (double)kSample * nm + 65536.0;
     if (cap > nm) cap = nm;

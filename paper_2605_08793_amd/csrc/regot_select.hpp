@@ -49,7 +49,7 @@ constexpr int kSampleSlots = 2;             // two more slots: second sample his
 constexpr int kSampleLog2 = 16;
 constexpr int kSample = 1 << kSampleLog2;   // sampled entries
 constexpr int kSamplePasses = 2;            // histogram kernels over the sample: its keys are located to 26 bits
-constexpr int kSampleFew = 4;               // a sample bucket of twice this many keys is not refined further
+constexpr int kSampleFew = 8;               // a sample bucket of this many keys is not refined further
 constexpr int kFinishKeys = 256;            // the result kernel selects among this many keys by itself ...
 constexpr int kFinishPool = 1 << 14;        // ... out of a pool of at most this many (step kernels then return at once)
 constexpr double kBracketZ = 5.0;           // half-width of the bracket in standard deviations of the sample rank
@@ -338,8 +338,8 @@ __device__ __forceinline__ SelState start_state(const SelectArgs &A)
 // does the sample search still have something to narrow down
 __device__ __forceinline__ bool sample_open(const SelState &st)
 {
-    return st.use_bracket && ((st.side[0].need && st.side[0].bucket > (unsigned)(2 * kSampleFew)) ||
-                              (st.side[1].need && st.side[1].bucket > (unsigned)(2 * kSampleFew)));
+    return st.use_bracket && ((st.side[0].need && st.side[0].bucket > (unsigned)kSampleFew) ||
+                              (st.side[1].need && st.side[1].bucket > (unsigned)kSampleFew));
 }
 
 // State at the entry of kernel idx (>= 1), from the record of kernel idx - 1 and what that kernel
