@@ -57,6 +57,11 @@ __device__ __forceinline__ double exp_eta_any(double s, const ExpParams &P)
     return t < -1100.0 ? 0.0 : (t > 1100.0 ? __builtin_inf() : e);
 }
 
+// The same for a d that is not above 0 by much: what a sum is to be multiplied by when it is brought from one maximum to
+// another, which may lie any distance apart.  One operation more than exp_eta.  (A NaN gives 0: such a d is the difference
+// of two infinite maxima, whose sum is NaN.)
+__device__ __forceinline__ double exp_eta_below(double d, const ExpParams &P) { return exp_eta(fmax(d, -1100.0 * P.l), P); }
+
 // true for NaN and for +-inf
 __device__ __forceinline__ bool not_finite(double x) { return !(__builtin_fabs(x) < __builtin_inf()); }
 

@@ -1725,7 +1725,7 @@ __device__ __forceinline__ void col_lse_pass(const Stage1Args &A, double (*lds_m
         double sum = 0.0;
 #pragma unroll
         for (int ww = 0; ww < kWaves; ++ww)
-            if (lds_sum[ww][c] != 0.0) sum += lds_sum[ww][c] * exp_eta_any(lds_max[ww][c] - mx, A.ex);
+            if (lds_sum[ww][c] != 0.0) sum += lds_sum[ww][c] * exp_eta_below(lds_max[ww][c] - mx, A.ex);
         const size_t k = ((size_t)g * A.m + col0 + c) * 2;
         A.colpart[k] = mx;
         A.colpart[k + 1] = sum;
@@ -1831,7 +1831,7 @@ __device__ __forceinline__ void col_lse_strip(const Stage1Args &A, double (*lds_
 #pragma unroll
                 for (int r = 0; r < kStripRowsPerLoad; ++r) {
                     const int k = 2 * (kStripLanes * r) + c;
-                    if (lds_sum[ww][k] != 0.0) sum += lds_sum[ww][k] * exp_eta_any(lds_max[ww][k] - mx, A.ex);
+                    if (lds_sum[ww][k] != 0.0) sum += lds_sum[ww][k] * exp_eta_below(lds_max[ww][k] - mx, A.ex);
                 }
             const size_t k = ((size_t)g * A.m + L.first + c) * 2;
             A.colpart[k] = mx;
@@ -1904,11 +1904,11 @@ __global__ __launch_bounds__(WAVES *kLanes) void lse_finalize_kernel(LseFinalize
                     nm = any ? fmax(nm, pr[j].x) : pr[j].x;
                     any = true;
                 }
-            if (sum != 0.0) sum *= exp_eta_any(mx - nm, L.ex);  // (exactly 1 where the maximum stays; maxima may lie any distance apart)
+            if (sum != 0.0) sum *= exp_eta_below(mx - nm, L.ex);  // (exactly 1 where the maximum stays; maxima may lie any distance apart)
             mx = nm;
 #pragma unroll
             for (int j = 0; j < kLseRegs; ++j)
-                if (pr[j].y != 0.0) sum += pr[j].y * exp_eta_any(pr[j].x - mx, L.ex);
+                if (pr[j].y != 0.0) sum += pr[j].y * exp_eta_below(pr[j].x - mx, L.ex);
         }
     }
     lds_max[sub][l] = mx;
@@ -1926,7 +1926,7 @@ __global__ __launch_bounds__(WAVES *kLanes) void lse_finalize_kernel(LseFinalize
     sum = 0.0;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w)
-        if (lds_sum[w][l] != 0.0) sum += lds_sum[w][l] * exp_eta_any(lds_max[w][l] - mx, L.ex);
+        if (lds_sum[w][l] != 0.0) sum += lds_sum[w][l] * exp_eta_below(lds_max[w][l] - mx, L.ex);
     L.out[i] = L.eta * log(L.marginal[i]) - (mx + L.eta * log(sum));
 }
 

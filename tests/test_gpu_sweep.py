@@ -67,7 +67,7 @@ def test_rows_off_16_byte_boundaries(n, m, ld, shift):
     store = torch.full((n * ld + shift,), float("nan"), dtype=torch.float64, device="cuda")
     Md = store[shift:].as_strided((n, m), (ld, 1), storage_offset=shift)
     Md.copy_(dev(M))
-    # one buffer that ends with the last entry of M: nothing behind it may be read
+    # (what lies between the rows and around them is NaN: a read there must not enter a result)
     check(M, a, b, eta, 2, beta, "unaligned", Md=Md)
 
 
