@@ -7,8 +7,9 @@
 //     T_ij = exp((alpha_i + beta_j - M_ij) / eta) = e_ij a_i / S_i,
 // one multiplication instead of another exponential, and with c_j = sum_i T_ij the exact maximiser in beta is
 //     beta_j + eta (log b_j - log c_j).
-// T_ij <= a_i, so nothing overflows; a column whose c_j is so small that terms may have been lost to underflow (or whose
-// old beta is not finite) is done again from alpha and M in the log domain (sweep_finalize_kernel).
+// T_ij <= a_i, so nothing overflows for masses that are anywhere near 1; a column whose c_j is so small that terms may have
+// been lost to underflow, or that has no T (beta = -inf), is done again from alpha and M in the log domain
+// (sweep_finalize_kernel).
 //
 // A row of 20000 doubles is 160 KB, too much for one compute unit to hold twice (the row being worked on and the one
 // in flight) next to the column sums, so K = ceil(m / 3840) workgroups -- a cluster, one workgroup per compute unit --
@@ -557,10 +558,11 @@ __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_
 // A column whose sum is too small is done again from alpha and M, as the beta half-step is written.  That is every column
 // whose beta is -inf (mass 0: there is no T), where one finite cost settles it, and columns so far below the others that all
 // of their T underflow: with eta = 1e-4 some in the first sweep from zero.  For those the `splits` workgroups of a group of
-// 64 columns share the rows; the last of them to be ready puts the parts together.  The others than the first see from a
-// few of the sums that there is nothing to do, nearly always, and cost next to nothing then.  Gaussian clouds in ten dimensions, one sweep from zero, us, eta = 1e-3 / 1e-4 / 3e-5: 3000^2
-// 33 / 52 / 54, 10000^2 166 / 190 / 265, 20000^2 619 / 646 / 976; by the one workgroup that has a column, row after row:
-// 33 / 352 / 340, 164 / 1190 / 1061, 616 / 2690 / 4220; the two half-steps: 53, 275, 988.
+// 64 columns share the rows; the last of them to be ready puts the parts together.  All but the first see from a few of
+// the sums that there is nothing to do, nearly always, and cost next to nothing then.  Gaussian clouds in ten dimensions,
+// one sweep from zero, us, eta = 1e-3 / 1e-4 / 3e-5: 3000^2 33 / 52 / 54, 10000^2 166 / 190 / 265, 20000^2 619 / 646 /
+// 976; by the one workgroup that has a column, row after row: 33 / 352 / 340, 164 / 1190 / 1061, 616 / 2690 / 4220; the
+// two half-steps: 53, 275, 988.
 constexpr int kSweepFinWaves = 16;
 constexpr int kSweepFinRows = 8;       // rows of a column that a lane asks for at a time
 constexpr int kSweepMaxSplits = 16;
