@@ -57,8 +57,8 @@ constexpr int kSweepLooks = 1 << 14;  // at the words of the other members, one 
 
 // c_j below this is recomputed: what underflow takes from a term is below 3e-308 kSweepHuge, so from up to 2^31 of them
 // less than 1e-16 of it.  Where a row's mass is beyond kSweepHuge (marginals are not asked to sum to 1), every column is.
-constexpr double kSweepTiny = 1e-250;
-constexpr double kSweepHuge = 1e30;
+constexpr double kSweepTiny = 1e-270;
+constexpr double kSweepHuge = 1e12;
 constexpr int kSweepHugeMark = 0x48554745;
 
 struct SweepArgs {
