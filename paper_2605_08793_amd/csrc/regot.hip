@@ -15,6 +15,8 @@
 #include "regot_refresh.hpp"
 #include "regot_sparse.hpp"
 #include "regot_pcg.hpp"
+#include "regot_schur.hpp"
+#include "regot_schur_wide.hpp"
 
 using namespace regot;
 
@@ -587,7 +589,7 @@ PcgLayout make_pcg_layout(int64_t n, int64_t m)
     L.Ap = take(N * kPcgMaxRhs * sizeof(double));
     // (the partial sums of the combination use the same region)
     L.part = take((size_t)(kCombineDots > kPcgPartRows ? kCombineDots : kPcgPartRows) * kPcgParts * sizeof(double));
-    L.sc = take(2 * sizeof(PcgScalars<kPcgMaxRhs>));
+    L.sc = take(std::max(2 * sizeof(PcgScalars<kPcgMaxRhs>), 2 * kPcgMaxRhs * sizeof(SchurState)));
     L.total = off;
     return L;
 }
@@ -686,36 +688,15 @@ int run_pcg(int64_t n, int64_t m, double eta, double tau, const int64_t *row_ptr
     return hip_status();
 }
 
-// regot_pcg_solve_reduced (R = 1) and regot_pcg_solve2_reduced (R = 2): conjugate gradients on the Schur
-// complement of the first block
+// The reduced solve where both blocks are longer than kSchurCap (regot_schur_wide.hpp); the arguments have been checked.
 template <int R>
-int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t *row_ptr, const int32_t *col_idx,
-                    const double *val, const int64_t *col_ptr, const int32_t *row_idx, const double *val_csc,
-                    int64_t capacity, const double *row_sum, const double *col_sum, const double *const (&rhs)[R],
-                    double *const (&x)[R], double rtol, int iterations, int restart, double *info, void *workspace,
-                    size_t workspace_bytes, regot_stream_t stream)
+int run_pcg_wide(int64_t n, int64_t m, double eta, double tau, const int64_t *row_ptr, const int32_t *col_idx, const double *val,
+                 const int64_t *col_ptr, const int32_t *row_idx, const double *val_csc, int64_t capacity, const double *row_sum,
+                 const double *col_sum, const double *const (&rhs)[R], double *const (&x)[R], double rtol, int iterations,
+                 int restart, double *info, void *workspace, const PcgLayout &L, regot_stream_t stream)
 {
-    if (n < 1 || m < 1 || n > kMaxDim || m > kMaxDim) return REGOT_ERR_DIM;
-    if (!(eta > 0.0) || !isfinite(eta)) return REGOT_ERR_ETA;
-    if (capacity < 0 || tau != tau || !(rtol >= 0.0) || iterations < 0 || iterations > 100000 ||
-        (restart != 0 && restart != 1))
-        return REGOT_ERR_ARG;
-    if (!row_ptr || !col_ptr || !row_sum || !col_sum || !info) return REGOT_ERR_NULL;
-    for (int k = 0; k < R; ++k) {
-        if (!rhs[k] || !x[k]) return REGOT_ERR_NULL;
-        if (misaligned(rhs[k], 8) || misaligned(x[k], 8)) return REGOT_ERR_ALIGN;
-    }
-    if (capacity > 0 && (!col_idx || !val || !row_idx || !val_csc)) return REGOT_ERR_NULL;
-    if (misaligned(row_ptr, 8) || misaligned(col_ptr, 8) || misaligned(val, 8) || misaligned(val_csc, 8) ||
-        misaligned(row_sum, 8) || misaligned(col_sum, 8) || misaligned(info, 8) || misaligned(col_idx, 4) ||
-        misaligned(row_idx, 4))
-        return REGOT_ERR_ALIGN;
-    const PcgLayout L = make_pcg_layout(n, m);
-    const int st = check_workspace(workspace, workspace_bytes, L.total);
-    if (st != REGOT_OK) return st;
-
     const int64_t mb = m - 1, N = n + mb;
-    SchurArgs<R> S{};
+    WideArgs<R> S{};
     S.mv.n = (int)n;
     S.mv.m = (int)m;
     S.mv.eta = eta;
@@ -766,12 +747,11 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
     V.vec_blocks = (int)vb;
     int64_t nb = (N + kThreads - 1) / kThreads;
     if (nb > kPcgParts) nb = kPcgParts;
-    const bool all = n * R <= kMatvecLdsCap && mb * R <= kMatvecLdsCap;  // either half fits the LDS
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     // packed vectors go in own[0] / out[0]
     auto half = [&](int mode, const double *in, const double *const (&own)[R], double *const (&out)[R], const int *skip) {
-        SchurArgs<R> H = S;
+        WideArgs<R> H = S;
         H.in = in;
         for (int k = 0; k < R; ++k) {
             H.own[k] = own[k];
@@ -779,17 +759,13 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
         }
         H.dot_part = V.part;
         H.skip = skip;
-        const dim3 grid(mode == kSchurRows || mode == kSchurRowsFinal ? row_wg : col_wg), block(kMatvecLdsThreads);
-#define REGOT_SCHUR_LAUNCH(MODE)                                                                  \
-    if (all) hipLaunchKernelGGL((schur_half_kernel<MODE, R, true>), grid, block, 0, s, H);       \
-    else hipLaunchKernelGGL((schur_half_kernel<MODE, R, false>), grid, block, 0, s, H)
+        const dim3 grid(mode == kWideRows || mode == kWideRowsFinal ? row_wg : col_wg), block(kMatvecLdsThreads);
         switch (mode) {
-        case kSchurRows: REGOT_SCHUR_LAUNCH(kSchurRows); break;
-        case kSchurRowsFinal: REGOT_SCHUR_LAUNCH(kSchurRowsFinal); break;
-        case kSchurCols: REGOT_SCHUR_LAUNCH(kSchurCols); break;
-        default: REGOT_SCHUR_LAUNCH(kSchurColsRhs); break;
+        case kWideRows: hipLaunchKernelGGL((wide_half_kernel<kWideRows, R>), grid, block, 0, s, H); break;
+        case kWideRowsFinal: hipLaunchKernelGGL((wide_half_kernel<kWideRowsFinal, R>), grid, block, 0, s, H); break;
+        case kWideCols: hipLaunchKernelGGL((wide_half_kernel<kWideCols, R>), grid, block, 0, s, H); break;
+        default: hipLaunchKernelGGL((wide_half_kernel<kWideColsRhs, R>), grid, block, 0, s, H); break;
         }
-#undef REGOT_SCHUR_LAUNCH
     };
     const double *none[R] = {};
     const double *g1[R], *g2[R], *p_packed[R] = {};
@@ -804,7 +780,7 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
     u_packed[0] = u;
     Ap_packed[0] = V.Ap;
     if (restart) {
-        SchurPrepareArgs<R> P{};
+        WidePrepareArgs<R> P{};
         P.n = n;
         P.N = N;
         for (int k = 0; k < R; ++k) P.rhs[k] = rhs[k];
@@ -813,22 +789,126 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
         P.tau = tau;
         P.u = u;
         P.part = V.part;
-        hipLaunchKernelGGL((schur_prepare_kernel<R>), dim3((unsigned)nb), dim3(kThreads), 0, s, P);
-        half(kSchurColsRhs, u, g2, rs, nullptr);
+        hipLaunchKernelGGL((wide_prepare_kernel<R>), dim3((unsigned)nb), dim3(kThreads), 0, s, P);
+        half(kWideColsRhs, u, g2, rs, nullptr);
         hipLaunchKernelGGL((pcg_start_kernel<R>), dim3((unsigned)vb), dim3(kThreads), 0, s, V);
         hipLaunchKernelGGL((pcg_start_scalars_kernel<R>), dim3(1), dim3(kThreads), 0, s, V, (int)nb);
     }
     for (int it = 0; it < iterations; ++it) {
         const int *skip = reinterpret_cast<const int *>(at<char>(workspace, L.sc) + (it & 1) * sizeof(PcgScalars<R>) +
                                                         offsetof(PcgScalars<R>, all_done));
-        half(kSchurRows, V.p, none, u_packed, skip);
-        half(kSchurCols, u, p_packed, Ap_packed, skip);
+        half(kWideRows, V.p, none, u_packed, skip);
+        half(kWideCols, u, p_packed, Ap_packed, skip);
         hipLaunchKernelGGL((pcg_update_kernel<R>), dim3((unsigned)vb), dim3(kThreads), 0, s, V, it);
         hipLaunchKernelGGL((pcg_direction_kernel<R>), dim3((unsigned)vb), dim3(kThreads), 0, s, V, it);
     }
     // the first blocks of the solutions for the second blocks as they stand, and the record of the iteration
-    half(kSchurRowsFinal, V.x, g1, x1, nullptr);
+    half(kWideRowsFinal, V.x, g1, x1, nullptr);
     hipLaunchKernelGGL((pcg_finish_kernel<R>), dim3(R == 1 ? 1u : (unsigned)vb), dim3(kThreads), 0, s, V, iterations);
+    return hip_status();
+}
+
+// regot_pcg_solve_reduced (R = 1) and regot_pcg_solve2_reduced (R = 2): conjugate gradients on the Schur
+// complement of the first block
+template <int R>
+int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t *row_ptr, const int32_t *col_idx,
+                    const double *val, const int64_t *col_ptr, const int32_t *row_idx, const double *val_csc,
+                    int64_t capacity, const double *row_sum, const double *col_sum, const double *const (&rhs)[R],
+                    double *const (&x)[R], double rtol, int iterations, int restart, double *info, void *workspace,
+                    size_t workspace_bytes, regot_stream_t stream)
+{
+    if (n < 1 || m < 1 || n > kMaxDim || m > kMaxDim) return REGOT_ERR_DIM;
+    if (!(eta > 0.0) || !isfinite(eta)) return REGOT_ERR_ETA;
+    if (capacity < 0 || tau != tau || !(rtol >= 0.0) || iterations < 0 || iterations > 100000 ||
+        (restart != 0 && restart != 1))
+        return REGOT_ERR_ARG;
+    if (!row_ptr || !col_ptr || !row_sum || !col_sum || !info) return REGOT_ERR_NULL;
+    for (int k = 0; k < R; ++k) {
+        if (!rhs[k] || !x[k]) return REGOT_ERR_NULL;
+        if (misaligned(rhs[k], 8) || misaligned(x[k], 8)) return REGOT_ERR_ALIGN;
+    }
+    if (capacity > 0 && (!col_idx || !val || !row_idx || !val_csc)) return REGOT_ERR_NULL;
+    if (misaligned(row_ptr, 8) || misaligned(col_ptr, 8) || misaligned(val, 8) || misaligned(val_csc, 8) ||
+        misaligned(row_sum, 8) || misaligned(col_sum, 8) || misaligned(info, 8) || misaligned(col_idx, 4) ||
+        misaligned(row_idx, 4))
+        return REGOT_ERR_ALIGN;
+    const PcgLayout L = make_pcg_layout(n, m);
+    const int st = check_workspace(workspace, workspace_bytes, L.total);
+    if (st != REGOT_OK) return st;
+
+    const int64_t mb = m - 1, N = n + mb;
+    // (not by the number of systems: a pair has to give the bits of two single solves)
+    if (n > kSchurCap && mb > kSchurCap)
+        return run_pcg_wide<R>(n, m, eta, tau, row_ptr, col_idx, val, col_ptr, row_idx, val_csc, capacity, row_sum, col_sum, rhs, x,
+                               rtol, iterations, restart, info, workspace, L, stream);
+    SchurArgs A{};
+    A.n = (int)n;
+    A.mb = (int)mb;
+    A.eta = eta;
+    A.tau = tau;
+    A.rtol = rtol;
+    A.row_ptr = row_ptr;
+    A.col_ptr = col_ptr;
+    A.col_idx = col_idx;
+    A.row_idx = row_idx;
+    A.val = val;
+    A.val_csc = val_csc;
+    A.capacity = capacity;
+    A.row_sum = row_sum;
+    A.col_sum = col_sum;
+    // The five regions of the workspace hold 2 N = 2 (n + m - 1) doubles each, n >= 1.  One system iterates in the caller's x.
+    // The vectors that go to LDS begin at multiples of 16 bytes.
+    const int64_t mb2 = (mb + 1) / 2 * 2;
+    double *part = at<double>(workspace, L.part);
+    for (int k = 0; k < R; ++k) {
+        A.rhs[k] = rhs[k];
+        A.x_out[k] = x[k];
+        A.x[k] = R == 1 ? x[0] + n : at<double>(workspace, L.x) + k * mb2;
+        A.r[k] = at<double>(workspace, L.r) + k * mb;
+        A.z[k] = at<double>(workspace, L.z) + k * mb2;
+        A.buf[k][0] = at<double>(workspace, L.p) + k * mb;
+        A.buf[k][1] = at<double>(workspace, L.Ap) + k * mb;
+        A.u[k] = at<double>(workspace, k == 0 ? L.p : L.Ap) + 2 * mb;  // (behind the two vectors of the region)
+        A.part[k] = part + k * kPcgParts;
+        A.part_rz[k] = part + (kPcgMaxRhs + k) * kPcgParts;
+        A.part_rr[k] = part + (2 * kPcgMaxRhs + k) * kPcgParts;
+        A.part_norm[k] = part + (3 * kPcgMaxRhs + k) * kPcgParts;
+    }
+    // (behind the partial sums of the first and the second system's p^T S p)
+    A.row_cut = reinterpret_cast<SchurCut *>(part + kSchurVecBlocks);
+    A.col_cut = reinterpret_cast<SchurCut *>(part + kPcgParts + kSchurVecBlocks);
+    static_assert(kSchurParts <= kSchurVecBlocks && kSchurVecBlocks * sizeof(double) + (kSchurParts + 1) * sizeof(SchurCut) <= kPcgParts * sizeof(double),
+                  "rows of part");
+    A.state = at<SchurState>(workspace, L.sc);
+    A.info = info;
+    const auto blocks_for = [](int64_t items) {
+        return (int)std::max<int64_t>(1, std::min<int64_t>((items + kThreads - 1) / kThreads, kSchurVecBlocks));
+    };
+    A.vec_blocks = blocks_for(mb);
+    A.norm_blocks = blocks_for(N);
+
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    // a half product; the rows gather from m - 1 entries, the columns from n
+    const auto half = [&](auto mode) {
+        constexpr int MODE = decltype(mode)::value;
+        const dim3 grid(kSchurParts / R, R), block(R * kSchurPartThreads);
+        if ((MODE == kSchurRows || MODE == kSchurRowsFinal ? mb : n) <= kSchurCap)
+            hipLaunchKernelGGL((schur_half_kernel<MODE, R, true>), grid, block, 0, s, A);
+        else
+            hipLaunchKernelGGL((schur_half_kernel<MODE, R, false>), grid, block, 0, s, A);
+    };
+    if (restart) {
+        constexpr int kCutBlocks = (kSchurCutWaves + kWaves - 1) / kWaves;
+        hipLaunchKernelGGL(schur_prepare_kernel, dim3((unsigned)(A.norm_blocks + kCutBlocks), R), dim3(kThreads), 0, s, A);
+        half(std::integral_constant<int, kSchurColsRhs>{});
+    }
+    for (A.it = 0; A.it < iterations; ++A.it) {
+        half(std::integral_constant<int, kSchurRows>{});
+        half(std::integral_constant<int, kSchurCols>{});
+        hipLaunchKernelGGL(schur_update_kernel, dim3((unsigned)A.vec_blocks, R), dim3(kThreads), 0, s, A);
+    }
+    // the first blocks of the solutions for the second blocks as they stand, and the record of the iteration
+    half(std::integral_constant<int, kSchurRowsFinal>{});
     return hip_status();
 }
 

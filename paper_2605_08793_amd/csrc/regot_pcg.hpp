@@ -19,8 +19,8 @@
 // keeps its own scalars and stops on its own: once it has converged its vectors are left alone, and
 // the arithmetic of a system does not depend on the other one being there.
 //
-// Further down: the same solve through the Schur complement of the first diagonal block (half the
-// iterations; regot_pcg_solve_reduced), which reuses the vector kernels on the second block alone.
+// The same solve through the Schur complement of the first diagonal block (half the iterations): regot_schur.hpp, and
+// regot_schur_wide.hpp, which reuses the vector kernels on the second block alone.
 #pragma once
 
 #include "regot_sparse.hpp"
@@ -29,6 +29,7 @@ namespace regot {
 
 constexpr int kPcgParts = 1024;   // most workgroups whose partial sums a later kernel adds up
 constexpr int kPcgMaxRhs = 2;
+constexpr int kPcgPartRows = 4 * kPcgMaxRhs;  // rows of `part`: p^T A p | r^T z | r^T r | ||rhs||^2 (reduced solves), one per system
 
 template <int R>
 struct PcgScalars {
@@ -277,157 +278,6 @@ __global__ __launch_bounds__(kThreads) void pcg_finish_kernel(PcgArgs A, int its
         A.info[4 * k + 1] = (double)s.done[k];
         A.info[4 * k + 2] = sqrt(s.rr[k]);
         A.info[4 * k + 3] = sqrt(s.bb[k]);
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
-// The same system through its Schur complement (regot_pcg_solve_reduced).  With
-//     H_Omega + tau I = [ D1   B  ]     D1 = diag(T 1) / eta + tau        (n)
-//                       [ B^T  D2 ]     D2 = diag(T_{-m}^T 1) / eta + tau (m - 1),   B = T^Omega_{-m} / eta
-// (eq. (7)) and rhs = (g1, g2), eliminating the first block leaves S x2 = g2 - B^T D1^{-1} g1 with
-// S = D2 - B^T D1^{-1} B (symmetric positive definite as the whole matrix is, Theorem 1), and
-// x1 = D1^{-1} (g1 - B x2).  Conjugate gradients on S preconditioned with D2 take about half the iterations
-// of the iteration on the whole matrix (the classical result for matrices whose diagonal blocks are diagonal) at
-// the same cost per iteration: one product with B (by rows) and one with B^T (by columns), now one after the
-// other, each by all compute units.  The vector kernels above run on the second block alone.
-// ---------------------------------------------------------------------------------------------
-// R systems at once as in the kernels above: the vectors the iteration itself produces (u, p, S p, the iterate) are
-// "packed", R side by side (see Pack); what the caller hands over or gets back (the right-hand sides, the solutions)
-// and the right-hand sides of the reduced systems are plain arrays, one per system.
-enum SchurMode {
-    kSchurRows = 0,       // out_i = (sum_j T_ij in_j / eta) / D1_i             u = D1^{-1} B p      out packed
-    kSchurRowsFinal = 1,  // out_i = (own_i - sum_j T_ij in_j / eta) / D1_i     x1, own = g1         own, out plain
-    kSchurCols = 2,       // out_j = D2_j own_j - sum_i T_ij in_i / eta         S p, own = p         own, out packed;
-                          //                                                    and own^T out
-    kSchurColsRhs = 3     // out_j = own_j - sum_i T_ij in_i / eta              own = g2             own, out plain
-};
-constexpr int kPcgPartRows = 4 * kPcgMaxRhs;  // rows of `part`: p^T A p | r^T z | r^T r | ||rhs||^2, R of each
-
-template <int R>
-struct SchurArgs {
-    MatvecArgs mv;       // pattern, values, sums, eta, tau (x, y, row_waves unused)
-    const double *in;    // packed: the vectors the entries are multiplied with, m - 1 entries (rows) or n (columns)
-    const double *own[R];  // see SchurMode; a packed vector is own[0]
-    double *out[R];        // a packed vector is out[0]
-    double *dot_part;    // kSchurCols: partial sums of own^T out, one per system and group of kWaves waves
-    const int *skip;     // the kernel does nothing if *skip is set (may be NULL)
-};
-
-template <int MODE, int R>
-struct SchurItem {
-    static constexpr bool kPacked = MODE == kSchurRows || MODE == kSchurCols;
-    const double *sums;
-    const double *own[R];
-    double *out[R];
-    double eta, inv_eta, tau;
-    double dg;
-    Pack<R> mine;
-    __device__ __forceinline__ void fetch(int64_t t)
-    {
-        dg = sums[t] / eta + tau;
-        if (MODE == kSchurCols) {
-            mine = load_pack<R>(own[0], t);
-        } else {
-#pragma unroll
-            for (int k = 0; k < R; ++k) mine.v[k] = MODE == kSchurRows ? 0.0 : own[k][t];
-        }
-    }
-    __device__ __forceinline__ Pack<R> finish(int64_t t, bool have, const Pack<R> &sum)
-    {
-        Pack<R> term, o;
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-            term.v[k] = 0.0;
-            const double bs = sum.v[k] * inv_eta;
-            if (MODE == kSchurRows) o.v[k] = bs / dg;
-            else if (MODE == kSchurRowsFinal) o.v[k] = (mine.v[k] - bs) / dg;
-            else if (MODE == kSchurCols) o.v[k] = dg * mine.v[k] - bs;
-            else o.v[k] = mine.v[k] - bs;
-            if (MODE == kSchurCols && have) term.v[k] = o.v[k] * mine.v[k];
-        }
-        if (have) {
-            if (kPacked) {
-                store_pack<R>(out[0], t, o);
-            } else {
-#pragma unroll
-                for (int k = 0; k < R; ++k) out[k][t] = o.v[k];
-            }
-        }
-        return term;
-    }
-};
-
-template <int MODE, int R, bool ALL>
-__global__ __launch_bounds__(kMatvecLdsThreads) void schur_half_kernel(SchurArgs<R> S)
-{
-    __shared__ __attribute__((aligned(16))) double xs[kMatvecLdsCap];
-    __shared__ double wave_dot[R][kMatvecLdsWaves];
-    if (S.skip != nullptr && *S.skip) return;
-    const MatvecArgs &A = S.mv;
-    constexpr bool ROWS = MODE == kSchurRows || MODE == kSchurRowsFinal;
-    const int lane = threadIdx.x & (kLanes - 1), w = threadIdx.x >> 6;
-    const int mb = A.m - 1;
-    const int limit = ROWS ? mb : A.n;
-    const int nl = limit < kMatvecLdsCap / R ? limit : kMatvecLdsCap / R;
-    double dot[R];
-    SchurItem<MODE, R> item;
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        dot[k] = 0.0;
-        item.own[k] = S.own[k];
-        item.out[k] = S.out[k];
-    }
-    item.sums = ROWS ? A.row_sum : A.col_sum;
-    item.eta = A.eta;
-    item.inv_eta = 1.0 / A.eta;
-    item.tau = A.tau;
-    const int64_t *ptr = ROWS ? A.row_ptr : A.col_ptr;
-    const int64_t count = ROWS ? A.n : mb;
-    const int64_t first = (int64_t)blockIdx.x * kMatvecLdsWaves + w, stride = (int64_t)gridDim.x * kMatvecLdsWaves;
-    const SweepHead head = lds_sweep_head(ptr, A.capacity, count, first, stride, lane, item);
-    lds_fill(xs, S.in, nl * R);
-    __syncthreads();
-    lds_sweep<R, ALL>(ptr, ROWS ? A.col_idx : A.row_idx, ROWS ? A.val : A.val_csc, A.capacity, S.in, xs, nl, limit, count,
-                      first, stride, lane, item, dot, head);
-    if constexpr (MODE == kSchurCols) lds_leave_dots<R>(dot, wave_dot, S.dot_part, (int)kPcgParts, lane, w);
-}
-
-// start of a reduced solve: u = D1^{-1} g1 (packed), and partial sums of ||rhs||^2 over both blocks -> rows 3R + k
-// of `part`
-template <int R>
-struct SchurPrepareArgs {
-    int64_t n, N;
-    const double *rhs[R];
-    const double *row_sum;
-    double eta, tau;
-    double *u;
-    double *part;
-};
-template <int R>
-__global__ __launch_bounds__(kThreads) void schur_prepare_kernel(SchurPrepareArgs<R> A)
-{
-    __shared__ double lds[kWaves];
-    double gg[R];
-#pragma unroll
-    for (int k = 0; k < R; ++k) gg[k] = 0.0;
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < A.N; t += (int64_t)gridDim.x * kThreads) {
-        Pack<R> g;
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-            g.v[k] = A.rhs[k][t];
-            gg[k] += g.v[k] * g.v[k];
-        }
-        if (t < A.n) {
-            const double d1 = A.row_sum[t] / A.eta + A.tau;
-#pragma unroll
-            for (int k = 0; k < R; ++k) g.v[k] = g.v[k] / d1;
-            store_pack<R>(A.u, t, g);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        const double s = block_sum(gg[k], lds);
-        if (threadIdx.x == 0) A.part[(size_t)(3 * R + k) * kPcgParts + blockIdx.x] = s;
     }
 }
 
