@@ -1437,9 +1437,10 @@ int regot_pattern_values(int64_t n, int64_t m, const double *M, int64_t ldM, con
     A.val = val;
     A.val_csc = val_csc;
     A.ex = make_exp_params(eta);
-    const int64_t want = (n + kWaves - 1) / kWaves;
-    const unsigned grid = (unsigned)(want < 16 * kNumCU ? want : 16 * kNumCU);
-    hipLaunchKernelGGL(pattern_values_kernel, dim3(grid), dim3(kThreads), 0, static_cast<hipStream_t>(stream), A);
+    const bool few = capacity < kTileFewBelow;
+    const dim3 grid((unsigned)(few ? tile_blocks<kTileFew>(capacity, 8 * kNumCU) : tile_blocks<kTileItems>(capacity, 8 * kNumCU)));
+    if (few) hipLaunchKernelGGL(pattern_values_kernel<kTileFew>, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), A);
+    else hipLaunchKernelGGL(pattern_values_kernel<kTileItems>, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), A);
     return hip_status();
 }
 
@@ -1548,9 +1549,11 @@ int regot_hessian_lower_csc(int64_t n, int64_t m, double eta, double tau, const 
         hipLaunchKernelGGL(lower_count_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, A);
         hipLaunchKernelGGL(lower_scan_kernel, dim3(1), dim3(kThreads), 0, s, A);
     }
-    int64_t beta_blocks = (m - 1 + kThreads - 1) / kThreads;
-    if (beta_blocks < 1) beta_blocks = 1;
-    hipLaunchKernelGGL(lower_fill_kernel, dim3((unsigned)(A.nblk + beta_blocks)), dim3(kThreads), 0, s, A);
+    const bool few = capacity < kTileFewBelow;
+    const int tiles = (int)(few ? tile_blocks<kTileFew>(capacity, 8 * kNumCU) : tile_blocks<kTileItems>(capacity, 8 * kNumCU));
+    const dim3 grid((unsigned)(tiles + (n + m - 1 + kThreads - 1) / kThreads));
+    if (few) hipLaunchKernelGGL(lower_fill_kernel<kTileFew>, grid, dim3(kThreads), 0, s, A, tiles);
+    else hipLaunchKernelGGL(lower_fill_kernel<kTileItems>, grid, dim3(kThreads), 0, s, A, tiles);
     return hip_status();
 }
 

@@ -187,6 +187,55 @@ __device__ __forceinline__ int lanes_below(uint64_t mask)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+constexpr int kDppRowShr = 0x110;       // + D: lanes move up by D inside each row of 16, 0 moves in
+constexpr int kDppWaveShr1 = 0x138;     // lanes move up by 1, 0 moves in
+constexpr int kDppRowBcast15 = 0x142;   // lane 15 of each row to the row behind it
+constexpr int kDppRowBcast31 = 0x143;   // lane 31 to the two rows behind it
+
+// inclusive sum over the wave
+__device__ __forceinline__ int wave_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, kDppRowShr + 1, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, kDppRowShr + 2, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, kDppRowShr + 4, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, kDppRowShr + 8, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, kDppRowBcast15, 0xa, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, kDppRowBcast31, 0xc, 0xf, true);
+    return v;
+}
+
+// The first x in [lo, hi) with reached(x), hi if there is none; reached is false up to some place and true from there on
+// (else: some place in [lo, hi]).  By the whole wave, 64 places at a time: 20000 are three loads one after the other.
+// slack: a place up to so many before it will do.
+template <typename F>
+__device__ __forceinline__ int64_t wave_first(int64_t lo, int64_t hi, int lane, F reached, int slack = 0)
+{
+    while (hi - lo > slack) {
+        const int64_t step = (hi - lo + kLanes - 1) / kLanes, at = lo + lane * step;
+        const uint64_t mask = __ballot(at >= hi || reached(at));
+        const int k = mask != 0 ? __builtin_ctzll(mask) : kLanes;
+        if (k == 0) {
+            hi = lo;
+        } else {
+            const int64_t top = lo + k * step;
+            lo += (k - 1) * step + 1;
+            hi = top < hi ? top : hi;
+        }
+    }
+    return lo;
+}
+
+// Workgroup b of a grid of die_grid(blocks) takes block die_block(b, blocks) (none if that is not below `blocks`), so that
+// neighbouring blocks run on one die: workgroups b with equal b % kDies are placed on one.  For kernels that write short pieces
+// next to the pieces of neighbouring blocks: each die has an L2 of its own, and a line written from several dies goes to
+// memory in parts.  Only the order of the work changes.
+constexpr int kDies = 8;
+__host__ __device__ constexpr int64_t die_grid(int64_t blocks) { return (blocks + kDies - 1) / kDies * kDies; }
+__device__ __forceinline__ int64_t die_block(int64_t b, int64_t blocks)
+{
+    return (b % kDies) * ((blocks + kDies - 1) / kDies) + b / kDies;
+}
+
 // How a workgroup treats the columns of its panel.
 //   kPanelFull     all kPanel columns exist and belong to this panel
 //   kPanelOverlap  the ragged last panel of a matrix with m >= kPanel: it is shifted left to start at

@@ -7,30 +7,32 @@
 // The positions start out in ascending order, so a STABLE sort by column alone gives that list: a
 // least-significant-digit radix sort on the column index, 8 bits per pass, ceil(bits(m) / 8) passes (two
 // for m < 65536), every kernel of this file:
-//   0. entry_row[p] = row of CSR position p (one wave per row);
+//   0. entry_row[p] = row of CSR position p (one wave per row; in the launch of the first pass's step 1);
 //   per pass:
 //   1. every workgroup counts the digits of its tile of 2048 keys (LDS) -> table[digit][workgroup];
 //   2. one workgroup per digit: exclusive scan of its row of the table, and the digit's total;
 //   3. every workgroup ranks its keys stably (a wave takes 64 consecutive keys at a time; lanes with the
 //      same digit find each other with eight ballots and rank by lane number behind the keys of that
 //      digit the wave has already seen), orders the tile by digit in LDS and writes each digit's run to
-//      its place: the digit's base + the table entry + the position inside the run;
-//   then, on the sorted (column, p) list:
-//   4. col_ptr[j] = number of keys below j (a binary search per column);
-//   5. row_idx[q] = entry_row[p], csc_pos[p] = q.
+//      its place: the digit's base + the table entry + the position inside the run; the last pass knows
+//      where in the column order that is and writes row_idx[q] and csc_pos[p] = q instead of another list;
+//   then, on the sorted columns:
+//   4. col_ptr[j] = number of keys below j (a binary search per column).
 // A col_idx outside [0, m) sorts as column m, behind every real column, and gets csc_pos = -1.
 // No atomics on memory and no order that depends on timing: the same bits on every call.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "regot.h"
+#include "regot_device.hpp"
 
 namespace {
+
+using namespace regot;
 
 constexpr int64_t kMaxDim = 2147483647LL;
 constexpr size_t kAlign = 256;
 constexpr int kBlock = 256;
-constexpr int kLanes = 64;
 constexpr int kWavesPerBlock = kBlock / kLanes;
 constexpr int kItems = 8;                        // keys per thread
 constexpr int kTile = kBlock * kItems;           // keys per workgroup
@@ -92,6 +94,8 @@ struct TransposeArgs {
 struct PassArgs {
     const uint32_t *key_in, *pay_in;
     uint32_t *key_out, *pay_out;
+    const int32_t *row_in;
+    int32_t *row_out;
     int shift;
 };
 
@@ -107,71 +111,75 @@ __device__ __forceinline__ uint32_t load_key(const TransposeArgs &A, const PassA
     return FIRST ? column_key(A, i) : P.key_in[i];
 }
 
-// Workgroup b of a grid of die_grid(blocks) takes block die_block(b, blocks) (none if that is not below `blocks`), so that
-// neighbouring blocks run on one die: workgroups b with equal b % kDies are placed on one.  The kernels below write
-// short pieces (a digit's run of a tile, a count, a position) next to the pieces of neighbouring blocks, and each die has an
-// L2 of its own: written from several dies a line goes to memory in parts.  Only the order of the work changes.  (2e6 entries:
-// a new pattern with its values and lower triangle 291 -> 257 us, a third of it here.)
-constexpr int kDies = 8;
-__host__ __device__ constexpr int64_t die_grid(int64_t blocks) { return (blocks + kDies - 1) / kDies * kDies; }
-__device__ __forceinline__ int64_t die_block(int64_t b, int64_t blocks)
-{
-    return (b % kDies) * ((blocks + kDies - 1) / kDies) + b / kDies;
-}
+// Neighbouring tiles run on one die (die_block): a digit's run of a tile, a count or a position is written next to those of the
+// tiles around it.  2e6 entries: a new pattern with its values and lower triangle 291 -> 257 us, a third of it here.
 
-// step 0: one wave per row
-__global__ __launch_bounds__(kBlock) void entry_row_kernel(TransposeArgs A)
-{
-    const int lane = threadIdx.x & (kLanes - 1);
-    const int64_t wave = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    for (int64_t i = wave; i < A.n; i += (int64_t)gridDim.x * kWavesPerBlock) {
-        int64_t p0 = A.row_ptr[i], p1 = A.row_ptr[i + 1];
-        if (p0 < 0) p0 = 0;
-        if (p1 > A.nnz) p1 = A.nnz;
-        for (int64_t p = p0 + lane; p < p1; p += kLanes) A.entry_row[p] = (int32_t)i;
-    }
-}
-
-// step 1
+// step 1; behind the tiles' workgroups of the first pass, step 0: one wave per row
 template <bool FIRST>
 __global__ __launch_bounds__(kBlock) void digit_count_kernel(TransposeArgs A, PassArgs P)
 {
     __shared__ unsigned hist[kDigits];
+    const int64_t tiles = die_grid(A.blocks);
+    if (FIRST && (int64_t)blockIdx.x >= tiles) {
+        const int lane = threadIdx.x & (kLanes - 1);
+        const int64_t wave = ((int64_t)blockIdx.x - tiles) * kWavesPerBlock + (threadIdx.x >> 6);
+        for (int64_t i = wave; i < A.n; i += ((int64_t)gridDim.x - tiles) * kWavesPerBlock) {
+            int64_t p0 = A.row_ptr[i], p1 = A.row_ptr[i + 1];
+            if (p0 < 0) p0 = 0;
+            if (p1 > A.nnz) p1 = A.nnz;
+            for (int64_t p = p0 + lane; p < p1; p += kLanes) A.entry_row[p] = (int32_t)i;
+        }
+        return;
+    }
     const int64_t tile = die_block(blockIdx.x, A.blocks);
     if (tile >= A.blocks) return;
     hist[threadIdx.x] = 0;
     __syncthreads();
     const int64_t base = tile * kTile;
+    uint32_t key[kItems];
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
         const int64_t i = base + k * kBlock + threadIdx.x;
-        if (i < A.nnz) atomicAdd(&hist[(load_key<FIRST>(A, P, i) >> P.shift) & (kDigits - 1)], 1u);
+        key[k] = i < A.nnz ? load_key<FIRST>(A, P, i) : 0u;
     }
+#pragma unroll
+    for (int k = 0; k < kItems; ++k)
+        if (base + k * kBlock + threadIdx.x < A.nnz) atomicAdd(&hist[(key[k] >> P.shift) & (kDigits - 1)], 1u);
     __syncthreads();
     A.table[(size_t)threadIdx.x * A.blocks + tile] = hist[threadIdx.x];
 }
 
-// exclusive scan of one value per thread across the workgroup; *total = sum of all (lds: [kBlock])
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t mine, uint32_t *lds, uint32_t *total)
+// exclusive scans of NV values per thread across the workgroup; total[] = the sums of all
+template <int NV>
+__device__ __forceinline__ void block_exclusive_scans(uint32_t (&v)[NV], uint32_t (&total)[NV], uint32_t (*lds)[kWavesPerBlock])
 {
-    lds[threadIdx.x] = mine;
-    __syncthreads();
-    for (int d = 1; d < kBlock; d <<= 1) {
-        const uint32_t up = (int)threadIdx.x >= d ? lds[threadIdx.x - d] : 0u;
-        __syncthreads();
-        lds[threadIdx.x] += up;
-        __syncthreads();
+    const int lane = threadIdx.x & (kLanes - 1), w = threadIdx.x >> 6;
+    uint32_t incl[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        incl[k] = (uint32_t)wave_scan((int)v[k]);
+        if (lane == kLanes - 1) lds[k][w] = incl[k];
     }
-    const uint32_t incl = lds[threadIdx.x];
-    *total = lds[kBlock - 1];
     __syncthreads();
-    return incl - mine;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        uint32_t before = 0, all = 0;
+#pragma unroll
+        for (int q = 0; q < kWavesPerBlock; ++q) {
+            const uint32_t t = lds[k][q];
+            before += q < w ? t : 0u;
+            all += t;
+        }
+        v[k] = before + incl[k] - v[k];
+        total[k] = all;
+    }
+    __syncthreads();
 }
 
 // step 2: workgroup d turns row d of the table into its exclusive prefix and leaves the row's sum
 __global__ __launch_bounds__(kBlock) void digit_scan_kernel(TransposeArgs A)
 {
-    __shared__ uint32_t lds[kBlock];
+    __shared__ uint32_t lds[1][kWavesPerBlock];
     constexpr int kPer = 4;
     uint32_t *row = A.table + (size_t)blockIdx.x * A.blocks;
     uint32_t carry = 0;
@@ -183,28 +191,31 @@ __global__ __launch_bounds__(kBlock) void digit_scan_kernel(TransposeArgs A)
             c[k] = first + k < A.blocks ? row[first + k] : 0u;
             mine += c[k];
         }
-        uint32_t total;
-        uint32_t run = carry + block_exclusive_scan(mine, lds, &total);
+        uint32_t start[1] = {mine}, total[1];
+        block_exclusive_scans<1>(start, total, lds);
+        uint32_t run = carry + start[0];
 #pragma unroll
         for (int k = 0; k < kPer; ++k)
             if (first + k < A.blocks) {
                 row[first + k] = run;
                 run += c[k];
             }
-        carry += total;
+        carry += total[0];
     }
     if (threadIdx.x == 0) A.digit_total[blockIdx.x] = carry;
 }
 
-// step 3
-template <bool FIRST>
+// step 3.  LAST: the positions are those of the column order.  CARRY: the entries' rows go along (as many passes as the workspace
+// has room for: two), else the last pass looks them up.
+template <bool FIRST, bool LAST, bool CARRY>
 __global__ __launch_bounds__(kBlock) void digit_scatter_kernel(TransposeArgs A, PassArgs P)
 {
     __shared__ uint32_t seen[kWavesPerBlock][kDigits];  // keys of a digit a wave has ranked so far; then the wave's offset
     __shared__ uint32_t run_start[kDigits];             // where the digit's run starts inside the tile
     __shared__ uint32_t run_dest[kDigits];              // where it goes in the output
-    __shared__ uint32_t scan_lds[kBlock];
+    __shared__ uint32_t scan_lds[2][kWavesPerBlock];
     __shared__ uint32_t tile_key[kTile], tile_pay[kTile];
+    __shared__ int32_t tile_row[CARRY ? kTile : 1];
     const int lane = threadIdx.x & (kLanes - 1), w = threadIdx.x >> 6;
     const int64_t tile = die_block(blockIdx.x, A.blocks);
     if (tile >= A.blocks) return;
@@ -219,13 +230,16 @@ __global__ __launch_bounds__(kBlock) void digit_scatter_kernel(TransposeArgs A, 
 
     // the wave's keys in input order: group g, lane l is key w * kWaveKeys + g * 64 + l of the tile
     uint32_t key[kItems], pay[kItems], rank[kItems];
+    int32_t row[kItems];
 #pragma unroll
     for (int g = 0; g < kItems; ++g) {
         const int t = w * kWaveKeys + g * kLanes + lane;
         const bool valid = t < count;
         key[g] = valid ? load_key<FIRST>(A, P, base + t) : 0u;
         pay[g] = valid ? (FIRST ? (uint32_t)(base + t) : P.pay_in[base + t]) : 0u;
+        if (CARRY) row[g] = valid ? (FIRST ? A.entry_row[base + t] : P.row_in[base + t]) : 0;
     }
+    const uint32_t digit_total = A.digit_total[threadIdx.x], digit_before = A.table[(size_t)threadIdx.x * A.blocks + tile];
 #pragma unroll
     for (int g = 0; g < kItems; ++g) {
         const int t = w * kWaveKeys + g * kLanes + lane;
@@ -259,11 +273,10 @@ __global__ __launch_bounds__(kBlock) void digit_scatter_kernel(TransposeArgs A, 
             seen[k][d] = run;
             run += c;
         }
-        uint32_t total;
-        const uint32_t start = block_exclusive_scan(run, scan_lds, &total);
-        const uint32_t digit_base = block_exclusive_scan(A.digit_total[d], scan_lds, &total);
-        run_start[d] = start;
-        run_dest[d] = digit_base + A.table[(size_t)d * A.blocks + tile];
+        uint32_t start[2] = {run, digit_total}, total[2];
+        block_exclusive_scans<2>(start, total, scan_lds);
+        run_start[d] = start[0];
+        run_dest[d] = start[1] + digit_before;
     }
     __syncthreads();
 #pragma unroll
@@ -274,6 +287,7 @@ __global__ __launch_bounds__(kBlock) void digit_scatter_kernel(TransposeArgs A, 
             const uint32_t at = run_start[d] + seen[w][d] + rank[g];
             tile_key[at] = key[g];
             tile_pay[at] = pay[g];
+            if (CARRY) tile_row[at] = row[g];
         }
     }
     __syncthreads();
@@ -286,14 +300,26 @@ __global__ __launch_bounds__(kBlock) void digit_scatter_kernel(TransposeArgs A, 
             const unsigned d = (kk >> P.shift) & (kDigits - 1);
             const int64_t at = (int64_t)run_dest[d] + (t - (int)run_start[d]);
             if (at < A.nnz) {  // always; a guard against a table that does not add up
+                const uint32_t p = tile_pay[t];
                 P.key_out[at] = kk;
-                P.pay_out[at] = tile_pay[t];
+                if (!LAST) {
+                    P.pay_out[at] = p;
+                    if (CARRY) P.row_out[at] = tile_row[t];
+                } else if ((int64_t)p < A.nnz) {  // always: the payloads are a permutation of the positions
+                    if ((int64_t)kk < A.m) {
+                        A.row_idx[at] = CARRY ? tile_row[t] : A.entry_row[p];
+                        A.csc_pos[p] = at;
+                    } else {
+                        A.csc_pos[p] = -1;  // not an entry of any column
+                    }
+                }
             }
         }
     }
 }
 
-// step 4: col_ptr[j] = number of sorted keys below j, j = 0 .. m
+// step 4: col_ptr[j] = number of sorted keys below j, j = 0 .. m.  (Two halves at a time: eight parts mean fewer loads one after
+// the other but a line of its own for each, 13.5 instead of 7.6 us with 2e6 entries.)
 __global__ __launch_bounds__(kBlock) void col_ptr_kernel(TransposeArgs A, const uint32_t *sorted_key)
 {
     const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -305,21 +331,6 @@ __global__ __launch_bounds__(kBlock) void col_ptr_kernel(TransposeArgs A, const 
         else hi = mid;
     }
     A.col_ptr[j] = lo;
-}
-
-// step 5
-__global__ __launch_bounds__(kBlock) void emit_kernel(TransposeArgs A, const uint32_t *sorted_key, const uint32_t *sorted_pay)
-{
-    const int64_t q = die_block(blockIdx.x, (A.nnz + kBlock - 1) / kBlock) * kBlock + threadIdx.x;
-    if (q >= A.nnz) return;
-    const int64_t p = sorted_pay[q];
-    if (p >= A.nnz) return;  // never: the payloads are a permutation of the positions
-    if ((int64_t)sorted_key[q] < A.m) {
-        A.row_idx[q] = A.entry_row[p];
-        A.csc_pos[p] = q;
-    } else {
-        A.csc_pos[p] = -1;  // not an entry of any column
-    }
 }
 
 int check_dims(int64_t n, int64_t m, int64_t nnz)
@@ -381,29 +392,31 @@ int regot_pattern_transpose(int64_t n, int64_t m, int64_t nnz, const int64_t *ro
         hipLaunchKernelGGL(col_ptr_kernel, dim3(col_blocks), dim3(kBlock), 0, s, A, (const uint32_t *)key[0]);
         return hipGetLastError() == hipSuccess ? REGOT_OK : REGOT_ERR_HIP;
     }
-    if (n > 0) {
-        int64_t row_blocks = (n + kWavesPerBlock - 1) / kWavesPerBlock;
-        if (row_blocks > 16 * 256) row_blocks = 16 * 256;
-        hipLaunchKernelGGL(entry_row_kernel, dim3((unsigned)row_blocks), dim3(kBlock), 0, s, A);
-    }
+    int64_t row_blocks = (n + kWavesPerBlock - 1) / kWavesPerBlock;
+    if (row_blocks > 16 * 256) row_blocks = 16 * 256;
     const unsigned tiles = (unsigned)die_grid(L.blocks);
+    const bool carry = L.passes <= 2;
     for (int pass = 0; pass < L.passes; ++pass) {
         PassArgs P{};
         P.key_in = pass == 0 ? nullptr : key[(pass - 1) & 1];
         P.pay_in = pass == 0 ? nullptr : pay[(pass - 1) & 1];
         P.key_out = key[pass & 1];
         P.pay_out = pay[pass & 1];
+        P.row_in = P.row_out = reinterpret_cast<int32_t *>(pay[1]);  // (two passes: the second writes no list of positions)
         P.shift = pass * kDigitBits;
-        if (pass == 0) hipLaunchKernelGGL(digit_count_kernel<true>, dim3(tiles), dim3(kBlock), 0, s, A, P);
+        const bool first = pass == 0, last = pass == L.passes - 1;
+        if (first) hipLaunchKernelGGL(digit_count_kernel<true>, dim3(tiles + (unsigned)row_blocks), dim3(kBlock), 0, s, A, P);
         else hipLaunchKernelGGL(digit_count_kernel<false>, dim3(tiles), dim3(kBlock), 0, s, A, P);
         hipLaunchKernelGGL(digit_scan_kernel, dim3(kDigits), dim3(kBlock), 0, s, A);
-        if (pass == 0) hipLaunchKernelGGL(digit_scatter_kernel<true>, dim3(tiles), dim3(kBlock), 0, s, A, P);
-        else hipLaunchKernelGGL(digit_scatter_kernel<false>, dim3(tiles), dim3(kBlock), 0, s, A, P);
+        if (first && last) hipLaunchKernelGGL((digit_scatter_kernel<true, true, true>), dim3(tiles), dim3(kBlock), 0, s, A, P);
+        else if (carry && first) hipLaunchKernelGGL((digit_scatter_kernel<true, false, true>), dim3(tiles), dim3(kBlock), 0, s, A, P);
+        else if (carry) hipLaunchKernelGGL((digit_scatter_kernel<false, true, true>), dim3(tiles), dim3(kBlock), 0, s, A, P);
+        else if (first) hipLaunchKernelGGL((digit_scatter_kernel<true, false, false>), dim3(tiles), dim3(kBlock), 0, s, A, P);
+        else if (!last) hipLaunchKernelGGL((digit_scatter_kernel<false, false, false>), dim3(tiles), dim3(kBlock), 0, s, A, P);
+        else hipLaunchKernelGGL((digit_scatter_kernel<false, true, false>), dim3(tiles), dim3(kBlock), 0, s, A, P);
     }
-    const uint32_t *sorted_key = key[(L.passes - 1) & 1], *sorted_pay = pay[(L.passes - 1) & 1];
+    const uint32_t *sorted_key = key[(L.passes - 1) & 1];
     hipLaunchKernelGGL(col_ptr_kernel, dim3(col_blocks), dim3(kBlock), 0, s, A, sorted_key);
-    hipLaunchKernelGGL(emit_kernel, dim3((unsigned)die_grid((nnz + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, A, sorted_key,
-                       sorted_pay);
     return hipGetLastError() == hipSuccess ? REGOT_OK : REGOT_ERR_HIP;
 }
 

@@ -156,23 +156,9 @@ __global__ __launch_bounds__(kThreads) void schur_prepare_kernel(SchurArgs A)
         // (whole parts and the rest apart: the product would not fit for any number of entries)
         const int64_t whole = (w1 - w0) / kSchurParts, rest = (w1 - w0) % kSchurParts;
         const int64_t target = w0 + whole * t + rest * t / kSchurParts;
-        int64_t lo = 0, hi = count;
-        if (t == 0) hi = 0;
-        if (t == kSchurParts) lo = count;
-        while (lo < hi) {
-            const int64_t step = (hi - lo + kLanes - 1) / kLanes, at = lo + lane * step;
-            const bool reached = at >= hi || clamp_entry(ptr[at], A.capacity) + kSchurRowCost * at >= target;
-            const uint64_t mask = __ballot(reached);
-            const int k = mask != 0 ? __builtin_ctzll(mask) : kLanes;
-            if (k == 0) {
-                hi = lo;
-            } else {
-                const int64_t top = lo + k * step;
-                lo += (k - 1) * step + 1;
-                hi = top < hi ? top : hi;
-            }
-        }
-        if (lane == 0) (rows ? A.row_cut : A.col_cut)[t] = SchurCut{lo, clamp_entry(ptr[lo], A.capacity)};
+        const auto reached = [&](int64_t r) { return clamp_entry(ptr[r], A.capacity) + kSchurRowCost * r >= target; };
+        const int64_t at = wave_first(t == kSchurParts ? count : 0, t == 0 ? 0 : count, lane, reached);
+        if (lane == 0) (rows ? A.row_cut : A.col_cut)[t] = SchurCut{at, clamp_entry(ptr[at], A.capacity)};
         return;
     }
     const int sys = (int)blockIdx.y;
@@ -215,11 +201,6 @@ __device__ __forceinline__ void schur_part_sums(double (&v)[NV], double (*lds)[k
     }
 }
 
-constexpr int kDppRowShr = 0x110;       // + D: lanes move up by D inside each row of 16, 0 moves in
-constexpr int kDppWaveShr1 = 0x138;     // lanes move up by 1, 0 moves in
-constexpr int kDppRowBcast15 = 0x142;   // lane 15 of each row to the row behind it
-constexpr int kDppRowBcast31 = 0x143;   // lane 31 to the two rows behind it
-
 // Segmented inclusive sum over the wave: lane l ends with the sum of lanes l - dist .. l, where a segment begins.
 struct SegmentedScan {
     int to15, to31;  // distances from which on a segment reaches into the row of lanes, and the half, before
@@ -242,18 +223,6 @@ struct SegmentedScan {
         return v;
     }
 };
-
-// inclusive sum over the wave
-__device__ __forceinline__ int wave_scan(int v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, kDppRowShr + 1, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, kDppRowShr + 2, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, kDppRowShr + 4, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, kDppRowShr + 8, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, kDppRowBcast15, 0xa, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, kDppRowBcast31, 0xc, 0xf, true);
-    return v;
-}
 
 struct SchurPartShared {
     union __attribute__((aligned(16))) {

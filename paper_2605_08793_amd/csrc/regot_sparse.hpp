@@ -16,8 +16,8 @@
 
 namespace regot {
 
-constexpr int kRowsPerScanBlock = 32;  // rows per block in the prefix count of dropped entries (a power of two <= 64)
-static_assert(kThreads % kRowsPerScanBlock == 0 && kRowsPerScanBlock <= kLanes, "row blocks");
+constexpr int kRowsPerScanBlock = 32;  // rows per block in the prefix count of dropped entries: a bit each in half a word
+static_assert(kLanes % kRowsPerScanBlock == 0, "row blocks");
 
 struct PatternArgs {
     int n, m;
@@ -43,49 +43,114 @@ __device__ __forceinline__ void row_range(const int64_t *row_ptr, int64_t i, int
     if (p1 > capacity) p1 = capacity;
 }
 
-// val[p] = T_{i, col_idx[p]}: one wave per row, a random 8-byte read of M per entry.
-__global__ __launch_bounds__(kThreads) void pattern_values_kernel(PatternArgs A)
-{
-    const int lane = threadIdx.x & (kLanes - 1);
-    // (Rows in turn to all workgroups.  Contiguous rows to each die put together the lines of val_csc that neighbouring rows
-    // share, 97 -> 90 us with 2e6 entries spread over the rows, but a die then has as many entries as its eighth of the rows:
-    // half of them in a sixth of the rows 173 us against 73, all in an eighth 331 against 72.)
-    const int64_t wave = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
-    const int64_t nwaves = (int64_t)gridDim.x * kWaves;
-    for (int64_t i = wave; i < A.n; i += nwaves) {
-        int64_t p0, p1;
-        row_range(A.row_ptr, i, A.capacity, p0, p1);
-        const double al = A.alpha[i];
-        const double *Mrow = A.M + i * A.ldM;
-        // four entries per lane in flight (the longest rows set the duration of the kernel)
-        constexpr int kDepth = 4;
-        for (int64_t p = p0 + lane; p < p1; p += kDepth * kLanes) {
-            int32_t j[kDepth];
-            double mij[kDepth], be[kDepth];
-            bool ok[kDepth];
-#pragma unroll
-            for (int d = 0; d < kDepth; ++d) {
-                const int64_t q = p + d * kLanes;
-                j[d] = q < p1 ? A.col_idx[q] : -1;
-                ok[d] = (uint32_t)j[d] < (uint32_t)A.m;  // anything else is not a column: the entry is left alone
+// Kernels that take the entries of a pattern in tiles of consecutive ones, whatever rows they are in: where the tile's rows
+// begin is found by a wave-wide search, and an entry's row by bisection in LDS, for all entries of a thread side by side.
+// ITEMS entries to a thread: kTileItems, or kTileFew where that would leave compute units without work (30000 entries: values
+// 6.0 us against 14, triangle 4.4 against 11; a wave per row and a workgroup per 32 rows took 4.4 and 4.8).
+constexpr int kTileItems = 8, kTileFew = 2;
+constexpr int64_t kTileFewBelow = 256 * kTileItems * kThreads;
+constexpr int kTileHeld = kTileItems * kThreads;  // rows whose ends are held (a power of two): all of a tile's, unless many have no entries
+static_assert((kTileHeld & (kTileHeld - 1)) == 0 && (kThreads & (kThreads - 1)) == 0, "bisection by halves");
+template <int ITEMS>
+struct TileRows {
+    static constexpr int kEntries = ITEMS * kThreads;
+    // the rows of entries base + k * kThreads + thread, k < ITEMS, of those below base + count; by the whole workgroup
+    __device__ __forceinline__ static void find(int *ends /* LDS [kTileHeld] */, const int64_t *ptr, int n, int64_t base, int count,
+                                                int64_t (&row)[ITEMS])
+    {
+        const int tid = (int)threadIdx.x;
+        const int64_t row0 = wave_first(1, n, tid & (kLanes - 1), [&](int64_t r) { return ptr[r] > base; }, kThreads / 2) - 1;
+        // where the rows from row0 on end (up to half of the first ones before the tile, which saves a load to wait for)
+        int held = 0, want = kThreads;
+        do {
+            for (; held < want; held += kThreads) {
+                const int64_t r = row0 + 1 + held + tid;
+                const int64_t e = r <= n ? ptr[r] - base : kEntries;
+                ends[held + tid] = (int)(e < 0 ? 0 : e > kEntries ? kEntries : e);
             }
+            want *= 2;
+            __syncthreads();
+        } while (held < kTileHeld && ends[held - 1] < count);
+        // the first end behind the entry
+        int at[ITEMS];
 #pragma unroll
-            for (int d = 0; d < kDepth; ++d) {
-                mij[d] = ok[d] ? __builtin_nontemporal_load(Mrow + j[d]) : 0.0;
-                be[d] = ok[d] ? A.beta[j[d]] : 0.0;
-            }
+        for (int k = 0; k < ITEMS; ++k) at[k] = 0;
+        for (int half = held / 2; half > 0; half >>= 1) {
 #pragma unroll
-            for (int d = 0; d < kDepth; ++d) {
-                if (!ok[d]) continue;
-                const int64_t q = p + d * kLanes;
-                const double t = exp_eta_any((al + be[d]) - mij[d], A.ex);
-                A.val[q] = t;
-                if (A.val_csc) {
-                    const int64_t c = A.csc_pos[q];
-                    if (c >= 0 && c < A.capacity) A.val_csc[c] = t;
+            for (int k = 0; k < ITEMS; ++k) at[k] += ends[at[k] + half - 1] <= k * kThreads + tid ? half : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) row[k] = row0 + at[k];
+        if (ends[held - 1] < count) {  // (more rows than are held: many without entries)
+            for (int k = 0; k < ITEMS; ++k) {
+                int64_t lo = row0, hi = (int64_t)n - 1;
+                while (lo < hi) {
+                    const int64_t mid = (lo + hi) >> 1;
+                    if (ptr[mid + 1] > base + k * kThreads + tid) hi = mid;
+                    else lo = mid + 1;
                 }
+                row[k] = lo;
             }
         }
+    }
+};
+
+// tiles of a pattern with room for `capacity` entries -> the workgroups of a kernel that takes them in turn
+template <int ITEMS>
+inline int64_t tile_blocks(int64_t capacity, int64_t most)
+{
+    const int64_t tiles = die_grid((capacity + TileRows<ITEMS>::kEntries - 1) / TileRows<ITEMS>::kEntries);
+    return tiles < most ? tiles : most;
+}
+
+// val[p] = T_{i, col_idx[p]}: a random 8-byte read of M per entry, everything of a tile requested at once.  Neighbouring tiles run
+// on one die, so that the lines of val_csc that neighbouring rows share are put together; a die has its share of the entries, not
+// of the rows, so it does not matter where they are.
+// What bounds it: 64-byte sectors of M at random places and 8-byte stores at random places (2e6 of them 48 and 37 us, each by
+// itself).  20000 x 20000, 2e6 entries: 101 -> 70 us; a wave per row waits for its row's range, columns and costs one after the
+// other, and the longest rows are the last to be ready.  4e6 entries in rows of equal length 155 -> 150.
+template <int ITEMS>
+__global__ __launch_bounds__(kThreads) void pattern_values_kernel(PatternArgs A)
+{
+    constexpr int kEntries = TileRows<ITEMS>::kEntries;
+    __shared__ int ends[kTileHeld];
+    const int tid = (int)threadIdx.x;
+    int64_t first, nnz, unused;
+    row_range(A.row_ptr, 0, A.capacity, first, unused);
+    nnz = A.row_ptr[A.n];
+    nnz = nnz < 0 ? 0 : nnz > A.capacity ? A.capacity : nnz;
+    const int64_t blocks = (nnz + kEntries - 1) / kEntries;
+    for (int64_t b = blockIdx.x; b < die_grid(blocks); b += gridDim.x) {
+        const int64_t tile = die_block(b, blocks);
+        if (tile >= blocks) continue;
+        const int64_t base = tile * kEntries;
+        const int count = (int)(nnz - base < kEntries ? nnz - base : kEntries);
+        int32_t j[ITEMS];
+        int64_t to[ITEMS], row[ITEMS];
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const int q = k * kThreads + tid;
+            j[k] = q < count ? A.col_idx[base + q] : -1;
+            to[k] = A.val_csc && q < count ? A.csc_pos[base + q] : -1;
+        }
+        TileRows<ITEMS>::find(ends, A.row_ptr, A.n, base, count, row);
+        double mij[ITEMS], s[ITEMS];
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            // (anything else is not a column, or in no row: the entry is left alone)
+            if ((uint32_t)j[k] >= (uint32_t)A.m || base + k * kThreads + tid < first) j[k] = -1;
+            const bool on = j[k] >= 0;
+            mij[k] = on ? __builtin_nontemporal_load(A.M + row[k] * A.ldM + j[k]) : 0.0;
+            s[k] = on ? A.alpha[row[k]] + A.beta[j[k]] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            if (j[k] < 0) continue;
+            const double t = exp_eta_any(s[k] - mij[k], A.ex);
+            A.val[base + k * kThreads + tid] = t;
+            if (to[k] >= 0 && to[k] < A.capacity) A.val_csc[to[k]] = t;
+        }
+        __syncthreads();  // (the next tile's rows)
     }
 }
 
@@ -476,7 +541,7 @@ struct LowerArgs {
     double *h_val;
     int64_t h_capacity;
     int64_t *info;        // [2]: entries, overflow
-    int64_t *blk;         // [nblk + 1] workspace: dropped entries per block of rows, then their prefix
+    int64_t *blk;         // [nblk + 1] workspace: dropped entries in the blocks of rows before << 32 | a bit per row of the block
     int nblk;
     int values_only;
 };
@@ -489,137 +554,144 @@ __device__ __forceinline__ int row_drops(const LowerArgs &A, int64_t i)
     return (p1 > p0 && A.col_idx[p1 - 1] == A.m - 1) ? 1 : 0;
 }
 
-// step 1: dropped entries per block of kRowsPerScanBlock rows; a thread per row, a 32-lane group per block
+// step 1: which rows of a block of kRowsPerScanBlock drop an entry; a thread per row, half a wave per block
 __global__ __launch_bounds__(kThreads) void lower_count_kernel(LowerArgs A)
 {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    int c = i < A.n ? row_drops(A, i) : 0;
-#pragma unroll
-    for (int off = kRowsPerScanBlock / 2; off >= 1; off >>= 1) c += __shfl_xor(c, off, kLanes);
+    const uint64_t drops = __ballot(i < A.n && row_drops(A, i));
     const int64_t rb = i / kRowsPerScanBlock;
-    if ((threadIdx.x & (kRowsPerScanBlock - 1)) == 0 && rb < A.nblk) A.blk[rb] = c;
+    if ((threadIdx.x & (kRowsPerScanBlock - 1)) == 0 && rb < A.nblk)
+        A.blk[rb] = (int64_t)(uint32_t)(drops >> (threadIdx.x & kRowsPerScanBlock & (kLanes - 1)));
 }
 
-// step 2: exclusive prefix over the blocks (one workgroup)
+// step 2: exclusive prefix over the blocks (one workgroup); all dropped entries in blk[nblk]
 __global__ __launch_bounds__(kThreads) void lower_scan_kernel(LowerArgs A)
 {
-    __shared__ int64_t part[kThreads + 1];
-    const int per = (A.nblk + kThreads - 1) / kThreads;
-    const int64_t b0 = (int64_t)threadIdx.x * per;
-    int64_t s = 0;
-    for (int64_t b = b0; b < b0 + per && b < A.nblk; ++b) s += A.blk[b];
-    part[threadIdx.x + 1] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        part[0] = 0;
-        for (int t = 1; t <= kThreads; ++t) part[t] += part[t - 1];
+    __shared__ int wave_total[kWaves];
+    constexpr int kPer = 4;  // blocks of a thread, asked for together
+    const int lane = threadIdx.x & (kLanes - 1), w = threadIdx.x >> 6;
+    int64_t carry = 0;
+    for (int64_t first = 0; first < A.nblk; first += kPer * kThreads) {
+        const int64_t b0 = first + (int64_t)threadIdx.x * kPer;
+        uint32_t bits[kPer];
+        int mine = 0;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) bits[k] = b0 + k < A.nblk ? (uint32_t)A.blk[b0 + k] : 0u;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) mine += __builtin_popcount(bits[k]);
+        const int incl = wave_scan(mine);
+        if (lane == kLanes - 1) wave_total[w] = incl;
+        __syncthreads();
+        int before = incl - mine, all = 0;
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q) {
+            before += q < w ? wave_total[q] : 0;
+            all += wave_total[q];
+        }
+        int64_t run = carry + before;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+            if (b0 + k < A.nblk) {
+                A.blk[b0 + k] = run << 32 | bits[k];
+                run += __builtin_popcount(bits[k]);
+            }
+        carry += all;
+        __syncthreads();
     }
-    __syncthreads();
-    int64_t run = part[threadIdx.x];
-    for (int64_t b = b0; b < b0 + per && b < A.nblk; ++b) {
-        const int64_t c = A.blk[b];
-        A.blk[b] = run;
-        run += c;
-    }
-    if (threadIdx.x == kThreads - 1) A.blk[A.nblk] = part[kThreads];  // all dropped entries
+    if (threadIdx.x == 0) A.blk[A.nblk] = carry;
 }
 
-// step 3: column i < n of the lower triangle = diagonal, then row i of T^Omega_{-m} as rows n + j;
-// columns n + j hold their diagonal only.  A workgroup takes one block of rows: it works out where
-// each of its columns starts, then all its threads walk the block's pattern entries together
-// (coalesced), finding each entry's row by bisection in LDS.  Workgroups beyond the row blocks write
-// the beta diagonal.
-__global__ __launch_bounds__(kThreads) void lower_fill_kernel(LowerArgs A)
+// entries dropped in the rows before row i
+__device__ __forceinline__ int64_t dropped_before(const LowerArgs &A, int64_t i)
 {
-    __shared__ int64_t rp[kRowsPerScanBlock + 1];
-    __shared__ int64_t base[kRowsPerScanBlock];
+    const int64_t b = A.blk[i / kRowsPerScanBlock];
+    return (b >> 32) + __builtin_popcount((uint32_t)b & ((1u << (i & (kRowsPerScanBlock - 1))) - 1u));
+}
+
+// step 3: column i < n of the lower triangle = diagonal, then row i of T^Omega_{-m} as rows n + j; columns n + j hold their
+// diagonal only.  i diagonals and row_ptr[i] pattern entries come before column i, minus the dropped ones.  The first
+// workgroups take tiles of consecutive pattern entries (TileRows); the others a column's beginning and its diagonal per
+// thread.  2e6 entries 24 -> 13.4 us (48 MB read and written), 4e6 25.5 -> 24: a workgroup per 32 rows was ready when the
+// longest 32 rows were.
+template <int ITEMS>
+__global__ __launch_bounds__(kThreads) void lower_fill_kernel(LowerArgs A, int tile_blocks)
+{
+    constexpr int kEntries = TileRows<ITEMS>::kEntries;
+    __shared__ int ends[kTileHeld];
+    const int tid = (int)threadIdx.x;
     const int mb = A.m - 1;
     const double inv_eta = 1.0 / A.eta;
-    if ((int64_t)blockIdx.x < A.nblk) {
-        const int64_t r0 = (int64_t)blockIdx.x * kRowsPerScanBlock;
-        const int rows = (int)(A.n - r0 < kRowsPerScanBlock ? A.n - r0 : kRowsPerScanBlock);
-        const int t = threadIdx.x;
-        if (t <= rows) {
-            int64_t v = A.row_ptr[r0 + t];
-            rp[t] = v < 0 ? 0 : v > A.capacity ? A.capacity : v;
-        }
-        __syncthreads();
-        if (t < kLanes) {  // first wave: lanes 0 .. rows-1 own a row each
-            const bool live = t < rows;
-            int64_t start = 0;
-            if (A.values_only) {
-                if (live) start = A.h_col_ptr[r0 + t];
-            } else {
-                // i diagonals and row_ptr[i] pattern entries come before column i, minus the dropped ones
-                const int flag = live ? row_drops(A, r0 + t) : 0;
-                int incl = flag;
+    int64_t first, pn, unused;
+    row_range(A.row_ptr, 0, A.capacity, first, unused);
+    pn = A.row_ptr[A.n];
+    pn = pn < 0 ? 0 : pn > A.capacity ? A.capacity : pn;
+    if ((int)blockIdx.x < tile_blocks) {
+        const int64_t blocks = (pn + kEntries - 1) / kEntries;
+        for (int64_t b = blockIdx.x; b < die_grid(blocks); b += tile_blocks) {
+            const int64_t tile = die_block(b, blocks);
+            if (tile >= blocks) continue;
+            const int64_t base = tile * kEntries;
+            const int count = (int)(pn - base < kEntries ? pn - base : kEntries);
+            int32_t j[ITEMS];
+            double v[ITEMS];
+            int64_t row[ITEMS], place[ITEMS];
 #pragma unroll
-                for (int off = 1; off < kRowsPerScanBlock; off <<= 1) {
-                    const int up = __shfl_up(incl, off, kLanes);
-                    if (t >= off) incl += up;
-                }
-                if (live) start = (r0 + t) + rp[t] - (A.blk[blockIdx.x] + (incl - flag));
+            for (int k = 0; k < ITEMS; ++k) {
+                const int q = k * kThreads + tid;
+                j[k] = q < count ? A.col_idx[base + q] : -1;
+                v[k] = q < count ? A.val[base + q] : 0.0;
             }
-            if (live) {
-                base[t] = start;
-                if (!A.values_only) A.h_col_ptr[r0 + t] = start;
-                if (start >= 0 && start < A.h_capacity) {
-                    if (!A.values_only) A.h_row_idx[start] = (int32_t)(r0 + t);
-                    A.h_val[start] = A.row_sum[r0 + t] * inv_eta + A.tau;
-                }
-            }
-        }
-        __syncthreads();
-        // (kDepth entries per thread at a time, all requested before the first is placed: a block's few thousand entries
-        // are a chain of rounds of loads otherwise; 2e6 entries 33.6 -> 23.8 us)
-        constexpr int kDepth = 4;
-        for (int64_t first = rp[0] + t; first < rp[rows]; first += kDepth * kThreads) {
-            int32_t j[kDepth];
-            double v[kDepth];
+            TileRows<ITEMS>::find(ends, A.row_ptr, A.n, base, count, row);
 #pragma unroll
-            for (int d = 0; d < kDepth; ++d) {
-                const int64_t p = first + d * kThreads;
-                j[d] = p < rp[rows] ? A.col_idx[p] : -1;
-                v[d] = p < rp[rows] ? A.val[p] : 0.0;
+            for (int k = 0; k < ITEMS; ++k) {
+                const int64_t p = base + k * kThreads + tid;
+                place[k] = -1;
+                if ((uint32_t)j[k] >= (uint32_t)mb || p < first) continue;
+                if (A.values_only) {
+                    int64_t p0, p1;
+                    row_range(A.row_ptr, row[k], A.capacity, p0, p1);
+                    place[k] = A.h_col_ptr[row[k]] - p0 + p + 1;
+                } else {
+                    place[k] = row[k] - dropped_before(A, row[k]) + p + 1;
+                }
             }
 #pragma unroll
-            for (int d = 0; d < kDepth; ++d) {
-                const int64_t p = first + d * kThreads;
-                if (p >= rp[rows]) break;
-                int lo = 0, hi = rows;  // rp[lo] <= p < rp[hi]
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (rp[mid] <= p) lo = mid;
-                    else hi = mid;
-                }
-                const int64_t q = base[lo] + 1 + (p - rp[lo]);
-                if ((uint32_t)j[d] < (uint32_t)mb && q >= 0 && q < A.h_capacity) {
-                    if (!A.values_only) A.h_row_idx[q] = A.n + j[d];
-                    A.h_val[q] = v[d] * inv_eta;
+            for (int k = 0; k < ITEMS; ++k) {
+                const int64_t q = place[k];
+                if (q >= 0 && q < A.h_capacity) {
+                    if (!A.values_only) A.h_row_idx[q] = A.n + j[k];
+                    A.h_val[q] = v[k] * inv_eta;
                 }
             }
+            __syncthreads();  // (the next tile's rows)
         }
-    } else {
-        // total entries: n + (m-1) diagonals + pattern entries outside the dropped column
-        int64_t pn = A.row_ptr[A.n];
-        if (pn > A.capacity) pn = A.capacity;
-        if (pn < 0) pn = 0;
-        const int64_t first_beta = A.values_only ? A.h_col_ptr[A.n + mb] - mb : (int64_t)A.n + pn - A.blk[A.nblk];
-        const int64_t j = ((int64_t)blockIdx.x - A.nblk) * kThreads + threadIdx.x;
-        if (j < mb) {
-            const int64_t q = first_beta + j;
-            if (!A.values_only) A.h_col_ptr[A.n + j] = q;
-            if (q >= 0 && q < A.h_capacity) {
-                if (!A.values_only) A.h_row_idx[q] = (int32_t)(A.n + j);
-                A.h_val[q] = A.col_sum[j] * inv_eta + A.tau;
-            }
+        return;
+    }
+    // total entries: n + (m-1) diagonals + pattern entries outside the dropped column
+    const int64_t first_beta = A.values_only ? A.h_col_ptr[A.n + mb] - mb : (int64_t)A.n + pn - A.blk[A.nblk];
+    const int64_t c = ((int64_t)blockIdx.x - tile_blocks) * kThreads + tid;
+    if (c < A.n) {
+        int64_t p = A.row_ptr[c];
+        p = p < 0 ? 0 : p > A.capacity ? A.capacity : p;
+        const int64_t q = A.values_only ? A.h_col_ptr[c] : c + p - dropped_before(A, c);
+        if (!A.values_only) A.h_col_ptr[c] = q;
+        if (q >= 0 && q < A.h_capacity) {
+            if (!A.values_only) A.h_row_idx[q] = (int32_t)c;
+            A.h_val[q] = A.row_sum[c] * inv_eta + A.tau;
         }
-        if ((int64_t)blockIdx.x == A.nblk && threadIdx.x == 0) {
-            const int64_t total = first_beta + mb;
-            if (!A.values_only) A.h_col_ptr[A.n + mb] = total;
-            A.info[0] = total;
-            A.info[1] = total > A.h_capacity ? 1 : 0;
+    } else if (c < (int64_t)A.n + mb) {
+        const int64_t q = first_beta + (c - A.n);
+        if (!A.values_only) A.h_col_ptr[c] = q;
+        if (q >= 0 && q < A.h_capacity) {
+            if (!A.values_only) A.h_row_idx[q] = (int32_t)c;
+            A.h_val[q] = A.col_sum[c - A.n] * inv_eta + A.tau;
         }
+    }
+    if (c == 0) {
+        const int64_t total = first_beta + mb;
+        if (!A.values_only) A.h_col_ptr[A.n + mb] = total;
+        A.info[0] = total;
+        A.info[1] = total > A.h_capacity ? 1 : 0;
     }
 }
 
