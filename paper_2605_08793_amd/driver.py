@@ -129,19 +129,21 @@ class SparseTerm:
         # the stored pattern is a copy: the buffers of the sparsify call are free to take the next pattern
         self.row_ptr = row_ptr.clone()
         self.col_idx = col_idx[:e].clone() if col_idx.numel() >= e else torch.zeros(e, dtype=torch.int32, device=dev)
-        self.col_ptr = torch.zeros(m + 1, dtype=torch.int64, device=dev)
-        self.row_idx = torch.zeros(e, dtype=torch.int32, device=dev)
-        self.csc_pos = torch.zeros(e, dtype=torch.int64, device=dev)
-        self.val = torch.zeros(e, dtype=torch.float64, device=dev)
-        self.val_csc = torch.zeros(e, dtype=torch.float64, device=dev)
+        self.h_capacity = n + m - 1 + self.nnz
+        # What the calls below leave as it is where an entry is no column's, or has no value yet, is zero from the start:
+        # one fill for all of it.  (What they always write whole is not filled.)
+        f64, i64, i32 = torch.float64, torch.int64, torch.int32
+        wanted = dict(row_idx=(e, i32), val=(e, f64), val_csc=(e, f64), h_col_ptr=(n + m, i64), h_row_idx=(self.h_capacity, i32),
+                      h_val=(self.h_capacity, f64), h_info=(2, i64))
+        words = {name: -(-count * kind.itemsize // 256) * 32 for name, (count, kind) in wanted.items()}
+        zeros = torch.zeros(sum(words.values()), dtype=f64, device=dev)
+        for (name, (count, kind)), part in zip(wanted.items(), zeros.split(list(words.values()))):
+            setattr(self, name, part.view(kind)[:count])
+        self.col_ptr = torch.empty(m + 1, dtype=i64, device=dev)
+        self.csc_pos = torch.empty(e, dtype=i64, device=dev) if self.nnz > 0 else torch.zeros(e, dtype=i64, device=dev)
         ws = torch.empty(max(B.regot_pattern_transpose_workspace_bytes(n, m, self.nnz), 256), dtype=torch.uint8, device=dev)
         B.regot_pattern_transpose(n, m, self.nnz, self.row_ptr, self.col_idx, self.col_ptr, self.row_idx, self.csc_pos,
                                   workspace=ws)
-        self.h_capacity = n + m - 1 + self.nnz
-        self.h_col_ptr = torch.zeros(n + m, dtype=torch.int64, device=dev)
-        self.h_row_idx = torch.zeros(self.h_capacity, dtype=torch.int32, device=dev)
-        self.h_val = torch.zeros(self.h_capacity, dtype=torch.float64, device=dev)
-        self.h_info = torch.zeros(2, dtype=torch.int64, device=dev)
         self.h_workspace = torch.empty(max(B.regot_hessian_workspace_bytes(n, m), 256), dtype=torch.uint8, device=dev)
         self._structure_done = False
 
