@@ -40,9 +40,16 @@ typedef unsigned long long u64;
 
 constexpr int kDigitBits = 13;              // bits fixed per histogram pass
 constexpr int kBins = 1 << kDigitBits;
-constexpr int kBracketBits = 7;             // leading bits of the bracket keys the bracket pass itself histograms
+constexpr int kBracketBits = 10;            // leading bits of the bracket keys the bracket pass itself histograms (with 7 the pool
+                                            // was one step longer in narrowing down: 40000 x 10000 592 -> 575 us)
 constexpr int kRadixPasses = (64 + kDigitBits - 1) / kDigitBits;  // radix passes (over M, then over the pool) in the worst case
 constexpr int kKeyBuf = 1024;               // keys a wave stages in LDS before it writes them to a pool
+// The bracket pass: 64-bit words of LDS for its histogram and count, and the keys a wave stages in what is left.  So many that
+// hardly a wave writes while the matrix streams (40000 x 10000, k = 4e6: 775 keys a wave; a buffer of 1024 that has to keep
+// room for a row of a panel was written out at 512), and the last keys of a workgroup's waves go out by one allocation:
+// with one of each of 2000 waves 618 -> 592 us there, 552 -> 541 at 20000 x 20000, 208 -> 197 at 10000 x 10000.
+constexpr int kBracketHist = (1 << kBracketBits) / 2 + 2;
+constexpr int kBracketBuf = (kBins - kBracketHist) / kWaves;
 constexpr int kSmallPool = 1 << 16;         // keys of the second, small pool
 constexpr int kHistSlots = 3;               // kernel i fills slot i % 3, reads slot (i-1) % 3, clears slot (i+1) % 3
 constexpr int kSampleSlots = 2;             // two more slots: second sample histogram of either end of the bracket
@@ -53,7 +60,7 @@ constexpr int kSampleFew = 8;               // a sample bucket of this many keys
 constexpr int kFinishKeys = 256;            // the result kernel selects among this many keys by itself ...
 constexpr int kFinishPool = 1 << 14;        // ... out of a pool of at most this many (step kernels then return at once)
 constexpr double kBracketZ = 5.0;           // half-width of the bracket in standard deviations of the sample rank
-static_assert((1 << kBracketBits) < kThreads, "one thread per bin of the bracket histogram");
+static_assert(kBracketBuf >= 2 * kPanel, "as kKeyBuf");
 static_assert(kKeyBuf >= 2 * kPanel, "a wave appends up to one panel row between two checks");
 static_assert(kSample % (kThreads * 16) == 0, "sample size");
 static_assert(kBracketBits + kRadixPasses * kDigitBits >= 64, "the passes after a bracket pass fix all bits");
@@ -130,11 +137,13 @@ struct SelState {
 };
 
 struct SelCounters {     // cleared by the gather kernel
+    // 64-bit: with more than 2^32 entries and heavy ties a 32-bit count of the keys inside a bracket could wrap.
+    // (The two that every workgroup of the bracket pass adds to, at its end, on lines of their own: additions to a line queue up.)
     u64 above;               // bracket pass: keys > hi
-    // 64-bit: with more than 2^32 entries and heavy ties a 32-bit count of the keys inside a bracket could wrap
-    u64 bracket_fill;        // bracket pass: keys inside the bracket (also those that did not fit the pool)
     u64 radix_fill;          // collecting histogram pass over M: keys appended
     u64 small_fill;          // collecting histogram pass over the pool: keys appended to the small pool
+    u64 other_line[13];
+    u64 bracket_fill;        // bracket pass: keys inside the bracket (also those that did not fit the pool)
 };
 
 struct SelectArgs {
@@ -477,7 +486,7 @@ __global__ __launch_bounds__(kThreads) void select_gather_kernel(SelectArgs A)
     for (int i = (int)t; i < (kHistSlots + kSampleSlots) * kBins; i += kSample) A.ghist[i] = 0;
     const SelState st0 = start_state(A);
     if (t == 0) {
-        SelCounters c;
+        SelCounters c{};
         c.above = 0;
         c.bracket_fill = 0;
         c.radix_fill = 0;
@@ -517,7 +526,7 @@ __global__ __launch_bounds__(kThreads) void select_gather_kernel(SelectArgs A)
 
 // Histogram of the next 13 bits of the sample keys that share what is known of either end's key.
 // A workgroup takes kSamplePer keys per thread, so that few workgroups add to the global slots.
-constexpr int kSamplePer = 16;
+constexpr int kSamplePer = 4;
 constexpr int kSampleGrid = kSample / (kThreads * kSamplePer);
 __global__ __launch_bounds__(kThreads) void select_sample_kernel(SelectArgs A, int idx)
 {
@@ -572,7 +581,8 @@ __global__ __launch_bounds__(kThreads) void select_sample_kernel(SelectArgs A, i
 
 // Keys a wave wants to keep go to its LDS buffer first and to the pool in large runs.
 struct KeyStage {
-    u64 *stage;          // [kKeyBuf] of this wave
+    u64 *stage;          // [cap] of this wave
+    int cap;
     u64 *pool;
     u64 *fill_ctr;       // global count of keys appended
     unsigned pool_cap;
@@ -612,7 +622,7 @@ struct KeyStage {
     // make room for up to `most` more keys
     __device__ __forceinline__ void reserve(int most)
     {
-        if (fill > kKeyBuf - most) flush();
+        if (fill > cap - most) flush();
     }
     __device__ __forceinline__ void push(bool keep, u64 key)
     {
@@ -688,7 +698,7 @@ __device__ __forceinline__ void hist_pass(const SelectArgs &A, const SelState &s
     const PanelCols<MODE> pc(block_panel(blockIdx.x, A.g_c), A.m, lane);
     double bet[kU][2];
     load_beta(A, pc, lane, bet);
-    KeyStage ks{stage_all + w * kKeyBuf, A.pool, &A.cnt->radix_fill, A.pool_cap, 0, lane};
+    KeyStage ks{stage_all + w * kKeyBuf, kKeyBuf, A.pool, &A.cnt->radix_fill, A.pool_cap, 0, lane};
 
     stream_task<ALIGNED, MODE>(A, pc, lane, w, [&](double al, const double (&v)[kU][2]) {
         if (collect) ks.reserve(kPanel);
@@ -712,7 +722,7 @@ __device__ __forceinline__ void hist_pass(const SelectArgs &A, const SelState &s
 // bracket; the copied keys are also counted by their st.width leading bits.
 template <bool ALIGNED, int MODE>
 __device__ __forceinline__ void bracket_pass(const SelectArgs &A, const SelState &st, unsigned *hist,
-                                             unsigned *block_above, u64 *stage_all)
+                                             unsigned *block_above, u64 *stage_all, u64 *wave_fill)
 {
     constexpr bool FULL = MODE == kPanelFull;
     const int lane = threadIdx.x & (kLanes - 1);
@@ -723,7 +733,7 @@ __device__ __forceinline__ void bracket_pass(const SelectArgs &A, const SelState
     const PanelCols<MODE> pc(block_panel(blockIdx.x, A.g_c), A.m, lane);
     double bet[kU][2];
     load_beta(A, pc, lane, bet);
-    KeyStage ks{stage_all + w * kKeyBuf, A.pool, &A.cnt->bracket_fill, A.pool_cap, 0, lane};
+    KeyStage ks{stage_all + w * kBracketBuf, kBracketBuf, A.pool, &A.cnt->bracket_fill, A.pool_cap, 0, lane};
     unsigned n_above = 0;  // this lane's count; a lane sees at most kMaxChunkRows * 8 entries
 
     stream_task<ALIGNED, MODE>(A, pc, lane, w, [&](double al, const double (&v)[kU][2]) {
@@ -747,7 +757,7 @@ __device__ __forceinline__ void bracket_pass(const SelectArgs &A, const SelState
             }
         }
     });
-    ks.flush();
+    ks.flush_workgroup(wave_fill, w);
     if (n_above != 0) atomicAdd(block_above, n_above);
 }
 
@@ -771,14 +781,15 @@ __device__ __forceinline__ void pool_pass(const SelectArgs &A, const SelState &s
     const bool collect = st.collecting != 0;
     const int lane = threadIdx.x & (kLanes - 1);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    KeyStage ks{stage + w * kKeyBuf, A.small_pool, &A.cnt->small_fill, (unsigned)kSmallPool, 0, lane};
-    // two steps (four keys per thread) in flight; the trip count is the same for all threads of the workgroup
+    KeyStage ks{stage + w * kKeyBuf, kKeyBuf, A.small_pool, &A.cnt->small_fill, (unsigned)kSmallPool, 0, lane};
+    // kFlight steps (two keys per thread each) in flight; the trip count is the same for all threads of the workgroup
+    constexpr int kFlight = 4;
     const size_t stride = (size_t)gridDim.x * kStep;
-    for (size_t base = first; base < count; base += 2 * stride) {
-        u64 key[4] = {0, 0, 0, 0};
-        bool hit[4] = {false, false, false, false};
+    for (size_t base = first; base < count; base += kFlight * stride) {
+        u64 key[2 * kFlight] = {};
+        bool hit[2 * kFlight] = {};
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < kFlight; ++h) {
             const size_t i = base + h * stride + 2 * threadIdx.x;
             if (i + 1 < count) {
                 const ulonglong2 kk = *reinterpret_cast<const ulonglong2 *>(src + i);
@@ -790,9 +801,9 @@ __device__ __forceinline__ void pool_pass(const SelectArgs &A, const SelState &s
                 hit[2 * h] = true;
             }
         }
-        if (collect) ks.reserve(4 * kLanes);
+        if (collect) ks.reserve(2 * kFlight * kLanes);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < 2 * kFlight; ++e) {
             hit[e] = hit[e] && ((key[e] ^ prefix) & fmask) == 0;
             if (hit[e]) atomicAdd(&hist[(unsigned)(key[e] >> shift) & bmask], 1u);
             if (collect) ks.push(hit[e], key[e]);
@@ -828,7 +839,9 @@ __global__ __launch_bounds__(kThreads) REGOT_WAVES_ATTR(REGOT_SELECT_WAVES_PER_E
     if (!st.error && st.bits < st.bits_end && !finish_open(st)) {
         if (st.collected) {
             st.act = kActHistPool;
-            const bool large = !st.small_pool && st.pool_count > (unsigned)kSmallPool;
+            // (the result kernel reads a pool of up to kFinishPool keys by itself: a larger one is left behind as soon as the bucket
+            // fits the small one.  3000 x 4000, 50000 keys in the bracket: 92 -> 77 us.)
+            const bool large = !st.small_pool && st.pool_count > (unsigned)kFinishPool;
             st.width = st.bits_end - st.bits < kDigitBits ? st.bits_end - st.bits : kDigitBits;
             st.collecting = large && st.bucket <= (long long)kSmallPool;
         } else if (idx == kIdxBracket && st.use_bracket) {
@@ -855,18 +868,17 @@ __global__ __launch_bounds__(kThreads) REGOT_WAVES_ATTR(REGOT_SELECT_WAVES_PER_E
     const int mode = panel_mode(block_panel(blockIdx.x, A.g_c), A.m);
     if (st.act == kActBracket) {
         constexpr int kB = 1 << kBracketBits;  // hist[kB] is the workgroup's count of keys above the bracket
-        if (threadIdx.x <= kB) hist[threadIdx.x] = 0;
+        for (int i = threadIdx.x; i <= kB; i += kThreads) hist[i] = 0;
         __syncthreads();
         switch (mode) {
-        case kPanelFull: bracket_pass<ALIGNED, kPanelFull>(A, st, hist, hist + kB, stage); break;
-        case kPanelOverlap: bracket_pass<ALIGNED, kPanelOverlap>(A, st, hist, hist + kB, stage); break;
-        case kPanelOverlapEven: bracket_pass<ALIGNED, kPanelOverlapEven>(A, st, hist, hist + kB, stage); break;
-        default: bracket_pass<ALIGNED, kPanelPartial>(A, st, hist, hist + kB, stage); break;
+        case kPanelFull: bracket_pass<ALIGNED, kPanelFull>(A, st, hist, hist + kB, lds_raw + kBracketHist, R.wave_fill); break;
+        case kPanelOverlap: bracket_pass<ALIGNED, kPanelOverlap>(A, st, hist, hist + kB, lds_raw + kBracketHist, R.wave_fill); break;
+        case kPanelOverlapEven: bracket_pass<ALIGNED, kPanelOverlapEven>(A, st, hist, hist + kB, lds_raw + kBracketHist, R.wave_fill); break;
+        default: bracket_pass<ALIGNED, kPanelPartial>(A, st, hist, hist + kB, lds_raw + kBracketHist, R.wave_fill); break;
         }
         __syncthreads();
         if (threadIdx.x == 0 && hist[kB] != 0) atomicAdd(&A.cnt->above, (u64)hist[kB]);
-        if (threadIdx.x < (1u << st.width) && hist[threadIdx.x] != 0)
-            atomicAdd(&main_slot(A, idx)[threadIdx.x], (u64)hist[threadIdx.x]);
+        merge_histogram(hist, main_slot(A, idx), 1 << st.width);
         return;
     }
     for (int i = threadIdx.x; i < kBins; i += kThreads) hist[i] = 0;
