@@ -927,9 +927,10 @@ constexpr int64_t kSweepMinEntries = 1LL << 20;
 struct SweepPlan {
     int K = 0, P = 0, width = 0;
     void (*kernel)(SweepArgs) = nullptr;
+    bool keep = false;  // see SweepRows
 };
 
-SweepPlan make_sweep_plan(int64_t n, int64_t m)
+SweepPlan make_sweep_plan(int64_t n, int64_t m, int sweeps)
 {
     SweepPlan S;
     if (n * m < kSweepMinEntries || n < 64 || m < 64) return S;
@@ -939,7 +940,9 @@ SweepPlan make_sweep_plan(int64_t n, int64_t m)
     const int64_t K = eight ? K1 : K2;
     if (K > kSweepMaxK) return S;
     S.K = (int)K;
-    S.kernel = eight ? sweep_pass_kernel<1, 8> : m <= kSweepCols1 ? sweep_pass_kernel<1, 4> : sweep_pass_kernel<2, 4>;
+    S.keep = sweeps > 1 && n * m <= kSweepKeep;
+    if (S.keep) S.kernel = eight ? sweep_pass_kernel<1, 8, false> : m <= kSweepCols1 ? sweep_pass_kernel<1, 4, false> : sweep_pass_kernel<2, 4, false>;
+    else S.kernel = eight ? sweep_pass_kernel<1, 8, true> : m <= kSweepCols1 ? sweep_pass_kernel<1, 4, true> : sweep_pass_kernel<2, 4, true>;
     S.P = (int)(kNumCU / K < n / 8 ? kNumCU / K : n / 8);  // (at least 4 rows each)
     S.width = (int)(((m + K - 1) / K + 1) / 2 * 2);
     return S;
@@ -982,9 +985,11 @@ int run_sweeps(const SweepPlan &Q, int64_t n, int64_t m, const double *M, int64_
     if (A.K > 1)
         hipLaunchKernelGGL(sweep_init_kernel, dim3(kNumCU), dim3(kThreads), 0, s, reinterpret_cast<unsigned long long *>(A.exch),
                            n * A.K * 2, A.ticket);
-    const dim3 grid((unsigned)(A.P * A.K)), fin((unsigned)groups, (unsigned)A.splits);
+    // (whole rounds over the dies: what is beyond the clusters, or the columns, returns)
+    const dim3 grid((unsigned)die_grid(A.P * A.K)), fin((unsigned)die_grid(groups), (unsigned)A.splits);
     for (int i = 0; i < sweeps; ++i) {
         A.turn = i & 1;
+        A.up = Q.keep ? i & 1 : 0;
         if (i == 0) prof_begin(s);
         hipLaunchKernelGGL(Q.kernel, grid, dim3(kSweepThreads), 0, s, A);
         if (i == 0) prof_end(s);
@@ -1386,7 +1391,7 @@ int regot_sinkhorn_sweeps(int64_t n, int64_t m, const double *M, int64_t ldM, co
         if (st != REGOT_OK) return st;
         return (!a || !b) ? REGOT_ERR_NULL : REGOT_OK;
     }
-    const SweepPlan Q = make_sweep_plan(n, m);
+    const SweepPlan Q = make_sweep_plan(n, m, sweeps);
     if (Q.K > 0) {
         int st = check_matrix(n, m, M, ldM, eta, false);
         if (st != REGOT_OK) return st;

@@ -48,6 +48,7 @@ constexpr int kSweepCols1 = kSweepWaves * 2 * kLanes;       // columns of a work
 constexpr int kSweepCols = 2 * kSweepCols1;                 // most columns a workgroup can own: two groups per wave (3840)
 constexpr int kSweepMaxK8 = 5;                              // most members and fewest rows of a cluster whose batches are
 constexpr int kSweepRows8 = 32;                             // eight rows (see above)
+constexpr int64_t kSweepKeep = 120000000;                   // most entries of a matrix whose sweeps alternate (see SweepRows)
 constexpr int kSweepMaxK = 16;                              // members of a cluster: one lane of a DPP row each
 static_assert(kSweepWaves <= 16, "a DPP row of 16 lanes per row in sweep_factors");
 
@@ -81,7 +82,22 @@ struct SweepArgs {
     ExpParams ex;
     int *huge;        // [2] kSweepHugeMark in [turn]: a mass beyond kSweepHuge was met
     int turn;         // parity of the sweep
+    int up;           // the clusters take their rows from the last to the first (see SweepRows)
 };
+
+// The rows of a cluster in the order it takes them: t-th row of `count`, t beyond the last being the last again.
+// Every other sweep of a call takes them from the last to the first, and M is read with ordinary loads (STREAM false): a sweep
+// begins with the 32 MB that the one before it has left in the L2s.  (The last-level cache gives no more than the memory does:
+// what limits either is between the dies.)  That holds where a workgroup's rows are read on the die that read them last, so
+// the grids are whole rounds over the dies.  All sweeps in order, with non-temporal loads, -> these, us a sweep: 2000 x 1900
+// 16.0 -> 15.1, 3000^2 28.5 -> 26.9, 5000 x 3000 36.2 -> 33.7, 6000^2 64.7 -> 60.7, 8000^2 110 -> 108, 10000^2 152 -> 151.  Not for a
+// single sweep, which has nothing to begin with (10000^2 152 -> 160: ordinary loads of a stream cost something), and not beyond
+// kSweepKeep entries, where hardly anything is left of it (20000^2 584 -> 581, 30000 x 50000 2361 -> 2422).
+struct SweepRows {
+    int first, step, count;
+    __device__ __forceinline__ int at(int t) const { return first + step * min(t, count - 1); }
+};
+
 
 // The arguments of the running kernel, fetched where this stands.  For code that hardly ever runs: what it needs would
 // otherwise be fetched when the kernel starts, and there is not room for it (0.2 us a launch).
@@ -112,9 +128,9 @@ struct SweepShared {
 // Batches a cluster works through; rows beyond the last are its last row again, with a factor of 0.  An even number of batches
 // of four: eight rows are little to round up to.
 template <int R>
-__device__ __forceinline__ int sweep_batches(int r_begin, int r_end)
+__device__ __forceinline__ int sweep_batches(int rows)
 {
-    const int nb = (r_end - r_begin + R - 1) / R;
+    const int nb = (rows + R - 1) / R;
     return R == 4 ? (nb + 1) & ~1 : nb;
 }
 
@@ -129,8 +145,8 @@ __device__ __forceinline__ double wave_reduce_rows(const double (&v)[4]) { retur
 // MASKED: not all of the wave's groups are full (the last columns of the member).
 // The loads of a batch are issued by every wave unconditionally and in the same number, so that waiting for one batch
 // never waits for the one requested behind it: where the member has no column a lane reads its last two again.
-template <int NU, int R, bool MASKED>
-__device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R> &L, int cluster, int r_begin, int r_end,
+template <int NU, int R, bool STREAM, bool MASKED>
+__device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R> &L, int cluster, const SweepRows &rows,
                                            int c0, int ncol, int w, int lane)
 {
     typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));  // 16 bytes wherever a double may lie
@@ -159,12 +175,14 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R
     int floor_on = 0;  // (see before the loops below)
     double floor = -INFINITY, floor_max = -kDblMax;
 
-    const double *M0 = A.M + c0;
+    const double *M0 = A.M + (int64_t)rows.first * A.ldM + c0;
+    const int64_t ld = rows.step * A.ldM;
     auto load_row = [&](double (&v)[NU][2], int row) {
-        const double *prow = M0 + (int64_t)min(row, r_end - 1) * A.ldM;
+        const double *prow = M0 + (int64_t)min(row, rows.count - 1) * ld;
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
-            const dbl2u x = __builtin_nontemporal_load(reinterpret_cast<const dbl2u *>(reinterpret_cast<const char *>(prow) + off[u]));
+            const dbl2u *src = reinterpret_cast<const dbl2u *>(reinterpret_cast<const char *>(prow) + off[u]);
+            const dbl2u x = STREAM ? __builtin_nontemporal_load(src) : *src;
             v[u][0] = x.x;
             v[u][1] = x.y;
         }
@@ -188,7 +206,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R
             // an infinite cost or an infinite beta in the row: again from memory, with the IEEE limits of exp
             acc = 0.0;
             floor_on = 1;
-            const double *prow = M0 + (int64_t)min(row, r_end - 1) * A.ldM + first;
+            const double *prow = M0 + (int64_t)min(row, rows.count - 1) * ld + first;
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
                 const dbl2 bet = L.beta[u][threadIdx.x];
@@ -227,7 +245,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R
     // pipeline of the compute unit, and the waves wait to issue them instead of computing.
     auto batch = [&](auto floor_tag, int b, double (&cur)[R][NU][2], double (&old)[R][NU][2]) {
         constexpr bool FLOOR = decltype(floor_tag)::value;
-        const int row0 = r_begin + b * R, par = b & 1;
+        const int row0 = b * R, par = b & 1;
 #pragma unroll
         for (int h = 0; h < R; h += G) {
             auto turn = [&](int r, dbl2 (&x)[NU]) {
@@ -277,7 +295,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R
         }
         __syncthreads();
     };
-    const int nb = sweep_batches<R>(r_begin, r_end);
+    const int nb = sweep_batches<R>(rows.count);
     double v0[R][NU][2], v1[R][NU][2];
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -289,7 +307,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs &A, SweepShared<NU, R
     // (the two batches before the first; read back by this wave only, before anyone writes it)
     if (lane < 2 * R) L.fac[lane / R][lane % R][w] = 0.0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) load_row(v0[r], r_begin + r);
+    for (int r = 0; r < R; ++r) load_row(v0[r], r);
     __builtin_amdgcn_sched_barrier(0);
     // Terms that are -inf (an infinite cost, a column without mass) make the reduction of exp_eta a NaN.  A wave that has
     // met one, or has such a column, puts a finite floor under its terms from then on, low enough to give exactly 0 and to lie
@@ -410,16 +428,16 @@ __device__ __forceinline__ dbl2 sweep_member_row(const SweepArgs &A, int row, in
 // The factors of every batch, by one wave: lanes 16 r + j work on rows r, r + 4 of the batch, j being a wave of the
 // workgroup or a member of the cluster.
 template <int NU, int R>
-__device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU, R> &L, int member, int r_begin, int r_end, int lane)
+__device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU, R> &L, int member, const SweepRows &rows, int lane)
 {
     constexpr int Q = R / 4;
     const int r16 = lane >> 4, j16 = lane & 15;
-    const int nb = sweep_batches<R>(r_begin, r_end);
+    const int nb = sweep_batches<R>(rows.count);
     unsigned long long *exch = reinterpret_cast<unsigned long long *>(A.exch);
     int patience = A.looks;
     // (now, while the workers wait for their first rows)
     bool huge = false;
-    for (int i = r_begin + lane; i < r_end; i += kLanes) huge = huge || A.a[i] > kSweepHuge;
+    for (int t = lane; t < rows.count; t += kLanes) huge = huge || A.a[rows.at(t)] > kSweepHuge;
     if (__ballot(huge) != 0 && lane == 0) {
         L.huge = 1;
         A.huge[A.turn] = kSweepHugeMark;
@@ -433,9 +451,9 @@ __device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU
         dbl2 mine[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            row[q] = r_begin + b * R + 4 * q + r16;
-            live[q] = row[q] < r_end;
-            row[q] = min(row[q], r_end - 1);
+            const int t = b * R + 4 * q + r16;
+            live[q] = t < rows.count;
+            row[q] = rows.at(t);
             ai[q] = A.a[row[q]];
         }
         __syncthreads();  // the workers' (max, sum) of batch b are there
@@ -484,7 +502,7 @@ __device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU
                     while (open != 0) {
                         const int at = __builtin_ctzll(open);
                         open &= open - 1;
-                        const dbl2 pair = sweep_member_row<NU, R>(A, r_begin + b * R + 4 * q + (at >> 4), at & 15, lane);
+                        const dbl2 pair = sweep_member_row<NU, R>(A, rows.at(b * R + 4 * q + (at >> 4)), at & 15, lane);
                         if (lane == at) {
                             x[q] = (unsigned long long)__double_as_longlong(pair.x);
                             y[q] = (unsigned long long)__double_as_longlong(pair.y);
@@ -520,7 +538,7 @@ __device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU
 // before it finish whatever happens, so a place for the missing members comes free unless other kernels hold all that is
 // left, or the stream may use fewer compute units than a cluster has members; then they are waited for for a while and
 // done without (see sweep_factors).  Which workgroup does what has no influence on the results.
-template <int NU, int R>
+template <int NU, int R, bool STREAM>
 __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_kernel(SweepArgs A)
 {
     static_assert(NU * R <= 8 && (R == 4 || R == 8), "registers and LDS of a lane; rows of sweep_factors");
@@ -537,6 +555,7 @@ __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_
     const int cluster = role / A.K, member = role - cluster * A.K;
     int r_begin, r_end;
     chunk_rows(cluster, A.P, A.n, r_begin, r_end);
+    const SweepRows rows{A.up ? r_end - 1 : r_begin, A.up ? -1 : 1, r_end - r_begin};
     const int c0 = member * A.width;
     const int ncol = min(A.width, A.m - c0);
     if (w == kSweepWaves) {
@@ -544,11 +563,11 @@ __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_
         if (role == 0 && lane == 0) C.huge[C.turn ^ 1] = 0;  // (last read behind the sweep before)
         if (role == 0 && C.splits > 1)  // (for sweep_finalize_kernel)
             for (int i = lane; i < (C.m + kLanes - 1) / kLanes; i += kLanes) C.redo_count[i] = 0;
-        sweep_factors<NU, R>(C, L, member, r_begin, r_end, lane);
+        sweep_factors<NU, R>(C, L, member, rows, lane);
     } else if (2 * kLanes * ((NU - 1) * kSweepWaves + w + 1) <= ncol) {  // the wave's last group is full
-        sweep_wave<NU, R, false>(A, L, cluster, r_begin, r_end, c0, ncol, w, lane);
+        sweep_wave<NU, R, STREAM, false>(A, L, cluster, rows, c0, ncol, w, lane);
     } else {
-        sweep_wave<NU, R, true>(A, L, cluster, r_begin, r_end, c0, ncol, w, lane);
+        sweep_wave<NU, R, STREAM, true>(A, L, cluster, rows, c0, ncol, w, lane);
     }
 }
 
