@@ -7,9 +7,10 @@
 //
 // The pattern is the CSR the sparsify calls produce (all m columns, ascending inside a row);
 // "-m" drops the last column, so its entries are skipped here.  All of this is O(nnz) work on
-// data that is a few MB: one wave per row (or column), lanes over the entries, sums in a fixed
-// order (bit-reproducible), no floating-point atomics -- the product with the transposed block
-// reads the pattern by columns, which regot_pattern_transpose prepares once per pattern.
+// data that is a few MB: tiles of consecutive entries where every entry is for itself (values,
+// lower triangle), one wave per row (or column) and lanes over the entries where rows are summed,
+// in a fixed order (bit-reproducible), no floating-point atomics -- the product with the transposed
+// block reads the pattern by columns, which regot_pattern_transpose prepares once per pattern.
 #pragma once
 
 #include "regot_device.hpp"
@@ -45,11 +46,13 @@ __device__ __forceinline__ void row_range(const int64_t *row_ptr, int64_t i, int
 
 // Kernels that take the entries of a pattern in tiles of consecutive ones, whatever rows they are in: where the tile's rows
 // begin is found by a wave-wide search, and an entry's row by bisection in LDS, for all entries of a thread side by side.
-// ITEMS entries to a thread: kTileItems, or kTileFew where that would leave compute units without work (30000 entries: values
-// 6.0 us against 14, triangle 4.4 against 11; a wave per row and a workgroup per 32 rows took 4.4 and 4.8).
-constexpr int kTileItems = 8, kTileFew = 2;
+// ITEMS entries to a thread: kTileItems (four: 2e6 entries 67 + 12.3 us for values and triangle, 4e6 in all calls of a new pattern
+// 332; with eight, fewer waves to wait side by side, 70 + 13.4 and 340), or kTileFew where that would leave compute units without
+// work (30000 entries: values 6.0 us against 14 by eights, triangle 4.4 against 11; a wave per row and a workgroup per 32 rows
+// took 4.4 and 4.8).
+constexpr int kTileItems = 4, kTileFew = 2;
 constexpr int64_t kTileFewBelow = 256 * kTileItems * kThreads;
-constexpr int kTileHeld = kTileItems * kThreads;  // rows whose ends are held (a power of two): all of a tile's, unless many have no entries
+constexpr int kTileHeld = 8 * kThreads;  // rows whose ends are held (a power of two): all of a tile's, unless many have no entries
 static_assert((kTileHeld & (kTileHeld - 1)) == 0 && (kThreads & (kThreads - 1)) == 0, "bisection by halves");
 template <int ITEMS>
 struct TileRows {
@@ -107,7 +110,7 @@ inline int64_t tile_blocks(int64_t capacity, int64_t most)
 // on one die, so that the lines of val_csc that neighbouring rows share are put together; a die has its share of the entries, not
 // of the rows, so it does not matter where they are.
 // What bounds it: 64-byte sectors of M at random places and 8-byte stores at random places (2e6 of them 48 and 37 us, each by
-// itself).  20000 x 20000, 2e6 entries: 101 -> 70 us; a wave per row waits for its row's range, columns and costs one after the
+// itself).  20000 x 20000, 2e6 entries: 101 -> 67 us; a wave per row waits for its row's range, columns and costs one after the
 // other, and the longest rows are the last to be ready.  4e6 entries in rows of equal length 155 -> 150.
 template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void pattern_values_kernel(PatternArgs A)
@@ -611,7 +614,7 @@ __device__ __forceinline__ int64_t dropped_before(const LowerArgs &A, int64_t i)
 // step 3: column i < n of the lower triangle = diagonal, then row i of T^Omega_{-m} as rows n + j; columns n + j hold their
 // diagonal only.  i diagonals and row_ptr[i] pattern entries come before column i, minus the dropped ones.  The first
 // workgroups take tiles of consecutive pattern entries (TileRows); the others a column's beginning and its diagonal per
-// thread.  2e6 entries 24 -> 13.4 us (48 MB read and written), 4e6 25.5 -> 24: a workgroup per 32 rows was ready when the
+// thread.  2e6 entries 24 -> 12.3 us (48 MB read and written), 4e6 25.5 -> 24: a workgroup per 32 rows was ready when the
 // longest 32 rows were.
 template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void lower_fill_kernel(LowerArgs A, int tile_blocks)

@@ -10,7 +10,7 @@ from paper_2605_08793_amd.driver import SparseTerm
 
 pytestmark = pytest.mark.gpu
 
-# (n, m, lengths of the rows): a tile is 512 entries below 524288 of them and 2048 from there on
+# (n, m, lengths of the rows): a tile is 512 entries below 262144 of them and 1024 from there on
 CASES = {
     "more empty rows than are held": (150000, 8, lambda rng, n, m: np.where(rng.random(n) < 0.01, m, 0)),
     "only the last row": (70000, 9, lambda rng, n, m: np.where(np.arange(n) == n - 1, m, 0)),
