@@ -48,7 +48,7 @@ constexpr int kSweepCols1 = kSweepWaves * 2 * kLanes;       // columns of a work
 constexpr int kSweepCols = 2 * kSweepCols1;                 // most columns a workgroup can own: two groups per wave (3840)
 constexpr int kSweepMaxK8 = 5;                              // most members and fewest rows of a cluster whose batches are
 constexpr int kSweepRows8 = 32;                             // eight rows (see above)
-constexpr int64_t kSweepKeep = 120000000;                   // most entries of a matrix whose sweeps alternate (see SweepRows)
+constexpr int64_t kSweepKeep = 40000000;                    // most entries of a matrix whose sweeps alternate (see SweepRows)
 constexpr int kSweepMaxK = 16;                              // members of a cluster: one lane of a DPP row each
 static_assert(kSweepWaves <= 16, "a DPP row of 16 lanes per row in sweep_factors");
 
@@ -90,9 +90,12 @@ struct SweepArgs {
 // begins with the 32 MB that the one before it has left in the L2s.  (The last-level cache gives no more than the memory does:
 // what limits either is between the dies.)  That holds where a workgroup's rows are read on the die that read them last, so
 // the grids are whole rounds over the dies.  All sweeps in order, with non-temporal loads, -> these, us a sweep: 2000 x 1900
-// 16.0 -> 15.1, 3000^2 28.5 -> 26.9, 5000 x 3000 36.2 -> 33.7, 6000^2 64.7 -> 60.7, 8000^2 110 -> 108, 10000^2 152 -> 151.  Not for a
+// 16.0 -> 15.1, 3000^2 28.5 -> 26.9, 5000 x 3000 36.2 -> 33.7, 6000^2 64.7 -> 60.7.  Not for a
 // single sweep, which has nothing to begin with (10000^2 152 -> 160: ordinary loads of a stream cost something), and not beyond
-// kSweepKeep entries, where hardly anything is left of it (20000^2 584 -> 581, 30000 x 50000 2361 -> 2422).
+// kSweepKeep entries, where 32 MB are too little of a sweep to make up for the ordinary loads: 10000^2, four sweeps, one call
+// behind the other 637 -> 624, but 672 -> 691 behind M being written and 643 -> 693 on new arrays (8000^2 480 -> 450, and
+// 511 -> 526 behind a pause; 7000^2 365 -> 338, 394 -> 413 behind M being written; 6000^2 298 -> 271, 327 -> 315 and on new arrays
+// 294 -> 294; 2000 x 20000, three, 268 -> 242, 254 -> 258, 233 -> 231; 7001 x 4999, three, 232 -> 218, 252 -> 255, 237 -> 231; 20000^2 584 -> 581 a sweep, 30000 x 50000 2361 -> 2422).
 struct SweepRows {
     int first, step, count;
     __device__ __forceinline__ int at(int t) const { return first + step * min(t, count - 1); }
