@@ -111,7 +111,7 @@ inline int64_t tile_blocks(int64_t capacity, int64_t most)
 // of the rows, so it does not matter where they are.
 // What bounds it: 64-byte sectors of M at random places and 8-byte stores at random places (2e6 of them 48 and 37 us, each by
 // itself).  20000 x 20000, 2e6 entries: 101 -> 67 us; a wave per row waits for its row's range, columns and costs one after the
-// other, and the longest rows are the last to be ready.  4e6 entries in rows of equal length 155 -> 150.
+// other, and the longest rows are the last to be ready.  4e6 entries in rows of equal length 155 -> 142.
 template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void pattern_values_kernel(PatternArgs A)
 {
@@ -614,7 +614,7 @@ __device__ __forceinline__ int64_t dropped_before(const LowerArgs &A, int64_t i)
 // step 3: column i < n of the lower triangle = diagonal, then row i of T^Omega_{-m} as rows n + j; columns n + j hold their
 // diagonal only.  i diagonals and row_ptr[i] pattern entries come before column i, minus the dropped ones.  The first
 // workgroups take tiles of consecutive pattern entries (TileRows); the others a column's beginning and its diagonal per
-// thread.  2e6 entries 24 -> 12.3 us (48 MB read and written), 4e6 25.5 -> 24: a workgroup per 32 rows was ready when the
+// thread.  2e6 entries 24 -> 12.3 us (48 MB read and written), 4e6 25.5 -> 22: a workgroup per 32 rows was ready when the
 // longest 32 rows were.
 template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void lower_fill_kernel(LowerArgs A, int tile_blocks)

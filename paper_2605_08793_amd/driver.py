@@ -208,9 +208,9 @@ def _portions(portion, max_iter):
     """Iterations to enqueue between two looks at the convergence flag: `portion`, then a quarter of it, doubling up to
     `portion` again.  A solve that ends a few iterations behind its first portion (17 or 18 are common where 16 are
     enqueued) would otherwise wait for a second full one, whose kernels return at once but still have to run (about
-    9 us an iteration).  Directions with the rank-two term at 2000 x 2000 (17 and 18 iterations) 0.64-0.68 -> 0.52-0.55 ms.
-    With 16 iterations or fewer nothing changes (20000 x 20000: 0.86-0.99 ms before and after); 25 iterations, where the
-    portions add one look to what they save: 0.82 -> 0.84 ms, within the noise."""
+    5 us an iteration of the reduced solve).  Directions with the rank-two term at 2000 x 2000 (17 and 18 iterations): 0.64-0.68 ->
+    0.52-0.55 ms with an iteration of four kernels, 0.44 with the three there are now.  With 16 iterations or fewer nothing
+    changes; 25 iterations, where the portions add one look to what they save: within the noise."""
     its = min(portion, max_iter)
     done, step = its, max(1, portion // 4)
     yield its, done
