@@ -89,6 +89,14 @@ struct SchurArgs {
     int vec_blocks, norm_blocks;
 };
 
+// The beginning of share `part` of [0, count) cut into kSchurParts (part == kSchurParts: the end), for what every part does to
+// its share of a vector.
+__host__ __device__ constexpr int64_t schur_share(int64_t count, int part)
+{
+    const int64_t at = (count + kSchurParts - 1) / kSchurParts * part;
+    return at < count ? at : count;
+}
+
 __device__ __forceinline__ int64_t clamp_entry(int64_t p, int64_t capacity) { return p < 0 ? 0 : p > capacity ? capacity : p; }
 
 // Sum of part[0 .. count), count <= kSchurVecBlocks, in a fixed order; every lane gets it.  In two steps, so that the loads
@@ -359,12 +367,12 @@ __global__ __launch_bounds__(R *kSchurPartThreads) REGOT_WAVES_ATTR(4) void schu
     int cnt = (int)(r1 - r0 < kSchurHeld ? r1 - r0 : kSchurHeld);
     load_rows(r0, cnt);
     // a share of p = z + ratio p_old is formed with every part (kSchurRows), or a share of x handed on (kSchurRowsFinal)
-    const int share = (A.mb + kSchurParts - 1) / kSchurParts, share0 = me * share;
-    const int share1 = share0 + share < A.mb ? share0 + share : A.mb;
+    const int64_t share0 = schur_share(A.mb, me);
+    const int share = (int)(schur_share(A.mb, me + 1) - share0);
     double p_mine = 0.0, z_mine = 0.0;
-    if (MODE == kSchurRows && share0 + tid < share1) {
-        p_mine = p_old[share0 + tid];
-        z_mine = xs[share0 + tid];
+    if (MODE == kSchurRows && tid < share) {
+        p_mine = (p_old + share0)[tid];
+        z_mine = (xs + share0)[tid];
     }
 
     double ratio = 0.0;
@@ -400,14 +408,13 @@ __global__ __launch_bounds__(R *kSchurPartThreads) REGOT_WAVES_ATTR(4) void schu
         S.xs[nl] = 0.0;
     }
     if (MODE == kSchurRows) {
-        for (int i = share0 + tid; i < share1; i += kSchurPartThreads) {
-            const bool asked = i < share0 + kSchurPartThreads;
-            const double p = asked ? p_mine : p_old[i], z = asked ? z_mine : xs[i];
-            other[i] = first ? z : __builtin_fma(ratio, p, z);
+        for (int i = tid; i < share; i += kSchurPartThreads) {
+            const double p = i == tid ? p_mine : (p_old + share0)[i], z = i == tid ? z_mine : (xs + share0)[i];
+            (other + share0)[i] = first ? z : __builtin_fma(ratio, p, z);
         }
     }
     if (MODE == kSchurRowsFinal && A.x[sys] != A.x_out[sys] + A.n)
-        for (int i = share0 + tid; i < share1; i += kSchurPartThreads) A.x_out[sys][A.n + i] = xs[i];
+        for (int i = tid; i < share; i += kSchurPartThreads) (A.x_out[sys] + A.n + share0)[i] = (xs + share0)[i];
 
     const double inv_eta = 1.0 / A.eta;
     const SegmentedScan scan_wave(lane);
