@@ -517,8 +517,8 @@ int regot_pcg_solve2_reduced(int64_t n, int64_t m, double eta, double tau,
  * with q = s_prev = y_prev = v = NULL (no previous step), d = -p.  All vectors have n + m - 1 entries.
  *     info[0] = 1 if the rank-two term was used, info[1] = (y^-)^T s^-.
  * The inner products are summed in two stages in a fixed order (bit-reproducible).  Workspace:
- * regot_pcg_workspace_bytes(n, m); the workspace of the solves can be used (their state is not needed
- * any more once p and q are there).
+ * regot_pcg_workspace_bytes(n, m); the workspace of the solves can be used, and leaves their state alone: a solve
+ * whose iterations come in portions can go on behind it (restart = 0).
  */
 int regot_splr_direction(int64_t n, int64_t m,
                          const double *p, const double *q,

@@ -589,7 +589,7 @@ PcgLayout make_pcg_layout(int64_t n, int64_t m)
     L.Ap = take(N * kPcgMaxRhs * sizeof(double));
     // (the partial sums of the combination use the same region)
     L.part = take((size_t)(kCombineDots > kPcgPartRows ? kCombineDots : kPcgPartRows) * kPcgParts * sizeof(double));
-    L.sc = take(std::max(2 * sizeof(PcgScalars<kPcgMaxRhs>), 2 * kPcgMaxRhs * sizeof(SchurState)));
+    L.sc = take(std::max(2 * sizeof(PcgScalars<kPcgMaxRhs>), kPcgMaxRhs * (2 * sizeof(SchurState) + sizeof(SchurSums))));
     L.total = off;
     return L;
 }
@@ -880,6 +880,7 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
     static_assert(kSchurParts <= kSchurVecBlocks && kSchurVecBlocks * sizeof(double) + (kSchurParts + 1) * sizeof(SchurCut) <= kPcgParts * sizeof(double),
                   "rows of part");
     A.state = at<SchurState>(workspace, L.sc);
+    A.kept = reinterpret_cast<SchurSums *>(A.state + 2 * kPcgMaxRhs);
     A.info = info;
     const auto blocks_for = [](int64_t items) {
         return (int)std::max<int64_t>(1, std::min<int64_t>((items + kThreads - 1) / kThreads, kSchurVecBlocks));
@@ -898,9 +899,10 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
             hipLaunchKernelGGL((schur_half_kernel<MODE, R, false>), grid, block, 0, s, A);
     };
     if (restart) {
-        constexpr int kCutBlocks = (kSchurCutWaves + kWaves - 1) / kWaves;
-        hipLaunchKernelGGL(schur_prepare_kernel, dim3((unsigned)(A.norm_blocks + kCutBlocks), R), dim3(kThreads), 0, s, A);
+        hipLaunchKernelGGL(schur_prepare_kernel, dim3((unsigned)(A.norm_blocks + kSchurCutBlocks), R), dim3(kThreads), 0, s, A);
         half(std::integral_constant<int, kSchurColsRhs>{});
+    } else {
+        hipLaunchKernelGGL(schur_resume_kernel, dim3(kSchurCutBlocks + R), dim3(kThreads), 0, s, A);
     }
     for (A.it = 0; A.it < iterations; ++A.it) {
         half(std::integral_constant<int, kSchurRows>{});
