@@ -914,6 +914,17 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
     return hip_status();
 }
 
+// How the kernels over the entries of a stored pattern deal them out: rows (items = 0), or tiles of `items` entries a thread.
+struct EntryPlan {
+    int items, blocks;
+};
+EntryPlan make_entry_plan(int64_t n, int64_t m, int64_t capacity)
+{
+    if (few_rows(n, m, capacity)) return EntryPlan{0, (int)((n + kWaves - 1) / kWaves)};
+    if (capacity < kTileFewBelow) return EntryPlan{kTileFew, (int)tile_blocks<kTileFew>(capacity, 8 * kNumCU)};
+    return EntryPlan{kTileItems, (int)tile_blocks<kTileItems>(capacity, 8 * kNumCU)};
+}
+
 // Whole sweeps from one read of M each (regot_sweep.hpp): the clusters for an n x m matrix, or K = 0 if the sweep is to be
 // run as its two half-steps.  A sweep of 1600 x 1200 takes 13.7 us against 31, 7001 x 4999 69 against 119, 10000^2 157
 // against 277, 20000^2 594 against 985, 50000^2 4.0 ms against 6.5; 64 x 16500 19 against 21 us, 512 x 61440 68 against 105,
@@ -1444,10 +1455,11 @@ int regot_pattern_values(int64_t n, int64_t m, const double *M, int64_t ldM, con
     A.val = val;
     A.val_csc = val_csc;
     A.ex = make_exp_params(eta);
-    const bool few = capacity < kTileFewBelow;
-    const dim3 grid((unsigned)(few ? tile_blocks<kTileFew>(capacity, 8 * kNumCU) : tile_blocks<kTileItems>(capacity, 8 * kNumCU)));
-    if (few) hipLaunchKernelGGL(pattern_values_kernel<kTileFew>, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), A);
-    else hipLaunchKernelGGL(pattern_values_kernel<kTileItems>, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), A);
+    const EntryPlan P = make_entry_plan(n, m, capacity);
+    const auto kernel = P.items == 0          ? pattern_values_rows_kernel
+                        : P.items == kTileFew ? pattern_values_kernel<kTileFew>
+                                              : pattern_values_kernel<kTileItems>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)P.blocks), dim3(kThreads), 0, static_cast<hipStream_t>(stream), A);
     return hip_status();
 }
 
@@ -1556,11 +1568,12 @@ int regot_hessian_lower_csc(int64_t n, int64_t m, double eta, double tau, const 
         hipLaunchKernelGGL(lower_count_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, A);
         hipLaunchKernelGGL(lower_scan_kernel, dim3(1), dim3(kThreads), 0, s, A);
     }
-    const bool few = capacity < kTileFewBelow;
-    const int tiles = (int)(few ? tile_blocks<kTileFew>(capacity, 8 * kNumCU) : tile_blocks<kTileItems>(capacity, 8 * kNumCU));
-    const dim3 grid((unsigned)(tiles + (n + m - 1 + kThreads - 1) / kThreads));
-    if (few) hipLaunchKernelGGL(lower_fill_kernel<kTileFew>, grid, dim3(kThreads), 0, s, A, tiles);
-    else hipLaunchKernelGGL(lower_fill_kernel<kTileItems>, grid, dim3(kThreads), 0, s, A, tiles);
+    const EntryPlan P = make_entry_plan(n, m, capacity);
+    const dim3 grid((unsigned)(P.blocks + (n + m - 1 + kThreads - 1) / kThreads));
+    const auto kernel = P.items == 0          ? lower_fill_kernel<0>
+                        : P.items == kTileFew ? lower_fill_kernel<kTileFew>
+                                              : lower_fill_kernel<kTileItems>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, A, P.blocks);
     return hip_status();
 }
 

@@ -47,11 +47,14 @@ __device__ __forceinline__ void row_range(const int64_t *row_ptr, int64_t i, int
 // Kernels that take the entries of a pattern in tiles of consecutive ones, whatever rows they are in: where the tile's rows
 // begin is found by a wave-wide search, and an entry's row by bisection in LDS, for all entries of a thread side by side.
 // ITEMS entries to a thread: kTileItems (four: 2e6 entries 67 + 12.3 us for values and triangle, 4e6 in all calls of a new pattern
-// 332; with eight, fewer waves to wait side by side, 70 + 13.4 and 340), or kTileFew where that would leave compute units without
-// work (30000 entries: values 6.0 us against 14 by eights, triangle 4.4 against 11; a wave per row and a workgroup per 32 rows
-// took 4.4 and 4.8).
+// 332; with eight, fewer waves to wait side by side, 70 + 13.4 and 340), or kTileFew up to three small tiles to a compute unit
+// (values by twos / by fours: 300000 entries 13.9 / 15.8 us, 360000 13.1 / 15.3, 400000 19.2 / 17.2, 500000 20.1 / 18.7, 2e6
+// 76 / 74).
+// A workgroup per 32 rows writes the triangle on a stored structure faster where rows are many and short and alike (20000 x 20000,
+// 50000 entries 3.3 us against 4.3; 100000 x 50, 30000 entries 4.4 / 6.1), and slower everywhere else (20000 x 20000, 2e6
+// 12.2 / 11.9; 10^6 of 10000 x 10000 10.6 / 7.5; 20 rows of 4400 173 / 3.7).
 constexpr int kTileItems = 4, kTileFew = 2;
-constexpr int64_t kTileFewBelow = 256 * kTileItems * kThreads;
+constexpr int64_t kTileFewBelow = 768 * kTileFew * kThreads;
 constexpr int kTileHeld = 8 * kThreads;  // rows whose ends are held (a power of two): all of a tile's, unless many have no entries
 static_assert((kTileHeld & (kTileHeld - 1)) == 0 && (kThreads & (kThreads - 1)) == 0, "bisection by halves");
 template <int ITEMS>
@@ -155,6 +158,85 @@ __global__ __launch_bounds__(kThreads) void pattern_values_kernel(PatternArgs A)
         }
         __syncthreads();  // (the next tile's rows)
     }
+}
+
+// The same for a small pattern (few_rows): a wave takes a row, and what is beyond its first trip (kRowTrip entries) is left to the
+// whole workgroup, whose rows lie far apart.  of_row(i): what is needed of row i;  body(that, p, end, stride): entries p,
+// p + stride, .. below `end`, kRowDepth of them.
+//
+// Few entries are a matter of loads that wait for one another (a row's range, its columns, its costs), and a tile has two more of
+// them, for its number of entries and its rows.  Values, and triangle on a stored structure, by rows / by tiles, us:
+//   1000 x 1000    10000 entries  3.0 / 4.3   2.9 / 3.9        3000 x 3000  276000  10.5 / 12.5  3.4 / 5.1
+//   1000 x 1000    95000          4.2 / 4.7   2.9 / 4.0        4000 x 4000  375000  15.8 / 14.3  3.6 / 5.3
+//   1000 x 1000   330000         12.7 / 6.9   5.7 / 4.8        6000 x 6000   60000   4.6 /  5.3  3.6 / 4.0
+//   2000 x 8000   180000          7.5 / 9.0   3.1 / 4.4        8000 x 8000   80000   5.7 /  5.3    -
+// (8000 x 8000: a wave per row without the rest for the workgroup).  All entries in a fiftieth of the rows, 1577 to each: 7.4 / 5.0
+// and 4.3 / 4.0, where a wave by itself takes 16 us; with columns to kRowsColumns a row is at most eight more trips.
+constexpr int kRowsMost = 6144, kRowsColumns = 8192;           // rows and columns
+constexpr int kRowsEntries = 96, kRowsAll = 1024 * kThreads;   // entries to a row, on average, and together
+constexpr int kRowDepth = 4, kRowTrip = kRowDepth * kLanes;
+inline bool few_rows(int64_t n, int64_t m, int64_t capacity)
+{
+    return n <= kRowsMost && m <= kRowsColumns && capacity <= kRowsEntries * n && capacity <= kRowsAll;
+}
+template <typename G, typename F>
+__device__ __forceinline__ void for_rows(const int64_t *row_ptr, int64_t n, int64_t capacity, int blocks, G of_row, F body)
+{
+    __shared__ int64_t begin[kWaves], end[kWaves];
+    const int tid = (int)threadIdx.x, lane = tid & (kLanes - 1), w = tid >> 6;
+    const int64_t i = (int64_t)w * blocks + blockIdx.x;
+    int64_t p0 = 0, p1 = 0;
+    if (i < n) {
+        row_range(row_ptr, i, capacity, p0, p1);
+        body(of_row(i), p0 + lane, p1 < p0 + kRowTrip ? p1 : p0 + kRowTrip, kLanes);
+    }
+    const bool more = p1 > p0 + kRowTrip;
+    if (lane == 0) {
+        begin[w] = p0 + kRowTrip;
+        end[w] = p1;
+    }
+    if (__syncthreads_or(more) == 0) return;
+    for (int k = 0; k < kWaves; ++k) {
+        const int64_t e = end[k];
+        int64_t p = begin[k];
+        if (p >= e) continue;
+        const auto row = of_row((int64_t)k * blocks + blockIdx.x);
+        for (; p < e; p += kRowDepth * kThreads) body(row, p + tid, e, kThreads);
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void pattern_values_rows_kernel(PatternArgs A)
+{
+    struct Row {
+        double al;
+        const double *M;
+    };
+    for_rows(
+        A.row_ptr, A.n, A.capacity, (int)gridDim.x, [&](int64_t i) { return Row{A.alpha[i], A.M + i * A.ldM}; },
+        [&](const Row &row, int64_t p, int64_t end, int stride) {
+            int32_t j[kRowDepth];
+            int64_t to[kRowDepth];
+            double mij[kRowDepth], be[kRowDepth];
+#pragma unroll
+            for (int d = 0; d < kRowDepth; ++d) {
+                const int64_t q = p + d * stride;
+                j[d] = q < end ? A.col_idx[q] : -1;
+                to[d] = A.val_csc && q < end ? A.csc_pos[q] : -1;
+            }
+#pragma unroll
+            for (int d = 0; d < kRowDepth; ++d) {
+                if ((uint32_t)j[d] >= (uint32_t)A.m) j[d] = -1;  // (not a column: the entry is left alone)
+                mij[d] = j[d] >= 0 ? __builtin_nontemporal_load(row.M + j[d]) : 0.0;
+                be[d] = j[d] >= 0 ? A.beta[j[d]] : 0.0;
+            }
+#pragma unroll
+            for (int d = 0; d < kRowDepth; ++d) {
+                if (j[d] < 0) continue;
+                const double t = exp_eta_any((row.al + be[d]) - mij[d], A.ex);
+                A.val[p + d * stride] = t;
+                if (to[d] >= 0 && to[d] < A.capacity) A.val_csc[to[d]] = t;
+            }
+        });
 }
 
 struct MatvecArgs {
@@ -616,11 +698,10 @@ __device__ __forceinline__ int64_t dropped_before(const LowerArgs &A, int64_t i)
 // workgroups take tiles of consecutive pattern entries (TileRows); the others a column's beginning and its diagonal per
 // thread.  2e6 entries 24 -> 12.3 us (48 MB read and written), 4e6 25.5 -> 22: a workgroup per 32 rows was ready when the
 // longest 32 rows were.
+// ITEMS 0: the entries by rows (for_rows).
 template <int ITEMS>
-__global__ __launch_bounds__(kThreads) void lower_fill_kernel(LowerArgs A, int tile_blocks)
+__global__ __launch_bounds__(kThreads) void lower_fill_kernel(LowerArgs A, int entry_blocks)
 {
-    constexpr int kEntries = TileRows<ITEMS>::kEntries;
-    __shared__ int ends[kTileHeld];
     const int tid = (int)threadIdx.x;
     const int mb = A.m - 1;
     const double inv_eta = 1.0 / A.eta;
@@ -628,9 +709,39 @@ __global__ __launch_bounds__(kThreads) void lower_fill_kernel(LowerArgs A, int t
     row_range(A.row_ptr, 0, A.capacity, first, unused);
     pn = A.row_ptr[A.n];
     pn = pn < 0 ? 0 : pn > A.capacity ? A.capacity : pn;
-    if ((int)blockIdx.x < tile_blocks) {
+    if constexpr (ITEMS == 0) {
+        if ((int)blockIdx.x < entry_blocks) {
+            for_rows(
+                A.row_ptr, A.n, A.capacity, entry_blocks,
+                [&](int64_t i) {  // place of entry p: that + p
+                    int64_t p0, p1;
+                    row_range(A.row_ptr, i, A.capacity, p0, p1);
+                    return (A.values_only ? A.h_col_ptr[i] - p0 : i - dropped_before(A, i)) + 1;
+                },
+                [&](int64_t place, int64_t p, int64_t end, int stride) {
+                    int32_t j[kRowDepth];
+                    double v[kRowDepth];
+#pragma unroll
+                    for (int d = 0; d < kRowDepth; ++d) {
+                        j[d] = p + d * stride < end ? A.col_idx[p + d * stride] : -1;
+                        v[d] = p + d * stride < end ? A.val[p + d * stride] : 0.0;
+                    }
+#pragma unroll
+                    for (int d = 0; d < kRowDepth; ++d) {
+                        const int64_t q = place + p + d * stride;
+                        if ((uint32_t)j[d] < (uint32_t)mb && q >= 0 && q < A.h_capacity) {
+                            if (!A.values_only) A.h_row_idx[q] = A.n + j[d];
+                            A.h_val[q] = v[d] * inv_eta;
+                        }
+                    }
+                });
+            return;
+        }
+    } else if ((int)blockIdx.x < entry_blocks) {
+        constexpr int kEntries = TileRows<ITEMS>::kEntries;
+        __shared__ int ends[kTileHeld];
         const int64_t blocks = (pn + kEntries - 1) / kEntries;
-        for (int64_t b = blockIdx.x; b < die_grid(blocks); b += tile_blocks) {
+        for (int64_t b = blockIdx.x; b < die_grid(blocks); b += entry_blocks) {
             const int64_t tile = die_block(b, blocks);
             if (tile >= blocks) continue;
             const int64_t base = tile * kEntries;
@@ -672,7 +783,7 @@ __global__ __launch_bounds__(kThreads) void lower_fill_kernel(LowerArgs A, int t
     }
     // total entries: n + (m-1) diagonals + pattern entries outside the dropped column
     const int64_t first_beta = A.values_only ? A.h_col_ptr[A.n + mb] - mb : (int64_t)A.n + pn - A.blk[A.nblk];
-    const int64_t c = ((int64_t)blockIdx.x - tile_blocks) * kThreads + tid;
+    const int64_t c = ((int64_t)blockIdx.x - entry_blocks) * kThreads + tid;
     if (c < A.n) {
         int64_t p = A.row_ptr[c];
         p = p < 0 ? 0 : p > A.capacity ? A.capacity : p;

@@ -10,7 +10,8 @@ from paper_2605_08793_amd.driver import SparseTerm
 
 pytestmark = pytest.mark.gpu
 
-# (n, m, lengths of the rows): a tile is 512 entries below 262144 of them and 1024 from there on
+# (n, m, lengths of the rows): a tile is 512 entries below 393216 of them and 1024 from there on; by rows instead with at most
+# 6144 rows, 8192 columns, 96 entries to a row on average and 262144 of them, 256 of a row by its wave, the others by four waves
 CASES = {
     "more empty rows than are held": (150000, 8, lambda rng, n, m: np.where(rng.random(n) < 0.01, m, 0)),
     "only the last row": (70000, 9, lambda rng, n, m: np.where(np.arange(n) == n - 1, m, 0)),
@@ -19,6 +20,15 @@ CASES = {
     "whole tiles": (64, 2048, lambda rng, n, m: np.full(n, m // 2)),
     "long and empty rows, many entries": (3000, 400, lambda rng, n, m: np.where(np.arange(n) % 2 == 0, m - 1, rng.integers(0, 3, n))),
     "short rows, many entries": (200000, 6, lambda rng, n, m: rng.integers(2, m + 1, n)),
+    "by rows: ends of trips": (1001, 1300, lambda rng, n, m: np.where(np.arange(n) % 25 == 3, np.resize([255, 256, 257, 1279, 1280, 1281, 1300], n), rng.integers(0, 4, n))),
+    "by rows: all of a workgroup's rows long": (400, 8192, lambda rng, n, m: np.where(np.arange(n) % 100 == 99, m, 0)),
+    "by rows: fewer rows than waves": (3, 700, lambda rng, n, m: np.array([96, 0, 190])),
+    "by rows: as many as there may be": (6144, 300, lambda rng, n, m: np.resize([42, 43], n)),
+    "one row more": (6145, 300, lambda rng, n, m: np.resize([42, 43], n)),
+    "one column more": (500, 8193, lambda rng, n, m: rng.integers(0, 97, n)),
+    "one entry more to a row": (1000, 300, lambda rng, n, m: np.where(np.arange(n) == 5, 97, 96)),
+    "large tiles just": (3000, 200, lambda rng, n, m: np.where(np.arange(n) < 216, 132, 131)),
+    "large tiles not yet": (3000, 200, lambda rng, n, m: np.where(np.arange(n) < 215, 132, 131)),
     "many entries in few rows": (50000, 30, lambda rng, n, m: np.where((np.arange(n) > 20000) & (np.arange(n) < 42000), m, 0)),
 }
 
