@@ -587,9 +587,9 @@ PcgLayout make_pcg_layout(int64_t n, int64_t m)
     L.z = take(N * kPcgMaxRhs * sizeof(double));
     L.p = take(N * kPcgMaxRhs * sizeof(double));
     L.Ap = take(N * kPcgMaxRhs * sizeof(double));
-    // (the partial sums of the combination use the same region)
-    L.part = take((size_t)(kCombineDots > kPcgPartRows ? kCombineDots : kPcgPartRows) * kPcgParts * sizeof(double));
-    L.sc = take(std::max(2 * sizeof(PcgScalars<kPcgMaxRhs>), kPcgMaxRhs * (2 * sizeof(SchurState) + sizeof(SchurSums))));
+    // (the partial sums of the combination use the first kCombineEnd doubles of the same region)
+    L.part = take((size_t)kPcgPartRows * kPcgParts * sizeof(double));
+    L.sc = take(std::max(2 * sizeof(PcgScalars<kPcgMaxRhs>), 2 * kPcgMaxRhs * sizeof(SchurState)));
     L.total = off;
     return L;
 }
@@ -859,7 +859,8 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
     // The five regions of the workspace hold 2 N = 2 (n + m - 1) doubles each, n >= 1.  One system iterates in the caller's x.
     // The vectors that go to LDS begin at multiples of 16 bytes.
     const int64_t mb2 = (mb + 1) / 2 * 2;
-    double *part = at<double>(workspace, L.part);
+    // Its sums and cuts, which a call with restart = 0 goes on from, lie behind those of the combination, which may run in between.
+    double *part = at<double>(workspace, L.part) + kCombineEnd;
     for (int k = 0; k < R; ++k) {
         A.rhs[k] = rhs[k];
         A.x_out[k] = x[k];
@@ -869,18 +870,17 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
         A.buf[k][0] = at<double>(workspace, L.p) + k * mb;
         A.buf[k][1] = at<double>(workspace, L.Ap) + k * mb;
         A.u[k] = at<double>(workspace, k == 0 ? L.p : L.Ap) + 2 * mb;  // (behind the two vectors of the region)
-        A.part[k] = part + k * kPcgParts;
-        A.part_rz[k] = part + (kPcgMaxRhs + k) * kPcgParts;
-        A.part_rr[k] = part + (2 * kPcgMaxRhs + k) * kPcgParts;
-        A.part_norm[k] = part + (3 * kPcgMaxRhs + k) * kPcgParts;
+        A.part[k] = part + k * kSchurVecBlocks;
+        A.part_rz[k] = part + (kPcgMaxRhs + k) * kSchurVecBlocks;
+        A.part_rr[k] = part + (2 * kPcgMaxRhs + k) * kSchurVecBlocks;
+        A.part_norm[k] = part + (3 * kPcgMaxRhs + k) * kSchurVecBlocks;
     }
-    // (behind the partial sums of the first and the second system's p^T S p)
-    A.row_cut = reinterpret_cast<SchurCut *>(part + kSchurVecBlocks);
-    A.col_cut = reinterpret_cast<SchurCut *>(part + kPcgParts + kSchurVecBlocks);
-    static_assert(kSchurParts <= kSchurVecBlocks && kSchurVecBlocks * sizeof(double) + (kSchurParts + 1) * sizeof(SchurCut) <= kPcgParts * sizeof(double),
-                  "rows of part");
+    A.row_cut = reinterpret_cast<SchurCut *>(part + 4 * kPcgMaxRhs * kSchurVecBlocks);
+    A.col_cut = A.row_cut + kSchurParts + 1;
+    static_assert(kSchurParts <= kSchurVecBlocks && kCombineEnd % 2 == 0, "partial sums, alignment of the cuts");
+    static_assert((kCombineEnd + 4 * kPcgMaxRhs * kSchurVecBlocks) * sizeof(double) + 2 * (kSchurParts + 1) * sizeof(SchurCut) <=
+                      kPcgPartRows * kPcgParts * sizeof(double), "the region of part");
     A.state = at<SchurState>(workspace, L.sc);
-    A.kept = reinterpret_cast<SchurSums *>(A.state + 2 * kPcgMaxRhs);
     A.info = info;
     const auto blocks_for = [](int64_t items) {
         return (int)std::max<int64_t>(1, std::min<int64_t>((items + kThreads - 1) / kThreads, kSchurVecBlocks));
@@ -899,10 +899,9 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
             hipLaunchKernelGGL((schur_half_kernel<MODE, R, false>), grid, block, 0, s, A);
     };
     if (restart) {
-        hipLaunchKernelGGL(schur_prepare_kernel, dim3((unsigned)(A.norm_blocks + kSchurCutBlocks), R), dim3(kThreads), 0, s, A);
+        constexpr int kCutBlocks = (kSchurCutWaves + kWaves - 1) / kWaves;
+        hipLaunchKernelGGL(schur_prepare_kernel, dim3((unsigned)(A.norm_blocks + kCutBlocks), R), dim3(kThreads), 0, s, A);
         half(std::integral_constant<int, kSchurColsRhs>{});
-    } else {
-        hipLaunchKernelGGL(schur_resume_kernel, dim3(kSchurCutBlocks + R), dim3(kThreads), 0, s, A);
     }
     for (A.it = 0; A.it < iterations; ++A.it) {
         half(std::integral_constant<int, kSchurRows>{});
@@ -1717,7 +1716,7 @@ int regot_splr_direction(int64_t n, int64_t m, const double *p, const double *q,
     A.info = info;
     A.part = at<double>(workspace, L.part);
     int64_t blocks = (A.N + kThreads - 1) / kThreads;
-    if (blocks > kPcgParts) blocks = kPcgParts;
+    if (blocks > kCombineParts) blocks = kCombineParts;
     A.blocks = (int)blocks;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (any) hipLaunchKernelGGL(splr_dots_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s, A);

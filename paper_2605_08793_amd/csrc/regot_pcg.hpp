@@ -289,13 +289,15 @@ __global__ __launch_bounds__(kThreads) void pcg_finish_kernel(PcgArgs A, int its
 // d = -p.
 // ---------------------------------------------------------------------------------------------
 constexpr int kCombineDots = 7;  // y.s, y.y, y.q, v.q, v.s, y.p, v.p
+constexpr int kCombineParts = 512;  // most workgroups: their sums leave room in `part` for what a reduced solve goes on from
+constexpr int kCombineEnd = kCombineDots * kCombineParts;  // where that begins
 
 struct CombineArgs {
     int64_t N;
     const double *p, *q, *s, *y, *v;  // q, s, y, v may be NULL together: no previous step
     double *d;
     double *info;  // [2]: 1 if the rank-two term was used, (y^-)^T s^-
-    double *part;  // [kCombineDots][kPcgParts]
+    double *part;  // [kCombineDots][kCombineParts]
     int blocks;    // workgroups of both kernels
 };
 
@@ -318,7 +320,7 @@ __global__ __launch_bounds__(kThreads) void splr_dots_kernel(CombineArgs A)
 #pragma unroll
     for (int k = 0; k < kCombineDots; ++k) {
         const double t = block_sum(acc[k], lds);
-        if (threadIdx.x == 0) A.part[(size_t)k * kPcgParts + blockIdx.x] = t;
+        if (threadIdx.x == 0) A.part[(size_t)k * kCombineParts + blockIdx.x] = t;
     }
 }
 
@@ -330,7 +332,7 @@ __global__ __launch_bounds__(kThreads) void splr_combine_kernel(CombineArgs A)
     if (use) {
         double dot[kCombineDots];
 #pragma unroll
-        for (int k = 0; k < kCombineDots; ++k) dot[k] = sum_parts(A.part + (size_t)k * kPcgParts, A.blocks, lds);
+        for (int k = 0; k < kCombineDots; ++k) dot[k] = sum_parts(A.part + (size_t)k * kCombineParts, A.blocks, lds);
         const double ys = dot[0], yy = dot[1], yq = dot[2], vq = dot[3], vs = dot[4], yp = dot[5], vp = dot[6];
         ys_out = ys;
         use = ys > 1e-6 * yy;

@@ -65,11 +65,6 @@ struct SchurState {
     int pad;
 };
 
-// The sums after the last step, for the call that goes on from there.
-struct SchurSums {
-    double rz, rr, bb;
-};
-
 struct SchurArgs {
     int n, mb;            // rows, columns that are variables (m - 1)
     double eta, tau, rtol;
@@ -88,7 +83,6 @@ struct SchurArgs {
     double *part[2];          // partial sums: p^T S p [kSchurParts]
     double *part_rz[2], *part_rr[2], *part_norm[2];  // [kSchurVecBlocks]
     SchurState *state;        // [2 slots][2 systems]
-    SchurSums *kept;          // [2 systems]
     SchurCut *row_cut, *col_cut;  // [kSchurParts + 1]
     double *info;             // [4] per system
     int it;                   // iteration of this call; the final kernel: the number of them
@@ -152,33 +146,27 @@ __device__ __forceinline__ SchurState schur_advance(const SchurState &cur, doubl
     return nx;
 }
 
-// The cuts, one per wave: the first row r at which ptr[r] + kSchurRowCost r reaches the part's share of the whole, 64 places at
-// a time.
+// u = D1^{-1} g1, partial sums of ||rhs||^2; and, by the workgroups behind the first norm_blocks, the cuts: a wave finds the
+// first row r at which ptr[r] + kSchurRowCost r reaches its share of the whole, 64 places at a time.
 constexpr int kSchurCutWaves = 2 * (kSchurParts + 1);
-constexpr int kSchurCutBlocks = (kSchurCutWaves + kWaves - 1) / kWaves;
-__device__ __forceinline__ void schur_find_cut(const SchurArgs &A, int wave, int lane)
-{
-    if (wave >= kSchurCutWaves) return;
-    const bool rows = wave <= kSchurParts;
-    const int t = rows ? wave : wave - (kSchurParts + 1);
-    const int64_t *ptr = rows ? A.row_ptr : A.col_ptr;
-    const int64_t count = rows ? A.n : A.mb;
-    const int64_t w0 = clamp_entry(ptr[0], A.capacity), w1 = clamp_entry(ptr[count], A.capacity) + kSchurRowCost * count;
-    // (whole parts and the rest apart: the product would not fit for any number of entries)
-    const int64_t whole = (w1 - w0) / kSchurParts, rest = (w1 - w0) % kSchurParts;
-    const int64_t target = w0 + whole * t + rest * t / kSchurParts;
-    const auto reached = [&](int64_t r) { return clamp_entry(ptr[r], A.capacity) + kSchurRowCost * r >= target; };
-    const int64_t at = wave_first(t == kSchurParts ? count : 0, t == 0 ? 0 : count, lane, reached);
-    if (lane == 0) (rows ? A.row_cut : A.col_cut)[t] = SchurCut{at, clamp_entry(ptr[at], A.capacity)};
-}
-
-// u = D1^{-1} g1, partial sums of ||rhs||^2; and, by the workgroups behind the first norm_blocks, the cuts
 __global__ __launch_bounds__(kThreads) void schur_prepare_kernel(SchurArgs A)
 {
     __shared__ double lds[kWaves];
     const int lane = threadIdx.x & (kLanes - 1);
     if ((int)blockIdx.x >= A.norm_blocks) {
-        if (blockIdx.y == 0) schur_find_cut(A, ((int)blockIdx.x - A.norm_blocks) * kWaves + (int)(threadIdx.x >> 6), lane);
+        const int wave = ((int)blockIdx.x - A.norm_blocks) * kWaves + (int)(threadIdx.x >> 6);
+        if (wave >= kSchurCutWaves || blockIdx.y != 0) return;
+        const bool rows = wave <= kSchurParts;
+        const int t = rows ? wave : wave - (kSchurParts + 1);
+        const int64_t *ptr = rows ? A.row_ptr : A.col_ptr;
+        const int64_t count = rows ? A.n : A.mb;
+        const int64_t w0 = clamp_entry(ptr[0], A.capacity), w1 = clamp_entry(ptr[count], A.capacity) + kSchurRowCost * count;
+        // (whole parts and the rest apart: the product would not fit for any number of entries)
+        const int64_t whole = (w1 - w0) / kSchurParts, rest = (w1 - w0) % kSchurParts;
+        const int64_t target = w0 + whole * t + rest * t / kSchurParts;
+        const auto reached = [&](int64_t r) { return clamp_entry(ptr[r], A.capacity) + kSchurRowCost * r >= target; };
+        const int64_t at = wave_first(t == kSchurParts ? count : 0, t == 0 ? 0 : count, lane, reached);
+        if (lane == 0) (rows ? A.row_cut : A.col_cut)[t] = SchurCut{at, clamp_entry(ptr[at], A.capacity)};
         return;
     }
     const int sys = (int)blockIdx.y;
@@ -193,24 +181,6 @@ __global__ __launch_bounds__(kThreads) void schur_prepare_kernel(SchurArgs A)
     const double s = block_sum(gg, lds);
     if (threadIdx.x == 0) A.part_norm[sys][blockIdx.x] = s;
 }
-
-// What a call that goes on (restart = 0) needs of the memory that is the combination's between the calls: the cuts; and the
-// sums, as partial sums of which all but the first are 0.  (Kept out of the combination's reach instead, the kernels of the
-// iteration would have to look where the sums are and read cuts of 12 bytes: a pair of 1000 x 1000 256 us for 16 iterations
-// against 252.  This is one small kernel in a call that is waited for before and after.)
-__global__ __launch_bounds__(kThreads) void schur_resume_kernel(SchurArgs A)
-{
-    if ((int)blockIdx.x < kSchurCutBlocks) {
-        schur_find_cut(A, (int)blockIdx.x * kWaves + (int)(threadIdx.x >> 6), threadIdx.x & (kLanes - 1));
-        return;
-    }
-    const int sys = (int)blockIdx.x - kSchurCutBlocks, t = (int)threadIdx.x;
-    const SchurSums s = A.kept[sys];
-    A.part_rz[sys][t] = t == 0 ? s.rz : 0.0;
-    A.part_rr[sys][t] = t == 0 ? s.rr : 0.0;
-    A.part_norm[sys][t] = t == 0 ? s.bb : 0.0;
-}
-static_assert(kSchurVecBlocks == kThreads, "a thread per partial sum");
 
 enum SchurMode {
     kSchurRows = 0,       // p = z + ratio p_old and u = D1^{-1} B p, as u_i = (sum_j T_ij z_j / eta) / D1_i + ratio u_old_i
@@ -423,9 +393,7 @@ __global__ __launch_bounds__(R *kSchurPartThreads) REGOT_WAVES_ATTR(4) void schu
             done = nx.done != 0;
             ratio = nx.rz / cur.rz;
         } else if (me == 0 && tid == 0) {
-            // (a later call goes on from there)
-            if ((A.it & 1) != 0) A.state[sys] = cur;
-            A.kept[sys] = SchurSums{nx.rz, nx.rr, nx.bb};
+            if ((A.it & 1) != 0) A.state[sys] = cur;  // (a later call goes on from there, with the partial sums as they are)
             double *info = A.info + 4 * sys;
             info[0] = (double)cur.steps;
             info[1] = (double)nx.done;
