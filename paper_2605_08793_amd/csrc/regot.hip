@@ -893,7 +893,7 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
     const auto half = [&](auto mode) {
         constexpr int MODE = decltype(mode)::value;
         const dim3 grid(kSchurParts / R, R), block(R * kSchurPartThreads);
-        if ((MODE == kSchurRows || MODE == kSchurRowsFinal ? mb : n) <= kSchurCap)
+        if ((MODE == kSchurCols || MODE == kSchurColsRhs ? n : mb) <= kSchurCap)
             hipLaunchKernelGGL((schur_half_kernel<MODE, R, true>), grid, block, 0, s, A);
         else
             hipLaunchKernelGGL((schur_half_kernel<MODE, R, false>), grid, block, 0, s, A);
@@ -904,7 +904,8 @@ int run_pcg_reduced(int64_t n, int64_t m, double eta, double tau, const int64_t 
         half(std::integral_constant<int, kSchurColsRhs>{});
     }
     for (A.it = 0; A.it < iterations; ++A.it) {
-        half(std::integral_constant<int, kSchurRows>{});
+        if (restart && A.it < kSchurRecurrent) half(std::integral_constant<int, kSchurRows>{});
+        else half(std::integral_constant<int, kSchurRowsLater>{});
         half(std::integral_constant<int, kSchurCols>{});
         hipLaunchKernelGGL(schur_update_kernel, dim3((unsigned)A.vec_blocks, R), dim3(kThreads), 0, s, A);
     }

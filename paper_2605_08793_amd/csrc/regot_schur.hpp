@@ -7,10 +7,11 @@
 // of the iteration on the whole matrix (the classical result for matrices whose diagonal blocks are diagonal).
 // (regot_schur_wide.hpp has the same for systems whose blocks are both longer than kSchurCap.)
 //
-// An iteration is three kernels: the half product by rows, which forms p = z + ratio p_old and u = D1^{-1} B p from
-// D1^{-1} B z and the u of the iteration before (so its gathers need z, and not what the ratio is still to be found for); the
-// half product S p = D2 p - B^T u by columns, with p^T S p; and x, r, z with their inner products.  Scalars are worked out by every wave that needs them from the partial sums the kernel before left, in a
-// fixed order; they live on the device, and after convergence the remaining kernels return at once.
+// An iteration is three kernels: the half product by rows, which forms p = z + ratio p_old and u = D1^{-1} B p, the latter from
+// D1^{-1} B z and the u of the iteration before (so its gathers need z, and not what the ratio is still to be found for; see
+// kSchurRecurrent); the half product S p = D2 p - B^T u by columns, with p^T S p; and x, r, z with their inner products.  Scalars
+// are worked out by every wave that needs them from the partial sums the kernel before left, in a fixed order; they live on the
+// device, and after convergence the remaining kernels return at once.
 //
 // A pair of systems is the same kernels with a second row of workgroups (blockIdx.y): a system's arithmetic does not
 // depend on the other one, and the two workgroups that read the same entries run on one die (the linear ids differ by
@@ -47,6 +48,14 @@ constexpr int kSchurHeld = 128;                                   // rows of a p
 constexpr int kSchurCap = 20000;                                  // entries of the vector in LDS
 constexpr int kSchurRowCost = 16;                                 // what a row costs besides its entries, in entries
 constexpr int kSchurVecBlocks = 256;                              // most workgroups of the vector kernels
+// From so many steps on every second u = D1^{-1} B p is the product again instead of the recurrence, whose rounding errors add
+// up: where the solution takes hundreds of iterations (a small tau, values over several orders of magnitude), the recurrence
+// throughout took 1.2 to 1.4 times as many of them, and left 3 to 7 times the residual of the whole system.  So it is neither
+// more iterations nor a larger residual than with products throughout, beyond what other orders of the sums make of either
+// (with every fourth a product 3 to 5 % more iterations, with every eighth 8 to 10 %).
+// A step with p in LDS instead of z takes longer: on average 25.1 -> 26.6 us at 20000 x 20000 with 2e6 entries, a pair 28.3 -> 30.1;
+// where z is longer than the LDS as well, 15000 x 100000 with 3e6, 45.3 -> 54 and 62.5 -> 82.
+constexpr int kSchurRecurrent = 32;
 static_assert(kSchurLaneEntries == 4 && kSchurTripSlices * 2 == kLanes, "four bits of the mask per lane and slice; two lanes per slice");
 
 // where a part begins: its first row (column) and that one's first entry
@@ -186,7 +195,8 @@ enum SchurMode {
     kSchurRows = 0,       // p = z + ratio p_old and u = D1^{-1} B p, as u_i = (sum_j T_ij z_j / eta) / D1_i + ratio u_old_i
     kSchurRowsFinal = 1,  // x1_i = (g1_i - sum_j T_ij x2_j / eta) / D1_i; x2 to the caller, the record of the iteration
     kSchurCols = 2,       // (S p)_j = D2_j p_j - sum_i T_ij u_i / eta; p^T S p
-    kSchurColsRhs = 3     // r_j = g2_j - sum_i T_ij u_i / eta; x = 0, z = D2^{-1} r; r^T z, r^T r
+    kSchurColsRhs = 3,    // r_j = g2_j - sum_i T_ij u_i / eta; x = 0, z = D2^{-1} r; r^T z, r^T r
+    kSchurRowsLater = 4   // kSchurRows where the step may be kSchurRecurrent or a later one, and u_i (sum_j T_ij p_j / eta) / D1_i
 };
 
 // sums over a part's waves of NV values per thread, in a fixed order; its first thread gets them
@@ -250,9 +260,10 @@ static_assert(2 * kSchurPartWaves <= kSchurHeld, "schur_part_sums in sums");
 static_assert(kSchurTrip / 32 <= kSchurPartThreads && kSchurHeld <= kSchurPartThreads, "a thread per word, and per row");
 
 // ALL: the vector fits the LDS.
-template <int MODE, int R, bool ALL>
+template <int KIND, int R, bool ALL>
 __global__ __launch_bounds__(R *kSchurPartThreads) REGOT_WAVES_ATTR(4) void schur_half_kernel(SchurArgs A)
 {
+    constexpr int MODE = KIND == kSchurRowsLater ? kSchurRows : KIND;
     constexpr bool ROWS = MODE == kSchurRows || MODE == kSchurRowsFinal;
     typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
     typedef int32_t int4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -274,6 +285,7 @@ __global__ __launch_bounds__(R *kSchurPartThreads) REGOT_WAVES_ATTR(4) void schu
         if (MODE == kSchurRows && me == 0 && tid == 0) A.state[2 * ((A.it + 1) & 1) + sys] = cur;
         return;
     }
+    const bool fresh = KIND == kSchurRowsLater && cur.steps >= kSchurRecurrent && (cur.steps & 1) == 0;  // u from p, not from z and the u before
     const int limit = ROWS ? A.mb : A.n;
     const int nl = limit < kSchurCap ? limit : kSchurCap;
     const double *xs = MODE == kSchurRows ? A.z[sys] : MODE == kSchurRowsFinal ? A.x[sys] : A.u[sys];
@@ -289,6 +301,19 @@ __global__ __launch_bounds__(R *kSchurPartThreads) REGOT_WAVES_ATTR(4) void schu
         }
     } else {  // (an iterate of the caller's, at an odd multiple of 8 bytes)
         for (int i = all_tid; i < 2 * pairs; i += kThreadsAll) S.xs[i] = xs[i];
+    }
+    const double *p_old = cur.flip ? A.buf[sys][1] : A.buf[sys][0];  // (kSchurCols: p)
+    double *other = cur.flip ? A.buf[sys][0] : A.buf[sys][1];        // p, or S p
+    // fresh: p_old as well, to registers as far as there are any
+    constexpr int kAhead = KIND == kSchurRowsLater ? (R == 1 ? kPer : 2) : 1;
+    dbl2u p_ahead[kAhead];
+    const auto p_pair = [&](int k) {
+        const int at = (k * kWavesAll + all_w) * kLanes + lane;
+        return *reinterpret_cast<const dbl2u *>(p_old + 2 * (at < pairs ? at : 0));
+    };
+    if (fresh && pairs > 0) {
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) p_ahead[k] = p_pair(k);
     }
     const double last = (nl & 1) != 0 && all_tid == 0 ? xs[nl - 1] : 0.0;
     if (tid < kSchurTrip / 32) L.ends[tid] = 0;
@@ -347,8 +372,6 @@ __global__ __launch_bounds__(R *kSchurPartThreads) REGOT_WAVES_ATTR(4) void schu
         prz.fetch(A.part_rz[sys], count, lane);
         prr.fetch(A.part_rr[sys], count, lane);
     }
-    const double *p_old = cur.flip ? A.buf[sys][1] : A.buf[sys][0];  // (kSchurCols: p)
-    double *other = cur.flip ? A.buf[sys][0] : A.buf[sys][1];        // p, or S p
 
     // rows ra .. of the part, a thread per row: its entries, and what its result is made with
     const double *diag = ROWS ? A.row_sum : A.col_sum;
@@ -404,8 +427,21 @@ __global__ __launch_bounds__(R *kSchurPartThreads) REGOT_WAVES_ATTR(4) void schu
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the vector is in LDS
     if (MODE == kSchurRows && done) return;
     if (all_tid == 0) {
-        if (nl & 1) S.xs[nl - 1] = last;
+        if (nl & 1) S.xs[nl - 1] = fresh ? __builtin_fma(ratio, p_old[nl - 1], last) : last;
         S.xs[nl] = 0.0;
+    }
+    if (fresh && pairs > 0) {  // p in place of z (what this wave has put there)
+        const auto put = [&](int k, const dbl2u &p) {
+            const int at = (k * kWavesAll + all_w) * kLanes + lane;
+            if (at < pairs) {
+                S.xs[2 * at] = __builtin_fma(ratio, p.x, S.xs[2 * at]);
+                S.xs[2 * at + 1] = __builtin_fma(ratio, p.y, S.xs[2 * at + 1]);
+            }
+        };
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) put(k, p_ahead[k]);
+#pragma unroll 4
+        for (int k = kAhead; k < kPer; ++k) put(k, p_pair(k));
     }
     if (MODE == kSchurRows) {
         for (int i = tid; i < share; i += kSchurPartThreads) {
@@ -471,12 +507,14 @@ __global__ __launch_bounds__(R *kSchurPartThreads) REGOT_WAVES_ATTR(4) void schu
             const int ends_up_to = wave_scan(here), ends_before = ends_up_to - here;
             __syncthreads();
             // (entries of the vector that are not in LDS are asked for a slice ahead; lanes that need none read its first)
-            double far[2][kSchurLaneEntries];
+            double far[2][kSchurLaneEntries], far_p[2][kSchurLaneEntries];
             auto load_far = [&](int h) {
 #pragma unroll
                 for (int e = 0; e < kSchurLaneEntries; ++e) {
                     const unsigned j = (unsigned)bj[h][e];
-                    far[h & 1][e] = xs[j >= (unsigned)nl && j < (unsigned)limit ? j : 0u];
+                    const unsigned at = j >= (unsigned)nl && j < (unsigned)limit ? j : 0u;
+                    far[h & 1][e] = xs[at];
+                    if (fresh) far_p[h & 1][e] = p_old[at];
                 }
             };
             if (!ALL) load_far(0);
@@ -491,7 +529,8 @@ __global__ __launch_bounds__(R *kSchurPartThreads) REGOT_WAVES_ATTR(4) void schu
                 for (int e = 0; e < kSchurLaneEntries; ++e) {
                     const unsigned j = (unsigned)bj[h][e];
                     x[e] = S.xs[j < (unsigned)nl ? j : (unsigned)nl];
-                    if (!ALL) x[e] = j >= (unsigned)nl && j < (unsigned)limit ? far[h & 1][e] : x[e];
+                    if (!ALL && j >= (unsigned)nl && j < (unsigned)limit)
+                        x[e] = fresh ? __builtin_fma(ratio, far_p[h & 1][e], far[h & 1][e]) : far[h & 1][e];
                 }
                 // t_e: of entry e's row, as far as it lies in the lane
                 const double(&v)[kSchurLaneEntries] = bv[h];
@@ -549,7 +588,7 @@ __global__ __launch_bounds__(R *kSchurPartThreads) REGOT_WAVES_ATTR(4) void schu
             const double d = dg / A.eta + A.tau, bs = sum * inv_eta;
             if (MODE == kSchurRows) {
                 const double v = bs / d;
-                A.u[sys][i] = first ? v : __builtin_fma(ratio, mine, v);
+                A.u[sys][i] = first || fresh ? v : __builtin_fma(ratio, mine, v);
             } else if (MODE == kSchurRowsFinal) {
                 A.x_out[sys][i] = (mine - bs) / d;
             } else if (MODE == kSchurCols) {
