@@ -953,7 +953,7 @@ SweepPlan make_sweep_plan(int64_t n, int64_t m, int sweeps)
     const int64_t K = eight ? K1 : K2;
     if (K > kSweepMaxK) return S;
     S.K = (int)K;
-    S.keep = sweeps > 1 && n * m <= kSweepKeep;
+    S.keep = sweeps > 1 && n * m <= (sweeps == 2 ? kSweepKeepTwo : kSweepKeep);
     if (S.keep) S.kernel = eight ? sweep_pass_kernel<1, 8, false> : m <= kSweepCols1 ? sweep_pass_kernel<1, 4, false> : sweep_pass_kernel<2, 4, false>;
     else S.kernel = eight ? sweep_pass_kernel<1, 8, true> : m <= kSweepCols1 ? sweep_pass_kernel<1, 4, true> : sweep_pass_kernel<2, 4, true>;
     S.P = (int)(kNumCU / K < n / 8 ? kNumCU / K : n / 8);  // (at least 4 rows each)

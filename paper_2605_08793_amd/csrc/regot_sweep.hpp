@@ -48,7 +48,8 @@ constexpr int kSweepCols1 = kSweepWaves * 2 * kLanes;       // columns of a work
 constexpr int kSweepCols = 2 * kSweepCols1;                 // most columns a workgroup can own: two groups per wave (3840)
 constexpr int kSweepMaxK8 = 5;                              // most members and fewest rows of a cluster whose batches are
 constexpr int kSweepRows8 = 32;                             // eight rows (see above)
-constexpr int64_t kSweepKeep = 40000000;                    // most entries of a matrix whose sweeps alternate (see SweepRows)
+constexpr int64_t kSweepKeepTwo = 27000000;                 // most entries of a matrix whose sweeps alternate: two in a call,
+constexpr int64_t kSweepKeep = 36000000;                    // and more of them (see SweepRows)
 constexpr int kSweepMaxK = 16;                              // members of a cluster: one lane of a DPP row each
 static_assert(kSweepWaves <= 16, "a DPP row of 16 lanes per row in sweep_factors");
 
@@ -88,14 +89,20 @@ struct SweepArgs {
 // The rows of a cluster in the order it takes them: t-th row of `count`, t beyond the last being the last again.
 // Every other sweep of a call takes them from the last to the first, and M is read with ordinary loads (STREAM false): a sweep
 // begins with the 32 MB that the one before it has left in the L2s.  (The last-level cache gives no more than the memory does:
-// what limits either is between the dies.)  That holds where a workgroup's rows are read on the die that read them last, so
-// the grids are whole rounds over the dies.  All sweeps in order, with non-temporal loads, -> these, us a sweep: 2000 x 1900
-// 16.0 -> 15.1, 3000^2 28.5 -> 26.9, 5000 x 3000 36.2 -> 33.7, 6000^2 64.7 -> 60.7.  Not for a
-// single sweep, which has nothing to begin with (10000^2 152 -> 160: ordinary loads of a stream cost something), and not beyond
-// kSweepKeep entries, where 32 MB are too little of a sweep to make up for the ordinary loads: 10000^2, four sweeps, one call
-// behind the other 637 -> 624, but 672 -> 691 behind M being written and 643 -> 693 on new arrays (8000^2 480 -> 450, and
-// 511 -> 526 behind a pause; 7000^2 365 -> 338, 394 -> 413 behind M being written; 6000^2 298 -> 271, 327 -> 315 and on new arrays
-// 294 -> 294; 2000 x 20000, three, 268 -> 242, 254 -> 258, 233 -> 231; 7001 x 4999, three, 232 -> 218, 252 -> 255, 237 -> 231; 20000^2 584 -> 581 a sweep, 30000 x 50000 2361 -> 2422).
+// what limits either is between the dies.)  That takes a workgroup whose rows were last read on its own die: with one member the
+// workgroup's id says which rows it has, and the grids are whole rounds over the dies; with several it is their order of arrival,
+// which mostly comes out alike.
+// All sweeps in order, with non-temporal loads, -> these, us a sweep in calls one behind the other: 2000 x 1900 16.0 -> 15.1, 3000^2
+// 28.5 -> 26.9, 5000 x 3000 36.2 -> 33.7, 6000^2 64.7 -> 60.7.  Ordinary loads of a stream cost something (a single sweep of
+// 10000^2, which has nothing to begin with, 152 -> 160), so the matrix must not be too large for 32 MB to make up for it, above
+// all with two sweeps, of which one has a beginning.  us a call, of a caller that goes on with the matrix / has just written it /
+// has new arrays:
+//   two,   4000 x 5000   119 -> 114    124 -> 115    114 -> 112        6000^2   170 -> 156    165 -> 163    153 -> 155
+//          6000 x 5000   149 -> 142    151 -> 151    143 -> 145        2000 x 20000   174 -> 165    172 -> 179    161 -> 161
+//   three, 6000 x 5000   213 -> 204    219 -> 215    207 -> 205        6000^2   231 -> 213    235 -> 236    217 -> 218
+//          7001 x 4999   238 -> 228    243 -> 246    225 -> 222        2000 x 20000   243 -> 223    246 -> 250    230 -> 227
+//   four,  7000^2   365 -> 338    394 -> 413    -        10000^2   637 -> 624    672 -> 691    643 -> 693
+//   ten,   5000^2   543 -> 521    580 -> 560    545 -> 531        6000^2   690 -> 633    698 -> 690    645 -> 639
 struct SweepRows {
     int first, step, count;
     __device__ __forceinline__ int at(int t) const { return first + step * min(t, count - 1); }
