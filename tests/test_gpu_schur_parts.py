@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import oracle
+from paper_2605_08793_amd import binding as B
 from paper_2605_08793_amd.driver import DirectionSolver, SparseTerm
 
 pytestmark = pytest.mark.gpu
@@ -80,3 +81,42 @@ def test_half_products(name):
         pair = solver.solve2(eta, tau, rd, cd, dev(rhs[0]), dev(rhs[1]), xa, xb, rtol=rtol, portion=portion, reduced=True)
         assert list(pair) == out
         assert torch.equal(xa, x[0]) and torch.equal(xb, x[1])
+
+
+@pytest.mark.parametrize("n,m", [(700, 900), (3, 21000), (21000, 3)])
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_arrays_at_multiples_of_their_elements_only(n, m, shift):
+    """Columns and rows at multiples of 4 bytes, everything else at multiples of 8: the same bits as at multiples of 256."""
+    rng = np.random.default_rng(n)
+    row_ptr, col_idx = pattern(rng, n, m, rng.integers(m // 3, m // 2 + 2, n) if m > n else rng.integers(0, min(m, 300), n))
+    nnz = len(col_idx)
+    val = rng.random(nnz) / nnz
+    rows = np.repeat(np.arange(n), np.diff(row_ptr))
+    r, c = np.bincount(rows, val, n) * 1.1 + 0.1 / n, np.bincount(col_idx, val, m) * 1.1 + 0.1 / m
+    N = n + m - 1
+    rhs = rng.standard_normal((2, N)) / N
+    print(f"[schur aligned] n={n} m={m} nnz={nnz} shift={shift}", flush=True)
+
+    def dev(x, off=0):
+        x = torch.from_numpy(np.ascontiguousarray(x))
+        store = torch.zeros(x.numel() + off, dtype=x.dtype, device="cuda")
+        store[off:].copy_(x)
+        assert store[off:].data_ptr() % 256 == off * x.element_size()
+        return store[off:]
+
+    term = SparseTerm(n, m, dev(row_ptr), dev(col_idx), nnz)
+    term.val[:] = dev(val)
+    term.val_csc[term.csc_pos] = term.val
+    arrays = [t.cpu().numpy() for t in (term.row_ptr, term.col_idx, term.val, term.col_ptr, term.row_idx, term.val_csc)]
+    workspace = torch.empty(B.regot_pcg_workspace_bytes(n, m), dtype=torch.uint8, device="cuda")
+
+    def solve(off):
+        pat, (rd, cd), g = [dev(a, off) for a in arrays], [dev(a, off) for a in (r, c)], [dev(a, off) for a in rhs]
+        x, info = [dev(np.full(N, np.nan), off) for _ in range(3)], dev(np.zeros(12), off)
+        B.regot_pcg_solve_reduced(n, m, 0.05, 1e-3, *pat, rd, cd, g[0], x[0], 1e-10, 40, True, info[:4], workspace=workspace)
+        B.regot_pcg_solve2_reduced(n, m, 0.05, 1e-3, *pat, rd, cd, *g, *x[1:], 1e-10, 40, True, info[4:], workspace=workspace)
+        return x + [info]
+
+    for got, want in zip(solve(shift), solve(0)):
+        assert torch.equal(got, want) and torch.isfinite(got).all()
+    assert torch.equal(got[:8], torch.cat([got[:4]] * 2))
