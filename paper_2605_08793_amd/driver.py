@@ -120,6 +120,9 @@ class SparseTerm:
     Built once per pattern from the CSR structure a sparsify call left on the device (the symbolic
     step: the pattern by columns); `refresh` then recomputes the values at the current dual point
     (Sec. 4.2), `matvec` applies H_Omega + tau I and `lower_csc` writes its lower triangle by columns.
+
+    row_idx, val, val_csc and h_col_ptr, h_row_idx, h_val, h_info are views of one allocation, which lives as long as any of
+    them, and which torch.save writes whole for any of them: clone what is to be kept or saved without the others.
     """
 
     def __init__(self, n: int, m: int, row_ptr, col_idx, nnz: int):
