@@ -33,8 +33,9 @@ namespace regot {
 // What bounds it (pair of systems, 20000 x 20000, 2e6 entries; time stamps): 4.3 us until 350 KB a workgroup have come (the
 // vector from L2, the entries from the last-level cache, both near the rate of a compute unit), 1.3 us for the mask, 2.3 us of
 // instructions for four slices a wave (64 entries of the scan cost as much as 256 gathers from LDS), 1 us to the results, and
-// about 2 us of launch.  12.0 us by columns, 13.5 by rows; a wave per row with the pair side by side, half of its gathers going
-// to L2, took 16.4 and 20.2, and an iteration 47 us in four kernels instead of 30 in three.  On the way: the row of a lane's
+// about 2 us of launch.  12.0 us by columns, 13.5 by rows between those stamps, 13.3 and 14.4 in a
+// kernel trace (update 4.1 to 4.8), an iteration 28.1 in launches one behind the other; a wave per row with the pair side by side,
+// half of its gathers going to L2, took 16.4 and 20.2, and an iteration 36 in four kernels.  On the way: the row of a lane's
 // first entry by bisection, 64-bit positions throughout 20.9 us (8.8 of them instructions); two trips of two slices 12.2.
 constexpr int kSchurParts = 256;
 constexpr int kSchurPartWaves = 8;

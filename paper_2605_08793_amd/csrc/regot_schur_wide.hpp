@@ -1,7 +1,14 @@
 // The reduced solve of regot_schur.hpp for systems both of whose blocks are longer than a vector that fits the LDS there
 // (kSchurCap): the kernels there gather what is not in LDS once per system, these once for both, the vectors of a pair side by
-// side.  A pair of systems at 50000 x 50000, 5e6 entries, 565 us against 710, a single one 465 against 506; where one block is
-// short, or both are, those are faster (300000 x 60 with 1.2e6 entries 2180 us here, 515 there; 10^6 x 1000 with 3e6 1896 / 1149).
+// side.  The line lies where the vectors cease to fit, not where the two meet, which is further on; 16 iterations here / there, us,
+// single and pair:
+//   22000 x 22000, 2e6 entries  490 / 459   621 / 532        32000 x 32000, 3e6  577 /  617    777 /  804
+//   25000 x 25000, 5e5          496 / 305   629 / 370        40000 x 40000, 4e6  736 /  840    947 / 1240
+//   26000 x 26000, 2e6          534 / 463   695 / 541        50000 x 50000, 5e6  936 / 1014   1168 / 1551
+//   22000 x 120000, 3e6        1014 / 832  1273 / 1187
+// Where one block is short those are faster: 40000 x 10000 with 4e6 entries 681 / 654 and 858 / 852, with 4e5 455 / 323 and
+// 593 / 397; 15000 x 100000, 3e6 919 / 763 and 1156 / 1064; 100000 x 15000 885 / 737 and 1083 / 1024; a whole pair of 300000 x 60,
+// 1.2e6 entries 2180 / 515, of 10^6 x 1000, 3e6 1896 / 1149.
 // An iteration is four kernels: the half products by rows and by columns (the sweep of the product kernel with
 // another last step per row), and the vector kernels of the iteration on the whole matrix, on the second block alone.
 #pragma once

@@ -138,7 +138,8 @@ struct SelState {
 
 struct SelCounters {     // cleared by the gather kernel
     // 64-bit: with more than 2^32 entries and heavy ties a 32-bit count of the keys inside a bracket could wrap.
-    // (The two that every workgroup of the bracket pass adds to, at its end, on lines of their own: additions to a line queue up.)
+    // (The two that every workgroup of the bracket pass adds to, at its end, on lines of their own: additions to a line queue up.
+    // 3000 x 4000, k = 120000 94.3 -> 91.5 us; no difference at 1000 x 1000 and from 5000 x 5000 on.)
     u64 above;               // bracket pass: keys > hi
     u64 radix_fill;          // collecting histogram pass over M: keys appended
     u64 small_fill;          // collecting histogram pass over the pool: keys appended to the small pool
