@@ -51,8 +51,9 @@ __device__ __forceinline__ void row_range(const int64_t *row_ptr, int64_t i, int
 // (values by twos / by fours: 300000 entries 13.9 / 15.8 us, 360000 13.1 / 15.3, 400000 19.2 / 17.2, 500000 20.1 / 18.7, 2e6
 // 76 / 74).
 // A workgroup per 32 rows writes the triangle on a stored structure faster where rows are many and short and alike (20000 x 20000,
-// 50000 entries 3.3 us against 4.3; 100000 x 50, 30000 entries 4.4 / 6.1), and slower everywhere else (20000 x 20000, 2e6
-// 12.2 / 11.9; 10^6 of 10000 x 10000 10.6 / 7.5; 20 rows of 4400 173 / 3.7).
+// 50000 entries 3.3 us against 4.3; 100000 x 50, 30000 entries 4.4 / 6.1; 40000 x 10000, 4e6 17.9 / 18.8), and slower elsewhere
+// (20000 x 20000, 2e6 12.2 / 11.9, 4e6 20.9 / 18.6; 10000 x 10000, 10^6 10.6 / 7.5; 4e6 in a fifth of the rows 39 / 18; 20 rows of
+// 4400 173 / 3.7).
 constexpr int kTileItems = 4, kTileFew = 2;
 constexpr int64_t kTileFewBelow = 768 * kTileFew * kThreads;
 constexpr int kTileHeld = 8 * kThreads;  // rows whose ends are held (a power of two): all of a tile's, unless many have no entries
