@@ -232,8 +232,8 @@ int regot_sinkhorn_half_step(int64_t n, int64_t m,
  * least 20000 rows of at most 128 columns, 37000 of 256, 90000 of 512) this is exactly the same sequence of
  * regot_sinkhorn_half_step calls, bit for bit.  Otherwise a sweep reads M once instead of twice: the
  * beta update is formed from the exponentials of the alpha update while they are on chip, which is the same update
- * up to rounding (a few 1e-16 of the duals; bit-reproducible run to run; the sweeps of a call may add a column's terms
- * up in different orders, so a call of several and several calls of one differ by rounding too), and a column whose terms would underflow
+ * up to rounding (a few 1e-16 of the duals; bit-reproducible run to run; the sweeps of a call behind its first one go on from
+ * what that one knows, so a call of several and several calls of one differ by rounding too), and a column whose terms would underflow
  * that way is done again from alpha and M relative to its maximum, as in the half-step.  A NaN among the costs of a
  * row makes that row's alpha and every beta NaN, as it does in the half-steps.  For m > 1920 up to 16 workgroups share
  * the rows; where they cannot run at the same time (a stream limited to a few compute units, kernels of other streams

@@ -939,7 +939,7 @@ EntryPlan make_entry_plan(int64_t n, int64_t m, int64_t capacity)
 constexpr int64_t kSweepMinEntries = 1LL << 20;
 struct SweepPlan {
     int K = 0, P = 0, width = 0;
-    void (*kernel)(SweepArgs) = nullptr;
+    void (*first)(SweepArgs) = nullptr, (*later)(SweepArgs) = nullptr;  // of the first sweep of a call, and the others
     bool keep = false;  // see SweepRows
 };
 
@@ -954,10 +954,16 @@ SweepPlan make_sweep_plan(int64_t n, int64_t m, int sweeps)
     if (K > kSweepMaxK) return S;
     S.K = (int)K;
     S.keep = sweeps > 1 && n * m <= (sweeps == 2 ? kSweepKeepTwo : kSweepKeep);
-    if (S.keep) S.kernel = eight ? sweep_pass_kernel<1, 8, false> : m <= kSweepCols1 ? sweep_pass_kernel<1, 4, false> : sweep_pass_kernel<2, 4, false>;
-    else S.kernel = eight ? sweep_pass_kernel<1, 8, true> : m <= kSweepCols1 ? sweep_pass_kernel<1, 4, true> : sweep_pass_kernel<2, 4, true>;
+    const auto pick = [&](auto near_tag) {
+        constexpr bool NEAR = decltype(near_tag)::value;
+        if (S.keep) return eight ? sweep_pass_kernel<1, 8, false, NEAR> : m <= kSweepCols1 ? sweep_pass_kernel<1, 4, false, NEAR> : sweep_pass_kernel<2, 4, false, NEAR>;
+        return eight ? sweep_pass_kernel<1, 8, true, NEAR> : m <= kSweepCols1 ? sweep_pass_kernel<1, 4, true, NEAR> : sweep_pass_kernel<2, 4, true, NEAR>;
+    };
+    S.first = pick(std::false_type{});
+    S.later = pick(std::true_type{});
     S.P = (int)(kNumCU / K < n / 8 ? kNumCU / K : n / 8);  // (at least 4 rows each)
     S.width = (int)(((m + K - 1) / K + 1) / 2 * 2);
+    if (n <= 8 * (int64_t)S.P) S.later = S.first;
     return S;
 }
 
@@ -983,6 +989,8 @@ int run_sweeps(const SweepPlan &Q, int64_t n, int64_t m, const double *M, int64_
     A.colpart = at<double>(workspace, L.colpart);
     A.ticket = at<int>(workspace, L.header) + HDR_SWEEP_TICKET;
     A.huge = at<int>(workspace, L.header) + HDR_SWEEP_HUGE;
+    A.far = at<int>(workspace, L.header) + HDR_SWEEP_FAR;
+    double *alpha_next = A.exch + (A.K > 1 ? 2 * n * A.K : 0);
     A.ex = make_exp_params(eta);
     A.looks = g_sweep_looks >= 0 ? g_sweep_looks : kSweepLooks;
     A.floor = -1e44 * eta;  // (-inf for an eta above 1e264: no floor.  exp_eta gives 0 up to about 1e46 eta below the maximum)
@@ -1000,13 +1008,16 @@ int run_sweeps(const SweepPlan &Q, int64_t n, int64_t m, const double *M, int64_
                            n * A.K * 2, A.ticket);
     // (whole rounds over the dies: what is beyond the clusters, or the columns, returns)
     const dim3 grid((unsigned)die_grid(A.P * A.K)), fin((unsigned)die_grid(groups), (unsigned)A.splits);
+    const auto finalize = Q.later != Q.first && sweeps > 1 ? sweep_finalize_kernel<true> : sweep_finalize_kernel<false>;
     for (int i = 0; i < sweeps; ++i) {
+        const auto kernel = i == 0 ? Q.first : Q.later;
         A.turn = i & 1;
         A.up = Q.keep ? i & 1 : 0;
+        A.alpha_out = kernel == Q.first || A.K == 1 ? alpha : alpha_next;  // (else another member might still read the old one)
         if (i == 0) prof_begin(s);
-        hipLaunchKernelGGL(Q.kernel, grid, dim3(kSweepThreads), 0, s, A);
+        hipLaunchKernelGGL(kernel, grid, dim3(kSweepThreads), 0, s, A);
         if (i == 0) prof_end(s);
-        hipLaunchKernelGGL(sweep_finalize_kernel, fin, dim3(kSweepFinWaves * kLanes), 0, s, A);
+        hipLaunchKernelGGL(finalize, fin, dim3(kSweepFinWaves * kLanes), 0, s, A);
     }
     return hip_status();
 }

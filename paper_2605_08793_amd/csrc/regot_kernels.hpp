@@ -37,7 +37,7 @@ namespace regot {
 #define REGOT_WAVES_ATTR(N) __attribute__((amdgpu_waves_per_eu(N, N)))
 
 // ints at the start of the workspace
-enum { HDR_SLOT_NEXT = 0, HDR_RANGE_NEXT = 1, HDR_POOL_OVERFLOW = 2, HDR_SWEEP_TICKET = 32, HDR_SWEEP_HUGE = 48, HDR_INTS = 64 };
+enum { HDR_SLOT_NEXT = 0, HDR_RANGE_NEXT = 1, HDR_POOL_OVERFLOW = 2, HDR_SWEEP_TICKET = 32, HDR_SWEEP_HUGE = 48, HDR_SWEEP_FAR = 50, HDR_INTS = 64 };
 
 constexpr double kDblMax = 1.7976931348623157e308;
 constexpr int kFinRows = 64;                     // rows per finalize workgroup

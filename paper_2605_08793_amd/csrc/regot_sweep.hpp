@@ -29,7 +29,9 @@
 // overlap less than twice as many of four (5000 x 1900, 20 rows: 28.3 -> 29.1; 2000 x 4999, 24: 32.2 -> 33.7;
 // 8192 x 1500, 32: 32.4 -> 31.8).
 //
-// What bounds it: memory latency times what a compute unit can keep in flight, with the exponentials on top.  20000 x 20000:
+// That is the first sweep of a call.  The ones behind it know how large their terms are and need no maxima: regot_sweep_near.hpp.
+//
+// What bounds it: instructions (32 an entry: with the loads taken out 447 us at 20000 x 20000) beside the memory.  20000 x 20000:
 // 596 us a sweep = 5.4 TB/s of M against 975 us for the two half-steps (two reads at 6.6 TB/s); with the exponentials
 // replaced by one operation 550 us.  A member's numbers take 0.8 us to reach the others, but the members of a cluster
 // drift apart by up to the one batch (5 us) they are allowed; a cluster of one (m <= 3840) runs at 5.8 TB/s.  Measured on
@@ -62,6 +64,9 @@ constexpr int kSweepLooks = 1 << 14;  // at the words of the other members, one 
 constexpr double kSweepTiny = 1e-270;
 constexpr double kSweepHuge = 1e12;
 constexpr int kSweepHugeMark = 0x48554745;
+// What sweep_finalize_kernel asks of masses, of b_j / c_j and of the duals before the terms of the next sweep are plan entries
+// (regot_sweep_near.hpp).
+constexpr double kNearLeastMass = 1e-150, kNearMostMass = 1e100, kNearLeastRatio = 1e-12, kNearMostDual = 1e13;  // the latter in units of eta
 
 struct SweepArgs {
     int n, m;
@@ -82,6 +87,8 @@ struct SweepArgs {
     double floor, floor_max;  // see sweep_wave
     ExpParams ex;
     int *huge;        // [2] kSweepHugeMark in [turn]: a mass beyond kSweepHuge was met
+    int *far;         // [2] [turn] not 0: it found that this sweep cannot
+    double *alpha_out;  // what the pass writes: alpha, or an array that sweep_finalize_kernel copies to alpha
     int turn;         // parity of the sweep
     int up;           // the clusters take their rows from the last to the first (see SweepRows)
 };
@@ -142,6 +149,14 @@ __device__ __forceinline__ int sweep_batches(int rows)
 {
     const int nb = (rows + R - 1) / R;
     return R == 4 ? (nb + 1) & ~1 : nb;
+}
+
+// The same for sweeps behind the first: an even number of batches where there are two sets of them.
+template <int R, int LAG>
+__device__ __forceinline__ int near_batches(int rows)
+{
+    const int nb = (rows + R - 1) / R;
+    return LAG == 1 ? (nb + 1) & ~1 : nb;
 }
 
 // Reductions of 2 or 4 rows at once: row r ends up in lane 32 (r & 1) + 16 (r >> 1)
@@ -538,29 +553,47 @@ __device__ __forceinline__ void sweep_factors(const SweepArgs &A, SweepShared<NU
         }
 #pragma unroll
         for (int q = 0; q < Q; ++q)
-            if (b % A.K == member && j16 == 0 && live[q]) A.alpha[row[q]] = A.eta * log(ai[q]) - (mx[q] + A.eta * log(sum[q]));
+            if (b % A.K == member && j16 == 0 && live[q]) A.alpha_out[row[q]] = A.eta * log(ai[q]) - (mx[q] + A.eta * log(sum[q]));
     }
     __syncthreads();
 }
+
+}  // namespace regot
+
+#include "regot_sweep_near.hpp"
+
+namespace regot {
 
 // Which member of which cluster a workgroup is follows from the order in which the workgroups start (a counter in the
 // workspace): only the cluster formed last can be incomplete while its members wait for each other, and the clusters
 // before it finish whatever happens, so a place for the missing members comes free unless other kernels hold all that is
 // left, or the stream may use fewer compute units than a cluster has members; then they are waited for for a while and
 // done without (see sweep_factors).  Which workgroup does what has no influence on the results.
-template <int NU, int R, bool STREAM>
+// R: rows of a batch of a sweep that finds its rows' maxima; the others take four.  NEAR: it may be one of those (a kernel of its own, since
+// what it has to look up first and the registers it takes cost the others 0.4 us).
+template <int NU, int R, bool STREAM, bool NEAR>
 __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_kernel(SweepArgs A)
 {
     static_assert(NU * R <= 8 && (R == 4 || R == 8), "registers and LDS of a lane; rows of sweep_factors");
-    __shared__ SweepShared<NU, R> L;
+    constexpr int LAG = NU == 1 && R == 8 ? 3 : 1;
+    typedef SweepNear<NU, 4, LAG> Near;
+    union Shared {
+        SweepShared<NU, R> first;
+        Near near;
+    };
+    __shared__ __attribute__((aligned(16))) char lds[NEAR ? sizeof(Shared) : sizeof(SweepShared<NU, R>)];
+    __shared__ int lds_role;
+    SweepShared<NU, R> &L = *reinterpret_cast<SweepShared<NU, R> *>(lds);
+    Near &N = *reinterpret_cast<Near *>(lds);
     const int lane = threadIdx.x & (kLanes - 1);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const bool near = NEAR && *((const __attribute__((address_space(4))) int *)A.far + A.turn) == 0;
     if (threadIdx.x == 0) {
-        L.huge = 0;
-        L.role = A.K > 1 ? atomicAdd(A.ticket, 1) : (int)blockIdx.x;
+        if (!near) L.huge = 0;
+        lds_role = A.K > 1 ? atomicAdd(A.ticket, 1) : (int)blockIdx.x;
     }
     __syncthreads();
-    const int role = __builtin_amdgcn_readfirstlane(L.role);
+    const int role = __builtin_amdgcn_readfirstlane(lds_role);
     if (role < 0 || role >= A.P * A.K) return;
     const int cluster = role / A.K, member = role - cluster * A.K;
     int r_begin, r_end;
@@ -570,14 +603,20 @@ __global__ __launch_bounds__(kSweepThreads) REGOT_WAVES_ATTR(4) void sweep_pass_
     const int ncol = min(A.width, A.m - c0);
     if (w == kSweepWaves) {
         const SweepArgs C = sweep_args_here();
-        if (role == 0 && lane == 0) C.huge[C.turn ^ 1] = 0;  // (last read behind the sweep before)
+        if (role == 0 && lane == 0) C.huge[C.turn ^ 1] = C.far[C.turn ^ 1] = 0;  // (last read behind the sweep before)
         if (role == 0 && C.splits > 1)  // (for sweep_finalize_kernel)
             for (int i = lane; i < (C.m + kLanes - 1) / kLanes; i += kLanes) C.redo_count[i] = 0;
-        sweep_factors<NU, R>(C, L, member, rows, lane);
-    } else if (2 * kLanes * ((NU - 1) * kSweepWaves + w + 1) <= ncol) {  // the wave's last group is full
-        sweep_wave<NU, R, STREAM, false>(A, L, cluster, rows, c0, ncol, w, lane);
+        if (NEAR && near) near_factors<NU, 4, LAG>(C, N, member, rows, lane);
+        else sweep_factors<NU, R>(C, L, member, rows, lane);
+        return;
+    }
+    const bool full = 2 * kLanes * ((NU - 1) * kSweepWaves + w + 1) <= ncol;  // the wave's last group is
+    if (NEAR && near) {
+        if (full) near_wave<NU, 4, LAG, STREAM, false>(A, N, cluster, rows, c0, ncol, w, lane);
+        else near_wave<NU, 4, LAG, STREAM, true>(A, N, cluster, rows, c0, ncol, w, lane);
     } else {
-        sweep_wave<NU, R, STREAM, true>(A, L, cluster, rows, c0, ncol, w, lane);
+        if (full) sweep_wave<NU, R, STREAM, false>(A, L, cluster, rows, c0, ncol, w, lane);
+        else sweep_wave<NU, R, STREAM, true>(A, L, cluster, rows, c0, ncol, w, lane);
     }
 }
 
@@ -597,6 +636,8 @@ constexpr int kSweepFinRows = 8;       // rows of a column that a lane asks for 
 constexpr int kSweepMaxSplits = 16;
 constexpr int kSweepMerge = 4;         // of their results asked for at a time
 
+// NEAR: for calls whose later sweeps may be those of regot_sweep_near.hpp.  (What it does for them costs 0.3 us.)
+template <bool NEAR>
 __global__ __launch_bounds__(kSweepFinWaves *kLanes) REGOT_WAVES_ATTR(8) void sweep_finalize_kernel(SweepArgs A)
 {
     __shared__ double lds_a[kSweepFinWaves][kLanes], lds_b[kSweepFinWaves][kLanes];
@@ -617,6 +658,13 @@ __global__ __launch_bounds__(kSweepFinWaves *kLanes) REGOT_WAVES_ATTR(8) void sw
     if (live && sub == 0 && split == 0) {
         bo = A.beta[j];
         bj = A.b[j];
+    }
+    // what becomes of row i0, asked for now and looked at behind the columns
+    const int64_t i0 = (int64_t)group * blockDim.x + threadIdx.x;
+    double mass0 = 0.0, alpha0 = 0.0;
+    if (NEAR && split == 0 && i0 < A.n) {
+        mass0 = A.a[i0];
+        alpha0 = A.alpha_out[i0];
     }
     if (split > 0) {
         const int huge = A.huge[A.turn];
@@ -650,9 +698,28 @@ __global__ __launch_bounds__(kSweepFinWaves *kLanes) REGOT_WAVES_ATTR(8) void sw
         // (c is NaN only where an alpha is NaN or +inf -- a NaN among a row's costs, or no finite one -- and so is then every
         // log-sum-exp of a column: NaN is the result)
         const bool ok = !live || c >= kSweepTiny || c != c;
-        if (live && ok && split == 0) A.beta[j] = bo + A.eta * (log(bj) - log(c));
+        const double bn = bo + A.eta * (log(bj) - log(c));
+        if (live && ok && split == 0) A.beta[j] = bn;
         const unsigned long long bad = __ballot(!ok);
         if (l == 0) lds_bad = bad;
+        // (a column without mass must have been -inf, so that no T of it is in the rows' sums)
+        const bool near = bj > 0.0 ? ok && bj <= kNearMostMass && bj >= kNearLeastRatio * c && __builtin_fabs(bn) <= kNearMostDual * A.eta
+                                   : bj == 0.0 && bo == -INFINITY;
+        if (NEAR && split == 0 && __ballot(live && !near) != 0 && l == 0) A.far[A.turn ^ 1] = 1;
+    }
+    if (NEAR && split == 0) {
+        // the new alpha, for the caller and the next sweep, which may have to find its maxima for some row's sake
+        bool far = false;
+        for (int64_t i = i0; i < A.n; i += (int64_t)gridDim.x * blockDim.x) {
+            if (i != i0) {
+                mass0 = A.a[i];
+                alpha0 = A.alpha_out[i];
+            }
+            far = far || !(mass0 > 0.0 ? mass0 >= kNearLeastMass && mass0 <= kSweepHuge && __builtin_fabs(alpha0) <= kNearMostDual * A.eta
+                                       : mass0 == 0.0 && alpha0 == -INFINITY);
+            if (A.alpha_out != A.alpha) A.alpha[i] = alpha0;
+        }
+        if (__ballot(far) != 0 && l == 0) A.far[A.turn ^ 1] = 1;
     }
     __syncthreads();
     const unsigned long long bad = lds_bad;
@@ -661,7 +728,7 @@ __global__ __launch_bounds__(kSweepFinWaves *kLanes) REGOT_WAVES_ATTR(8) void sw
     const bool redo = ((bad >> l) & 1) != 0;
     bj = redo ? A.b[j] : 1.0;
     const int64_t per = ((int64_t)C.n + C.splits - 1) / C.splits, r0 = split * per, r1 = r0 + per < C.n ? r0 + per : C.n;
-    const auto *alpha = (const __attribute__((address_space(4))) double *)C.alpha;  // (complete: written by the pass)
+    const auto *alpha = (const __attribute__((address_space(4))) double *)C.alpha_out;  // (complete: written by the pass)
     double mx = -kDblMax, sum = 0.0;
     for (int64_t i = r0 + sub; i < r1; i += kSweepFinWaves * kSweepFinRows) {
         // (a column without mass is -inf as soon as it has one finite cost)
