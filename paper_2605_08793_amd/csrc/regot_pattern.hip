@@ -4,9 +4,11 @@
 //
 // The pattern by columns is the list of CSR positions p sorted by (column, p): CSR positions grow with
 // the row and a column holds at most one entry per row, so inside a column ascending p is ascending row.
-// The positions start out in ascending order, so a STABLE sort by column alone gives that list: a
+// There are two ways to it; by_counting says which one a pattern takes, and the text there why.
+// Counting, for patterns that are not too sparse, is described further down, at its kernels.  The other:
+// the positions start out in ascending order, so a STABLE sort by column alone gives that list: a
 // least-significant-digit radix sort on the column index, 8 bits per pass, ceil(bits(m) / 8) passes (two
-// for m < 65536), every kernel of this file:
+// for m < 65536):
 //   0. entry_row[p] = row of CSR position p (one wave per row; in the launch of the first pass's step 1);
 //   per pass:
 //   1. every workgroup counts the digits of its tile of 2048 keys (LDS) -> table[digit][workgroup];
@@ -19,9 +21,11 @@
 //   then, on the sorted columns:
 //   4. col_ptr[j] = number of keys below j (a binary search per column).
 // A col_idx outside [0, m) sorts as column m, behind every real column, and gets csc_pos = -1.
-// No atomics on memory and no order that depends on timing: the same bits on every call.
+// Either way there are no atomics on memory and no order that depends on timing: the same bits on every call.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "regot.h"
 #include "regot_device.hpp"
@@ -334,6 +338,352 @@ __global__ __launch_bounds__(kBlock) void col_ptr_kernel(TransposeArgs A, const 
     A.col_ptr[j] = lo;
 }
 
+// ---------------------------------------------------------------------------
+// The same by counting.  The rows are taken in blocks: row r and the entries before it come to r / 32 + entries / E, and block b
+// has the rows where that is in [b, b + 1), so it has at most 32 rows and at most E entries more than its last row has.  Per
+// block a bit mask for every column says which of its rows have an entry there, so that an entry's rank among the block's
+// entries of its column is a count of bits, whatever order they come in, and nothing has to be sorted:
+//   1. column_count_kernel: the masks of a block in LDS; rank[p] of its entries and count[block][column];
+//   2. column_scan_kernel: per column, the counts of the blocks before (base[block][column]), and the column's place among 128;
+//   3. column_place_kernel: csc_pos[p] = column's beginning + base + rank, row_idx[csc_pos[p]]; col_ptr.
+// Every access is consecutive but the gathers from LDS and the stores of row_idx.  Those go to the next free place of a column, one
+// line for 32 rows' entries or more, so blocks that lie next to each other run on one die, whose L2 puts the lines together; the dies
+// share the blocks by entries, since rows without any also make blocks (20000 x 20000, all 2e6 entries in 4000 of the rows, us:
+// 53, with the same number of blocks to a die 74).  E is nnz / 128, in 2048 .. 16384: more entries to a block are fewer rows of the
+// table, as long as there are blocks enough for the compute units (2e6 entries in 20000 x 20000, E = 8192 / 16384: 51 / 46 us; 0.9e6
+// in 200 x 40000, 41 / 51).
+// What bounds it: 6 bytes of table traffic per column and block (0.2 an entry of the matrix) and 37 bytes an entry of the pattern, which
+// at 20000 x 20000 and 2e6 entries are 149 MB, 22 us at a copy's rate; count, scan and place take 14 + 11 + 24 in a trace, where the last
+// waits for its scattered stores.
+// A row holds a column at most once, as the pattern's definition has it; a second one would take the first one's place.
+// ---------------------------------------------------------------------------
+constexpr int kCountThreads = 1024;
+constexpr int kBlockRows = 32, kBlockLeastEntries = 2048, kBlockMostEntries = 16384;
+constexpr int kCountHeld = 4;                    // entries of a thread at a time
+constexpr int kGroupCols = 128;                  // columns of a workgroup of the scan,
+constexpr int kScanCols = 8;                     // of a thread
+constexpr int kScanParts = kCountThreads * kScanCols / kGroupCols;  // shares of the blocks in it
+constexpr int kScanHeld = 10;                    // blocks of a share requested at once
+constexpr int kCountMaxCols = 40000, kCountMostRows = 65535;   // (the masks in LDS; base has 16 bits)
+constexpr int padded(int cols) { return (cols + kGroupCols - 1) / kGroupCols * kGroupCols; }
+constexpr int kMaxGroups = (kCountMaxCols + kGroupCols - 1) / kGroupCols, kGroupsPerLane = (kMaxGroups + kLanes - 1) / kLanes;
+
+struct BlockRows {  // of a block: its first entry, how many, its first row, how many
+    int64_t first;
+    int32_t count, row, rows;
+};
+
+struct CountLayout {
+    size_t count, base, rank, col_off, group_total, rows, die_start;
+    int64_t blocks, pitch, entries;
+    size_t total;
+};
+
+// By counting / by sorting, us: 20000 x 20000, 2e6 entries 46 / 72, 790000 40 / 50; 40000 x 10000, 4e6 67 / 118; 10000 x 10000, 200000 22 / 34;
+// 1000 x 1000, 9000 14 / 28; 5000 x 5000, 12000 15 / 28; 100 x 40000, 1.6e6 50 / 64.  Not (the table) where the pattern of a large matrix
+// has fewer entries than one in 512, at 20000 x 20000 with 390000 40.0 / 39.5, or one in 200 where m > 20000 leaves room for one workgroup
+// on a compute unit, at 5000 x 40000 with 600000 44.9 / 45.3, 30000 x 40000 with 2.5e6 105 / 85; nor where there are more blocks than the
+// compute units take at once and (few columns to share the scan) 65000 x 100, 35 / 21, or (few entries in a block) 65535 x 2048 with
+// 327000, 51 / 40 (65535 x 3000 with 1e6: 56 / 58); nor (a row is one block's) at 32 x 40000 with 480000, 54 / 43; nor where the sort has
+// one pass over few entries, at 64 x 64 with 98, 11.0 / 10.5 (2135: 11 / 17).
+bool by_counting(int64_t n, int64_t m, int64_t nnz)
+{
+    if (n < 1 || m < 1 || nnz < 1 || n > kCountMostRows || m > kCountMaxCols) return false;
+    return n * m <= std::max<int64_t>(40'000'000, (m <= kCountMaxCols / 2 ? 512 : 200) * nnz) && (n <= 20480 || (m >= 2048 && nnz >= 16 * n)) && m <= 512 * n && (m >= kDigits || nnz >= kTile);
+}
+
+CountLayout make_count_layout(int64_t n, int64_t m, int64_t nnz)
+{
+    CountLayout L{};
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        size_t at = off;
+        off = align_up(off + bytes);
+        return at;
+    };
+    L.entries = std::clamp<int64_t>(nnz / 128, kBlockLeastEntries, kBlockMostEntries);
+    L.blocks = (n * L.entries + nnz * kBlockRows) / (kBlockRows * L.entries) + 1;
+    L.pitch = (m + kGroupCols - 1) / kGroupCols * kGroupCols;
+    L.count = take((size_t)(L.blocks * L.pitch));
+    L.base = take((size_t)(L.blocks * L.pitch) * sizeof(uint16_t));
+    L.rank = take((size_t)nnz);
+    L.col_off = take((size_t)L.pitch * sizeof(uint32_t));
+    L.group_total = take((size_t)(L.pitch / kGroupCols) * sizeof(uint32_t));
+    L.rows = take((size_t)L.blocks * sizeof(BlockRows));
+    L.die_start = take((kDies + 1) * sizeof(int32_t));
+    L.total = off;
+    return L;
+}
+
+struct CountArgs {
+    int n, m, blocks, pitch, entries;  // (entries: as a block of one row may have)
+    int64_t nnz;
+    const int64_t *row_ptr;
+    const int32_t *col_idx;
+    int64_t *col_ptr;
+    int32_t *row_idx;
+    int64_t *csc_pos;
+    uint8_t *count;         // [blocks][pitch]
+    uint16_t *base;         // [blocks][pitch]
+    uint8_t *rank;          // [nnz]
+    uint32_t *col_off;      // [pitch] entries of the columns before in the group of 128
+    uint32_t *group_total;  // [pitch / 128]
+    BlockRows *rows;        // [blocks]
+    int32_t *die_start;     // [kDies + 1] first blocks of the dies in column_place_kernel
+};
+
+__device__ __forceinline__ int64_t entries_before(const CountArgs &A, int64_t r)
+{
+    const int64_t p = A.row_ptr[r];
+    return p < 0 ? 0 : p > A.nnz ? A.nnz : p;
+}
+
+// The first row of block b, by a wave: among the 64 rows around where it would be if all had the same number of entries, or else
+// among all.
+__device__ __forceinline__ int block_first_row(const CountArgs &A, int b, int lane)
+{
+    const int64_t target = (int64_t)b * kBlockRows * A.entries;
+    const auto reached = [&](int64_t r) { return r >= A.n || r * A.entries + entries_before(A, r) * kBlockRows >= target; };
+    int64_t r = (int64_t)b * A.n / A.blocks - kLanes / 2;
+    r = r < 0 ? 0 : r;
+    const uint64_t mask = __ballot(reached(r + lane));
+    if (mask != 0 && (r == 0 || (mask & 1) == 0)) return (int)r + __builtin_ctzll(mask) < A.n ? (int)r + __builtin_ctzll(mask) : A.n;
+    return (int)wave_first(0, A.n, lane, reached);
+}
+
+// The entries of a block of rows, one to a thread whatever rows they are in.
+struct BlockEntries {
+    int64_t first;
+    int r0, count;
+    // ends: LDS [kBlockRows], complete after the next barrier
+    __device__ __forceinline__ BlockEntries(const CountArgs &A, const BlockRows &B, int *ends) : first(B.first), r0(B.row), count(B.count)
+    {
+        if ((int)threadIdx.x < kBlockRows) ends[threadIdx.x] = (int)threadIdx.x < B.rows ? (int)(entries_before(A, r0 + threadIdx.x + 1) - first) : INT32_MAX;
+    }
+    // the row of the block that entry q is in
+    static __device__ __forceinline__ int row(const int *ends, int q)
+    {
+        int r = 0;
+#pragma unroll
+        for (int half = kBlockRows / 2; half > 0; half >>= 1) r += ends[r + half - 1] <= q ? half : 0;
+        return r;
+    }
+};
+
+template <int COLS>
+__global__ __launch_bounds__(kCountThreads) void column_count_kernel(CountArgs A)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t mask[padded(COLS)];
+    __shared__ int ends[kBlockRows];
+    __shared__ int cut[2];
+    const int tid = (int)threadIdx.x, block = (int)blockIdx.x;
+    if (tid < 2 * kLanes) {
+        const int k = tid / kLanes, first = block_first_row(A, block + k, tid % kLanes);
+        if (tid % kLanes == 0) cut[k] = first;
+    }
+    __syncthreads();
+    const int rows = max(0, min(kBlockRows, cut[1] - cut[0]));  // (never more, unless row_ptr does not ascend)
+    const int64_t first = entries_before(A, cut[0]), after = entries_before(A, cut[0] + rows);
+    const BlockRows B{first, (int32_t)(after > first ? after - first : 0), cut[0], rows};
+    const BlockEntries E(A, B, ends);
+    if (tid == 0) A.rows[block] = B;
+    if (tid <= kDies) {  // the dies that begin behind this block: the next one is the first whose entries begin in their shares
+        const auto die_of = [&](int64_t p) { return min((int)(p * kDies / A.nnz), kDies - 1); };
+        const int here = block == 0 ? -1 : die_of(first), next = block + 1 == A.blocks ? kDies : die_of(after);
+        if (block == 0 && tid == 0) A.die_start[0] = 0;
+        else if (tid > max(here, 0) && tid <= next) A.die_start[tid] = block + 1;
+    }
+    int32_t j[kCountHeld];
+    int r[kCountHeld];
+    // kCountHeld entries a thread from q0 on: their columns (none: -1), and the rows of those that are in one
+    const auto fetch = [&](int q0) {
+#pragma unroll
+        for (int k = 0; k < kCountHeld; ++k) {
+            const int q = q0 + k * kCountThreads + tid;
+            j[k] = q < E.count ? A.col_idx[E.first + q] : -1;
+            j[k] = (uint32_t)j[k] < (uint32_t)A.m ? j[k] : -1;
+        }
+    };
+    const auto find_rows = [&](int q0) {
+#pragma unroll
+        for (int k = 0; k < kCountHeld; ++k) r[k] = BlockEntries::row(ends, q0 + k * kCountThreads + tid);
+    };
+    fetch(0);
+    for (int c = 4 * tid; c < A.pitch; c += 4 * kCountThreads) *reinterpret_cast<uint4 *>(mask + c) = uint4{0, 0, 0, 0};
+    __syncthreads();
+    constexpr int kTrip = kCountHeld * kCountThreads;
+    const int last = E.count > 0 ? (E.count - 1) / kTrip * kTrip : 0;
+    for (int q0 = 0;; q0 += kTrip) {
+        find_rows(q0);
+#pragma unroll
+        for (int k = 0; k < kCountHeld; ++k)
+            if (j[k] >= 0) atomicOr(&mask[j[k]], 1u << r[k]);
+        if (q0 >= last) break;
+        fetch(q0 + kTrip);
+    }
+    __syncthreads();
+    for (int q0 = last;; q0 -= kTrip) {  // (what was fetched last first)
+#pragma unroll
+        for (int k = 0; k < kCountHeld; ++k) {
+            const int q = q0 + k * kCountThreads + tid;
+            if (q < E.count) A.rank[E.first + q] = j[k] >= 0 ? (uint8_t)__builtin_popcount(mask[j[k]] & ((1u << r[k]) - 1u)) : (uint8_t)0;
+        }
+        if (q0 == 0) break;
+        fetch(q0 - kTrip);
+        find_rows(q0 - kTrip);
+    }
+    uint8_t *count = A.count + (size_t)block * A.pitch;
+    for (int c = 4 * tid; c < A.pitch; c += 4 * kCountThreads) {
+        const uint4 four = *reinterpret_cast<const uint4 *>(mask + c);
+        *reinterpret_cast<uint32_t *>(count + c) = (uint32_t)__builtin_popcount(four.x) | (uint32_t)__builtin_popcount(four.y) << 8 |
+                                                   (uint32_t)__builtin_popcount(four.z) << 16 | (uint32_t)__builtin_popcount(four.w) << 24;
+    }
+}
+
+// Eight columns to a thread, two to a word: a column has at most kCountMostRows entries.  The blocks are shared out among groups of
+// 16 threads.
+__global__ __launch_bounds__(kCountThreads) void column_scan_kernel(CountArgs A)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t part[kScanParts][kGroupCols];
+    const int tid = (int)threadIdx.x, share = tid / (kGroupCols / kScanCols), at = kScanCols * (tid % (kGroupCols / kScanCols));
+    const int c = (int)blockIdx.x * kGroupCols + at;
+    const int per = (A.blocks + kScanParts - 1) / kScanParts, g0 = min(A.blocks, share * per), g1 = min(A.blocks, g0 + per);
+    const uint8_t *count = A.count + c;
+    uint4 s{0, 0, 0, 0};
+    const auto add = [&](uint2 eight) {
+        s.x += __builtin_amdgcn_perm(0u, eight.x, 0x0c010c00u);
+        s.y += __builtin_amdgcn_perm(0u, eight.x, 0x0c030c02u);
+        s.z += __builtin_amdgcn_perm(0u, eight.y, 0x0c010c00u);
+        s.w += __builtin_amdgcn_perm(0u, eight.y, 0x0c030c02u);
+    };
+    uint2 eight[kScanHeld];  // (all requested at once; the first ones are kept)
+    const auto fetch = [&](int g) {
+#pragma unroll
+        for (int k = 0; k < kScanHeld; ++k) eight[k] = g + k < g1 ? *reinterpret_cast<const uint2 *>(count + (size_t)(g + k) * A.pitch) : uint2{0, 0};
+    };
+    for (int g = g0 + kScanHeld; g < g1; g += kScanHeld) {
+        fetch(g);
+#pragma unroll
+        for (int k = 0; k < kScanHeld; ++k) add(eight[k]);
+    }
+    fetch(g0);
+#pragma unroll
+    for (int k = 0; k < kScanHeld; ++k) add(eight[k]);
+    *reinterpret_cast<uint4 *>(&part[share][at]) = s;
+    __syncthreads();
+    if (tid < kLanes) {  // two columns a lane: what is before each share, and their sums
+        uint32_t run = 0;
+#pragma unroll 16
+        for (int k = 0; k < kScanParts; ++k) {
+            uint32_t *two = reinterpret_cast<uint32_t *>(&part[k][2 * tid]);
+            const uint32_t t = *two;
+            *two = run;
+            run += t;
+        }
+        const uint32_t t0 = run & 0xffffu, t1 = run >> 16, up_to = (uint32_t)wave_scan((int)(t0 + t1));
+        uint32_t *col_off = A.col_off + (int)blockIdx.x * kGroupCols + 2 * tid;
+        col_off[0] = up_to - t1 - t0;
+        col_off[1] = up_to - t1;
+        if (tid == kLanes - 1) A.group_total[blockIdx.x] = up_to;
+    }
+    __syncthreads();
+    s = *reinterpret_cast<const uint4 *>(&part[share][at]);
+    uint16_t *base = A.base + c;
+    for (int g = g0; g < g1; g += kScanHeld) {
+        if (g != g0) fetch(g);
+#pragma unroll
+        for (int k = 0; k < kScanHeld; ++k) {
+            if (g + k < g1) *reinterpret_cast<uint4 *>(base + (size_t)(g + k) * A.pitch) = s;
+            add(eight[k]);
+        }
+    }
+}
+
+template <int COLS>
+__global__ __launch_bounds__(kCountThreads) void column_place_kernel(CountArgs A)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t at[padded(COLS)];  // where the block's first entry of a column goes
+    __shared__ uint32_t group_at[kGroupsPerLane * kLanes + 1];
+    __shared__ int ends[kBlockRows];
+    const int die = (int)blockIdx.x % kDies;
+    int block = max(A.die_start[die], 0) + (int)blockIdx.x / kDies;
+    const int end = min(A.die_start[die + 1], A.blocks);
+    for (bool first = true; first || block < end; first = false, block += (int)gridDim.x / kDies) {
+        int tid = (int)threadIdx.x;
+        asm volatile("" : "+v"(tid));  // (no addresses kept over the loop: with more than 64 registers a compute unit has one workgroup)
+        const BlockEntries E(A, block < end ? A.rows[block] : BlockRows{}, ends);
+        if (!first && E.count == 0) continue;
+        int32_t j[kCountHeld];
+        uint32_t rank[kCountHeld];
+        const auto fetch = [&](int q0) {
+#pragma unroll
+            for (int k = 0; k < kCountHeld; ++k) {
+                const int q = q0 + k * kCountThreads + tid;
+                j[k] = q < E.count ? A.col_idx[E.first + q] : -1;
+                rank[k] = q < E.count ? A.rank[E.first + q] : 0u;
+            }
+        };
+        fetch(0);
+        constexpr int kStage = (padded(COLS) / kScanCols + kCountThreads - 1) / kCountThreads;
+        const uint16_t *base = A.base + (size_t)min(block, A.blocks - 1) * A.pitch;
+        uint4 b[kStage];
+#pragma unroll
+        for (int k = 0; k < kStage; ++k) {
+            const int c = kScanCols * (k * kCountThreads + tid);
+            b[k] = c < A.pitch ? *reinterpret_cast<const uint4 *>(base + c) : uint4{0, 0, 0, 0};
+        }
+        if (first && tid < kLanes) {
+            const int groups = A.pitch / kGroupCols;
+            uint32_t t[kGroupsPerLane], sum = 0;
+#pragma unroll
+            for (int k = 0; k < kGroupsPerLane; ++k) {
+                const int i = tid * kGroupsPerLane + k;
+                t[k] = i < groups ? A.group_total[i] : 0u;
+                sum += t[k];
+            }
+            const uint32_t up_to = (uint32_t)wave_scan((int)sum);
+            uint32_t run = up_to - sum;
+#pragma unroll
+            for (int k = 0; k < kGroupsPerLane; ++k) {
+                group_at[tid * kGroupsPerLane + k] = run;
+                run += t[k];
+            }
+            if (tid == kLanes - 1) group_at[kGroupsPerLane * kLanes] = up_to;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kStage; ++k) {
+            const int c = kScanCols * (k * kCountThreads + tid);
+            if (c >= A.pitch) break;
+            const uint32_t g = group_at[c / kGroupCols];
+            const uint4 o0 = *reinterpret_cast<const uint4 *>(A.col_off + c), o1 = *reinterpret_cast<const uint4 *>(A.col_off + c + 4);
+            *reinterpret_cast<uint4 *>(at + c) = uint4{g + o0.x + (b[k].x & 0xffffu), g + o0.y + (b[k].x >> 16), g + o0.z + (b[k].y & 0xffffu), g + o0.w + (b[k].y >> 16)};
+            *reinterpret_cast<uint4 *>(at + c + 4) = uint4{g + o1.x + (b[k].z & 0xffffu), g + o1.y + (b[k].z >> 16), g + o1.z + (b[k].w & 0xffffu), g + o1.w + (b[k].w >> 16)};
+        }
+        if (first)
+            for (int64_t c = (int64_t)blockIdx.x * kCountThreads + tid; c <= A.m; c += (int64_t)gridDim.x * kCountThreads)
+                A.col_ptr[c] = c < A.m ? group_at[c / kGroupCols] + A.col_off[c] : group_at[kGroupsPerLane * kLanes];
+        __syncthreads();
+        constexpr int kTrip = kCountHeld * kCountThreads;
+        for (int q0 = 0; q0 < E.count; q0 += kTrip) {
+            if (q0 != 0) fetch(q0);
+#pragma unroll
+            for (int k = 0; k < kCountHeld; ++k) {
+                const int q = q0 + k * kCountThreads + tid;
+                if (q >= E.count) break;
+                int64_t to = -1;  // (not an entry of any column)
+                if ((uint32_t)j[k] < (uint32_t)A.m) {
+                    to = (int64_t)at[j[k]] + rank[k];
+                    if (to < A.nnz) A.row_idx[to] = E.r0 + BlockEntries::row(ends, q);  // (always, unless row_ptr does not add up)
+                }
+                A.csc_pos[E.first + q] = to;
+            }
+        }
+        if (block + (int)gridDim.x / kDies >= end) break;
+        __syncthreads();  // at and ends are read
+    }
+}
+
 int check_dims(int64_t n, int64_t m, int64_t nnz)
 {
     if (n < 0 || m < 0 || n > kMaxDim || m > kMaxDim) return REGOT_ERR_DIM;
@@ -351,6 +701,7 @@ int regot_pattern_transpose_workspace_bytes(int64_t n, int64_t m, int64_t nnz, s
     const int st = check_dims(n, m, nnz);
     if (st != REGOT_OK) return st;
     *bytes = make_transpose_layout(m, nnz).total;
+    if (by_counting(n, m, nnz)) *bytes = std::max(*bytes, make_count_layout(n, m, nnz).total);
     return REGOT_OK;
 }
 
@@ -367,10 +718,24 @@ int regot_pattern_transpose(int64_t n, int64_t m, int64_t nnz, const int64_t *ro
     const TransposeLayout L = make_transpose_layout(m, nnz);
     if (!workspace) return REGOT_ERR_NULL;
     if (misaligned(workspace, kAlign)) return REGOT_ERR_ALIGN;
-    if (workspace_bytes < L.total) return REGOT_ERR_WORKSPACE;
+    const bool counting = by_counting(n, m, nnz);
+    if (workspace_bytes < (counting ? std::max(L.total, make_count_layout(n, m, nnz).total) : L.total)) return REGOT_ERR_WORKSPACE;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
+    if (counting) {
+        const CountLayout K = make_count_layout(n, m, nnz);
+        const CountArgs C{(int)n, (int)m, (int)K.blocks, (int)K.pitch, (int)K.entries, nnz, row_ptr, col_idx, col_ptr, row_idx, csc_pos,
+                          reinterpret_cast<uint8_t *>(ws + K.count), reinterpret_cast<uint16_t *>(ws + K.base),
+                          reinterpret_cast<uint8_t *>(ws + K.rank), reinterpret_cast<uint32_t *>(ws + K.col_off),
+                          reinterpret_cast<uint32_t *>(ws + K.group_total), reinterpret_cast<BlockRows *>(ws + K.rows), reinterpret_cast<int32_t *>(ws + K.die_start)};
+        const bool narrow = m <= kCountMaxCols / 2;  // (two workgroups to a compute unit)
+        const dim3 threads(kCountThreads);
+        hipLaunchKernelGGL(narrow ? column_count_kernel<kCountMaxCols / 2> : column_count_kernel<kCountMaxCols>, dim3((unsigned)K.blocks), threads, 0, s, C);
+        hipLaunchKernelGGL(column_scan_kernel, dim3((unsigned)(K.pitch / kGroupCols)), threads, 0, s, C);
+        hipLaunchKernelGGL(narrow ? column_place_kernel<kCountMaxCols / 2> : column_place_kernel<kCountMaxCols>, dim3((unsigned)die_grid(K.blocks)), threads, 0, s, C);
+        return hipGetLastError() == hipSuccess ? REGOT_OK : REGOT_ERR_HIP;
+    }
     TransposeArgs A{};
     A.n = n;
     A.m = m;

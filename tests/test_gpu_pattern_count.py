@@ -1,0 +1,124 @@
+"""regot_pattern_transpose by counting (regot_pattern.hip): at the edges of its rule, of its blocks (32 rows, 2048 to 16384 entries)
+and of its column groups (128 columns; 20000 columns, above which a workgroup has a compute unit to itself), bit for bit against
+the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def rows_of(n, m, lengths, seed):
+    """Row i has lengths[i] columns: the multiples of a step prime to m, behind a random one, so that none occurs twice."""
+    rng = np.random.default_rng(seed)
+    lengths = np.minimum(np.asarray(lengths, dtype=np.int64), m)
+    rp = np.zeros(n + 1, dtype=np.int64); rp[1:] = np.cumsum(lengths)
+    step = next(s for s in range(int(m * 0.618) | 1, 2 * m + 3, 2) if np.gcd(s, m) == 1) % m or 1
+    first = rng.integers(0, m, size=n)
+    k = np.arange(rp[-1]) - np.repeat(rp[:-1], lengths)
+    cols = (np.repeat(first, lengths) + k * step) % m
+    key = np.sort(np.repeat(np.arange(n), lengths) * m + cols)
+    return rp, (key % m).astype(np.int32)
+
+
+def some(n, each, at=(), long=0):
+    lengths = np.full(n, each)
+    lengths[list(at)] = long
+    return lengths
+
+
+CASES = {
+    # the smallest, one block; its 32 rows, one row over; full and empty columns
+    "1x256": (1, 256, [256]), "8x4096": (8, 4096, some(8, 300)), "31x300": (31, 300, some(31, 100)), "32x300": (32, 300, some(32, 300)),
+    "33x300": (33, 300, some(33, 100)), "64x257": (64, 257, some(64, 40)),
+    # few columns: one group, one over
+    "127": (500, 127, some(500, 20)), "128": (500, 128, some(500, 20)), "129": (500, 129, some(500, 20)),
+    # a thread's entries (4096 a workgroup), one over; a block's least entries, one row with more than all the others
+    "4096": (4, 1500, [1024] * 4), "4097": (4, 1500, [1024] * 3 + [1025]), "2048": (64, 700, some(64, 64)), "long row": (700, 9000, some(700, 20, (350,), 9000)),
+    # rows without entries: before, between (more than a block of them), behind; the entries in a few of the rows
+    "empty rows": (3000, 2000, np.where(np.isin(np.arange(3000) // 100, [3, 4, 20]), 300, 0)), "skewed": (9000, 3000, np.where(np.arange(9000) % 4500 < 200, 1000, 1)),
+    "last row": (2000, 1500, some(2000, 0, (1999,), 1500) + (np.arange(2000) < 40) * 200), "first row": (2000, 1500, some(2000, 0, (0,), 1500) + (np.arange(2000) > 1950) * 200),
+    # more than 2.1e6 entries: blocks of 16384
+    "most entries": (3000, 4000, 500 + np.arange(3000) % 500),
+    # the widest for two workgroups to a compute unit, and above; the widest at all
+    "20000": (200, 20000, some(200, 150)), "20001": (200, 20001, some(200, 250)), "40000": (90, 40000, some(90, 777)),
+    # the rule's other edges, on either side: one entry in 512, in 200; a matrix of 4e7 entries; 20480 rows of few columns; 512 columns to a row; 40000; 65535 rows
+    "one in 512": (8192, 8192, some(8192, 16)), "fewer": (8192, 8192, some(8192, 16, (5,), 15)), "one in 200": (1200, 40000, some(1200, 200)), "fewer, wide": (1200, 40000, some(1200, 200, (7,), 199)),
+    "4e7": (2000, 20000, some(2000, 1)), "above 4e7": (2001, 20000, some(2001, 1)),
+    "20480 rows": (20480, 300, some(20480, 3)), "20481 rows": (20481, 300, some(20481, 3)), "512": (40, 20480, some(40, 300)), "512 and one": (40, 20481, some(40, 300)),
+    "40001": (90, 40001, some(90, 777)), "65535 rows": (65535, 2048, some(65535, 16)), "65536 rows": (65536, 2048, some(65536, 16)), "few a row": (65535, 2048, some(65535, 16, (9,), 15)),
+    "full column": (65535, 2050, some(65535, 18)),
+    "one pass": (30, 255, some(30, 68, (3,), 75)), "one pass, more": (30, 255, some(30, 68, (3,), 77)),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_transpose_by_counting(name):
+    from paper_2605_08793_amd import binding as B
+    n, m, lengths = CASES[name]
+    rp, ci = rows_of(n, m, lengths, seed=n + m)
+    if name == "full column":  # column 2049 has an entry in every row: 65535, the most that 16 bits hold
+        ci = ci.reshape(n, -1).copy(); ci[:, -1] = m - 1
+        ci[:, :-1] = np.where(ci[:, :-1] == m - 1, -1, ci[:, :-1]); ci = np.sort(ci, axis=1)
+        rows, keep = np.repeat(np.arange(n), ci.shape[1]), (ci >= 0).ravel()
+        ci = ci.ravel()[keep]; rp = np.zeros(n + 1, dtype=np.int64); rp[1:] = np.cumsum(np.bincount(rows[keep], minlength=n))
+    nnz = int(rp[-1])
+    print(f"[count] {name}: n={n} m={m} nnz={nnz}", flush=True)
+    o_cp, o_ri, o_pos = oracle.pattern_transpose(n, m, rp, ci)
+    rpd, cid = torch.as_tensor(rp).cuda(), torch.as_tensor(ci).cuda()
+    ws = torch.empty(B.regot_pattern_transpose_workspace_bytes(n, m, nnz), dtype=torch.uint8, device="cuda")
+    guard = 64
+    for rep in range(2):
+        ws.fill_(0xA5 if rep else 0x7F)
+        cp = torch.full((m + 1 + guard,), -5, dtype=torch.int64, device="cuda")
+        ri = torch.full((nnz + guard,), -5, dtype=torch.int32, device="cuda")
+        pos = torch.full((nnz + guard,), -5, dtype=torch.int64, device="cuda")
+        B.regot_pattern_transpose(n, m, nnz, rpd, cid, cp[:m + 1], ri, pos, workspace=ws)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(cp.cpu().numpy()[:m + 1], o_cp)
+        np.testing.assert_array_equal(ri.cpu().numpy()[:nnz], o_ri)
+        np.testing.assert_array_equal(pos.cpu().numpy()[:nnz], o_pos)
+        assert (cp[m + 1:] == -5).all() and (ri[nnz:] == -5).all() and (pos[nnz:] == -5).all()
+
+
+def test_entries_that_are_no_columns():
+    from paper_2605_08793_amd import binding as B
+    n, m = 500, 2000
+    rp, ci = rows_of(n, m, some(n, 30), seed=3)
+    nnz = int(rp[-1])
+    where = np.array([0, 1, 29, 30, 960, nnz // 2, nnz - 1])
+    bad = ci.copy(); bad[where] = [m, -1, m + 5, -2 ** 31, 2 ** 31 - 1, m, -7]
+    keep = np.ones(nnz, dtype=bool); keep[where] = False
+    rows = np.repeat(np.arange(n), np.diff(rp))
+    rp2 = np.zeros(n + 1, dtype=np.int64); rp2[1:] = np.cumsum(np.bincount(rows[keep], minlength=n))
+    o_cp, o_ri, o_pos = oracle.pattern_transpose(n, m, rp2, ci[keep])
+    ws = torch.empty(B.regot_pattern_transpose_workspace_bytes(n, m, nnz), dtype=torch.uint8, device="cuda")
+    cp = torch.empty(m + 1, dtype=torch.int64, device="cuda")
+    ri = torch.full((nnz,), -5, dtype=torch.int32, device="cuda"); pos = torch.full((nnz,), -5, dtype=torch.int64, device="cuda")
+    B.regot_pattern_transpose(n, m, nnz, torch.as_tensor(rp).cuda(), torch.as_tensor(bad).cuda(), cp, ri, pos, workspace=ws)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(cp.cpu().numpy(), o_cp)
+    np.testing.assert_array_equal(ri.cpu().numpy()[:keep.sum()], o_ri)
+    got = pos.cpu().numpy()
+    assert (got[where] == -1).all()
+    np.testing.assert_array_equal(got[keep], o_pos)
+
+
+@pytest.mark.parametrize("edge", [(65535, 40000), (1, 512), (20000, 20000)])
+def test_workspace_is_asked_for(edge):
+    """One byte less than the size that is asked for is refused, with the outputs untouched."""
+    from paper_2605_08793_amd import binding as B
+    n, m = edge
+    nnz = n * m // (200 if m > 20000 else 512)
+    nnz = max(nnz, 2048)
+    need = B.regot_pattern_transpose_workspace_bytes(n, m, nnz)
+    assert need >= 3 * (n // 32) * m
+    rp, cp = torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(m + 1, dtype=torch.int64, device="cuda")
+    ci, ri, pos = (torch.zeros(nnz, dtype=t, device="cuda") for t in (torch.int32, torch.int32, torch.int64))
+    ws = torch.empty(need - 1, dtype=torch.uint8, device="cuda")
+    with pytest.raises(B.RegotError):
+        B.regot_pattern_transpose(n, m, nnz, rp, ci, cp, ri, pos, workspace=ws)
+    torch.cuda.synchronize()
+    assert not (cp.any() or ri.any() or pos.any())
