@@ -10,6 +10,7 @@
 #include "regot.h"
 #include "exp_poly_coeffs.h"
 #include "regot_kernels.hpp"
+#include "regot_finish_small.hpp"
 #include "regot_sweep.hpp"
 #include "regot_select.hpp"
 #include "regot_refresh.hpp"
@@ -438,11 +439,22 @@ int run_plan_pass(int64_t n, int64_t m, const double *M, int64_t ldM, const doub
             hipLaunchKernelGGL(refresh_drop_kernel, dim3((unsigned)run_blocks), dim3(kThreads), 0, s, T, Q.delta, A.seg_count);
         }
     }
-    hipLaunchKernelGGL((finalize_kernel<REDUCE, SPARSIFY>), dim3(fin_blocks), dim3(kFinThreads), 0, s, F);
+    // a small matrix: the objective beside the sums, and with few counts the whole rest of the call in one launch
+    F.nblk_cols = G.nblk_cols;
+    const bool small = !rc && nblocks > 0 && G.g_c <= kOncePanels && G.nblk_rows + G.nblk_cols <= kOnceParts;
+    const bool once = REDUCE && !SPARSIFY && small && n * G.g_c + 2 * (n + m) <= kOnceDoubles;
+    bool whole = false;
+    if (SPARSIFY && small) {
+        const int64_t tallest = (n + G.g_r - 1) / G.g_r + kRB - 1;  // (chunk boundaries are rounded down to multiples of kRB)
+        whole = capacity <= kOnceEntries * G.g_r && n * G.g_c <= kOnceCounts && tallest * G.g_c <= kOnceChunk;
+    }
+    if constexpr (REDUCE && !SPARSIFY)
+        if (once) hipLaunchKernelGGL((finalize_kernel<true, false, true>), dim3(fin_blocks + 1), dim3(kFinThreads), 0, s, F);
+    if (!once && !whole) hipLaunchKernelGGL((finalize_kernel<REDUCE, SPARSIFY>), dim3(fin_blocks), dim3(kFinThreads), 0, s, F);
     // With few row workgroups the scatter kernel also does the one-workgroup work (scan of the
     // per-workgroup counts, scalars of the call): one launch less on the critical path.
     const bool fold = SPARSIFY && G.nblk_rows <= kFoldBlocks;
-    if (!fold) hipLaunchKernelGGL((epilogue_kernel<REDUCE, SPARSIFY>), dim3(1), dim3(kThreads), 0, s, F, fin_blocks);
+    if (!fold && !once) hipLaunchKernelGGL((epilogue_kernel<REDUCE, SPARSIFY>), dim3(1), dim3(kThreads), 0, s, F, fin_blocks);
 
     if (SPARSIFY) {
         ScatterArgs S{};
@@ -467,6 +479,10 @@ int run_plan_pass(int64_t n, int64_t m, const double *M, int64_t ldM, const doub
         S.val = val;
         // Workgroups that place records (a multiple of kXcds, at most 4096): one per run with a fixed
         // id, plus room for a quarter as many runs of earlier flushes (the kernel loops if there are more).
+        if (whole) {
+            hipLaunchKernelGGL((finish_small_kernel<REDUCE>), dim3((REDUCE ? 1 + G.nblk_cols : 0) + G.g_r), dim3(kFinThreads), 0, s, S, F);
+            return hip_status();
+        }
         const int64_t fixed_items = scatter_fixed_items(G.g_r, G.g_c);
         int64_t spare = L.max_ranges - A.fixed_runs;
         if (spare > fixed_items / 4 + kXcds) spare = fixed_items / 4 + kXcds;

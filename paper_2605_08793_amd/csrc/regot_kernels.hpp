@@ -1026,6 +1026,7 @@ struct FinalizeArgs {
     int64_t capacity;
     int64_t *info;
     int *cu_table;       // PaceKeeperHw's records: cleared for the next call (nullptr: not used by this call)
+    int nblk_cols;       // column workgroups
 };
 
 // sum of part[p * stride + idx] over p in [p0, p1), fetched in one batch when there are at most kFinRegs
@@ -1046,9 +1047,104 @@ __device__ __forceinline__ double sum_partials(const double *part, size_t stride
     return r;
 }
 
-template <bool REDUCE, bool SPARSIFY>
+// The objective from the panels' partials, by one workgroup of kFinThreads beside those that form the sums, for matrices that are small
+// enough (at most kOnceParts of their workgroups, kOncePanels panels): every wave adds up the rows of some of them once more.
+// It saves a launch: plain evaluation, us, launch behind / this, 64 x 64 8.8 / 6.9, 1000 x 1000 11.0 / 10.2, 2000 x 2000 15.6 / 14.7.  A
+// workgroup has no more in flight than a compute unit holds, so with more than kOnceDoubles it is what the call waits for: 1000 x 4000
+// 15.0 / 16.4, 3000 x 3000 24.5 / 27.3.  The additions are those of finalize_kernel and write_objective in the same order: the same bits.
+constexpr int kOnceParts = 128, kOncePanels = 8;
+constexpr int kOnceDoubles = 16384;  // partials and vector elements of a plain evaluation
+constexpr int kOnceHeld = 4;  // parts whose loads a wave has under way at a time
+
+// the parts of one wave, k = w, w + kFinSub, ..., with at most P panels; loads of what is not there are of something that is
+template <int P>
+__device__ __forceinline__ void objective_parts(const FinalizeArgs &F, int w, int l, double (*lds_obj)[3])
+{
+    const int nparts = F.nblk_rows + F.nblk_cols;
+    for (int k0 = w; k0 < nparts; k0 += kOnceHeld * kFinSub) {
+        double v[kOnceHeld][P], x[kOnceHeld], y[kOnceHeld];
+#pragma unroll
+        for (int h = 0; h < kOnceHeld; ++h) {
+            const int k = min(k0 + h * kFinSub, nparts - 1);
+            const bool rows = k < F.nblk_rows;
+            const int i = min((rows ? k : k - F.nblk_rows) * kLanes + l, (rows ? F.n : F.m) - 1);
+            const double *xs = rows ? F.alpha : F.beta, *ys = rows ? F.a : F.b;
+            x[h] = xs[i];
+            y[h] = ys[i];
+            if (rows) {
+#pragma unroll
+                for (int p = 0; p < P; ++p) v[h][p] = F.rowpart[(size_t)min(p, F.g_c - 1) * F.n + i];
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < kOnceHeld; ++h) {
+            const int k = k0 + h * kFinSub;
+            const bool rows = k < F.nblk_rows, live = (rows ? k : k - F.nblk_rows) * kLanes + l < (rows ? F.n : F.m);
+            double r = 0.0;
+            if (rows && live) {
+                r = v[h][0];
+#pragma unroll
+                for (int p = 1; p < P; ++p) r += p < F.g_c ? v[h][p] : 0.0;
+            }
+            const double S = wave_reduce1<OpSum>(r), d = wave_reduce1<OpSum>(live ? x[h] * y[h] : 0.0);
+            if (l == 0 && k < nparts) {
+                lds_obj[k][0] = S;
+                lds_obj[k][1] = rows ? d : 0.0;
+                lds_obj[k][2] = rows ? 0.0 : d;
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ void objective_at_once(const FinalizeArgs &F)
+{
+    __shared__ double lds_obj[kOnceParts][3];
+    const int tid = threadIdx.x, l = tid & (kLanes - 1), w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nparts = F.nblk_rows + F.nblk_cols;
+    if (F.g_c <= 2) objective_parts<2>(F, w, l, lds_obj);
+    else if (F.g_c <= 4) objective_parts<4>(F, w, l, lds_obj);
+    else objective_parts<kOncePanels>(F, w, l, lds_obj);
+    __syncthreads();
+    if (w != 0) return;
+    double sum[3][kOnceParts / kLanes];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int h = 0; h < kOnceParts / kLanes; ++h) sum[c][h] = wave_reduce1<OpSum>(h * kLanes + l < nparts ? lds_obj[h * kLanes + l][c] : 0.0);
+    static_assert(kOnceParts == 2 * kLanes && kOnceParts <= kThreads, "write_objective's order");
+    if (l == 0) *F.obj = -F.eta * (sum[0][0] + sum[0][1]) + ((sum[1][0] + sum[1][1]) + (sum[2][0] + sum[2][1]));
+}
+
+// sums of 64 columns over the row chunks by a workgroup of kFinThreads: gradient and, in the first wave's lanes, the terms of beta . b
+__device__ __forceinline__ double finalize_columns(const FinalizeArgs &F, int block, double (*lds_part)[kLanes])
+{
+    const int l = threadIdx.x & (kLanes - 1), sub = threadIdx.x >> 6;
+    const int64_t j = (int64_t)block * kLanes + l;
+    const int per = (F.g_r + kFinSub - 1) / kFinSub;
+    const int g0 = min(F.g_r, sub * per), g1 = min(F.g_r, g0 + per);
+    lds_part[sub][l] = sum_partials(F.colpart, (size_t)F.m, j, g0, g1, j < F.m);
+    __syncthreads();
+    if (sub != 0 || j >= F.m) return 0.0;
+    double c = lds_part[0][l];
+#pragma unroll
+    for (int s = 1; s < kFinSub; ++s) c += lds_part[s][l];
+    const double bj = F.b[j];
+    if (F.col_sum) F.col_sum[j] = c;
+    F.grad_beta[j] = bj - c;
+    return F.beta[j] * bj;
+}
+
+// ONCE: workgroup 0 forms the objective (a kernel of its own: its registers would leave room for one workgroup of the others a compute
+// unit).
+template <bool REDUCE, bool SPARSIFY, bool ONCE = false>
 __global__ __launch_bounds__(kFinThreads) void finalize_kernel(FinalizeArgs F)
 {
+    if constexpr (ONCE)
+        if (blockIdx.x == 0) {
+            objective_at_once(F);
+            return;
+        }
+    const int block = (int)blockIdx.x - (ONCE ? 1 : 0);
     __shared__ double lds_part[kFinSub][kLanes];
     __shared__ int lds_cnt[kFinSub][kLanes];
     const int tid = threadIdx.x;
@@ -1057,8 +1153,8 @@ __global__ __launch_bounds__(kFinThreads) void finalize_kernel(FinalizeArgs F)
     if (blockIdx.x == gridDim.x - 1 && F.cu_table != nullptr)
         for (int i = tid; i < kCuKeys * (int)(sizeof(CuSlot) / sizeof(int)); i += kFinThreads) F.cu_table[i] = 0;
     double pS = 0.0, pA = 0.0, pB = 0.0;
-    if ((int)blockIdx.x < F.nblk_rows) {
-        const int64_t i = (int64_t)blockIdx.x * kFinRows + l;
+    if (block < F.nblk_rows) {
+        const int64_t i = (int64_t)block * kFinRows + l;
         const bool live = i < F.n;
         const int per = (F.g_c + kFinSub - 1) / kFinSub;
         const int p0 = min(F.g_c, sub * per), p1 = min(F.g_c, p0 + per);
@@ -1126,33 +1222,20 @@ __global__ __launch_bounds__(kFinThreads) void finalize_kernel(FinalizeArgs F)
                     if (l >= d) inc += up;
                 }
                 if (live) F.row_excl[i] = inc - v;
-                if (l == kLanes - 1) F.blk_nnz[blockIdx.x] = inc;
+                if (l == kLanes - 1) F.blk_nnz[block] = inc;
             }
         }
     } else if constexpr (REDUCE) {
-        const int64_t j = (int64_t)((int)blockIdx.x - F.nblk_rows) * kLanes + l;
-        const int per = (F.g_r + kFinSub - 1) / kFinSub;
-        const int g0 = min(F.g_r, sub * per), g1 = min(F.g_r, g0 + per);
-        lds_part[sub][l] = sum_partials(F.colpart, (size_t)F.m, j, g0, g1, j < F.m);
-        __syncthreads();
-        if (sub == 0 && j < F.m) {
-            double c = lds_part[0][l];
-#pragma unroll
-            for (int s = 1; s < kFinSub; ++s) c += lds_part[s][l];
-            const double bj = F.b[j];
-            if (F.col_sum) F.col_sum[j] = c;
-            F.grad_beta[j] = bj - c;
-            pB = F.beta[j] * bj;
-        }
+        pB = finalize_columns(F, block - F.nblk_rows, lds_part);
     }
     if constexpr (REDUCE) {
         // only the first wave holds terms of the objective
-        if (sub == 0) {
+        if (!ONCE && sub == 0) {
             const double bS = wave_reduce1<OpSum>(pS), bA = wave_reduce1<OpSum>(pA), bB = wave_reduce1<OpSum>(pB);
             if (l == 0) {
-                F.objpart[(size_t)blockIdx.x * 3 + 0] = bS;
-                F.objpart[(size_t)blockIdx.x * 3 + 1] = bA;
-                F.objpart[(size_t)blockIdx.x * 3 + 2] = bB;
+                F.objpart[(size_t)block * 3 + 0] = bS;
+                F.objpart[(size_t)block * 3 + 1] = bA;
+                F.objpart[(size_t)block * 3 + 2] = bB;
             }
         }
     }

@@ -1,0 +1,111 @@
+"""The last launch of a small matrix's plan pass (csrc/regot_finish_small.hpp, objective_at_once): at the edges of its rules and of its
+chunks, panels and workgroups, against the oracle; the rules' other side takes the launches of larger matrices."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+from paper_2605_08793_amd import binding as B
+from paper_2605_08793_amd import workloads as W
+from paper_2605_08793_amd.driver import DualPass
+from parity_utils import assert_csr_close, assert_dual_eval_close
+from test_gpu_parity import dev, full_check, gpu_eval_dict
+
+pytestmark = pytest.mark.gpu
+
+
+def problem(n, m, eta=0.3):
+    M, a, b, alpha, beta = W.random_small(n, m, seed=n + 7 * m, eta=eta)
+    return M, a, b, alpha, beta, eta
+
+
+SHAPES = [
+    (1, 1), (2, 512), (15, 513), (16, 511), (17, 1024), (63, 100), (64, 64), (65, 65),  # one chunk, one over; one column workgroup, one over
+    (129, 2049), (1000, 1000), (1031, 517), (333, 1030),                               # 517, 1030: the last panel is a strip's
+    (100, 4096), (100, 4097),                                                          # eight panels, nine
+    (3072, 4096), (3073, 4096), (6140, 2048), (6148, 2048),                            # 24576 counts, and above
+    (7680, 512), (7681, 512),                                                          # 128 workgroups for rows and columns, 129
+    (1365, 2731), (1366, 2731),                                                        # 16384 numbers for the objective of a plain evaluation, 16392
+]
+
+
+@pytest.mark.parametrize("n,m", SHAPES)
+def test_edges(n, m):
+    M, a, b, alpha, beta, eta = problem(n, m)
+    T = oracle.plan_dense(M, alpha, beta, eta)
+    full_check(dev(M), M, a, b, alpha, beta, eta, float(np.quantile(T, 0.97)), label="finish small")
+
+
+@pytest.mark.parametrize("n,m,rows,cols", [
+    (64, 2000, 3, 2000),       # full rows in one wave: its buffer is full twice over, runs beyond the fixed ones
+    (300, 1029, 9, 1029),      # the same with a strip, over several chunks
+    (640, 40, 640, 40),        # all entries of a narrow matrix
+    (17, 3000, 1, 3000),       # the last chunk's odd row
+])
+def test_runs_of_full_buffers(n, m, rows, cols):
+    M, a, b, alpha, beta, eta = problem(n, m)
+    M = M + 50.0
+    at = np.linspace(0, n - 1, rows).astype(int) if rows > 3 else np.arange(n - rows, n) if rows == 1 else np.arange(rows)
+    M[at, :cols] -= 50.0
+    T = oracle.plan_dense(M, alpha, beta, eta)
+    delta = float(T[at, :cols].min())
+    full_check(dev(M), M, a, b, alpha, beta, eta, delta, label="full buffers")
+
+
+@pytest.mark.parametrize("n,m", [(200, 700), (1000, 600)])
+def test_capacity(n, m):
+    """At, one below and far above the number of entries, on either side of what a chunk's workgroup is given to place: the same CSR,
+    or the overflow flag, the true number of entries and row_ptr, and nothing in the entries."""
+    M, a, b, alpha, beta, eta = problem(n, m)
+    T = oracle.plan_dense(M, alpha, beta, eta)
+    delta = float(np.quantile(T, 0.95))
+    ref = oracle.sparsify_csr(M, alpha, beta, eta, delta)
+    nnz = int(ref[0][-1])
+    g_r = B.regot_plan_geometry(n, m, nnz)[0]
+    for cap in (nnz, nnz - 1, 0, 6144 * g_r, 6144 * g_r + 1, n * m):
+        dp = DualPass(n, m, cap)
+        dp.workspace.fill_(0x5B); dp.val.fill_(-3.0); dp.col_idx.fill_(-3)
+        dp.dual_eval_sparsify(dev(M), dev(a), dev(b), dev(alpha), dev(beta), eta, delta)
+        got = gpu_eval_dict(dp)
+        assert_dual_eval_close(got, oracle.dual_eval(M, a, b, alpha, beta, eta), a, b, alpha, beta, eta)
+        info = dp.info.cpu().numpy()
+        assert info[0] == nnz and info[1] == (1 if cap < nnz else 0)
+        np.testing.assert_array_equal(dp.row_ptr.cpu().numpy(), ref[0])
+        if cap < nnz:
+            assert (dp.val == -3.0).all() and (dp.col_idx == -3).all()
+        else:
+            assert_csr_close((dp.row_ptr.cpu().numpy(), dp.col_idx.cpu().numpy()[:nnz], dp.val.cpu().numpy()[:nnz]), ref, delta, m)
+            assert (dp.val[nnz:] == -3.0).all() and (dp.col_idx[nnz:] == -3).all()
+
+
+def test_no_entries_and_infinite_costs():
+    n, m = 130, 600
+    M, a, b, alpha, beta, eta = problem(n, m)
+    M[5, 1:] = np.inf; M[1:, 599] = np.inf  # (a row and a column of one finite cost)
+    full_check(dev(M), M, a, b, alpha, beta, eta, 1e300, label="no entries")
+    T = oracle.plan_dense(M, alpha, beta, eta)
+    full_check(dev(M), M, a, b, alpha, beta, eta, float(np.quantile(T, 0.9)), label="infinite costs")
+
+
+def test_replayed_graph():
+    n, m = 500, 900
+    M, a, b, alpha, beta, eta = problem(n, m)
+    T = oracle.plan_dense(M, alpha, beta, eta)
+    delta = float(np.quantile(T, 0.95))
+    dp = DualPass(n, m, n * m // 10)
+    d = [dev(x) for x in (M, a, b, alpha, beta)]
+    dp.dual_eval_sparsify(*d, eta, delta)
+    torch.cuda.synchronize()
+    names = ("obj", "grad_alpha", "grad_beta", "row_sum", "col_sum", "row_ptr", "col_idx", "val", "info")
+    eager = [getattr(dp, x).clone() for x in names]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        dp.dual_eval_sparsify(*d, eta, delta)
+    for _ in range(4):
+        for x in names:
+            getattr(dp, x).zero_()
+        dp.workspace.fill_(0xA5)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(getattr(dp, x), e) for x, e in zip(names, eager))
