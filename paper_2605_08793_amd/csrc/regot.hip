@@ -113,6 +113,26 @@ int plan_rounds(int64_t staged)
     return (int)(want < 1 ? 1 : want > kMaxRounds ? kMaxRounds : want);
 }
 
+// The same for a fused or sparsify call on an n x m matrix: two rounds also where the tasks of one leave at least kIdlePercent of the
+// places empty and those of two fill them better, since a place left empty is idle for the whole call; if chunks are tall, since
+// two rounds have twice as many beginnings and ends.  Fused pass, 0.2 % of the entries, us, one round / two: 1000 x 131500
+// 333 / 254, 70000 x 24000 2616 / 2433, 30000 x 30000 1301 / 1248, 10000 x 24000 (chunks of 1000 rows) 382 / 377; 5000 x 30000 (628 rows) 238 / 239, 2000 x 30000 109 / 115.
+constexpr int kIdlePercent = 7, kFillGain = 4, kTallChunk = 1000;
+
+int plan_rounds(int64_t n, int64_t m, int64_t staged)
+{
+    const int rounds = plan_rounds(staged);
+    if (rounds != 1 || kMaxRounds < 2) return rounds;
+    if (n < kTallChunk * (int64_t)make_geometry(n, m, REGOT_PLAN_WAVES_PER_EU, true).g_r) return rounds;
+    const auto percent = [&](int of) {  // of the places that are taken
+        const Geometry G = make_geometry(n, m, REGOT_PLAN_WAVES_PER_EU * of, true);
+        const int64_t blocks = (int64_t)G.g_r * (G.strip_blocks > 0 ? G.g_c - 1 : G.g_c) + G.strip_blocks;
+        return 100.0 * (double)blocks / (double)((int64_t)kNumCU * REGOT_PLAN_WAVES_PER_EU * of);
+    };
+    const double one = percent(1);
+    return one <= 100 - kIdlePercent && percent(2) >= one + kFillGain ? 2 : 1;
+}
+
 struct Layout {
     size_t header, progress, cu_table, rowpart, colpart, objpart, metric_part;
     size_t seg_count, row_excl, blk_nnz, ranges, pool_val, pool_packed;
@@ -308,7 +328,7 @@ int run_plan_pass(int64_t n, int64_t m, const double *M, int64_t ldM, const doub
     // round can keep on chip (kRecCap each): then as many rounds of lower chunks as it takes (at most
     // kMaxRounds), which keeps most waves from writing their records to HBM in the middle of the pass.
     const int64_t staged = rc ? rc->cand_capacity : capacity;  // records the pass is expected to stage
-    int rounds = SPARSIFY ? plan_rounds(staged) : 1;
+    int rounds = !SPARSIFY ? 1 : rc ? plan_rounds(staged) : plan_rounds(n, m, staged);
     // (The pool of a pattern refresh is laid out with a margin of a quarter.  Where that margin alone asks for a second
     // round while the candidates the sample lets one expect exceed what the waves of one round hold by less than a
     // fifth, one round it is: the few waves that fill up write once in mid-stream, which costs less than giving up the
@@ -1078,7 +1098,7 @@ int regot_plan_geometry(int64_t n, int64_t m, int64_t csr_capacity, int64_t *geo
     if (!geometry) return REGOT_ERR_NULL;
     if (n < 0 || m < 0 || n > kMaxDim || m > kMaxDim) return REGOT_ERR_DIM;
     if (csr_capacity < -1) return REGOT_ERR_ARG;
-    const int rounds = csr_capacity >= 0 ? plan_rounds(csr_capacity) : 1;
+    const int rounds = csr_capacity >= 0 ? plan_rounds(n, m, csr_capacity) : 1;
     const Geometry G = make_geometry(n, m, REGOT_PLAN_WAVES_PER_EU * rounds, true);
     int64_t tallest = 0;
     for (int g = 0; g < G.g_r; ++g) {
