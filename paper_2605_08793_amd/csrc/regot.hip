@@ -327,6 +327,7 @@ int run_plan_pass(int64_t n, int64_t m, const double *M, int64_t ldM, const doub
     // One round of resident workgroups, unless the caller expects more entries than the waves of one
     // round can keep on chip (kRecCap each): then as many rounds of lower chunks as it takes (at most
     // kMaxRounds), which keeps most waves from writing their records to HBM in the middle of the pass.
+    // (Or where one round leaves too many places empty: plan_rounds.  A refresh goes by its candidates alone.)
     const int64_t staged = rc ? rc->cand_capacity : capacity;  // records the pass is expected to stage
     int rounds = !SPARSIFY ? 1 : rc ? plan_rounds(staged) : plan_rounds(n, m, staged);
     // (The pool of a pattern refresh is laid out with a margin of a quarter.  Where that margin alone asks for a second
