@@ -702,7 +702,7 @@ __global__ __launch_bounds__(kSweepFinWaves *kLanes) REGOT_WAVES_ATTR(8) void sw
         if (live && ok && split == 0) A.beta[j] = bn;
         const unsigned long long bad = __ballot(!ok);
         if (l == 0) lds_bad = bad;
-        // (a column without mass must have been -inf, so that no T of it is in the rows' sums)
+        // (a column without mass must have been -inf, so that no T of it is in the rows' sums; what becomes of it is seen below)
         const bool near = bj > 0.0 ? ok && bj <= kNearMostMass && bj >= kNearLeastRatio * c && __builtin_fabs(bn) <= kNearMostDual * A.eta
                                    : bj == 0.0 && bo == -INFINITY;
         if (NEAR && split == 0 && __ballot(live && !near) != 0 && l == 0) A.far[A.turn ^ 1] = 1;
@@ -797,7 +797,10 @@ __global__ __launch_bounds__(kSweepFinWaves *kLanes) REGOT_WAVES_ATTR(8) void sw
             for (int q = 0; q < kSweepMerge; ++q) sum += ps[q] * exp_eta_any(pm[q] - mx, C.ex);
         }
     }
-    if (redo) A.beta[j] = A.eta * log(bj) - (mx + A.eta * log(sum));
+    const double bn = A.eta * log(bj) - (mx + A.eta * log(sum));
+    if (redo) A.beta[j] = bn;
+    // (one that is not -inf again -- no mass and no finite cost: NaN -- is for the maxima to pass on)
+    if (NEAR && __ballot(redo && bn != -INFINITY) != 0 && l == 0) C.far[C.turn ^ 1] = 1;
 }
 
 }  // namespace regot

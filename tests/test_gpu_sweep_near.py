@@ -28,7 +28,7 @@ def check(M, a, b, eta, sweeps, beta0, label):
             B.regot_sweep_patience(looks)
         B.regot_sinkhorn_sweeps(Md, ad, bd, al, be, eta, sweeps, workspace=dp.workspace)
         out.append((al.cpu().numpy(), be.cpu().numpy()))
-    assert all(np.array_equal(x, y) for x, y in zip(*out))
+    assert all(np.array_equal(x, y, equal_nan=True) for x, y in zip(*out))
     for got, ref, what in zip(out[0], oracle.sinkhorn_sweeps(M, a, b, eta, sweeps, np.zeros(n), beta0), ("alpha", "beta")):
         some = np.isfinite(ref)
         np.testing.assert_array_equal(got[~some], ref[~some], err_msg=what)
@@ -83,3 +83,16 @@ def test_duals_that_eta_is_small_against():
             B.regot_sinkhorn_sweeps(Md, ad, ad, al, be, eta, sweeps, workspace=dp.workspace)
             ra, rb = oracle.sinkhorn_sweeps(M, a, a, eta, sweeps, np.zeros(n), beta0)
             assert np.abs(al.cpu().numpy() - ra).max() <= 2e-15 and np.abs(be.cpu().numpy() - rb).max() <= 2e-15, eta
+
+
+@pytest.mark.parametrize("n,m,sweeps", [(3001, 700, 2), (3001, 700, 3), (600, 20000, 2), (4097, 2500, 4)])   # rows of a column shared by three workgroups, by one, by five
+def test_no_mass_and_no_cost(n, m, sweeps):
+    """A column of mass 0 whose costs are all infinite comes out as NaN (-inf + inf) and takes every alpha of the next sweep with it, those
+    of the rows without mass too, whose alpha is -inf otherwise."""
+    eta = 0.05
+    M, a, b, _, beta = W.random_small(n, m, seed=n + m, eta=eta)
+    M[:, m // 2] = np.inf
+    a[::17] = 0.0
+    b[m // 2] = 0.0
+    beta[m // 2] = -np.inf
+    check(M, a / a.sum(), b / b.sum(), eta, sweeps, beta, "no mass, no cost")
