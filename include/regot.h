@@ -344,8 +344,10 @@ int regot_pattern_values(int64_t n, int64_t m,
  * whose col_idx is outside [0, m): it belongs to no column).
  * nnz is a HOST value and must equal row_ptr[n] (the caller has read info[0] of the sparsify call);
  * nnz <= 2^31 - 1.  Workspace: regot_pattern_transpose_workspace_bytes(n, m, nnz), 256-byte aligned
- * (20.5 bytes per entry + a few KB, or 1 byte per entry + 3 n m / 32, whichever is more, where
- * n < 65536, m <= 40000 and the pattern is not too sparse).  Those patterns are transposed by counting (a row
+ * (to be asked for: it depends on all three, and for a given matrix does not fall as nnz grows.  At most 4 KB more than
+ * 20.5 nnz bytes or, where n < 65536 and m <= 40000, if that is more, than nnz + (3 p + 24) b + 5 p bytes with
+ * p = m rounded up to a multiple of 128 and b = n / 32 + max(nnz / 16384, min(nnz / 2048, 128)) + 2, quotients rounded
+ * down: 47.6 MB for 2e6 entries of 20000 x 20000).  Patterns of such matrices that are not too sparse are transposed by counting (a row
  * must hold a column at most once, as above); of the others the CSR positions, which start out in
  * ascending order, are sorted stably by column (a radix sort of this library, 8 bits per pass: two passes
  * for m < 65536); inside a column ascending position is ascending row.  No atomics on memory: the same

@@ -376,6 +376,7 @@ struct BlockRows {  // of a block: its first entry, how many, its first row, how
 struct CountLayout {
     size_t count, base, rank, col_off, group_total, rows, die_start;
     int64_t blocks, pitch, entries;
+    int64_t room;  // blocks that the tables have room for
     size_t total;
 };
 
@@ -403,13 +404,16 @@ CountLayout make_count_layout(int64_t n, int64_t m, int64_t nnz)
     };
     L.entries = std::clamp<int64_t>(nnz / 128, kBlockLeastEntries, kBlockMostEntries);
     L.blocks = (n * L.entries + nnz * kBlockRows) / (kBlockRows * L.entries) + 1;
+    // (blocks = floor(n / 32 + nnz / E) + 1 may fall as nnz grows, by one where E = nnz / 128 is rounded down to less; a caller's workspace for
+    // more entries has to do for fewer, so the tables' size goes by a bound of it that does not)
+    L.room = n / kBlockRows + std::max(nnz / kBlockMostEntries, std::min<int64_t>(nnz / kBlockLeastEntries, 128)) + 2;
     L.pitch = (m + kGroupCols - 1) / kGroupCols * kGroupCols;
-    L.count = take((size_t)(L.blocks * L.pitch));
-    L.base = take((size_t)(L.blocks * L.pitch) * sizeof(uint16_t));
+    L.count = take((size_t)(L.room * L.pitch));
+    L.base = take((size_t)(L.room * L.pitch) * sizeof(uint16_t));
     L.rank = take((size_t)nnz);
     L.col_off = take((size_t)L.pitch * sizeof(uint32_t));
     L.group_total = take((size_t)(L.pitch / kGroupCols) * sizeof(uint32_t));
-    L.rows = take((size_t)L.blocks * sizeof(BlockRows));
+    L.rows = take((size_t)L.room * sizeof(BlockRows));
     L.die_start = take((kDies + 1) * sizeof(int32_t));
     L.total = off;
     return L;
