@@ -347,11 +347,12 @@ int regot_pattern_values(int64_t n, int64_t m,
  * (to be asked for: it depends on all three, and for a given matrix does not fall as nnz grows.  At most 4 KB more than
  * 20.5 nnz bytes or, where n < 65536 and m <= 40000, if that is more, than nnz + (3 p + 24) b + 5 p bytes with
  * p = m rounded up to a multiple of 128 and b = n / 32 + max(nnz / 16384, min(nnz / 2048, 128)) + 2, quotients rounded
- * down: 47.6 MB for 2e6 entries of 20000 x 20000).  Patterns of such matrices that are not too sparse are transposed by counting (a row
- * must hold a column at most once, as above); of the others the CSR positions, which start out in
- * ascending order, are sorted stably by column (a radix sort of this library, 8 bits per pass: two passes
- * for m < 65536); inside a column ascending position is ascending row.  No atomics on memory: the same
- * bits on every call.
+ * down: 47.6 MB for 2e6 entries of 20000 x 20000).  Patterns of such matrices that are not too sparse are
+ * transposed by counting; of the others the CSR positions, which start out in ascending order, are sorted stably
+ * by column (a radix sort of this library, 8 bits per pass: two passes for m < 65536); inside a column ascending
+ * position is ascending row.  A structure whose rows hold a column more than once, which a pattern does not, has every
+ * entry listed in order all the same (where counting is the way, at many times the cost).  No atomics on memory: the
+ * same bits on every call.
  */
 int regot_pattern_transpose_workspace_bytes(int64_t n, int64_t m, int64_t nnz, size_t *bytes /* host, out */);
 int regot_pattern_transpose(int64_t n, int64_t m, int64_t nnz /* host */,

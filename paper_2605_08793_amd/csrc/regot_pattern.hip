@@ -355,7 +355,9 @@ __global__ __launch_bounds__(kBlock) void col_ptr_kernel(TransposeArgs A, const 
 // What bounds it: 6 bytes of table traffic per column and block (0.2 an entry of the matrix) and 37 bytes an entry of the pattern, which
 // at 20000 x 20000 and 2e6 entries are 149 MB, 22 us at a copy's rate; count, scan and place take 14 + 11 + 24 in a trace, where the last
 // waits for its scattered stores.
-// A row holds a column at most once, as the pattern's definition has it; a second one would take the first one's place.
+// A row holds a column at most once, as the pattern's definition has it.  The masks can't hold a second one, so where any block finds
+// one (the bit is set already) column_scan_kernel lists every column entry by entry instead, with the result that the sort has:
+// correct, but 128 columns for the time of a look at all entries.
 // ---------------------------------------------------------------------------
 constexpr int kCountThreads = 1024;
 constexpr int kBlockRows = 32, kBlockLeastEntries = 2048, kBlockMostEntries = 16384;
@@ -369,12 +371,11 @@ constexpr int padded(int cols) { return (cols + kGroupCols - 1) / kGroupCols * k
 constexpr int kMaxGroups = (kCountMaxCols + kGroupCols - 1) / kGroupCols, kGroupsPerLane = (kMaxGroups + kLanes - 1) / kLanes;
 
 struct BlockRows {  // of a block: its first entry, how many, its first row, how many
-    int64_t first;
-    int32_t count, row, rows;
+    int32_t first, count, row, rows;
 };
 
 struct CountLayout {
-    size_t count, base, rank, col_off, group_total, rows, die_start;
+    size_t count, base, rank, col_off, group_total, rows, repeats, die_start;
     int64_t blocks, pitch, entries;
     int64_t room;  // blocks that the tables have room for
     size_t total;
@@ -414,7 +415,8 @@ CountLayout make_count_layout(int64_t n, int64_t m, int64_t nnz)
     L.col_off = take((size_t)L.pitch * sizeof(uint32_t));
     L.group_total = take((size_t)(L.pitch / kGroupCols) * sizeof(uint32_t));
     L.rows = take((size_t)L.room * sizeof(BlockRows));
-    L.die_start = take((kDies + 1) * sizeof(int32_t));
+    L.repeats = take((size_t)L.room);
+    L.die_start = take((kDies + 2) * sizeof(int32_t));
     L.total = off;
     return L;
 }
@@ -433,7 +435,8 @@ struct CountArgs {
     uint32_t *col_off;      // [pitch] entries of the columns before in the group of 128
     uint32_t *group_total;  // [pitch / 128]
     BlockRows *rows;        // [blocks]
-    int32_t *die_start;     // [kDies + 1] first blocks of the dies in column_place_kernel
+    uint8_t *repeats;       // [blocks] a row of it holds a column twice
+    int32_t *die_start;     // [kDies + 1] first blocks of the dies in column_place_kernel; behind them: a block has repeats
 };
 
 __device__ __forceinline__ int64_t entries_before(const CountArgs &A, int64_t r)
@@ -480,6 +483,7 @@ __global__ __launch_bounds__(kCountThreads) void column_count_kernel(CountArgs A
     __shared__ __attribute__((aligned(16))) uint32_t mask[padded(COLS)];
     __shared__ int ends[kBlockRows];
     __shared__ int cut[2];
+    __shared__ int repeats;
     const int tid = (int)threadIdx.x, block = (int)blockIdx.x;
     if (tid < 2 * kLanes) {
         const int k = tid / kLanes, first = block_first_row(A, block + k, tid % kLanes);
@@ -488,9 +492,12 @@ __global__ __launch_bounds__(kCountThreads) void column_count_kernel(CountArgs A
     __syncthreads();
     const int rows = max(0, min(kBlockRows, cut[1] - cut[0]));  // (never more, unless row_ptr does not ascend)
     const int64_t first = entries_before(A, cut[0]), after = entries_before(A, cut[0] + rows);
-    const BlockRows B{first, (int32_t)(after > first ? after - first : 0), cut[0], rows};
+    const BlockRows B{(int32_t)first, (int32_t)(after > first ? after - first : 0), cut[0], rows};
     const BlockEntries E(A, B, ends);
-    if (tid == 0) A.rows[block] = B;
+    if (tid == 0) {
+        A.rows[block] = B;
+        repeats = 0;
+    }
     if (tid <= kDies) {  // the dies that begin behind this block: the next one is the first whose entries begin in their shares
         const auto die_of = [&](int64_t p) { return min((int)(p * kDies / A.nnz), kDies - 1); };
         const int here = block == 0 ? -1 : die_of(first), next = block + 1 == A.blocks ? kDies : die_of(after);
@@ -521,11 +528,12 @@ __global__ __launch_bounds__(kCountThreads) void column_count_kernel(CountArgs A
         find_rows(q0);
 #pragma unroll
         for (int k = 0; k < kCountHeld; ++k)
-            if (j[k] >= 0) atomicOr(&mask[j[k]], 1u << r[k]);
+            if (j[k] >= 0 && (atomicOr(&mask[j[k]], 1u << r[k]) >> r[k] & 1u) != 0) repeats = 1;
         if (q0 >= last) break;
         fetch(q0 + kTrip);
     }
     __syncthreads();
+    if (tid == 0) A.repeats[block] = (uint8_t)repeats;
     for (int q0 = last;; q0 -= kTrip) {  // (what was fetched last first)
 #pragma unroll
         for (int k = 0; k < kCountHeld; ++k) {
@@ -544,15 +552,86 @@ __global__ __launch_bounds__(kCountThreads) void column_count_kernel(CountArgs A
     }
 }
 
+// The columns of a group in the order of their entries, whatever the rows hold: for patterns with repeats.  Every wave takes a share of the
+// blocks; its entries of a column go behind those of the shares before.
+__device__ __forceinline__ void list_columns(const CountArgs &A, int c0)
+{
+    constexpr int kShares = kCountThreads / kLanes;
+    __shared__ int32_t next[kShares][kGroupCols];
+    __shared__ int32_t before;  // entries of the columns before the group
+    const int tid = (int)threadIdx.x, lane = tid % kLanes, share = tid / kLanes;
+    const int b0 = (int)((int64_t)A.blocks * share / kShares), b1 = (int)((int64_t)A.blocks * (share + 1) / kShares);
+    for (int k = tid; k < kShares * kGroupCols; k += kCountThreads) next[k / kGroupCols][k % kGroupCols] = 0;
+    if (tid == 0) before = 0;
+    __syncthreads();
+    int32_t less = 0;
+    for (int b = b0; b < b1; ++b) {
+        const BlockRows B = A.rows[b];
+        for (int q = lane; q < B.count; q += kLanes) {
+            const int32_t j = A.col_idx[(int64_t)B.first + q];
+            less += (uint32_t)j < (uint32_t)c0 ? 1 : 0;
+            if ((uint32_t)j < (uint32_t)A.m && j >= c0 && j < c0 + kGroupCols) atomicAdd(&next[share][j - c0], 1);
+        }
+    }
+    if (less != 0) atomicAdd(&before, less);
+    __syncthreads();
+    if (share == 0) {  // two columns a lane: where the shares' entries of each begin
+        int32_t sum[2] = {0, 0};
+        for (int k = 0; k < kShares; ++k)
+            for (int h = 0; h < 2; ++h) sum[h] += next[k][2 * lane + h];
+        const int32_t up_to = before + wave_scan(sum[0] + sum[1]);
+        int32_t run[2] = {up_to - sum[1] - sum[0], up_to - sum[1]};
+        for (int h = 0; h < 2; ++h) {
+            const int c = c0 + 2 * lane + h;
+            if (c < A.m) A.col_ptr[c] = run[h];
+            if (c == A.m - 1) A.col_ptr[A.m] = (int64_t)run[h] + sum[h];
+        }
+        for (int k = 0; k < kShares; ++k)
+            for (int h = 0; h < 2; ++h) {
+                const int32_t count = next[k][2 * lane + h];
+                next[k][2 * lane + h] = run[h];
+                run[h] += count;
+            }
+    }
+    __syncthreads();
+    for (int b = b0; b < b1; ++b) {
+        const BlockRows B = A.rows[b];
+        const int end = lane < B.rows ? (int)(entries_before(A, B.row + lane + 1) - B.first) : INT32_MAX;
+        for (int q0 = 0; q0 < B.count; q0 += kLanes) {
+            const int q = q0 + lane;
+            const int32_t j = q < B.count ? A.col_idx[(int64_t)B.first + q] : -1;
+            const bool real = (uint32_t)j < (uint32_t)A.m, mine = real && j >= c0 && j < c0 + kGroupCols;
+            if (q < B.count && !real && c0 == 0) A.csc_pos[(int64_t)B.first + q] = -1;
+            for (uint64_t open = __ballot(mine); open != 0;) {  // a column at a time, lanes in order
+                const int32_t column = __builtin_amdgcn_readlane(j, __builtin_ctzll(open));
+                const uint64_t same = __ballot(mine && j == column);
+                const int32_t first = next[share][column - c0];
+                if ((same >> lane & 1) != 0) {
+                    const int32_t to = first + __builtin_popcountll(same & ((1ull << lane) - 1));
+                    int row = 0;  // how many of the block's rows end at or before q
+                    for (int k = 0; k < kBlockRows; ++k) row += __builtin_amdgcn_readlane(end, k) <= q ? 1 : 0;
+                    if (to < A.nnz) A.row_idx[to] = B.row + row;
+                    A.csc_pos[(int64_t)B.first + q] = to;
+                }
+                next[share][column - c0] = first + __builtin_popcountll(same);  // (the same from all lanes)
+                open &= ~same;
+            }
+        }
+    }
+}
+
 // Eight columns to a thread, two to a word: a column has at most kCountMostRows entries.  The blocks are shared out among groups of
 // 16 threads.
 __global__ __launch_bounds__(kCountThreads) void column_scan_kernel(CountArgs A)
 {
     __shared__ __attribute__((aligned(16))) uint16_t part[kScanParts][kGroupCols];
+    __shared__ int wave_repeats[kCountThreads / kLanes];
     const int tid = (int)threadIdx.x, share = tid / (kGroupCols / kScanCols), at = kScanCols * (tid % (kGroupCols / kScanCols));
     const int c = (int)blockIdx.x * kGroupCols + at;
     const int per = (A.blocks + kScanParts - 1) / kScanParts, g0 = min(A.blocks, share * per), g1 = min(A.blocks, g0 + per);
     const uint8_t *count = A.count + c;
+    int repeats = 0;
+    for (int b = tid; b < A.blocks; b += kCountThreads) repeats |= A.repeats[b];
     uint4 s{0, 0, 0, 0};
     const auto add = [&](uint2 eight) {
         s.x += __builtin_amdgcn_perm(0u, eight.x, 0x0c010c00u);
@@ -574,7 +653,17 @@ __global__ __launch_bounds__(kCountThreads) void column_scan_kernel(CountArgs A)
 #pragma unroll
     for (int k = 0; k < kScanHeld; ++k) add(eight[k]);
     *reinterpret_cast<uint4 *>(&part[share][at]) = s;
+    const uint64_t in_wave = __ballot(repeats != 0);
+    if (tid % kLanes == 0) wave_repeats[tid / kLanes] = in_wave != 0 ? 1 : 0;
     __syncthreads();
+    repeats = 0;
+#pragma unroll
+    for (int k = 0; k < kCountThreads / kLanes; ++k) repeats |= wave_repeats[k];
+    if (blockIdx.x == 0 && tid == 0) A.die_start[kDies + 1] = repeats;
+    if (repeats != 0) {
+        list_columns(A, (int)blockIdx.x * kGroupCols);
+        return;
+    }
     if (tid < kLanes) {  // two columns a lane: what is before each share, and their sums
         uint32_t run = 0;
 #pragma unroll 16
@@ -609,6 +698,7 @@ __global__ __launch_bounds__(kCountThreads) void column_place_kernel(CountArgs A
     __shared__ __attribute__((aligned(16))) uint32_t at[padded(COLS)];  // where the block's first entry of a column goes
     __shared__ uint32_t group_at[kGroupsPerLane * kLanes + 1];
     __shared__ int ends[kBlockRows];
+    if (A.die_start[kDies + 1] != 0) return;  // (all is done)
     const int die = (int)blockIdx.x % kDies;
     int block = max(A.die_start[die], 0) + (int)blockIdx.x / kDies;
     const int end = min(A.die_start[die + 1], A.blocks);
@@ -732,7 +822,8 @@ int regot_pattern_transpose(int64_t n, int64_t m, int64_t nnz, const int64_t *ro
         const CountArgs C{(int)n, (int)m, (int)K.blocks, (int)K.pitch, (int)K.entries, nnz, row_ptr, col_idx, col_ptr, row_idx, csc_pos,
                           reinterpret_cast<uint8_t *>(ws + K.count), reinterpret_cast<uint16_t *>(ws + K.base),
                           reinterpret_cast<uint8_t *>(ws + K.rank), reinterpret_cast<uint32_t *>(ws + K.col_off),
-                          reinterpret_cast<uint32_t *>(ws + K.group_total), reinterpret_cast<BlockRows *>(ws + K.rows), reinterpret_cast<int32_t *>(ws + K.die_start)};
+                          reinterpret_cast<uint32_t *>(ws + K.group_total), reinterpret_cast<BlockRows *>(ws + K.rows),
+                          reinterpret_cast<uint8_t *>(ws + K.repeats), reinterpret_cast<int32_t *>(ws + K.die_start)};
         const bool narrow = m <= kCountMaxCols / 2;  // (two workgroups to a compute unit)
         const dim3 threads(kCountThreads);
         hipLaunchKernelGGL(narrow ? column_count_kernel<kCountMaxCols / 2> : column_count_kernel<kCountMaxCols>, dim3((unsigned)K.blocks), threads, 0, s, C);
