@@ -465,9 +465,12 @@ int run_plan_pass(int64_t n, int64_t m, const double *M, int64_t ldM, const doub
     const bool small = !rc && nblocks > 0 && G.g_c <= kOncePanels && G.nblk_rows + G.nblk_cols <= kOnceParts;
     const bool once = REDUCE && !SPARSIFY && small && n * G.g_c + 2 * (n + m) <= kOnceDoubles;
     bool whole = false;
+    int64_t parts = 1;  // workgroups for the records of a chunk, which may all be in one: as many as the chip takes at once
     if (SPARSIFY && small) {
         const int64_t tallest = (n + G.g_r - 1) / G.g_r + kRB - 1;  // (chunk boundaries are rounded down to multiples of kRB)
-        whole = capacity <= kOnceEntries * G.g_r && n * G.g_c <= kOnceCounts && tallest * G.g_c <= kOnceChunk;
+        const int64_t most = std::min<int64_t>(capacity, tallest * m), wave_turn = kFinSub * kOncePortion;
+        parts = std::max<int64_t>(1, std::min((most + kOnceEasy * wave_turn - 1) / (kOnceEasy * wave_turn), (2 * kNumCU - 1 - G.nblk_cols) / (int64_t)G.g_r));
+        whole = capacity <= kOnceEntries * G.g_r && n * G.g_c <= kOnceCounts && tallest * G.g_c <= kOnceChunk && most <= kOnceMost * wave_turn * parts;
     }
     if constexpr (REDUCE && !SPARSIFY)
         if (once) hipLaunchKernelGGL((finalize_kernel<true, false, true>), dim3(fin_blocks + 1), dim3(kFinThreads), 0, s, F);
@@ -501,7 +504,7 @@ int run_plan_pass(int64_t n, int64_t m, const double *M, int64_t ldM, const doub
         // Workgroups that place records (a multiple of kXcds, at most 4096): one per run with a fixed
         // id, plus room for a quarter as many runs of earlier flushes (the kernel loops if there are more).
         if (whole) {
-            hipLaunchKernelGGL((finish_small_kernel<REDUCE>), dim3((REDUCE ? 1 + G.nblk_cols : 0) + G.g_r), dim3(kFinThreads), 0, s, S, F);
+            hipLaunchKernelGGL((finish_small_kernel<REDUCE>), dim3((REDUCE ? 1 + G.nblk_cols : 0) + G.g_r, (unsigned)parts), dim3(kFinThreads), 0, s, S, F, (int)parts);
             return hip_status();
         }
         const int64_t fixed_items = scatter_fixed_items(G.g_r, G.g_c);

@@ -42,6 +42,9 @@ def test_edges(n, m):
     (300, 1029, 9, 1029),      # the same with a strip, over several chunks
     (640, 40, 640, 40),        # all entries of a narrow matrix
     (17, 3000, 1, 3000),       # the last chunk's odd row
+    (3072, 4096, 90, 4096),    # two chunks hold all entries: six workgroups for each, most of their runs on the list
+    (300, 2000, 50, 2000),     # four chunks
+    (7680, 512, 7680, 360),    # 1920 runs on the list, of all chunks
 ])
 def test_runs_of_full_buffers(n, m, rows, cols):
     M, a, b, alpha, beta, eta = problem(n, m)
@@ -51,6 +54,33 @@ def test_runs_of_full_buffers(n, m, rows, cols):
     T = oracle.plan_dense(M, alpha, beta, eta)
     delta = float(T[at, :cols].min())
     full_check(dev(M), M, a, b, alpha, beta, eta, delta, label="full buffers")
+
+
+def test_time_does_not_hang_on_where_the_entries_are():
+    """All entries in a few rows: their chunk's records are several workgroups' to place.  (By one workgroup, and in it mostly one wave, the
+    call took 123 us, where with the same number of entries all over the matrix it takes 36; the launches of larger matrices differ by a tenth.)"""
+    n = m = 3000
+    cap, eta, rows = 90000, 0.5, 28
+    M = torch.rand(n, m, dtype=torch.float64, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    a = torch.full((n,), 1.0 / n, dtype=torch.float64, device="cuda")
+    zero = torch.zeros(n, dtype=torch.float64, device="cuda")
+    time = []
+    for near in (0, rows):
+        M[n // 2:n // 2 + near] -= 2.0
+        delta = float(torch.exp(-torch.kthvalue(M.flatten(), rows * m).values / eta)) * (1 - 1e-12)
+        dp = DualPass(n, m, cap)
+        best = float("inf")
+        for k in range(30):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(10):
+                dp.dual_eval_sparsify(M, a, a, zero, zero, eta, delta)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, begin.elapsed_time(end))
+        assert dp.info.cpu().tolist() == [rows * m, 0]
+        time.append(best)
+    assert time[1] < 2.0 * time[0], time
 
 
 @pytest.mark.parametrize("n,m", [(200, 700), (1000, 600)])
