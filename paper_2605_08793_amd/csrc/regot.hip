@@ -117,6 +117,9 @@ int plan_rounds(int64_t staged)
 // places empty and those of two fill them better, since a place left empty is idle for the whole call; if chunks are tall, since
 // two rounds have twice as many beginnings and ends.  Fused pass, 0.2 % of the entries, us, one round / two: 1000 x 131500
 // 333 / 254, 70000 x 24000 2616 / 2433, 30000 x 30000 1301 / 1248, 10000 x 24000 (chunks of 1000 rows) 382 / 377; 5000 x 30000 (628 rows) 238 / 239, 2000 x 30000 109 / 115.
+// The plain evaluation keeps one round: it has no records to write at the ends of chunks, and the rule does not tell its sizes apart, 30000 x 30000
+// 1095 / 1125, 26000 x 45000 1556 / 1542, 70000 x 24000 2243 / 2230, 1000 x 131500 280 / 224, 10000 x 24000 340 / 340.  The refresh has kept
+// one too, though it would gain: 30000 x 30000 1413 / 1312, 1000 x 131500 405 / 317, 10000 x 24000 446 / 438, the other two alike.
 constexpr int kIdlePercent = 7, kFillGain = 4, kTallChunk = 1000;
 
 int plan_rounds(int64_t n, int64_t m, int64_t staged)
@@ -327,7 +330,7 @@ int run_plan_pass(int64_t n, int64_t m, const double *M, int64_t ldM, const doub
     // One round of resident workgroups, unless the caller expects more entries than the waves of one
     // round can keep on chip (kRecCap each): then as many rounds of lower chunks as it takes (at most
     // kMaxRounds), which keeps most waves from writing their records to HBM in the middle of the pass.
-    // (Or where one round leaves too many places empty: plan_rounds.  A refresh goes by its candidates alone.)
+    // (Or where one round leaves too many places empty: plan_rounds, with the times of the calls that do not go by it.)
     const int64_t staged = rc ? rc->cand_capacity : capacity;  // records the pass is expected to stage
     int rounds = !SPARSIFY ? 1 : rc ? plan_rounds(staged) : plan_rounds(n, m, staged);
     // (The pool of a pattern refresh is laid out with a margin of a quarter.  Where that margin alone asks for a second
@@ -966,9 +969,9 @@ EntryPlan make_entry_plan(int64_t n, int64_t m, int64_t capacity)
 }
 
 // Whole sweeps from one read of M each (regot_sweep.hpp): the clusters for an n x m matrix, or K = 0 if the sweep is to be
-// run as its two half-steps.  A sweep of 1600 x 1200 takes 13.7 us against 31, 7001 x 4999 69 against 119, 10000^2 157
+// run as its two half-steps.  The first sweep of a call takes 13.7 us at 1600 x 1200 against 31, at 7001 x 4999 69 against 119, 10000^2 157
 // against 277, 20000^2 594 against 985, 50000^2 4.0 ms against 6.5; 64 x 16500 19 against 21 us, 512 x 61440 68 against 105,
-// 1000000 x 1536 2.4 ms against 3.8.  The half-steps it is
+// 1000000 x 1536 2.4 ms against 3.8 (the ones behind it a tenth less from 10000^2 on: regot_sweep_near.hpp).  The half-steps it is
 //   - below 2^20 entries, where sweeps stay the half-steps' bit for bit (1025 x 1024: 15 us a sweep against the half-steps' 25);
 //   - for more columns than 16 members can own, and a handful of rows or columns;
 //   - for tall and narrow matrices: a wave takes 128 columns, so fewer than five of the fifteen have work, and a row costs
@@ -1007,7 +1010,8 @@ SweepPlan make_sweep_plan(int64_t n, int64_t m, int sweeps)
     return S;
 }
 
-// The exchange words use the region of the row partials (2 g_c n doubles, g_c >= K) and the column sums that of the
+// The exchange words, 2 K n for K > 1, and n doubles of the new alpha behind them use the region of the row partials (2 g_c n doubles;
+// g_c > K, as a member has more columns than three panels) and the column sums that of the
 // column partials (2 g_r m doubles: g_c <= 7.5 K + 1 panels, so 2 floor(2048 / g_c) >= 256 / K, and 2 ceil(n / 16) >= n / 8).
 int run_sweeps(const SweepPlan &Q, int64_t n, int64_t m, const double *M, int64_t ldM, const double *a, const double *b,
                double *alpha, double *beta, double eta, int sweeps, void *workspace, const Layout &L, hipStream_t s)
@@ -1031,6 +1035,7 @@ int run_sweeps(const SweepPlan &Q, int64_t n, int64_t m, const double *M, int64_
     A.huge = at<int>(workspace, L.header) + HDR_SWEEP_HUGE;
     A.far = at<int>(workspace, L.header) + HDR_SWEEP_FAR;
     double *alpha_next = A.exch + (A.K > 1 ? 2 * n * A.K : 0);
+    static_assert(kSweepCols1 >= 3 * kPanel, "K > 1 members have more than K - 1 times kSweepCols1 columns, so g_c >= 3 (K - 1) + 1 >= K + 1");
     A.ex = make_exp_params(eta);
     A.looks = g_sweep_looks >= 0 ? g_sweep_looks : kSweepLooks;
     A.floor = -1e44 * eta;  // (-inf for an eta above 1e264: no floor.  exp_eta gives 0 up to about 1e46 eta below the maximum)

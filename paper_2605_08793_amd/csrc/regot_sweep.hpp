@@ -32,11 +32,13 @@
 // That is the first sweep of a call.  The ones behind it know how large their terms are and need no maxima: regot_sweep_near.hpp.
 //
 // What bounds it: instructions (32 an entry: with the loads taken out 447 us at 20000 x 20000) beside the memory.  20000 x 20000:
-// 596 us a sweep = 5.4 TB/s of M against 975 us for the two half-steps (two reads at 6.6 TB/s); with the exponentials
-// replaced by one operation 550 us.  A member's numbers take 0.8 us to reach the others, but the members of a cluster
+// 596 us a sweep = 5.4 TB/s of M against 975 us for the two half-steps (two reads at 6.6 TB/s; the sweeps behind the first one
+// take 540); with the exponentials replaced by one operation 550 us.  A member's numbers take 0.8 us to reach the others, but the members of a cluster
 // drift apart by up to the one batch (5 us) they are allowed; a cluster of one (m <= 3840) runs at 5.8 TB/s.  Measured on
 // the way: seven workers with twice the columns each 616 us; all of a batch's loads requested at once 673 us (the waves then
 // stand in line to issue them); counters in LDS instead of the barrier: no change; members on one die: no change.
+// (With two groups of columns a wave two or three of the 128 registers are spilled: addresses of the results, written before the loops and
+// read behind them.)
 #pragma once
 
 #include "regot_kernels.hpp"
@@ -139,7 +141,7 @@ struct SweepShared {
     dbl2 beta[NU][kSweepLanes];                // a lane's beta; likewise
     dbl2 pairs[2][R][kSweepWaves];  // (max, sum) per row and wave, by parity of the batch
     double fac[2][R][kSweepWaves];  // what a wave's exponentials of a row are to be multiplied by
-    int role, huge;                 // (huge: a row's mass is beyond kSweepHuge)
+    int huge;                       // a row's mass is beyond kSweepHuge
 };
 
 // Batches a cluster works through; rows beyond the last are its last row again, with a factor of 0.  An even number of batches

@@ -17,7 +17,7 @@
 // 10000 x 10000 143 -> 134, 20000 x 3840 106 -> 102, 7001 x 4999 66 -> 60, 3000 x 3000 27.5 -> 25.8.  What bounds it now: the memory at what this
 // pattern of rows gets (505 without waiting for the other members' numbers, whatever the arithmetic), and that waiting.
 // Blocks of two batches (1600 x 1200: 8 rows) gain nothing in the pass and lose 0.6 us a sweep around it, hence the line at 8 rows
-// (SweepPlan::near): 1600 x 1200 138 us by maxima against 144 for ten sweeps, 1400 x 3000 181 / 184; 2300 x 1200, 9 rows, 179 / 177; 3000 x 3000 267 / 256;
+// (SweepPlan::later): 1600 x 1200 138 us by maxima against 144 for ten sweeps, 1400 x 3000 181 / 184; 2300 x 1200, 9 rows, 179 / 177; 3000 x 3000 267 / 256;
 // 600 x 20000, 14 rows in six members, 192 / 182 for six.
 #pragma once
 
