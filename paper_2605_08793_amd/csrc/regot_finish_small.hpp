@@ -19,9 +19,9 @@ namespace regot {
 // records are dealt out in portions, to the waves of as many workgroups as that takes (the grid's second dimension: most of
 // them see that they are not needed, and return).  All entries of a matrix may be in one chunk, and one workgroup, which took runs of the list as
 // they lay, so mostly by one wave, was slow at that.  3000 x 3000, 84000 entries in 28 rows, us, two launches / one workgroup a chunk / this:
-// 43 / 241 / 47; 3072 x 4096, 118784 in 29 rows 44 / 261 / 50; 2000 x 2000, 36000 in 18 rows 28 / 81 / 31; 1000 x 1000, 9000 in 9 rows 21.5 / 31.6 / 21.7.
-// Fused pass with 1 % of the entries all over the matrix, us a call, the two launches / this: 64 x 64 16.2 / 13.5, 1000 x 1000 19.2 / 16.3, 2000 x
-// 2000 27.5 / 24.0, 3000 x 3000 38.3 / 35.2; sparsification alone 1000 x 1000 17.4 / 14.9.  Beyond kOnceCounts the sums over all counts and the
+// 43 / 242 / 47; 3072 x 4096, 118784 in 29 rows 44 / 262 / 50; 2000 x 2000, 36000 in 18 rows 28 / 81 / 30; 1000 x 1000, 9000 in 9 rows 21.7 / 32.1 / 21.9.
+// Fused pass with 1 % of the entries all over the matrix, us a call, the two launches / this: 64 x 64 16.3 / 13.6, 1000 x 1000 19.2 / 16.1, 2000 x
+// 2000 27.5 / 23.6, 3000 x 3000 38.0 / 34.8; sparsification alone 1000 x 1000 17.4 / 14.7.  Beyond kOnceCounts the sums over all counts and the
 // objective's workgroup take what the launch took: 4999 x 3001 47.3 / 46.2, 4000 x 4000 47.4 / 48.0.  kOnceEntries lies where one workgroup a chunk
 // met the two launches (1000 x 1000 with half of its entries, 7900 a chunk); with several it is still ahead behind that line, there 23.8 / 22.1, with all of
 // the entries 33.9 / 32.4.  kOnceMost keeps a chunk of a few wide rows, whose workgroups have more than that each, with the launches.
@@ -70,13 +70,14 @@ __global__ __launch_bounds__(kFinThreads) void finish_small_kernel(ScatterArgs S
     // the latter: then part 0 places a run a wave.
     const PoolRange *runs = S.ranges + ((int64_t)block * S.g_c) * kWaves;
     const int fixed_runs = S.g_c * kWaves;
+    // (Asked for by lanes: the compiler would wait at once for what is the same in all of a wave.)
+    int none = 0;
+    asm volatile("" : "+v"(none));
+    const int hdr_runs = S.header[HDR_RANGE_NEXT + none], hdr_overflow = S.header[HDR_POOL_OVERFLOW + none];
     PoolRange R{}, fixed{};
-    int extra = 0, hdr_overflow = 0;
-    const auto look_up = [&] {  // (part 0 behind the counts: a scalar load before them would have to be waited for)
-        hdr_overflow = S.header[HDR_POOL_OVERFLOW];
-        extra = min(S.header[HDR_RANGE_NEXT], S.max_ranges - S.fixed_runs);
-        if (lane < fixed_runs) fixed = runs[lane];
-    };
+    if (w < fixed_runs) R = runs[w + none];
+    if (lane < fixed_runs) fixed = runs[lane];
+    int extra = 0;
     const auto listed = [&](int e) {  // run e of the list, if it is the chunk's
         PoolRange X{};
         if (e < extra) X = S.ranges[S.fixed_runs + e];
@@ -100,7 +101,7 @@ __global__ __launch_bounds__(kFinThreads) void finish_small_kernel(ScatterArgs S
         parts = max(1, min(most_parts, (portions + kOnceEasy * kFinSub - 1) / (kOnceEasy * kFinSub)));
     };
     if (part > 0) {
-        look_up();
+        extra = min(__builtin_amdgcn_readfirstlane(hdr_runs), S.max_ranges - S.fixed_runs);
         if (extra <= 0 && __ballot(fixed.count > kOncePortion) == 0) return;
         share_out();
         if (part >= parts) return;
@@ -119,10 +120,6 @@ __global__ __launch_bounds__(kFinThreads) void finish_small_kernel(ScatterArgs S
     for (int e = 0; e < kOnceEach; ++e) {
         const int at = kOnceEach * tid + e, row = at / S.g_c, p = at - row * S.g_c;
         mine[e] = row < rows ? S.seg_rel[(size_t)p * S.n + r_begin + row] : 0;
-    }
-    if (part == 0) {
-        if (w < fixed_runs) R = runs[w];
-        look_up();
     }
     if constexpr (REDUCE) {
         const int end = part == 0 ? rows : 0;
@@ -145,6 +142,7 @@ __global__ __launch_bounds__(kFinThreads) void finish_small_kernel(ScatterArgs S
     const int up_to = wave_scan(sum);
     all = wave_scan(all);
     before = wave_scan(before);
+    extra = min(__builtin_amdgcn_readfirstlane(hdr_runs), S.max_ranges - S.fixed_runs);
     const bool usual = extra <= 0 && __ballot(fixed.count > kOncePortion) == 0;
     if (lane == kLanes - 1) {
         lds_scan[w] = up_to;
@@ -160,7 +158,7 @@ __global__ __launch_bounds__(kFinThreads) void finish_small_kernel(ScatterArgs S
         all += lds_all[0][q];
         before += lds_all[1][q];
     }
-    const bool overflow = all > S.capacity || hdr_overflow != 0;
+    const bool overflow = all > S.capacity || __builtin_amdgcn_readfirstlane(hdr_overflow) != 0;
     if (block == 0 && part == 0) {
         if (tid == 0) {
             S.info[0] = all;
@@ -211,7 +209,7 @@ __global__ __launch_bounds__(kFinThreads) void finish_small_kernel(ScatterArgs S
         if (usual) {
             for (int q = w; q < fixed_runs; q += kFinSub) {
                 if (q != w) R = runs[q];
-                const Portion P{R.start, R.count, R.panel};
+                const Portion P{__builtin_amdgcn_readfirstlane(R.start), __builtin_amdgcn_readfirstlane(R.count), __builtin_amdgcn_readfirstlane(R.panel)};
                 place_portions(std::integral_constant<int, 1>{}, &P);
             }
             return;
