@@ -339,8 +339,9 @@ __global__ __launch_bounds__(kBlock) void col_ptr_kernel(TransposeArgs A, const 
 }
 
 // ---------------------------------------------------------------------------
-// The same by counting.  The rows are taken in blocks: row r and the entries before it come to r / 32 + entries / E, and block b
-// has the rows where that is in [b, b + 1), so it has at most 32 rows and at most E entries more than its last row has.  Per
+// The same by counting.  The entries are taken in blocks: the entry at position p in row r comes to r / 32 + p / E, and block b
+// has the entries where that is in [b, b + 1), so they are at most E and of at most 32 rows, and a long row is several blocks' (five full rows
+// of 1000 x 40000, us: 31; with blocks of whole rows 68, by sorting 49, as many entries in all rows 28).  Per
 // block a bit mask for every column says which of its rows have an entry there, so that an entry's rank among the block's
 // entries of its column is a count of bits, whatever order they come in, and nothing has to be sorted:
 //   1. column_count_kernel: the masks of a block in LDS; rank[p] of its entries and count[block][column];
@@ -370,7 +371,7 @@ constexpr int kCountMaxCols = 40000, kCountMostRows = 65535;   // (the masks in 
 constexpr int padded(int cols) { return (cols + kGroupCols - 1) / kGroupCols * kGroupCols; }
 constexpr int kMaxGroups = (kCountMaxCols + kGroupCols - 1) / kGroupCols, kGroupsPerLane = (kMaxGroups + kLanes - 1) / kLanes;
 
-struct BlockRows {  // of a block: its first entry, how many, its first row, how many
+struct BlockRows {  // of a block: its first entry, how many, their first row, how many
     int32_t first, count, row, rows;
 };
 
@@ -386,7 +387,8 @@ struct CountLayout {
 // has fewer entries than one in 512, at 20000 x 20000 with 390000 40.0 / 39.5, or one in 200 where m > 20000 leaves room for one workgroup
 // on a compute unit, at 5000 x 40000 with 600000 44.9 / 45.3, 30000 x 40000 with 2.5e6 105 / 85; nor where there are more blocks than the
 // compute units take at once and (few columns to share the scan) 65000 x 100, 35 / 21, or (few entries in a block) 65535 x 2048 with
-// 327000, 51 / 40 (65535 x 3000 with 1e6: 56 / 58); nor (a row is one block's) at 32 x 40000 with 480000, 54 / 43; nor where the sort has
+// 327000, 51 / 40 (65535 x 3000 with 1e6: 56 / 58); nor (as a row was one block's: 32 x 40000 with 480000 54 / 43,
+// 30 / 42 since it is not) for more than 512 n columns; nor where the sort has
 // one pass over few entries, at 64 x 64 with 98, 11.0 / 10.5 (2135: 11 / 17).
 bool by_counting(int64_t n, int64_t m, int64_t nnz)
 {
@@ -422,7 +424,7 @@ CountLayout make_count_layout(int64_t n, int64_t m, int64_t nnz)
 }
 
 struct CountArgs {
-    int n, m, blocks, pitch, entries;  // (entries: as a block of one row may have)
+    int n, m, blocks, pitch, entries;  // (entries: as a block may have)
     int64_t nnz;
     const int64_t *row_ptr;
     const int32_t *col_idx;
@@ -445,17 +447,28 @@ __device__ __forceinline__ int64_t entries_before(const CountArgs &A, int64_t r)
     return p < 0 ? 0 : p > A.nnz ? A.nnz : p;
 }
 
-// The first row of block b, by a wave: among the 64 rows around where it would be if all had the same number of entries, or else
-// among all.
-__device__ __forceinline__ int block_first_row(const CountArgs &A, int b, int lane)
+struct BlockStart {
+    int64_t entry;
+    int row;
+    bool inside;  // of the row: some of its entries are the block before's
+};
+
+// Where block b begins, by a wave: the first row that is the block's is among the 64 around where it would be if all had the same number of
+// entries, or else among all.
+__device__ __forceinline__ BlockStart block_start(const CountArgs &A, int b, int lane)
 {
     const int64_t target = (int64_t)b * kBlockRows * A.entries;
     const auto reached = [&](int64_t r) { return r >= A.n || r * A.entries + entries_before(A, r) * kBlockRows >= target; };
     int64_t r = (int64_t)b * A.n / A.blocks - kLanes / 2;
     r = r < 0 ? 0 : r;
     const uint64_t mask = __ballot(reached(r + lane));
-    if (mask != 0 && (r == 0 || (mask & 1) == 0)) return (int)r + __builtin_ctzll(mask) < A.n ? (int)r + __builtin_ctzll(mask) : A.n;
-    return (int)wave_first(0, A.n, lane, reached);
+    if (mask != 0 && (r == 0 || (mask & 1) == 0)) r += __builtin_ctzll(mask);
+    else r = wave_first(0, A.n, lane, reached);
+    r = r < A.n ? r : A.n;
+    // the end of the row before may be
+    const int64_t p = entries_before(A, r), in_row = r > 0 ? (target - (r - 1) * A.entries + kBlockRows - 1) / kBlockRows : p;
+    if (in_row < p && in_row >= entries_before(A, r - 1)) return BlockStart{in_row, (int)r - 1, true};
+    return BlockStart{p, (int)r, false};
 }
 
 // The entries of a block of rows, one to a thread whatever rows they are in.
@@ -482,17 +495,18 @@ __global__ __launch_bounds__(kCountThreads) void column_count_kernel(CountArgs A
 {
     __shared__ __attribute__((aligned(16))) uint32_t mask[padded(COLS)];
     __shared__ int ends[kBlockRows];
-    __shared__ int cut[2];
+    __shared__ BlockStart cut[2];
     __shared__ int repeats;
     const int tid = (int)threadIdx.x, block = (int)blockIdx.x;
     if (tid < 2 * kLanes) {
-        const int k = tid / kLanes, first = block_first_row(A, block + k, tid % kLanes);
-        if (tid % kLanes == 0) cut[k] = first;
+        const int k = tid / kLanes;
+        const BlockStart start = block_start(A, block + k, tid % kLanes);
+        if (tid % kLanes == 0) cut[k] = start;
     }
     __syncthreads();
-    const int rows = max(0, min(kBlockRows, cut[1] - cut[0]));  // (never more, unless row_ptr does not ascend)
-    const int64_t first = entries_before(A, cut[0]), after = entries_before(A, cut[0] + rows);
-    const BlockRows B{(int32_t)first, (int32_t)(after > first ? after - first : 0), cut[0], rows};
+    const int rows = max(0, min(kBlockRows, cut[1].row - cut[0].row + (cut[1].inside ? 1 : 0)));  // (never more, unless row_ptr does not ascend)
+    const int64_t first = cut[0].entry, after = cut[1].entry;
+    const BlockRows B{(int32_t)first, (int32_t)(after > first ? after - first : 0), cut[0].row, rows};
     const BlockEntries E(A, B, ends);
     if (tid == 0) {
         A.rows[block] = B;

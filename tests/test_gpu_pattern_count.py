@@ -40,6 +40,9 @@ CASES = {
     # rows without entries: before, between (more than a block of them), behind; the entries in a few of the rows
     "empty rows": (3000, 2000, np.where(np.isin(np.arange(3000) // 100, [3, 4, 20]), 300, 0)), "skewed": (9000, 3000, np.where(np.arange(9000) % 4500 < 200, 1000, 1)),
     "last row": (2000, 1500, some(2000, 0, (1999,), 1500) + (np.arange(2000) < 40) * 200), "first row": (2000, 1500, some(2000, 0, (0,), 1500) + (np.arange(2000) > 1950) * 200),
+    # rows of more entries than a block has: several blocks each, between rows with none and next to short ones; of a block's entries, one fewer and one more
+    "full rows": (1000, 40000, some(1000, 0, range(500, 505), 40000)), "few and long": (300, 9000, some(300, 1, (0, 5, 6, 299), 9000)), "one row": (100, 30000, some(100, 0, (31,), 30000)),
+    "2047": (40, 9000, some(40, 2047)), "2048 a row": (40, 9000, some(40, 2048)), "2049": (40, 9000, some(40, 2049)), "16385": (140, 20000, some(140, 16385)),
     # more than 2.1e6 entries: blocks of 16384
     "most entries": (3000, 4000, 500 + np.arange(3000) % 500),
     # the widest for two workgroups to a compute unit, and above; the widest at all
@@ -122,3 +125,28 @@ def test_workspace_is_asked_for(edge):
         B.regot_pattern_transpose(n, m, nnz, rp, ci, cp, ri, pos, workspace=ws)
     torch.cuda.synchronize()
     assert not (cp.any() or ri.any() or pos.any())
+
+
+def test_time_does_not_hang_on_where_the_entries_are():
+    """All entries in five full rows: a row is as many workgroups' as it has entries for.  (By one workgroup each they took 68 us, where as many
+    entries in all rows take 28; the several take 31.)"""
+    from paper_2605_08793_amd import binding as B
+    n, m, time = 1000, 40000, []
+    for lengths in (some(n, 200), some(n, 0, range(500, 505), m)):
+        rp, ci = rows_of(n, m, lengths, seed=1)
+        nnz = int(rp[-1])
+        assert nnz == 200000
+        rpd, cid = torch.as_tensor(rp).cuda(), torch.as_tensor(ci).cuda()
+        cp, ri, pos = (torch.empty(k, dtype=t, device="cuda") for k, t in ((m + 1, torch.int64), (nnz, torch.int32), (nnz, torch.int64)))
+        ws = torch.empty(B.regot_pattern_transpose_workspace_bytes(n, m, nnz), dtype=torch.uint8, device="cuda")
+        best = float("inf")
+        for _ in range(30):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(10):
+                B.regot_pattern_transpose(n, m, nnz, rpd, cid, cp, ri, pos, workspace=ws)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, begin.elapsed_time(end))
+        time.append(best)
+    assert time[1] < 1.6 * time[0], time
