@@ -547,6 +547,15 @@ __global__ __launch_bounds__(kCountThreads) void column_count_kernel(CountArgs A
         fetch(q0 + kTrip);
     }
     __syncthreads();
+    // A row that begins in a block before this one, and holds a column there and here, is two entries to the column's place in base: right, unless
+    // they add up to more than its 16 bits.  (65535 x 10000, 6e6 entries, us, without a look / with one: 98.2 / 99.2.)
+    if (A.n + A.blocks > kCountMostRows && cut[0].inside) {
+        for (int64_t p = entries_before(A, cut[0].row) + tid; p < first; p += kCountThreads) {
+            const int32_t c = A.col_idx[p];
+            if ((uint32_t)c < (uint32_t)A.m && (mask[c] & 1u) != 0) repeats = 1;
+        }
+        __syncthreads();
+    }
     if (tid == 0) A.repeats[block] = (uint8_t)repeats;
     for (int q0 = last;; q0 -= kTrip) {  // (what was fetched last first)
 #pragma unroll

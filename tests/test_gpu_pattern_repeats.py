@@ -74,3 +74,32 @@ def test_repeats_beside_entries_of_no_column():
     got = pos.cpu().numpy()
     assert (got[bad] == -1).all()
     np.testing.assert_array_equal(got[keep], o_pos)
+
+
+def test_repeats_on_either_side_of_a_cut():
+    """65535 rows, the most that are transposed by counting, with an entry each in one column, and a second one in the rows that two blocks
+    share, so that no block has both: more entries of the column than the 16 bits of a column's place count."""
+    from paper_2605_08793_amd import binding as B
+    n, m, each, column = 65535, 2048, 17, 1000
+    nnz = n * each
+    share = min(max(nnz // 128, 2048), 16384)  # entries of a block; the entry at position p of row r is block (r / 32 + p / share)'s
+    p = np.arange(nnz, dtype=np.int64)
+    block = ((p // each) * share + 32 * p) // (32 * share)
+    block = block.reshape(n, each)
+    ci = np.sort(np.random.default_rng(2).integers(0, 58, size=(n, each)) + 58 * np.arange(each), axis=1).astype(np.int32)   # up to 985
+    ci[:, -1] = column
+    cut = block[:, 0] != block[:, -1]
+    assert cut.sum() > 100
+    ci[cut, 0] = column
+    rp, ci = np.arange(n + 1, dtype=np.int64) * each, ci.ravel()
+    o_cp, o_ri, o_pos = oracle.pattern_transpose(n, m, rp, ci)
+    assert o_cp[column + 1] - o_cp[column] > 65535
+    ws = torch.full((B.regot_pattern_transpose_workspace_bytes(n, m, nnz),), 0x7F, dtype=torch.uint8, device="cuda")
+    cp = torch.empty(m + 1, dtype=torch.int64, device="cuda")
+    ri = torch.full((nnz,), -5, dtype=torch.int32, device="cuda"); pos = torch.full((nnz,), -5, dtype=torch.int64, device="cuda")
+    print(f"[repeats] cut rows: n={n} m={m} nnz={nnz} cut={int(cut.sum())}", flush=True)
+    B.regot_pattern_transpose(n, m, nnz, torch.as_tensor(rp).cuda(), torch.as_tensor(ci).cuda(), cp, ri, pos, workspace=ws)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(cp.cpu().numpy(), o_cp)
+    np.testing.assert_array_equal(ri.cpu().numpy(), o_ri)
+    np.testing.assert_array_equal(pos.cpu().numpy(), o_pos)
